@@ -66,15 +66,24 @@ struct FwdOut {
     float* wide_out = nullptr;  // matrix-core kernels: the result goes here in fp32 instead of to main_out
 };
 
-// ---- attn_simple.hip : straightforward scalar-FMA kernels (fp32 arithmetic, any element type)
-int simple_fwd(const Geom& g, int dtype, const RowSet& rs, const void* q, const void* k, const void* v,
-               const FwdOut& out, hipStream_t st);
-int simple_bwd_dq(const Geom& g, int dtype, const RowSet& rs, const void* q, const void* k, const void* v,
-                  const void* dO, const float* lse, float* delta, void* dq, int accumulate, hipStream_t st);
+// ---- attn_fp32.hip : fp32 matrix-core kernels (D = 64 or 128)
+int fp32_fwd(const Geom& g, const RowSet& rs, const void* q, const void* k, const void* v, const FwdOut& out,
+             hipStream_t st);
+int fp32_bwd_dq(const Geom& g, const RowSet& rs, const void* q, const void* k, const void* v, const void* dO,
+                const float* lse, float* delta, void* dq, int accumulate, hipStream_t st);
 // dk, dv of every key token; `sets` (1 or 2 row sets: local and/or global) accumulate into the same outputs
-int simple_bwd_dkdv(const Geom& g, int dtype, const RowSet* sets, int nsets, const void* q, const void* k,
-                    const void* v, const void* dO, const float* const* lse, const float* const* delta, void* dk,
-                    void* dv, hipStream_t st);
+int fp32_bwd_dkdv(const Geom& g, const RowSet* sets, int nsets, const void* q, const void* k, const void* v,
+                  const void* dO, const float* const* lse, const float* const* delta, void* dk, void* dv,
+                  hipStream_t st);
+
+// ---- attn_simple.hip : straightforward scalar-FMA kernels (bf16 storage, fp32 arithmetic, D = 64 or 128)
+int simple_fwd(const Geom& g, const RowSet& rs, const void* q, const void* k, const void* v, const FwdOut& out,
+               hipStream_t st);
+int simple_bwd_dq(const Geom& g, const RowSet& rs, const void* q, const void* k, const void* v, const void* dO,
+                  const float* lse, float* delta, void* dq, int accumulate, hipStream_t st);
+int simple_bwd_dkdv(const Geom& g, const RowSet* sets, int nsets, const void* q, const void* k, const void* v,
+                    const void* dO, const float* const* lse, const float* const* delta, void* dk, void* dv,
+                    hipStream_t st);
 
 // ---- router.hip : logit = <w, x_t> + bias; mask = [logit >= thr]; optional sigmoid score and logit
 int router_decide(const l2a_params& p, int C, const void* x, const float* w, float bias, float thr, float* logit,

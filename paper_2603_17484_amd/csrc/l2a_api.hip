@@ -203,7 +203,7 @@ int l2a_attn_fwd(const l2a_params* p, const void* q_loc, const void* k_loc, cons
 
     hipStream_t st = (hipStream_t)stream;
     const Geom g = make_geom(*p);
-    const bool mfma = use_mfma(*p);
+    const bool mfma = use_mfma(*p), fp32 = p->dtype == L2A_FP32;
     int r = L2A_OK;
     // matrix-core path: token-minor copy of each distinct V (layout pre-pass, one pass over V)
     char* vt_loc = (char*)workspace;
@@ -233,8 +233,8 @@ int l2a_attn_fwd(const l2a_params* p, const void* q_loc, const void* k_loc, cons
     auto fwd_branch = [&](const RowSet& rs, const void* q, const void* k, const void* v, const void* vt,
                           const FwdOut& out) {
         int32_t* redo = (int32_t*)((char*)workspace + 2 * kv_copy_bytes(*p));
-        return mfma ? mfma_fwd(g, rs, q, k, v, vt, kv_cap(*p), redo, out, st)
-                    : simple_fwd(g, p->dtype, rs, q, k, v, out, st);
+        if (mfma) return mfma_fwd(g, rs, q, k, v, vt, kv_cap(*p), redo, out, st);
+        return fp32 ? fp32_fwd(g, rs, q, k, v, out, st) : simple_fwd(g, rs, q, k, v, out, st);
     };
     if (do_local) {
         const RowSet rs{nullptr, nullptr, nullptr, 1};
@@ -292,11 +292,12 @@ int l2a_attn_bwd(const l2a_params* p, const void* dO, const void* q_loc, const v
     int r;
     float* delta_l = (float*)workspace;
     float* delta_g = delta_glb_opt ? delta_glb_opt : (float*)((char*)workspace + delta_bytes(*p));
-    const bool mfma = use_mfma(*p);
+    const bool mfma = use_mfma(*p), fp32 = p->dtype == L2A_FP32;
     auto bwd_dq = [&](const RowSet& rs, const void* q, const void* k, const void* v, const float* lse, float* delta,
                       void* dq, int acc) {
-        return mfma ? mfma_bwd_dq(g, rs, q, k, v, dO, lse, delta, dq, acc, st)
-                    : simple_bwd_dq(g, p->dtype, rs, q, k, v, dO, lse, delta, dq, acc, st);
+        if (mfma) return mfma_bwd_dq(g, rs, q, k, v, dO, lse, delta, dq, acc, st);
+        return fp32 ? fp32_bwd_dq(g, rs, q, k, v, dO, lse, delta, dq, acc, st)
+                    : simple_bwd_dq(g, rs, q, k, v, dO, lse, delta, dq, acc, st);
     };
     if ((r = row_deltas(g, p->dtype, dO, do_local ? S : nullptr, do_global ? A : nullptr, delta_l, delta_g, st)) !=
         L2A_OK)
@@ -322,7 +323,8 @@ int l2a_attn_bwd(const l2a_params* p, const void* dO, const void* q_loc, const v
     const int cap = rows_cap(*p);
     auto dkdv = [&](const RowSet* sets, int n, const void* const* qs, const float* const* lses,
                     const float* const* deltas, const void* k, const void* v, void* dk, void* dv) -> int {
-        if (!mfma) return simple_bwd_dkdv(g, p->dtype, sets, n, qs[0], k, v, dO, lses, deltas, dk, dv, st);
+        if (fp32) return fp32_bwd_dkdv(g, sets, n, qs[0], k, v, dO, lses, deltas, dk, dv, st);
+        if (!mfma) return simple_bwd_dkdv(g, sets, n, qs[0], k, v, dO, lses, deltas, dk, dv, st);
         const void* packed[2][5];
         for (int i = 0; i < n; ++i) {
             char* base = packed_base + (sets[i].local ? 0 : packed_set_bytes(*p));
