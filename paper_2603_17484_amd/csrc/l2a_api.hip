@@ -303,8 +303,9 @@ int l2a_attn_bwd(const l2a_params* p, const void* dO, const void* q_loc, const v
         L2A_OK)
         return r;
     if (p->dtype == L2A_BF16) {  // outputs saved in bf16: the first tokens' deltas come from the definition instead
-        if (do_local && (r = head_deltas(g, q_loc, k_loc, v_loc, dO, lse_local, delta_l, 1, st)) != L2A_OK) return r;
-        if (do_global && (r = head_deltas(g, q_glb, k_glb, v_glb, dO, lse_global, delta_g, 0, st)) != L2A_OK) return r;
+        const HeadDeltas l{q_loc, k_loc, v_loc, lse_local, delta_l, 1}, gl{q_glb, k_glb, v_glb, lse_global, delta_g, 0};
+        const HeadDeltas br[2] = {do_local ? l : gl, gl};
+        if ((r = head_deltas(g, br, both ? 2 : 1, dO, st)) != L2A_OK) return r;
     }
 
     const RowSet rs_l{nullptr, nullptr, nullptr, 1};

@@ -68,34 +68,53 @@ __global__ __launch_bounds__(kThreads) void row_deltas_kernel(Geom gm, const E* 
 // which enters dq_t as  scale * error * sum_j p_tj k_j.  Both factors shrink like 1 / sqrt(keys) for
 // rows that average many keys, but for the first few tokens they do not (token 2 with N(0,1) inputs:
 // up to 1.2e-2 per branch, twice that when both branches read the same tensors, since s_t = a_t
-// there), so the first kHeadTokens deltas are recomputed exactly.  One wavefront per (token, head);
-// lane = key.  A row whose log-sum-exp is -inf (not routed: a_t = 0) gets delta = 0.
+// there), so the first kHeadTokens deltas are recomputed exactly.  One wavefront per (token, head, branch);
+// lane = key.  A row whose log-sum-exp is -inf (not routed: a_t = 0) gets delta = 0.  Bound by the latency of
+// the rows' loads: 16 bytes at a time, eight of each row in flight (element by element this took 99 us for
+// two sequences of 28 heads and a launch per branch, now 30 us for both branches together).
 constexpr int kHeadTokens = 64;
 
-__global__ __launch_bounds__(64) void head_deltas_kernel(Geom gm, const __bf16* __restrict__ q,
-                                                         const __bf16* __restrict__ k, const __bf16* __restrict__ v,
-                                                         const __bf16* __restrict__ dO, const float* __restrict__ lse,
-                                                         float* __restrict__ delta, int local) {
-    const int t = blockIdx.x, h = blockIdx.y, b = blockIdx.z, j = threadIdx.x;
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+struct HeadBranch {
+    const __bf16 *q, *k, *v;
+    const float* lse;
+    float* delta;
+    int local;
+};
+
+__global__ __launch_bounds__(64) void head_deltas_kernel(Geom gm, HeadBranch br0, HeadBranch br1,
+                                                         const __bf16* __restrict__ dO) {
+    const int nt = min(gm.T, kHeadTokens), second = (int)blockIdx.x >= nt;
+    const int t = (int)blockIdx.x - second * nt, h = blockIdx.y, b = blockIdx.z, j = threadIdx.x;
+    const HeadBranch br = second ? br1 : br0;
     const int hk = h / gm.G;
     const size_t so = ((size_t)b * gm.Hq + h) * gm.T + t;
-    const float l = lse[so];
+    const float l = br.lse[so];
     float term = 0.f;
-    const bool in_reach = j <= t && (!local || t - j <= gm.W);
+    const bool in_reach = j <= t && (!br.local || t - j <= gm.W);
     if (in_reach && l != -INFINITY) {
-        const __bf16* qr = q + (((size_t)b * gm.T + t) * gm.Hq + h) * gm.D;
-        const __bf16* gr = dO + (((size_t)b * gm.T + t) * gm.Hq + h) * gm.D;
-        const __bf16* kr = k + (((size_t)b * gm.T + j) * gm.Hkv + hk) * gm.D;
-        const __bf16* vr = v + (((size_t)b * gm.T + j) * gm.Hkv + hk) * gm.D;
+        const size_t row = (((size_t)b * gm.T + t) * gm.Hq + h) * gm.D, key = (((size_t)b * gm.T + j) * gm.Hkv + hk) * gm.D;
+        const bf16x8* qr = reinterpret_cast<const bf16x8*>(br.q + row);
+        const bf16x8* gr = reinterpret_cast<const bf16x8*>(dO + row);
+        const bf16x8* kr = reinterpret_cast<const bf16x8*>(br.k + key);
+        const bf16x8* vr = reinterpret_cast<const bf16x8*>(br.v + key);
         float s = 0.f, dp = 0.f;
-        for (int c = 0; c < gm.D; ++c) {
-            s = fmaf((float)qr[c], (float)kr[c], s);
-            dp = fmaf((float)gr[c], (float)vr[c], dp);
+        for (int c0 = 0; c0 < gm.D / 8; c0 += 8) {  // D = 64 or 128
+            bf16x8 q8[8], g8[8], k8[8], v8[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) q8[i] = qr[c0 + i], k8[i] = kr[c0 + i], g8[i] = gr[c0 + i], v8[i] = vr[c0 + i];
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    s = fmaf((float)q8[i][e], (float)k8[i][e], s);
+                    dp = fmaf((float)g8[i][e], (float)v8[i][e], dp);
+                }
         }
         term = expf(s * gm.scale - l) * dp;
     }
     for (int o = 32; o > 0; o >>= 1) term += __shfl_xor(term, o);
-    if (j == 0) delta[so] = term;
+    if (j == 0) br.delta[so] = term;
 }
 
 __global__ __launch_bounds__(kThreads) void fill_u32_kernel(uint32_t* p, size_t n, uint32_t value) {
@@ -129,13 +148,15 @@ int row_deltas(const Geom& g, int dtype, const void* dO, const void* S, const vo
     return launch_status();
 }
 
-int head_deltas(const Geom& g, const void* q, const void* k, const void* v, const void* dO, const float* lse,
-                float* delta, int local, hipStream_t st) {
+int head_deltas(const Geom& g, const HeadDeltas* branches, int n, const void* dO, hipStream_t st) {
     static_assert(kHeadTokens <= 64, "one lane per key");
-    const dim3 grid((unsigned)std::min(g.T, kHeadTokens), (unsigned)g.Hq, (unsigned)g.B);
+    HeadBranch br[2] = {};
+    for (int i = 0; i < n; ++i)
+        br[i] = HeadBranch{(const __bf16*)branches[i].q, (const __bf16*)branches[i].k, (const __bf16*)branches[i].v,
+                           branches[i].lse, branches[i].delta, branches[i].local};
+    const dim3 grid((unsigned)(std::min(g.T, kHeadTokens) * n), (unsigned)g.Hq, (unsigned)g.B);
     KernelTimer kt("head_deltas", st);
-    hipLaunchKernelGGL(head_deltas_kernel, grid, dim3(64), 0, st, g, (const __bf16*)q, (const __bf16*)k,
-                       (const __bf16*)v, (const __bf16*)dO, lse, delta, local);
+    hipLaunchKernelGGL(head_deltas_kernel, grid, dim3(64), 0, st, g, br[0], br[1], (const __bf16*)dO);
     return launch_status();
 }
 
