@@ -51,8 +51,8 @@ enum {
                                  FlashAttention-style mode; mask and index arrays are ignored, may be NULL */
     L2A_FLAG_SKIP_LOCAL = 2,  /* run the Global branch only:  O = d a  */
     L2A_FLAG_SKIP_GLOBAL = 4, /* run the Local branch only:   O = s    */
-    L2A_FLAG_SEQUENTIAL = 8,  /* forward: run the branches one after the other at every length (see
-                                 l2a_attn_fwd: short sequences otherwise run them in one launch) */
+    L2A_FLAG_SEQUENTIAL = 8,  /* run the branches one after the other at every length (see l2a_attn_fwd: short
+                                 sequences otherwise run them in one launch; the backward's dQ alike) */
     L2A_FLAG_RING_CACHE = 16, /* l2a_attn_decode with L2A_FLAG_SKIP_GLOBAL: the cache is a ring (see there) */
     L2A_FLAG_SCALAR = 1 << 16 /* bf16 only: use the scalar-FMA kernels instead of the matrix-core ones
                                  (slow; for cross-checking, and the only bf16 path for D = 64) */

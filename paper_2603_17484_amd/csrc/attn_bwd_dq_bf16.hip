@@ -40,6 +40,7 @@ struct DqArgs {
     float* delta;  // in: <dO, saved out>; out: sum_j P dP
     __bf16* dq;
     int accumulate;
+    float* wide_out = nullptr;  // the rows' results in fp32 go here instead of to dq
 };
 
 struct SdP {
@@ -50,15 +51,17 @@ struct SdP {
 // share a SIMD: the loop over unmasked blocks fits without spills and gains 14 %, the masked blocks
 // spill -- so the Global rows (a handful of masked blocks out of hundreds per tile) run with 8
 // wavefronts and the Local rows (every twentieth block masked) with 4.
+// (bx, by) of (gx, nbh): the workgroup's index in its branch's part of the grid (a launch may carry both branches)
+typedef __bf16 DqLds[2][3][kBK * 128];
 template <bool LOCAL, int NW>
-__global__ __launch_bounds__(64 * NW) void bwd_dq_kernel(DqArgs a) {
+__device__ __forceinline__ void dq_body(const DqArgs& a, const int bx, const int by, const int gx, const int nbh,
+                                        DqLds& lds_kv) {
     constexpr int kNW = NW;
     constexpr int kBQ = NW * kRW;            // rows per workgroup
     constexpr int kNL = 16 / NW;             // 16-byte loads a wavefront issues per K, V or K^T block
     constexpr int kLoadSlot0 = 23 - 2 * kNL;  // the loads of later blocks go out in the last slots of a block's first half
     // K and V tiles in one array: a V tile lies a fixed 48 KB behind the K tile of the same buffer, so
     // the reads of both share their per-lane addresses (the distance goes into the offset field)
-    __shared__ __attribute__((aligned(1024))) __bf16 lds_kv[2][3][kBK * 128];
     auto& lds_k = lds_kv[0];
     auto& lds_v = lds_kv[1];
     constexpr int kVBehindK = 3 * kBK * 128;  // elements
@@ -77,17 +80,16 @@ __global__ __launch_bounds__(64 * NW) void bwd_dq_kernel(DqArgs a) {
     // their position like the Global ones' and they are ordered the same way.
     int bh, rank;
     const bool by_range = LOCAL && gm.T / 4 > gm.W;
-    const int nbh = gridDim.y;
     if (by_range) {
-        bh = blockIdx.y;
-        rank = ((int)blockIdx.x & 7) * ((int)gridDim.x >> 3) + ((int)blockIdx.x >> 3);
+        bh = by;
+        rank = (bx & 7) * (gx >> 3) + (bx >> 3);
     } else if ((long long)nbh * gm.T <= kAllHeadsMaxTokens) {
-        const int lin = (int)(blockIdx.y * gridDim.x + blockIdx.x);
+        const int lin = by * gx + bx;
         rank = lin / nbh;
         bh = (lin - rank * nbh + rank) % nbh;
     } else {
-        bh = blockIdx.y;
-        rank = blockIdx.x;
+        bh = by;
+        rank = bx;
     }
     const int b = bh / gm.Hkv, hk = bh - b * gm.Hkv;
     const int n_rows = rows_total(a.rs, gm, bh);
@@ -345,6 +347,10 @@ __global__ __launch_bounds__(64 * NW) void bwd_dq_kernel(DqArgs a) {
             const size_t off = row_off + 4 * h + d * 32 + 8 * rg;
             f32x4 x = {acc[d][4 * rg + 0] * gm.scale, acc[d][4 * rg + 1] * gm.scale, acc[d][4 * rg + 2] * gm.scale,
                        acc[d][4 * rg + 3] * gm.scale};
+            if (a.wide_out) {
+                *reinterpret_cast<f32x4*>(a.wide_out + off) = x;
+                continue;
+            }
             if (a.accumulate) {
                 const bf16x4 old = *reinterpret_cast<const bf16x4*>(a.dq + off);
                 x += __builtin_convertvector(old, f32x4);
@@ -352,6 +358,24 @@ __global__ __launch_bounds__(64 * NW) void bwd_dq_kernel(DqArgs a) {
             *reinterpret_cast<bf16x4*>(a.dq + off) = __builtin_convertvector(x, bf16x4);
         }
     if (h == 0) a.delta[so] = de;
+}
+
+template <bool LOCAL, int NW>
+__global__ __launch_bounds__(64 * NW) void bwd_dq_kernel(DqArgs a) {
+    __shared__ __attribute__((aligned(1024))) DqLds lds_kv;
+    dq_body<LOCAL, NW>(a, (int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x, (int)gridDim.y, lds_kv);
+}
+
+// Both branches in one launch, for sequences so short that the Global rows' tiles alone leave most compute units idle:
+// the first gx_global workgroups (per b, KV head) take the Global rows' tiles, the others the Local rows'.
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void bwd_dq_pair_kernel(DqArgs ag, DqArgs al, int gx_global) {
+    __shared__ __attribute__((aligned(1024))) DqLds lds_kv;
+    if ((int)blockIdx.x < gx_global)
+        dq_body<false, NW>(ag, (int)blockIdx.x, (int)blockIdx.y, gx_global, (int)gridDim.y, lds_kv);
+    else
+        dq_body<true, NW>(al, (int)blockIdx.x - gx_global, (int)blockIdx.y, (int)gridDim.x - gx_global, (int)gridDim.y,
+                          lds_kv);
 }
 
 }  // namespace
@@ -372,6 +396,23 @@ int mfma_bwd_dq(const Geom& g, const RowSet& rs, const void* q, const void* k, c
         hipLaunchKernelGGL((bwd_dq_kernel<true, kNwLocal>), grid, dim3(64 * kNwLocal), 0, st, a);
     else
         hipLaunchKernelGGL((bwd_dq_kernel<false, kNwGlobal>), grid, dim3(64 * kNwGlobal), 0, st, a);
+    return launch_status();
+}
+
+// Both branches at once (bwd_dq_pair_kernel); wide_g: the Global rows' dQ in fp32 instead of to dq_g
+int mfma_bwd_dq_pair(const Geom& g, const RowSet& rs_l, const void* q_l, const void* k_l, const void* v_l,
+                     const float* lse_l, float* delta_l, void* dq_l, const RowSet& rs_g, const void* q_g,
+                     const void* k_g, const void* v_g, const float* lse_g, float* delta_g, void* dq_g, float* wide_g,
+                     const void* dO, hipStream_t st) {
+    if (g.D != kD) return L2A_ERR_UNSUPPORTED;
+    if (64ull * g.Hkv * kD * 2ull > 0xffffffffull) return L2A_ERR_UNSUPPORTED;
+    DqArgs al{g, rs_l, (const __bf16*)q_l, (const __bf16*)k_l, (const __bf16*)v_l, (const __bf16*)dO, lse_l, delta_l, (__bf16*)dq_l, 0};
+    DqArgs ag{g, rs_g, (const __bf16*)q_g, (const __bf16*)k_g, (const __bf16*)v_g, (const __bf16*)dO, lse_g, delta_g, (__bf16*)dq_g, 0, wide_g};
+    const long long rows = (long long)g.T * g.G;
+    constexpr int kNw = 4, kBq = kNw * kRW;
+    const unsigned gx = (unsigned)(((rows + kBq - 1) / kBq + 7) / 8 * 8);  // per branch
+    KernelTimer kt("bwd_dq_pair", st);
+    hipLaunchKernelGGL((bwd_dq_pair_kernel<kNw>), dim3(2 * gx, g.B * g.Hkv), dim3(64 * kNw), 0, st, ag, al, (int)gx);
     return launch_status();
 }
 

@@ -128,6 +128,10 @@ int pack_rows(const Geom& g, const RowSet& rs, const void* q, const void* dO, co
               void* qc, void* gc, float* lse2_c, float* delta_c, int32_t* pos_c, int cap, hipStream_t st);
 int mfma_bwd_dq(const Geom& g, const RowSet& rs, const void* q, const void* k, const void* v, const void* dO,
                 const float* lse, float* delta, void* dq, int accumulate, hipStream_t st);
+int mfma_bwd_dq_pair(const Geom& g, const RowSet& rs_l, const void* q_l, const void* k_l, const void* v_l,
+                     const float* lse_l, float* delta_l, void* dq_l, const RowSet& rs_g, const void* q_g,
+                     const void* k_g, const void* v_g, const float* lse_g, float* delta_g, void* dq_g, float* wide_g,
+                     const void* dO, hipStream_t st);
 // packed[s]: the five outputs of pack_rows for set s (qc, gc, lse2_c, delta_c, pos_c)
 // part: scratch for dkdv_splits(g) x 2 x (B T Hkv D) floats when dkdv_splits(g) > 1 (short sequences)
 int dkdv_splits(const Geom& g);

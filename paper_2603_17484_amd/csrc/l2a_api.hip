@@ -60,6 +60,10 @@ bool pair_fwd(const l2a_params& p) {
     return use_mfma(p) && !(f & (L2A_FLAG_DENSE | L2A_FLAG_SKIP_LOCAL | L2A_FLAG_SKIP_GLOBAL | L2A_FLAG_SEQUENTIAL)) &&
            mfma_fwd_redo_entries(make_geom(p)) <= kPairMaxTiles;
 }
+// The backward's dQ alike (its workspace is the same either way).  Measured, Hq = 28, Hkv = 4, both kernels / the pair, us:
+// T = 1000, 5 % routed 174 / 33, 20 % 122 / 33; T = 4096, W = 4096, 5 / 20 / 50 % 446 / 217, 389 / 244, 397 / 296;
+// T = 16384 1842 / 1348, 1868 / 1754, 2686 / 2563; at T = 32768 (beyond the limit) 20 % 5010 / 4879 plus the merge.
+bool pair_bwd(const l2a_params& p) { return pair_fwd(p); }
 // two token-minor copies of V (one per branch) and the forward kernels' redo flags; short sequences:
 // flags for both branches at once and room for A in fp32
 size_t fwd_workspace_bytes(const l2a_params& p) {
@@ -311,16 +315,27 @@ int l2a_attn_bwd(const l2a_params* p, const void* dO, const void* q_loc, const v
     const RowSet rs_l{nullptr, nullptr, nullptr, 1};
     const RowSet rs_g = dense ? RowSet{nullptr, nullptr, nullptr, 0} : RowSet{row_idx, count, kblk_first_row, 0};
 
-    // dQ: one pass per branch over that branch's rows
-    if (do_local && (r = bwd_dq(rs_l, q_loc, k_loc, v_loc, lse_local, delta_l, dq_loc, 0)) != L2A_OK) return r;
-    if (do_global) {
-        if (!out_alias && !dense && (r = fill_zero(dq_glb, q_elems(*p) * elem_bytes(*p), st)) != L2A_OK) return r;
-        if ((r = bwd_dq(rs_g, q_glb, k_glb, v_glb, lse_global, delta_g, dq_glb, out_alias ? 1 : 0)) != L2A_OK)
+    // dQ: one pass per branch over that branch's rows; short sequences: both in one launch, the Global branch's
+    // share of a summed dQ in fp32 first (where the packed rows go afterwards) and added with the one rounding
+    // the sequential order has
+    char* packed_base = (char*)workspace + 2 * delta_bytes(*p);
+    if (pair_bwd(*p)) {
+        if (!out_alias && (r = fill_zero(dq_glb, q_elems(*p) * elem_bytes(*p), st)) != L2A_OK) return r;
+        float* wide = out_alias ? (float*)packed_base : nullptr;
+        if ((r = mfma_bwd_dq_pair(g, rs_l, q_loc, k_loc, v_loc, lse_local, delta_l, dq_loc, rs_g, q_glb, k_glb, v_glb,
+                                  lse_global, delta_g, dq_glb, wide, dO, st)) != L2A_OK)
             return r;
+        if (wide && (r = merge_rows(g, rs_g, wide, dq_loc, st)) != L2A_OK) return r;
+    } else {
+        if (do_local && (r = bwd_dq(rs_l, q_loc, k_loc, v_loc, lse_local, delta_l, dq_loc, 0)) != L2A_OK) return r;
+        if (do_global) {
+            if (!out_alias && !dense && (r = fill_zero(dq_glb, q_elems(*p) * elem_bytes(*p), st)) != L2A_OK) return r;
+            if ((r = bwd_dq(rs_g, q_glb, k_glb, v_glb, lse_global, delta_g, dq_glb, out_alias ? 1 : 0)) != L2A_OK)
+                return r;
+        }
     }
     // dK, dV: one pass over the key tokens; with shared inputs both branches accumulate in registers.
     // The matrix-core kernel reads each branch's rows from compact copies (layout pre-pass).
-    char* packed_base = (char*)workspace + 2 * delta_bytes(*p);
     const int cap = rows_cap(*p);
     auto dkdv = [&](const RowSet* sets, int n, const void* const* qs, const float* const* lses,
                     const float* const* deltas, const void* k, const void* v, void* dk, void* dv) -> int {

@@ -1,0 +1,36 @@
+"""dQ of both branches in one launch (short sequences) against the sequential order: the same tiles of 32 rows per
+wavefront, one rounding of the sum -- the branches' own gradients agree bit for bit where both orders give a row the
+same key blocks, and everything agrees with the oracle in the parity tests, which run both orders."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2603_17484_amd import binding as B
+from paper_2603_17484_amd.runner import layer_from_numpy, to_device, to_host
+from tests.gpu_helpers import make_case, run_and_check
+from tests.tolerance import compare
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("separate", [False, True])
+@pytest.mark.parametrize("T,W,Hm,f", [(1, 0, 1, 1.0), (127, 5, 1, 0.0), (129, 200, 4, 1.0), (700, 64, 4, 0.02), (1300, 1300, 1, 0.3)])
+def test_pair_against_the_oracle(oracle, T, W, Hm, f, separate):
+    run_and_check(oracle, make_case(B_=2, T=T, Hq=4, Hkv=2, W=W, Hm=Hm, f=f, seed=T + 5), separate=separate, twice=True)
+
+
+def test_pair_and_sequential_agree():
+    x = make_case(B_=2, T=1500, Hq=14, Hkv=2, W=300, Hm=14, f=0.1, seed=77)
+    got = {}
+    for flags in (0, B.L2A_FLAG_SEQUENTIAL):
+        lay = layer_from_numpy(x.q, x.k, x.v, x.mask, x.w.W, "bf16", flags, guard=True)
+        lay.route()
+        lay.forward()
+        lay.backward(to_device(x.dO, "bf16"), want_delta=True)
+        torch.cuda.synchronize()
+        lay.alloc.check()
+        got[flags] = [to_host(t) for t in (lay.dq, lay.dk, lay.dv, lay.delta_g)]
+    for name, a, b in zip(("dq", "dk", "dv"), got[0], got[B.L2A_FLAG_SEQUENTIAL]):
+        compare(name, a, b, "bf16")
+    # sums of at most 1500 products in another grouping of the same fp32 terms
+    assert np.abs(got[0][3] - got[B.L2A_FLAG_SEQUENTIAL][3]).max() <= 1e-4
