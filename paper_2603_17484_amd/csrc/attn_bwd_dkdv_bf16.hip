@@ -62,7 +62,8 @@ struct PairArgs {
     const __bf16* v;
     __bf16* dk;
     __bf16* dv;
-    int nsplit;             // workgroups per key block (grid.z): each takes a share of the row tiles
+    int groups;             // > 0: the launch order head_job with that many XCD groups (one-dimensional grid)
+    int nsplit;             // workgroups per key block: each takes a share of the row tiles
     float* part;            // nsplit > 1: partial sums [nsplit][2][B, T, Hkv, D] instead of dk, dv
 };
 
@@ -81,8 +82,10 @@ __global__ __launch_bounds__(64 * kPairWaves) void bwd_dkdv_kernel(PairArgs a) {
     __shared__ __attribute__((aligned(16))) u32x4 lds_p[2][4][2][64];
 
     const Geom& gm = a.gm;
-    const int bh = blockIdx.y, b = bh / gm.Hkv, hk = bh - b * gm.Hkv;
-    const int kblk = walk::key_block((int)blockIdx.x, a.chunk);  // XCD-aware: chunks of neighbours, snake order
+    // XCD-aware: whole heads, or chunks of neighbouring key blocks in snake order
+    const walk::Job job = a.groups ? walk::head_job((int)blockIdx.x, (gm.T + kKeysPerWg - 1) / kKeysPerWg, a.groups, a.nsplit)
+                                   : walk::Job{(int)blockIdx.y, walk::key_block((int)blockIdx.x, a.chunk), 0};
+    const int bh = job.bh, b = bh / gm.Hkv, hk = bh - b * gm.Hkv, kblk = job.kblk;
     const int k0 = kblk * kKeysPerWg;
     if (k0 >= a.gm.T) return;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -115,10 +118,12 @@ __global__ __launch_bounds__(64 * kPairWaves) void bwd_dkdv_kernel(PairArgs a) {
             f_lo = first[k0 >> 6];
             f_hi = first[min((k0 + kKeysPerWg) >> 6, nkb)];
         }
-        return walk::tile_runs(kind, k0, gm.T, gm.G, gm.W, f_lo, f_hi, rows, a.nsplit, (int)blockIdx.z);
+        return walk::tile_runs(kind, k0, gm.T, gm.G, gm.W, f_lo, f_hi, rows, a.nsplit, job.z);
     };
-    const walk::Plan plan = walk::make_plan(a.nsets, tile_runs(0), a.rs[0].local != 0, tile_runs(1),
-                                            a.nsets > 1 && a.rs[1].local != 0, kblk, a.chunk, gm.T, gm.G, a.set_stride);
+    const bool down = a.groups && walk::walk_down(kblk, a.chunk, gm.T, gm.W);
+    const walk::Plan plan = walk::make_plan(a.nsets, tile_runs(0), a.rs[0].local != 0 && !down, tile_runs(1),
+                                            a.nsets > 1 && a.rs[1].local != 0 && !down, kblk, a.chunk, gm.T, gm.G,
+                                            a.set_stride);
     const int total = plan.total;
 
     // ---- loads (second role).  A cursor names the tile of each step (advanced once per step, branch-free);
@@ -399,7 +404,7 @@ __global__ __launch_bounds__(64 * kPairWaves) void bwd_dkdv_kernel(PairArgs a) {
                 const size_t off = (((size_t)b * gm.T + kk) * gm.Hkv + hk) * kD + d * 32 + n;
                 if (a.nsplit > 1) {
                     const size_t elems = (size_t)gm.B * gm.T * gm.Hkv * kD;
-                    float* pz = a.part + (size_t)blockIdx.z * 2 * elems + (second ? 0 : elems);
+                    float* pz = a.part + (size_t)job.z * 2 * elems + (second ? 0 : elems);
                     pz[off] = acc[d][e] * out_scale;
                 } else {
                     (second ? a.dk : a.dv)[off] = (__bf16)(acc[d][e] * out_scale);
@@ -423,7 +428,7 @@ __global__ __launch_bounds__(kThreads) void dkdv_reduce_kernel(const float* __re
 }  // namespace
 
 // Workgroups per key block (short sequences share a key block's row tiles between several)
-int dkdv_splits(const Geom& g) { return walk::launch_shape(g.T, (long long)g.B * g.Hkv).nsplit; }
+int dkdv_splits(const Geom& g) { return walk::host_launch(g.T, (long long)g.B * g.Hkv, g.W).nsplit; }
 
 // packed[s]: compact copies of set s made by pack_rows (5 pointers in the order of PackedRows).
 // With two sets every array of the second must lie the same number of bytes after the first's.
@@ -447,12 +452,13 @@ int mfma_bwd_dkdv(const Geom& g, const RowSet* sets, int nsets, const void* cons
     a.v = (const __bf16*)v;
     a.dk = (__bf16*)dk;
     a.dv = (__bf16*)dv;
-    const walk::LaunchShape shape = walk::launch_shape(g.T, (long long)g.B * g.Hkv);
-    a.chunk = shape.chunk;
-    a.nsplit = shape.nsplit;
+    const walk::Launch l = walk::host_launch(g.T, (long long)g.B * g.Hkv, g.W);
+    a.groups = l.groups;
+    a.chunk = l.chunk;
+    a.nsplit = l.nsplit;
     a.part = part;
     if (a.nsplit > 1 && !part) return L2A_ERR_WORKSPACE;
-    const dim3 grid(shape.grid_x, g.B * g.Hkv, a.nsplit);
+    const dim3 grid = l.groups ? dim3(l.jobs) : dim3(walk::launch_shape(g.T, (long long)g.B * g.Hkv).grid_x, g.B * g.Hkv);
     {
         KernelTimer kt("bwd_dkdv", st);
         hipLaunchKernelGGL(bwd_dkdv_kernel, grid, dim3(64 * kPairWaves), 0, st, a);

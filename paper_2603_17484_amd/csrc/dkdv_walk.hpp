@@ -54,6 +54,57 @@ inline LaunchShape launch_shape(int T, long long batch_x_kv_heads) {
     return s;
 }
 
+// The other launch order, for few key blocks: whole (b, KV head)s per XCD instead of chunks of key blocks.
+// gcd(heads, 8) groups of XCDs take every gcd-th head; the XCDs of a group share its heads' key blocks by
+// residue, so all XCDs get the same work.  On an XCD the jobs run head by head, longest key blocks (the first
+// ones) first, the splits of a key block next to each other: what is left at the end is short, and the resident
+// workgroups belong to one head and read its rows through one L2.  Jobs of the one-dimensional grid are numbered as
+// dispatched (XCD = job mod 8); kblk may lie past the last block (rounding): such a job is empty.
+struct Job {
+    int bh, kblk, z;
+};
+L2A_WALK_FN int xcd_groups(int heads) { return (heads & 7) == 0 ? 8 : (heads & 3) == 0 ? 4 : (heads & 1) == 0 ? 2 : 1; }
+L2A_WALK_FN int head_jobs(int nblk, int groups, int nsplit) { return (nblk * groups + 7) / 8 * nsplit; }  // of a head on one XCD
+L2A_WALK_FN Job head_job(int lin, int nblk, int groups, int nsplit) {
+    const int x = lin & 7, j = lin >> 3, per = head_jobs(nblk, groups, nsplit);
+    const int i = j / per, r = j - i * per, kb = r / nsplit;
+    return Job{x % groups + groups * i, kb * (8 / groups) + x / groups, r - kb * nsplit};
+}
+
+// What the host launches: the order of head_job where groups > 0, else the one of key_block.
+// With chunks, adjacent workgroups walk a head's rows at different places and few of their loads meet in L2 (T = 4096:
+// 3 % hits), which is why splitting key blocks used to gain nothing there.  By head and split, kernel and reduction, us,
+// against chunks: 8 heads (G = 4) T = 4096 349 / 450, T = 8192 (T <= 2 W) 1011 / 1165; 4 heads (G = 7) T = 4096 322 / 446,
+// T = 8192 969 / 994, its W = 1024 form 452 / 502, T = 16384 2348 / 2589 and 1174 / 1354 (unsplit); 1 head (G = 6) T = 32768
+// 1318 / 1548.  With more key blocks than two per compute unit the chunks fill the chip evenly and are as good or better (4
+// heads: T = 24576 4120 against 4243, T = 32768 with W = 1024 3517 / 3571, T = 65536 16930 / 17680), except where
+// every XCD has heads of its own (8 heads: T = 12288 1814 / 1894, T = 16384 2705 / 2824).
+struct Launch {
+    int nblk, groups, chunk, nsplit, jobs;  // jobs: workgroups of the one-dimensional grid where groups > 0
+};
+inline Launch host_launch(int T, long long batch_x_kv_heads, int W) {
+    const LaunchShape s = launch_shape(T, batch_x_kv_heads);
+    const long long blocks = (long long)s.nblk * batch_x_kv_heads;
+    Launch l{s.nblk, 0, s.chunk, s.nsplit, 0};
+    const int groups = batch_x_kv_heads > 1024 ? 0 : xcd_groups((int)batch_x_kv_heads);
+    if (groups == 0 || blocks > (groups == 8 ? 1024 : 512)) return l;
+    l.groups = groups;
+    // Split until there are two workgroups per compute unit, four where the key blocks' lengths differ most (a window
+    // of half the sequence or more).  One head per XCD and a short window are even as they are (8 heads,
+    // T = 4096, W = 1024: 216 unsplit, 218 + 15 split).
+    const bool uneven = (long long)T <= 2ll * W;
+    if (l.nsplit == 1 && (uneven ? blocks < 1024 : blocks < 512 && groups < 8)) l.nsplit = 2;
+    l.chunk = imax(1, 32 * (8 / groups) / l.nsplit);  // the key blocks at work on an XCD group
+    l.jobs = 8 * (int)(batch_x_kv_heads / groups) * head_jobs(s.nblk, groups, l.nsplit);
+    return l;
+}
+
+// Local rows may be walked downwards like the Global ones where every key block of the chunk sees rows up to the end
+// of the sequence: all its workgroups then start on the same tile and merely stop at different ones.
+L2A_WALK_FN bool walk_down(int kblk, int chunk, int T, int W) {
+    return (long long)(kblk / chunk * chunk + 1) * kKeysPerWg + W >= T;
+}
+
 // Row sets as the walk sees them.
 enum RowKind { kLocalRows = 0, kDenseRows = 1, kListRows = 2 };
 
