@@ -53,7 +53,7 @@ struct SdP {
 // wavefronts and the Local rows (every twentieth block masked) with 4.
 // (bx, by) of (gx, nbh): the workgroup's index in its branch's part of the grid (a launch may carry both branches)
 typedef __bf16 DqLds[2][3][kBK * 128];
-template <bool LOCAL, int NW>
+template <bool LOCAL, int NW, bool PAIR>
 __device__ __forceinline__ void dq_body(const DqArgs& a, const int bx, const int by, const int gx, const int nbh,
                                         DqLds& lds_kv) {
     constexpr int kNW = NW;
@@ -169,9 +169,6 @@ __device__ __forceinline__ void dq_body(const DqArgs& a, const int bx, const int
         unsigned kdst, vdst;
         int krows;  // rows of the K, V block that exist
     };
-    unsigned tr_off[4][2];  // this lane's part of the transposed reads' addresses
-#pragma unroll
-    for (int d = 0; d < 4; ++d) tr_off[d][0] = rm_tr_col_offset(d, 0, lane), tr_off[d][1] = rm_tr_col_offset(d, 1, lane);
     auto issue_block_load = [&](const BlockLoads& L, auto ic) __attribute__((always_inline)) {
         constexpr int i = decltype(ic)::value;
         constexpr int j = i % kNL;
@@ -292,19 +289,20 @@ __device__ __forceinline__ void dq_body(const DqArgs& a, const int bx, const int
 
     // K, V blocks rotate through three buffers: block jb in buf, jb+1 in buf1, and the block loaded now, jb+2, in buf2
     int buf = 0, buf1 = 1, buf2 = 2;
+    // The block's K, read transposed for dQ += dS K: addresses of this lane's pieces, moved along with the buffers (the
+    // offsets kept besides them would cost eight registers, and the loop over unmasked blocks would spill)
+    lds_cptr trp[4][2];
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        trp[d][0] = (lds_cptr)(uintptr_t)(lds_k0 + rm_tr_col_offset(d, 0, lane));
+        trp[d][1] = (lds_cptr)(uintptr_t)(lds_k0 + rm_tr_col_offset(d, 1, lane));
+    }
     auto run = [&](auto mask_tag, int j_begin, int j_end) __attribute__((always_inline)) {
         for (int jb = j_begin; jb < j_end; ++jb) {
             // prefetch: K, V of block jb+2 (their buffer held block jb-1), issued in the slots of the first
             // half-block where the VALU has nothing to do.  Past the last block the last one is loaded again, into buffers nobody reads any more.
             const int jk = min(jb + 2, jb1);
             {  // wavefronts whose rows all lie past the end compute on a repeated row and store nothing
-                // this block's K, read transposed for dQ += dS K: this lane's pieces of the reads, for both half-blocks
-                lds_cptr trp[4][2];
-#pragma unroll
-                for (int d = 0; d < 4; ++d) {
-                    trp[d][0] = (lds_cptr)(uintptr_t)(lds_offset(&lds_k[buf][0]) + tr_off[d][0]);
-                    trp[d][1] = (lds_cptr)(uintptr_t)(lds_offset(&lds_k[buf][0]) + tr_off[d][1]);
-                }
                 BlockLoads L;
                 half_block(mask_tag, Int<0>{}, Xa, Xb, &lds_k[buf][0], 32, trp, jb * kBK, [&](auto mc) {
                     constexpr int mm = decltype(mc)::value;
@@ -323,6 +321,9 @@ __device__ __forceinline__ void dq_body(const DqArgs& a, const int bx, const int
             }
             dma_wait();
             __syncthreads();
+            const int step = (buf1 - buf) * (kBK * 256);
+#pragma unroll
+            for (int d = 0; d < 4; ++d) trp[d][0] += step, trp[d][1] += step;
             const int t = buf;
             buf = buf1, buf1 = buf2, buf2 = t;
         }
@@ -347,11 +348,11 @@ __device__ __forceinline__ void dq_body(const DqArgs& a, const int bx, const int
             const size_t off = row_off + 4 * h + d * 32 + 8 * rg;
             f32x4 x = {acc[d][4 * rg + 0] * gm.scale, acc[d][4 * rg + 1] * gm.scale, acc[d][4 * rg + 2] * gm.scale,
                        acc[d][4 * rg + 3] * gm.scale};
-            if (a.wide_out) {
+            if (PAIR && a.wide_out) {
                 *reinterpret_cast<f32x4*>(a.wide_out + off) = x;
                 continue;
             }
-            if (a.accumulate) {
+            if (!PAIR && a.accumulate) {
                 const bf16x4 old = *reinterpret_cast<const bf16x4*>(a.dq + off);
                 x += __builtin_convertvector(old, f32x4);
             }
@@ -363,7 +364,7 @@ __device__ __forceinline__ void dq_body(const DqArgs& a, const int bx, const int
 template <bool LOCAL, int NW>
 __global__ __launch_bounds__(64 * NW) void bwd_dq_kernel(DqArgs a) {
     __shared__ __attribute__((aligned(1024))) DqLds lds_kv;
-    dq_body<LOCAL, NW>(a, (int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x, (int)gridDim.y, lds_kv);
+    dq_body<LOCAL, NW, false>(a, (int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x, (int)gridDim.y, lds_kv);
 }
 
 // Both branches in one launch, for sequences so short that the Global rows' tiles alone leave most compute units idle:
@@ -372,9 +373,9 @@ template <int NW>
 __global__ __launch_bounds__(64 * NW) void bwd_dq_pair_kernel(DqArgs ag, DqArgs al, int gx_global) {
     __shared__ __attribute__((aligned(1024))) DqLds lds_kv;
     if ((int)blockIdx.x < gx_global)
-        dq_body<false, NW>(ag, (int)blockIdx.x, (int)blockIdx.y, gx_global, (int)gridDim.y, lds_kv);
+        dq_body<false, NW, true>(ag, (int)blockIdx.x, (int)blockIdx.y, gx_global, (int)gridDim.y, lds_kv);
     else
-        dq_body<true, NW>(al, (int)blockIdx.x - gx_global, (int)blockIdx.y, (int)gridDim.x - gx_global, (int)gridDim.y,
+        dq_body<true, NW, true>(al, (int)blockIdx.x - gx_global, (int)blockIdx.y, (int)gridDim.x - gx_global, (int)gridDim.y,
                           lds_kv);
 }
 
