@@ -2,7 +2,8 @@
 // (the "consolidate active queries" preprocessing of the sparse kernel, Sec. 3.2 and App. C
 // Alg. 1 step 1; its cost is part of the kernel's time, App. D.1).
 //
-// Two launches, no host read-back, no spin waits:
+// Two launches, no host read-back, no spin waits (one for short sequences, whose workgroups count the rows before
+// theirs themselves):
 //   1. route_count : every workgroup counts the routed rows of its chunk of positions;
 //   2. route_write : every workgroup sums the counts of the chunks before it (at most a few
 //      hundred integers), then walks its chunk 256 positions at a time; inside a wavefront a
@@ -53,6 +54,28 @@ __device__ __forceinline__ int block_sum(int v, int* lds4) {
     return lds4[0] + lds4[1] + lds4[2] + lds4[3];
 }
 
+// bytes that are not zero among the four of x
+__device__ __forceinline__ int nonzero_bytes(uint32_t x) {
+    return __popc((((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x) & 0x80808080u);
+}
+// this thread's part of the number of set bytes in m[0 .. n), 16 at a time between the aligned addresses
+__device__ __forceinline__ int count_set(const uint8_t* m, int n) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    const int head = min(n, (int)(-(uintptr_t)m & 15)), nv = (n - head) / 16, tail = n - head - 16 * nv;
+    const int t = threadIdx.x;
+    int c = 0;
+    if (t < head) c += m[t] != 0;
+    if (t < tail) c += m[head + 16 * nv + t] != 0;
+    for (int i = t; i < nv; i += kThreads) {
+        const u32x4 x = *reinterpret_cast<const u32x4*>(m + head + 16 * i);
+        c += nonzero_bytes(x[0]) + nonzero_bytes(x[1]) + nonzero_bytes(x[2]) + nonzero_bytes(x[3]);
+    }
+    return c;
+}
+// Mask bytes up to which every workgroup of the second kernel counts for itself (its own KV head's rows, T for each
+// distinct one) and the first is not launched (T = 1001, one mask row: 2.6 + 4.8 us -> 4.8; beyond it the counting of one workgroup is the longer).
+constexpr int kSelfCountBytes = 32768;
+
 __global__ __launch_bounds__(kThreads) void route_count_kernel(RouteArgs a) {
     __shared__ int lds4[4];
     const int chunk = blockIdx.x, bh = blockIdx.y;
@@ -81,10 +104,21 @@ __global__ __launch_bounds__(kThreads) void route_write_kernel(RouteArgs a) {
 
     // rows before this chunk, and rows in total
     int before = 0, all = 0;
-    for (int c = threadIdx.x; c < a.nchunks; c += kThreads) {
-        const int v = a.chunk_cnt[(size_t)bh * a.nchunks + c];
-        all += v;
-        if (c < chunk) before += v;
+    if (a.chunk_cnt) {
+        for (int c = threadIdx.x; c < a.nchunks; c += kThreads) {
+            const int v = a.chunk_cnt[(size_t)bh * a.nchunks + c];
+            all += v;
+            if (c < chunk) before += v;
+        }
+    } else {
+        const int gdistinct = (a.Hm == a.Hq) ? G : 1, at = chunk * a.chunk;
+        for (int g = 0; g < gdistinct; ++g) {
+            const uint8_t* m = mask_row(a, b, hk, g);
+            before += count_set(m, at);
+            all += count_set(m + at, a.T - at);
+        }
+        if (a.Hm != a.Hq) before *= G, all *= G;  // rows contributed by one set byte
+        all += before;
     }
     before = block_sum(before, lds4);
     all = block_sum(all, lds4);
@@ -193,7 +227,9 @@ int route_compact(const l2a_params& p, const uint8_t* mask, int32_t* row_idx, in
     a.nkb = (p.T + 63) / 64;
     if (a.G > kMaxG) return L2A_ERR_UNSUPPORTED;
     const dim3 grid(a.nchunks, p.B * p.Hkv);
-    {
+    if ((long long)a.T * (a.Hm == a.Hq ? a.G : 1) <= kSelfCountBytes) {
+        a.chunk_cnt = nullptr;
+    } else {
         KernelTimer kt("route_count", st);
         hipLaunchKernelGGL(route_count_kernel, grid, dim3(kThreads), 0, st, a);
     }
