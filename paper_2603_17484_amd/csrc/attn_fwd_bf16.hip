@@ -58,15 +58,16 @@ struct ScoresT {
 template <int V>
 using Int = std::integral_constant<int, V>;
 
-// NW wavefronts of NQB x 32 rows each (NW * NQB = 8): 4 x 2 runs one wavefront per SIMD with 500 registers,
+// NW wavefronts of NQB x 32 rows each.  256 rows (NW * NQB = 8): 4 x 2 runs one wavefront per SIMD with 500 registers,
 // 8 x 1 runs two per SIMD with 256 each, so that one wavefront's softmax arithmetic can overlap the
 // other's matrix instructions.
 // (bx, by) of (gx, nbh): the workgroup's index in its branch's part of the grid (a launch may carry both branches)
 template <bool LOCAL, int NQB, int NW>
 __device__ __forceinline__ void fwd_body(const FwdArgs& a, const int bx, const int by, const int gx, const int nbh,
                                          __bf16 (&lds_k)[3][kBK * 128], __bf16 (&lds_v)[2][kD * kBK]) {
-    static_assert(NW * NQB * 32 == kBQ, "a workgroup covers kBQ rows");
     constexpr int RW = 32 * NQB;       // rows per wavefront
+    constexpr int BQ = RW * NW;        // rows per workgroup: a fix-up tile, or a whole part of one
+    static_assert(kBQ % BQ == 0, "a workgroup's rows lie in one fix-up tile");
     constexpr int NS = 16 * NQB;       // slots (matrix instructions) per half-block: NS / 2 for S, NS / 2 for P V
     constexpr int NL = 16 / NW;        // 16-byte loads a wavefront issues per K or V block
     constexpr int kLoadSlot0 = NS - 1 - 2 * NL;  // the loads of later blocks go out in the last slots of a block's first half
@@ -99,7 +100,7 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const int bx, const i
     }
     const int b = bh / gm.Hkv, hk = bh - b * gm.Hkv;
     const int n_rows = rows_total(a.rs, gm, bh);
-    const int n_tiles = (n_rows + kBQ - 1) / kBQ;
+    const int n_tiles = (n_rows + BQ - 1) / BQ;
     const int tile = by_range ? rank : n_tiles - 1 - rank;
     if (tile < 0 || tile >= n_tiles) return;
 
@@ -107,8 +108,8 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const int bx, const i
     const int n = lane & 31, h = lane >> 5;
 
     // ---- rows of this workgroup / wavefront / lane
-    const int wg_r0 = tile * kBQ;
-    const int wg_r1 = min(wg_r0 + kBQ, n_rows);  // exclusive
+    const int wg_r0 = tile * BQ;
+    const int wg_r1 = min(wg_r0 + BQ, n_rows);  // exclusive
     const int wg_pmin = row_code(a.rs, gm, bh, wg_r0) / gm.G;
     const int wg_pmax = row_code(a.rs, gm, bh, wg_r1 - 1) / gm.G;
     const int wv_r0 = wg_r0 + wave * RW;
@@ -131,8 +132,10 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const int bx, const i
     }
 
     // ---- block range of the workgroup, and its three runs: blocks that need the window-start
-    // mask (LOCAL only), blocks no row of the tile needs a mask for, blocks on the causal diagonal
-    const int jb0 = LOCAL ? max(wg_pmin - gm.W, 0) / kBK : 0;
+    // mask (LOCAL only), blocks no row of the tile needs a mask for, blocks on the causal diagonal.  Parts of a
+    // fix-up tile start where the whole one would: a row's reference, and so its bits, are the same either way.
+    const int pmin_all = BQ == kBQ ? wg_pmin : row_code(a.rs, gm, bh, wg_r0 / kBQ * kBQ) / gm.G;
+    const int jb0 = LOCAL ? max(pmin_all - gm.W, 0) / kBK : 0;
     const int jb1 = wg_pmax / kBK;  // inclusive
     int j_mid = jb0;                // first block without window-start masking
     if (LOCAL) j_mid = min(jb1 + 1, max(jb0, (max(wg_pmax - gm.W, 0) + kBK - 1) / kBK));
@@ -380,7 +383,7 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const int bx, const i
     if (bad) *vote = 1;
     __syncthreads();
     if (*vote) {
-        if (threadIdx.x == 0) a.redo[(size_t)bh * gx + tile] = 1;
+        if (threadIdx.x == 0) a.redo[(size_t)bh * (gx / (kBQ / BQ)) + tile / (kBQ / BQ)] = 1;
         return;
     }
 
@@ -434,7 +437,7 @@ __global__ __launch_bounds__(64 * NW) void fwd_kernel(FwdArgs a) {
 // writes its rows of A only (in fp32, besides the caller's bf16 copy), and O = S + A is formed
 // afterwards (merge_rows) with the one rounding the sequential order has.
 template <int NQB, int NW>
-__global__ __launch_bounds__(64 * NW) void fwd_pair_kernel(FwdArgs ag, FwdArgs al, int gx_global) {
+__global__ __launch_bounds__(64 * NW, 2) void fwd_pair_kernel(FwdArgs ag, FwdArgs al, int gx_global) {
     __shared__ __attribute__((aligned(1024))) __bf16 lds_k[3][kBK * 128];
     __shared__ __attribute__((aligned(1024))) __bf16 lds_v[2][kD * kBK];
     if ((int)blockIdx.x < gx_global)
@@ -448,21 +451,21 @@ __global__ __launch_bounds__(64 * NW) void fwd_pair_kernel(FwdArgs ag, FwdArgs a
 // row's fixed reference by so much that a row sum left the safe range).  Same tiling, classical
 // streaming softmax with a running maximum and rescaling (App. C Alg. 1 as printed, with the
 // rescaling factor read as exp(m_old - m_new)); V is transposed on its way into LDS.
+typedef __bf16 FixK[2][kTileRows * kRowPad];
+typedef __bf16 FixV[2][kD * kColPad];
 template <bool LOCAL>
-__global__ __launch_bounds__(kThreads) void fwd_fixup_kernel(FwdArgs a) {
+__device__ __forceinline__ void fixup_body(const FwdArgs& a, const int bx, const int gx, FixK& lds_k, FixV& lds_v) {
     constexpr int NQB = kNQB;
     constexpr int RW = 32 * NQB;
     constexpr int BQ = 4 * RW;
-    __shared__ __attribute__((aligned(16))) __bf16 lds_k[2][kTileRows * kRowPad];
-    __shared__ __attribute__((aligned(16))) __bf16 lds_v[2][kD * kColPad];
 
     const Geom& gm = a.gm;
     const int bh = blockIdx.y, b = bh / gm.Hkv, hk = bh - b * gm.Hkv;
     const int n_rows = rows_total(a.rs, gm, bh);
     const int n_tiles = (n_rows + BQ - 1) / BQ;
-    if ((int)blockIdx.x >= n_tiles) return;
-    const int tile = n_tiles - 1 - (int)blockIdx.x;
-    if (!a.redo[(size_t)bh * gridDim.x + tile]) return;
+    if (bx >= n_tiles) return;
+    const int tile = n_tiles - 1 - bx;
+    if (!a.redo[(size_t)bh * gx + tile]) return;
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int n = lane & 31, h = lane >> 5;
@@ -670,6 +673,25 @@ __global__ __launch_bounds__(kThreads) void fwd_fixup_kernel(FwdArgs a) {
     }
 }
 
+template <bool LOCAL>
+__global__ __launch_bounds__(kThreads) void fwd_fixup_kernel(FwdArgs a) {
+    __shared__ __attribute__((aligned(16))) FixK lds_k;
+    __shared__ __attribute__((aligned(16))) FixV lds_v;
+    fixup_body<LOCAL>(a, (int)blockIdx.x, (int)gridDim.x, lds_k, lds_v);
+}
+__global__ __launch_bounds__(kThreads) void fwd_fixup_pair_kernel(FwdArgs ag, FwdArgs al, int gx) {
+    __shared__ __attribute__((aligned(16))) FixK lds_k;
+    __shared__ __attribute__((aligned(16))) FixV lds_v;
+    if ((int)blockIdx.x < gx) fixup_body<false>(ag, (int)blockIdx.x, gx, lds_k, lds_v);
+    else fixup_body<true>(al, (int)blockIdx.x - gx, gx, lds_k, lds_v);
+}
+
+// One launch for both branches: workgroups of 128 rows up to this many 256-row tiles of a branch.  The longest tile's
+// walk sets the time of a short sequence, and half of it takes less; in longer ones every block of K and V
+// passes through LDS twice as often for nothing.  Measured, whole forward, 256 / 128 rows, us (28 / 4 heads, W = 4096): T =
+// 512 43.8 / 37.9, 1001 56.0 / 49.3, 2048 (224 tiles) 81.1 / 75.8, 4096 (448) 184.6 / 180.1, 8192 (896) 474.0 / 476.8, 16384
+// 1192 / 1214; 32 / 8 heads, W = 1024: T = 4096 (512) 136.3 / 135.9, 16384 588 / 574.
+bool half_tiles(size_t tiles) { return tiles <= 512; }
 
 }  // namespace
 
@@ -701,7 +723,7 @@ int mfma_fwd(const Geom& g, const RowSet& rs, const void* q, const void* k, cons
 }
 
 // Both branches at once (fwd_pair_kernel): the Global branch's result goes to out_g.wide_out, and
-// neither branch may write where the other does.  redo: 2 x mfma_fwd_redo_entries flags.
+// neither branch may write where the other does.  redo: 2 x mfma_fwd_redo_entries flags, set to zero.
 int mfma_fwd_pair(const Geom& g, const RowSet& rs_l, const void* q_l, const void* k_l, const void* v_l,
                   const void* vt_l, const FwdOut& out_l, const RowSet& rs_g, const void* q_g, const void* k_g,
                   const void* v_g, const void* vt_g, const FwdOut& out_g, int vt_cap, int32_t* redo, hipStream_t st) {
@@ -713,20 +735,17 @@ int mfma_fwd_pair(const Geom& g, const RowSet& rs_l, const void* q_l, const void
     FwdArgs al{g, rs_l, (const __bf16*)q_l, (const __bf16*)k_l, (const __bf16*)v_l, (const __bf16*)vt_l, vt_cap, redo, out_l};
     FwdArgs ag{g, rs_g, (const __bf16*)q_g, (const __bf16*)k_g, (const __bf16*)v_g, (const __bf16*)vt_g, vt_cap,
                redo + entries, out_g};
-    int r = fill_zero(redo, sizeof(int32_t) * 2 * entries, st);
-    if (r != L2A_OK) return r;
     {
         KernelTimer kt("fwd_pair", st);
-        hipLaunchKernelGGL((fwd_pair_kernel<kFwdNQB, kFwdNW>), dim3(2 * gx, g.B * g.Hkv), dim3(64 * kFwdNW), 0, st, ag, al,
-                           (int)gx);
+        if (half_tiles(entries))
+            hipLaunchKernelGGL((fwd_pair_kernel<1, 4>), dim3(4 * gx, g.B * g.Hkv), dim3(256), 0, st, ag, al, (int)(2 * gx));
+        else
+            hipLaunchKernelGGL((fwd_pair_kernel<kFwdNQB, kFwdNW>), dim3(2 * gx, g.B * g.Hkv), dim3(64 * kFwdNW), 0, st, ag,
+                               al, (int)gx);
     }
     {
-        KernelTimer kt("fwd_local_fixup", st);
-        hipLaunchKernelGGL((fwd_fixup_kernel<true>), dim3(gx, g.B * g.Hkv), dim3(kThreads), 0, st, al);
-    }
-    {
-        KernelTimer kt("fwd_global_fixup", st);
-        hipLaunchKernelGGL((fwd_fixup_kernel<false>), dim3(gx, g.B * g.Hkv), dim3(kThreads), 0, st, ag);
+        KernelTimer kt("fwd_pair_fixup", st);
+        hipLaunchKernelGGL(fwd_fixup_pair_kernel, dim3(2 * gx, g.B * g.Hkv), dim3(kThreads), 0, st, ag, al, (int)gx);
     }
     return launch_status();
 }

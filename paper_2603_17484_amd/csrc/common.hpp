@@ -109,7 +109,7 @@ int fill_f32(float* ptr, size_t n, float value, hipStream_t st);
 int mfma_fwd(const Geom& g, const RowSet& rs, const void* q, const void* k, const void* v, const void* vt,
              int vt_cap, int32_t* redo, const FwdOut& out, hipStream_t st);
 size_t mfma_fwd_redo_entries(const Geom& g);
-// both branches in one launch; out_g must not merge; redo: 2 x mfma_fwd_redo_entries(g) int32
+// both branches in one launch; out_g must not merge; redo: 2 x mfma_fwd_redo_entries(g) int32, all zero
 int mfma_fwd_pair(const Geom& g, const RowSet& rs_l, const void* q_l, const void* k_l, const void* v_l,
                   const void* vt_l, const FwdOut& out_l, const RowSet& rs_g, const void* q_g, const void* k_g,
                   const void* v_g, const void* vt_g, const FwdOut& out_g, int vt_cap, int32_t* redo, hipStream_t st);
@@ -121,7 +121,14 @@ int mfma_decode(const Geom& g, const void* q, const void* k, const void* v, cons
                 float* lse_g, hipStream_t st);
 
 // ---- pack.hip : layout pre-passes (token-minor copies for the matrix-core kernels)
-int pack_kv(const Geom& g, const void* x, void* xt, int cap, hipStream_t st);
+struct Fill {  // n 32-bit words of one value
+    uint32_t* p;
+    size_t n;
+    uint32_t value;
+};
+// one or two V tensors; up to three buffers are filled by the same launch
+int pack_kv(const Geom& g, int n, const void* const* x, void* const* xt, int cap, const Fill* fills, int nfills,
+            hipStream_t st);
 // O += A on the rows of rs (O bf16, A fp32, D = 128)
 int merge_rows(const Geom& g, const RowSet& rs, const float* A, void* O, hipStream_t st);
 int pack_rows(const Geom& g, const RowSet& rs, const void* q, const void* dO, const float* lse, const float* delta,

@@ -212,19 +212,28 @@ int l2a_attn_fwd(const l2a_params* p, const void* q_loc, const void* k_loc, cons
     // matrix-core path: token-minor copy of each distinct V (layout pre-pass, one pass over V)
     char* vt_loc = (char*)workspace;
     char* vt_glb = vt_loc;
+    const bool pair = pair_fwd(*p);
     if (mfma) {
-        if (do_local && (r = pack_kv(g, v_loc, vt_loc, kv_cap(*p), st)) != L2A_OK) return r;
+        const void* vs[2];
+        void* vts[2];
+        int nv = 0;
+        if (do_local) vs[nv] = v_loc, vts[nv++] = vt_loc;
         if (do_global && (!do_local || v_glb != v_loc)) {
             vt_glb = (char*)workspace + kv_copy_bytes(*p);
-            if ((r = pack_kv(g, v_glb, vt_glb, kv_cap(*p), st)) != L2A_OK) return r;
+            vs[nv] = v_glb, vts[nv++] = vt_glb;
         }
+        Fill fills[3];
+        int nf = 0;
+        if (pair) {  // flags of the tiles to be computed again; what the Global branch leaves for tokens it never visits
+            fills[nf++] = Fill{(uint32_t*)((char*)workspace + 2 * kv_copy_bytes(*p)), 2 * mfma_fwd_redo_entries(g), 0u};
+            fills[nf++] = Fill{(uint32_t*)lse_global, stat_elems(*p), 0xff800000u};  // -inf
+            if (A_opt) fills[nf++] = Fill{(uint32_t*)A_opt, q_elems(*p) / 2, 0u};
+        }
+        if ((r = pack_kv(g, nv, vs, vts, kv_cap(*p), fills, nf, st)) != L2A_OK) return r;
     }
-    if (pair_fwd(*p)) {
+    if (pair) {
         char* after_v = (char*)workspace + 2 * kv_copy_bytes(*p);
         float* A32 = (float*)(after_v + 2 * redo_bytes(*p));
-        // tokens the Global branch never visits
-        if (A_opt && (r = fill_zero(A_opt, q_elems(*p) * elem_bytes(*p), st)) != L2A_OK) return r;
-        if ((r = fill_f32(lse_global, stat_elems(*p), -INFINITY, st)) != L2A_OK) return r;
         const RowSet rs_l{nullptr, nullptr, nullptr, 1};
         const RowSet rs_g{row_idx, count, kblk_first_row, 0};
         const FwdOut out_l{O, S_opt, lse_local, nullptr, nullptr, 0};

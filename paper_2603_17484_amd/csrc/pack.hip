@@ -30,13 +30,31 @@ struct PackArgs {
     float* delta_c;
     int32_t* pos_c;       // position of the row, -1 for padding
     int cap;              // rows per (b, kv head) in the outputs; multiple of 64
+    Fill fill[3];         // buffers to be filled on the way
 };
+
+// A launch costs a short forward as much as the kernel it carries (about 3 us each), so the constants that its
+// kernels expect are written by the workgroups of the one that runs first.  16-byte stores where the buffer allows.
+__device__ __forceinline__ void run_fill(const Fill& f) {
+    const size_t step = (size_t)gridDim.x * gridDim.y * kThreads;
+    size_t i = ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * kThreads + threadIdx.x;
+    size_t done = 0;
+    if (((uintptr_t)f.p & 15) == 0) {
+        const u32x4 v = {f.value, f.value, f.value, f.value};
+        for (size_t j = i; j < f.n / 4; j += step) reinterpret_cast<u32x4*>(f.p)[j] = v;
+        done = f.n / 4 * 4;
+    }
+    for (i += done; i < f.n; i += step) f.p[i] = f.value;
+}
 
 __global__ __launch_bounds__(kThreads) void pack_token_minor_kernel(PackArgs a) {
     __shared__ __attribute__((aligned(16))) __bf16 lds[2][kTileRows * kRowPad];
     const Geom& gm = a.gm;
     const int bh = blockIdx.y, b = bh / gm.Hkv, hk = bh - b * gm.Hkv;
     const int r0 = blockIdx.x * 64;
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+        if (a.fill[i].n) run_fill(a.fill[i]);
     const int n_rows = a.kv_rows ? gm.T : rows_total(a.rs, gm, bh);
     if (r0 >= n_rows) return;
 
@@ -124,14 +142,19 @@ __global__ __launch_bounds__(kThreads) void merge_rows_kernel(Geom gm, RowSet rs
 
 }  // namespace
 
-// rows = tokens of each KV head: x [B,T,Hkv,128] -> xt [B*Hkv][128][cap], cap = round_up(T, 64)
-int pack_kv(const Geom& g, const void* x, void* xt, int cap, hipStream_t st) {
+// rows = tokens of each KV head: x[i] [B,T,Hkv,128] -> xt[i] [B*Hkv][128][cap], cap = round_up(T, 64)
+int pack_kv(const Geom& g, int n, const void* const* x, void* const* xt, int cap, const Fill* fills, int nfills,
+            hipStream_t st) {
+    if (n < 1 || n > 2 || nfills < 0 || nfills > 3) return L2A_ERR_UNSUPPORTED;
     PackArgs a{};
     a.gm = g;
     a.rs = RowSet{nullptr, nullptr, nullptr, 0};
     a.kv_rows = 1;
-    a.x[0] = (const __bf16*)x;
-    a.xt[0] = (__bf16*)xt;
+    for (int i = 0; i < n; ++i) {
+        a.x[i] = (const __bf16*)x[i];
+        a.xt[i] = (__bf16*)xt[i];
+    }
+    for (int i = 0; i < nfills; ++i) a.fill[i] = fills[i];
     a.cap = cap;
     KernelTimer kt("pack_kv", st);
     hipLaunchKernelGGL(pack_token_minor_kernel, dim3(cap / 64, g.B * g.Hkv), dim3(kThreads), 0, st, a);
