@@ -5,7 +5,7 @@
 // The kernel also emits delta_t = sum_j P_tj dP_tj, which equals <dO_t, out_t> without the
 // rounding of the saved bf16 output; the dK/dV kernel uses that value.
 //
-// Same decomposition as the forward: a workgroup owns a tile of consecutive rows (4 wavefronts
+// Same decomposition as the forward: a workgroup owns a tile of consecutive rows (8 wavefronts
 // x 32 rows), a lane owns a row, everything is computed transposed:
 //   S^T  = K Q^T        A = K block (LDS),            B = Q  (registers)
 //   dP^T = V dO^T       A = V block (LDS),            B = dO (registers)
@@ -47,10 +47,9 @@ struct SdP {
     f32x16 s, dp;  // 32 keys x 32 rows each
 };
 
-// NW wavefronts of 32 rows per workgroup.  With 8 the register budget is 256 per wavefront and two
-// share a SIMD: the loop over unmasked blocks fits without spills and gains 14 %, the masked blocks
-// spill -- so the Global rows (a handful of masked blocks out of hundreds per tile) run with 8
-// wavefronts and the Local rows (every twentieth block masked) with 4.
+// NW wavefronts of 32 rows per workgroup.  With 8 the register budget is 256 per wavefront and two share a SIMD.  That
+// fits because one loop serves masked and unmasked blocks (a loop of its own for each spilled 65 registers into the masked
+// one: Local rows ran with 4 wavefronts then, 11.4 ms at 128K tokens, now 9.4; Global rows 28.2, unchanged).
 // (bx, by) of (gx, nbh): the workgroup's index in its branch's part of the grid (a launch may carry both branches)
 typedef __bf16 DqLds[2][3][kBK * 128];
 template <bool LOCAL, int NW, bool PAIR>
@@ -131,7 +130,7 @@ __device__ __forceinline__ void dq_body(const DqArgs& a, const int bx, const int
     for (int e = 0; e < 16; ++e) ndl16[e] = -dlt;
     float dlt_exact = 0.f;
 
-    // ---- block range and its three runs (window-start masks / no masks / causal diagonal)
+    // ---- block range; blocks before j_mid need the window-start mask, those from j_diag on the causal one
     const int jb0 = LOCAL ? max(wg_pmin - gm.W, 0) / kBK : 0;
     const int jb1 = wg_pmax / kBK;
     int j_mid = jb0;
@@ -187,9 +186,8 @@ __device__ __forceinline__ void dq_body(const DqArgs& a, const int bx, const int
 
     // One half-block (32 keys k0..k0+31, half KB of its block): dS from `cur`, overlapped with S, dP
     // of the next half-block into `nxt` (rows krow0.. of K tile kt_ and the V tile behind it) and dQ += K^T dS (this block's K tile through trp).
-    auto half_block = [&](auto mask_tag, auto kb_tag, SdP& cur, SdP& nxt, const __bf16* kt_,
+    auto half_block = [&](const bool masked, auto kb_tag, SdP& cur, SdP& nxt, const __bf16* kt_,
                           int krow0, const lds_cptr (&trp)[4][2], int k0, auto&& side) __attribute__((always_inline)) {
-        constexpr bool MASK = decltype(mask_tag)::value;
         constexpr int KB = decltype(kb_tag)::value;
         const float c2 = gm.scale_log2;
         bf16x8 opnd[24 + kAhead];
@@ -229,27 +227,28 @@ __device__ __forceinline__ void dq_body(const DqArgs& a, const int bx, const int
             constexpr int grp = q >> 2, i2 = (q & 3) * 2, e = grp * 8 + i2;
             float p0 = fast_exp2(fmaf(cur.s[e], c2, neg_lse2));
             float p1 = fast_exp2(fmaf(cur.s[e + 1], c2, neg_lse2));
-            if (MASK) {
-                const int key0 = k0 + c_row(e, h), key1 = k0 + c_row(e + 1, h);
-                bool ok0 = key0 <= pos, ok1 = key1 <= pos;
-                if (LOCAL) {
-                    ok0 = ok0 && (key0 >= pos - gm.W);
-                    ok1 = ok1 && (key1 >= pos - gm.W);
-                }
-                p0 = ok0 ? p0 : 0.f;
-                p1 = ok1 ? p1 : 0.f;
-            }
             const float dp0 = cur.dp[e], dp1 = cur.dp[e + 1];
             f32x2 f = {p0 * dp0, p1 * dp1};  // dp already holds dP - delta
             dsum += f[0] + f[1];
             dsw[grp][i2 >> 1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));
         };
 
+        // Masks before the slots and not among them, behind a uniform branch: scores out of reach become -inf, and the slots
+        // are the same for masked and unmasked blocks.  Key k0 + c_row(e, h) lies in [pos - W, pos], or in [0, pos]: one comparison.
+        if (masked) {
+            const int at = LOCAL ? k0 + 4 * h - pos + gm.W : pos - k0 - 4 * h;
+            static_for<0, 16>([&](auto ec) {
+                constexpr int e = decltype(ec)::value, ce = c_row(e, 0);
+                const bool ok = LOCAL ? (unsigned)(at + ce) <= (unsigned)gm.W : ce <= at;
+                cur.s[e] = ok ? cur.s[e] : -INFINITY;
+            });
+            L2A_FENCE();
+        }
         static_for<0, kAhead>([&](auto mc) { read_operand(mc); });
         L2A_FENCE();
         static_for<0, 24>([&](auto mc) {
             constexpr int mm = decltype(mc)::value;
-            // Two wavefronts share a SIMD (the Global rows' shape): each is at high priority through the slots
+            // Two wavefronts share a SIMD (NW = 8): each is at high priority through the slots
             // that carry its S, dP instructions and the softmax arithmetic, so that the other's dQ slots fill the
             // gaps (Global rows -3.5 %; the same in the forward kernel changed nothing).
             if constexpr (mm == 0) __builtin_amdgcn_s_setprio(3);
@@ -297,44 +296,35 @@ __device__ __forceinline__ void dq_body(const DqArgs& a, const int bx, const int
         trp[d][0] = (lds_cptr)(uintptr_t)(lds_k0 + rm_tr_col_offset(d, 0, lane));
         trp[d][1] = (lds_cptr)(uintptr_t)(lds_k0 + rm_tr_col_offset(d, 1, lane));
     }
-    auto run = [&](auto mask_tag, int j_begin, int j_end) __attribute__((always_inline)) {
-        for (int jb = j_begin; jb < j_end; ++jb) {
-            // prefetch: K, V of block jb+2 (their buffer held block jb-1), issued in the slots of the first
-            // half-block where the VALU has nothing to do.  Past the last block the last one is loaded again, into buffers nobody reads any more.
-            const int jk = min(jb + 2, jb1);
-            {  // wavefronts whose rows all lie past the end compute on a repeated row and store nothing
-                BlockLoads L;
-                half_block(mask_tag, Int<0>{}, Xa, Xb, &lds_k[buf][0], 32, trp, jb * kBK, [&](auto mc) {
-                    constexpr int mm = decltype(mc)::value;
-                    if constexpr (mm == kLoadSlot0 - 1) {
-                        const size_t src = (size_t)jk * kBK * kv_row_bytes;
-                        L.ksrc = kbase + src;
-                        L.vsrc = vbase + src;
-                        L.kdst = lds_k0 + buf2 * (kBK * 256);
-                        L.vdst = lds_v0 + buf2 * (kBK * 256);
-                        L.krows = min(kBK, gm.T - jk * kBK);
-                    }
-                    if constexpr (mm >= kLoadSlot0 && mm < kLoadSlot0 + 2 * kNL) issue_block_load(L, Int<mm - kLoadSlot0>{});
-                });
-                half_block(mask_tag, Int<1>{}, Xb, Xa, &lds_k[buf1][0], 0, trp, jb * kBK + 32,
-                           [](auto) {});
-            }
-            dma_wait();
-            __syncthreads();
-            const int step = (buf1 - buf) * (kBK * 256);
-#pragma unroll
-            for (int d = 0; d < 4; ++d) trp[d][0] += step, trp[d][1] += step;
-            const int t = buf;
-            buf = buf1, buf1 = buf2, buf2 = t;
+    for (int jb = jb0; jb <= jb1; ++jb) {
+        const bool masked = jb < j_mid || jb >= j_diag;
+        // prefetch: K, V of block jb+2 (their buffer held block jb-1), issued in the slots of the first
+        // half-block where the VALU has nothing to do.  Past the last block the last one is loaded again, into buffers nobody reads any more.
+        const int jk = min(jb + 2, jb1);
+        {  // wavefronts whose rows all lie past the end compute on a repeated row and store nothing
+            BlockLoads L;
+            half_block(masked, Int<0>{}, Xa, Xb, &lds_k[buf][0], 32, trp, jb * kBK, [&](auto mc) {
+                constexpr int mm = decltype(mc)::value;
+                if constexpr (mm == kLoadSlot0 - 1) {
+                    const size_t src = (size_t)jk * kBK * kv_row_bytes;
+                    L.ksrc = kbase + src;
+                    L.vsrc = vbase + src;
+                    L.kdst = lds_k0 + buf2 * (kBK * 256);
+                    L.vdst = lds_v0 + buf2 * (kBK * 256);
+                    L.krows = min(kBK, gm.T - jk * kBK);
+                }
+                if constexpr (mm >= kLoadSlot0 && mm < kLoadSlot0 + 2 * kNL) issue_block_load(L, Int<mm - kLoadSlot0>{});
+            });
+            half_block(masked, Int<1>{}, Xb, Xa, &lds_k[buf1][0], 0, trp, jb * kBK + 32,
+                       [](auto) {});
         }
-    };
-    for (int seg = 0; seg < 3; ++seg) {
-        const int j_begin = seg == 0 ? jb0 : (seg == 1 ? j_mid : j_diag);
-        const int j_end = seg == 0 ? j_mid : (seg == 1 ? j_diag : jb1 + 1);
-        if (seg == 1)
-            run(std::false_type{}, j_begin, j_end);
-        else
-            run(std::true_type{}, j_begin, j_end);
+        dma_wait();
+        __syncthreads();
+        const int step = (buf1 - buf) * (kBK * 256);
+#pragma unroll
+        for (int d = 0; d < 4; ++d) trp[d][0] += step, trp[d][1] += step;
+        const int t = buf;
+        buf = buf1, buf1 = buf2, buf2 = t;
     }
 
     // ---- epilogue
@@ -389,14 +379,13 @@ int mfma_bwd_dq(const Geom& g, const RowSet& rs, const void* q, const void* k, c
     DqArgs a{g, rs, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (const __bf16*)dO, lse, delta,
              (__bf16*)dq, accumulate};
     const long long rows = (long long)g.T * g.G;
-    constexpr int kNwLocal = 4, kNwGlobal = 8;
-    const int bq = (rs.local ? kNwLocal : kNwGlobal) * kRW;
+    constexpr int kNw = 8, bq = kNw * kRW;
     const dim3 grid((unsigned)(((rows + bq - 1) / bq + 7) / 8 * 8), g.B * g.Hkv);  // a multiple of 8: see the tile order
     KernelTimer kt_(rs.local ? "bwd_dq_local" : "bwd_dq_global", st);
     if (rs.local)
-        hipLaunchKernelGGL((bwd_dq_kernel<true, kNwLocal>), grid, dim3(64 * kNwLocal), 0, st, a);
+        hipLaunchKernelGGL((bwd_dq_kernel<true, kNw>), grid, dim3(64 * kNw), 0, st, a);
     else
-        hipLaunchKernelGGL((bwd_dq_kernel<false, kNwGlobal>), grid, dim3(64 * kNwGlobal), 0, st, a);
+        hipLaunchKernelGGL((bwd_dq_kernel<false, kNw>), grid, dim3(64 * kNw), 0, st, a);
     return launch_status();
 }
 
@@ -410,10 +399,16 @@ int mfma_bwd_dq_pair(const Geom& g, const RowSet& rs_l, const void* q_l, const v
     DqArgs al{g, rs_l, (const __bf16*)q_l, (const __bf16*)k_l, (const __bf16*)v_l, (const __bf16*)dO, lse_l, delta_l, (__bf16*)dq_l, 0};
     DqArgs ag{g, rs_g, (const __bf16*)q_g, (const __bf16*)k_g, (const __bf16*)v_g, (const __bf16*)dO, lse_g, delta_g, (__bf16*)dq_g, 0, wide_g};
     const long long rows = (long long)g.T * g.G;
-    constexpr int kNw = 4, kBq = kNw * kRW;
-    const unsigned gx = (unsigned)(((rows + kBq - 1) / kBq + 7) / 8 * 8);  // per branch
+    // Workgroups of 128 rows up to 256 tiles of 256: there the longest tile's walk sets the time.  Measured, whole training
+    // step, 128 / 256 rows, us (28 / 4 heads): T = 1000 (112 tiles) 178.5 / 190.3, 2048 (224) 293 / 303, 4096 (448) 799 / 776,
+    // 2 x 4000 separate modules 1507 / 1470, 16379 (32 / 8 heads) 6573 / 6235.
+    const long long tiles = (rows + 255) / 256 * g.B * g.Hkv;
     KernelTimer kt("bwd_dq_pair", st);
-    hipLaunchKernelGGL((bwd_dq_pair_kernel<kNw>), dim3(2 * gx, g.B * g.Hkv), dim3(64 * kNw), 0, st, ag, al, (int)gx);
+    auto width = [&](int bq) { return (unsigned)(((rows + bq - 1) / bq + 7) / 8 * 8); };  // per branch
+    if (tiles <= 256)
+        hipLaunchKernelGGL((bwd_dq_pair_kernel<4>), dim3(2 * width(128), g.B * g.Hkv), dim3(256), 0, st, ag, al, (int)width(128));
+    else
+        hipLaunchKernelGGL((bwd_dq_pair_kernel<8>), dim3(2 * width(256), g.B * g.Hkv), dim3(512), 0, st, ag, al, (int)width(256));
     return launch_status();
 }
 

@@ -60,7 +60,8 @@ bool pair_fwd(const l2a_params& p) {
     return use_mfma(p) && !(f & (L2A_FLAG_DENSE | L2A_FLAG_SKIP_LOCAL | L2A_FLAG_SKIP_GLOBAL | L2A_FLAG_SEQUENTIAL)) &&
            mfma_fwd_redo_entries(make_geom(p)) <= kPairMaxTiles;
 }
-// The backward's dQ alike (its workspace is the same either way).  Measured, Hq = 28, Hkv = 4, both kernels / the pair, us:
+// The backward's dQ alike (its workspace is the same either way).  Measured with 128 Local rows per workgroup in both,
+// Hq = 28, Hkv = 4, both kernels / the pair, us:
 // T = 1000, 5 % routed 174 / 33, 20 % 122 / 33; T = 4096, W = 4096, 5 / 20 / 50 % 446 / 217, 389 / 244, 397 / 296;
 // T = 16384 1842 / 1348, 1868 / 1754, 2686 / 2563; at T = 32768 (beyond the limit) 20 % 5010 / 4879 plus the merge.
 bool pair_bwd(const l2a_params& p) { return pair_fwd(p); }

@@ -56,7 +56,7 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 constexpr long long kAllHeadsMaxTokens = 1 << 19;
 
 // index along the M dimension held by register r of a C/D tile
-__device__ __forceinline__ int c_row(int r, int h) { return 8 * (r >> 2) + 4 * h + (r & 3); }
+__device__ __forceinline__ constexpr int c_row(int r, int h) { return 8 * (r >> 2) + 4 * h + (r & 3); }
 
 // eight fp32 -> one bf16 MFMA operand (registers 8*half .. 8*half+7 of a C/D tile)
 __device__ __forceinline__ bf16x8 pack8(const f32x16& x, int half) {

@@ -34,3 +34,10 @@ def test_pair_and_sequential_agree():
         compare(name, a, b, "bf16")
     # sums of at most 1500 products in another grouping of the same fp32 terms
     assert np.abs(got[0][3] - got[B.L2A_FLAG_SEQUENTIAL][3]).max() <= 1e-4
+
+
+@pytest.mark.parametrize("T,W,f", [(1700, 300, 0.3), (1601, 1601, 0.02)])
+def test_pair_with_tiles_of_256_rows(oracle, T, W, f):
+    # 8 tiles of 256 rows x 40 (batch, KV head): beyond the 256 that workgroups of 128 rows take
+    x = make_case(B_=2, T=T, Hq=20, Hkv=20, W=W, Hm=20, f=f, seed=78)
+    run_and_check(oracle, x, kv_heads=(0, 19), twice=True)
