@@ -1,12 +1,10 @@
 // Small memory-bound helpers: the backward pass's per-row dot products and fills.
-#include "common.hpp"
+#include "mfma.hpp"
 
 #include <algorithm>
 
 namespace l2a {
 namespace {
-
-constexpr int kThreads = 256;
 
 // delta_l[b,h,t] = <dO, S>, delta_g[b,h,t] = <dO, A>  (the "D" vector of the FlashAttention
 // backward, one per branch; delta_g is also the task-loss part of the router-score gradient,
@@ -68,13 +66,12 @@ __global__ __launch_bounds__(kThreads) void row_deltas_kernel(Geom gm, const E* 
 // which enters dq_t as  scale * error * sum_j p_tj k_j.  Both factors shrink like 1 / sqrt(keys) for
 // rows that average many keys, but for the first few tokens they do not (token 2 with N(0,1) inputs:
 // up to 1.2e-2 per branch, twice that when both branches read the same tensors, since s_t = a_t
-// there), so the first kHeadTokens deltas are recomputed exactly.  One wavefront per (token, head, branch);
-// lane = key.  A row whose log-sum-exp is -inf (not routed: a_t = 0) gets delta = 0.  Bound by the latency of
-// the rows' loads: 16 bytes at a time, eight of each row in flight (element by element this took 99 us for
-// two sequences of 28 heads and a launch per branch, now 30 us for both branches together).
+// there), so the first kHeadTokens deltas are recomputed exactly.  A row whose log-sum-exp is -inf (not routed: a_t = 0)
+// gets delta = 0.  Workgroup = (branch, head, sequence), wavefront = 32 tokens, on the matrix cores: S^T = K Q^T and dP^T
+// = V dO^T of 32 keys at a time, a lane owns a token.  With a wavefront per token and a lane per key the 64 separate cache
+// lines of every load set the time: 30 us for two sequences of 28 heads, both branches, now 12.
 constexpr int kHeadTokens = 64;
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 struct HeadBranch {
     const __bf16 *q, *k, *v;
     const float* lse;
@@ -82,39 +79,44 @@ struct HeadBranch {
     int local;
 };
 
-__global__ __launch_bounds__(64) void head_deltas_kernel(Geom gm, HeadBranch br0, HeadBranch br1,
-                                                         const __bf16* __restrict__ dO) {
-    const int nt = min(gm.T, kHeadTokens), second = (int)blockIdx.x >= nt;
-    const int t = (int)blockIdx.x - second * nt, h = blockIdx.y, b = blockIdx.z, j = threadIdx.x;
-    const HeadBranch br = second ? br1 : br0;
-    const int hk = h / gm.G;
+__global__ __launch_bounds__(128) void head_deltas_kernel(Geom gm, HeadBranch br0, HeadBranch br1,
+                                                          const __bf16* __restrict__ dO) {
+    const HeadBranch br = blockIdx.x ? br1 : br0;
+    const int h = blockIdx.y, b = blockIdx.z, hk = h / gm.G;
+    const int lane = threadIdx.x & 63, n = lane & 31, half = lane >> 5;
+    const int t0 = (int)(threadIdx.x >> 6) * 32, nt = min(gm.T, kHeadTokens);
+    if (t0 >= nt) return;
+    const int t = min(t0 + n, nt - 1);  // lanes past the end repeat the last token and write nothing
+    const size_t row = (((size_t)b * gm.T + t) * gm.Hq + h) * gm.D + 8 * half;
     const size_t so = ((size_t)b * gm.Hq + h) * gm.T + t;
     const float l = br.lse[so];
-    float term = 0.f;
-    const bool in_reach = j <= t && (!br.local || t - j <= gm.W);
-    if (in_reach && l != -INFINITY) {
-        const size_t row = (((size_t)b * gm.T + t) * gm.Hq + h) * gm.D, key = (((size_t)b * gm.T + j) * gm.Hkv + hk) * gm.D;
-        const bf16x8* qr = reinterpret_cast<const bf16x8*>(br.q + row);
-        const bf16x8* gr = reinterpret_cast<const bf16x8*>(dO + row);
-        const bf16x8* kr = reinterpret_cast<const bf16x8*>(br.k + key);
-        const bf16x8* vr = reinterpret_cast<const bf16x8*>(br.v + key);
-        float s = 0.f, dp = 0.f;
-        for (int c0 = 0; c0 < gm.D / 8; c0 += 8) {  // D = 64 or 128
-            bf16x8 q8[8], g8[8], k8[8], v8[8];
+    float sum = 0.f;
+    for (int k0 = 0; k0 <= min(t0 + 31, nt - 1); k0 += 32) {
+        const int j = min(k0 + n, gm.T - 1);  // keys past the end: out of every token's reach
+        const size_t key = (((size_t)b * gm.T + j) * gm.Hkv + hk) * gm.D + 8 * half;
+        f32x16 s, dp;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) q8[i] = qr[c0 + i], k8[i] = kr[c0 + i], g8[i] = gr[c0 + i], v8[i] = vr[c0 + i];
+        for (int r = 0; r < 16; ++r) s[r] = dp[r] = 0.f;
+        for (int c0 = 0; c0 < gm.D; c0 += 64) {  // D = 64 or 128
+            bf16x8 q8[4], g8[4], k8[4], v8[4];
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
+            for (int i = 0; i < 4; ++i) {
+                const int c = c0 + 16 * i;
+                q8[i] = *reinterpret_cast<const bf16x8*>(br.q + row + c), k8[i] = *reinterpret_cast<const bf16x8*>(br.k + key + c);
+                g8[i] = *reinterpret_cast<const bf16x8*>(dO + row + c), v8[i] = *reinterpret_cast<const bf16x8*>(br.v + key + c);
+            }
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    s = fmaf((float)q8[i][e], (float)k8[i][e], s);
-                    dp = fmaf((float)g8[i][e], (float)v8[i][e], dp);
-                }
+            for (int i = 0; i < 4; ++i) s = mfma32(k8[i], q8[i], s), dp = mfma32(v8[i], g8[i], dp);
         }
-        term = expf(s * gm.scale - l) * dp;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int kr = k0 + c_row(r, half);
+            const bool in_reach = kr <= t && (!br.local || t - kr <= gm.W);
+            sum += in_reach && l != -INFINITY ? expf(s[r] * gm.scale - l) * dp[r] : 0.f;
+        }
     }
-    for (int o = 32; o > 0; o >>= 1) term += __shfl_xor(term, o);
-    if (j == 0) br.delta[so] = term;
+    sum += __shfl_xor(sum, 32);
+    if (half == 0 && t0 + n < nt) br.delta[so] = sum;
 }
 
 __global__ __launch_bounds__(kThreads) void fill_u32_kernel(uint32_t* p, size_t n, uint32_t value) {
@@ -149,14 +151,14 @@ int row_deltas(const Geom& g, int dtype, const void* dO, const void* S, const vo
 }
 
 int head_deltas(const Geom& g, const HeadDeltas* branches, int n, const void* dO, hipStream_t st) {
-    static_assert(kHeadTokens <= 64, "one lane per key");
+    static_assert(kHeadTokens <= 64, "two wavefronts of 32 tokens");
     HeadBranch br[2] = {};
     for (int i = 0; i < n; ++i)
         br[i] = HeadBranch{(const __bf16*)branches[i].q, (const __bf16*)branches[i].k, (const __bf16*)branches[i].v,
                            branches[i].lse, branches[i].delta, branches[i].local};
-    const dim3 grid((unsigned)(std::min(g.T, kHeadTokens) * n), (unsigned)g.Hq, (unsigned)g.B);
     KernelTimer kt("head_deltas", st);
-    hipLaunchKernelGGL(head_deltas_kernel, grid, dim3(64), 0, st, g, br[0], br[1], (const __bf16*)dO);
+    hipLaunchKernelGGL(head_deltas_kernel, dim3((unsigned)n, (unsigned)g.Hq, (unsigned)g.B), dim3(128), 0, st, g, br[0], br[1],
+                       (const __bf16*)dO);
     return launch_status();
 }
 
