@@ -195,7 +195,9 @@ int l2a_attn_fwd(const l2a_params* p, const void* q_loc, const void* k_loc, cons
  * decision is 1 -- skipped entirely, cache not read, when no head of a KV group is routed; merged
  * as o = s + d a (Sec. 3.1 Eq. 5).  bf16, D = 128, Hq / Hkv <= 16; both branches read the same
  * q / cache (for separate Local and Global modules call twice with L2A_FLAG_SKIP_GLOBAL /
- * L2A_FLAG_SKIP_LOCAL).  HBM-bound: every cache row in reach is read once per branch.
+ * L2A_FLAG_SKIP_LOCAL).  HBM-bound: every cache row in reach is read once, the window of a routed head for both
+ * branches together (all but the chunk of 512 keys it begins inside of).  A sequence's results depend, to the bit,
+ * on its own q, cache rows, pos and decisions and on p->T, not on the other sequences of the batch.
  *
  *   p->T        capacity of the cache in tokens (the row stride of k_cache / v_cache)
  *   q           in  [B,Hq,D]      the new token's queries
@@ -208,7 +210,7 @@ int l2a_attn_fwd(const l2a_params* p, const void* q_loc, const void* k_loc, cons
  *   O           out [B,Hq,D]
  *   lse_local, lse_global  out optional [B,Hq]; lse_global is -inf where d = 0
  *   S_opt, A_opt  out optional [B,Hq,D]; A is zero where d = 0
- *   workspace   l2a_decode_workspace_bytes(p): one partial (max, sum, O) per 512 keys, head and branch
+ *   workspace   l2a_decode_workspace_bytes(p): room for two partials (max, sum, O) per 512 keys of capacity and query head
  *
  * L2A_FLAG_RING_CACHE (with L2A_FLAG_SKIP_GLOBAL; a Local module of its own keeps only its window):
  * the cache is a ring of p->T >= W + 1 slots (a multiple of 32), the K, V of token j in slot j mod p->T, and pos[b] is the

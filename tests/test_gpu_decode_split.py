@@ -1,6 +1,6 @@
-"""The decode step's split of a call into chunks, which every workgroup derives from the positions and decisions of
-the whole batch: batches of one, two and more lane groups and beyond the scanned size, caches with room for one
-chunk per segment only, windows that start inside a sub-block, per-head decisions, unrouted sequences."""
+"""The decode step's units of work, which every workgroup finds from the positions and decisions of the whole batch:
+batches of one, two and more groups of 64 lanes, caches of one chunk and of several, windows that start inside a
+sub-block, per-head decisions, unrouted sequences."""
 import pytest
 
 from paper_2603_17484_amd import binding as B
