@@ -2,8 +2,8 @@
 // (the "consolidate active queries" preprocessing of the sparse kernel, Sec. 3.2 and App. C
 // Alg. 1 step 1; its cost is part of the kernel's time, App. D.1).
 //
-// Two launches, no host read-back, no spin waits (one for short sequences, whose workgroups count the rows before
-// theirs themselves):
+// Two launches, no host read-back, no spin waits (one for short sequences and few mask rows, whose workgroups count the
+// rows before theirs themselves):
 //   1. route_count : every workgroup counts the routed rows of its chunk of positions;
 //   2. route_write : every workgroup sums the counts of the chunks before it (at most a few
 //      hundred integers), then walks its chunk 256 positions at a time; inside a wavefront a
@@ -72,9 +72,18 @@ __device__ __forceinline__ int count_set(const uint8_t* m, int n) {
     }
     return c;
 }
-// Mask bytes up to which every workgroup of the second kernel counts for itself (its own KV head's rows, T for each
-// distinct one) and the first is not launched (T = 1001, one mask row: 2.6 + 4.8 us -> 4.8; beyond it the counting of one workgroup is the longer).
-constexpr int kSelfCountBytes = 32768;
+// Whether every workgroup of the second kernel counts the rows of its KV head for itself and the first is not launched.
+// A launch takes 2.3 us; a workgroup counts `rows` distinct mask rows of T bytes one after the other, and where the workgroups
+// are many or the rows are, that takes longer.  Both calls back to back, us, two launches / one: one mask row, 1 x 1000 and
+// 1 x 16384 tokens (4 KV heads) 10.5 / 8.1, 16 x 32768 26.1 / 23.9, 64 x 8192 (8 KV heads, 128 MB counted) 35.5 / 33.3, 64 x
+// 16384 (512 MB) 65.4 / 69.6; 4 rows, 16 x 4000 (1024 workgroups) 10.2 / 8.2, 128 x 1000 (2048) 12.0 / 12.0, 128 x 4000 31.7 /
+// 36.2; 7 rows, 1 x 4096 10.4 / 8.2, 16 x 4096 (1024) 11.2 / 11.8; 8 rows, 1 x 1000 9.8 / 9.8, 128 x 1000 16.5 / 23.2; 16 rows, 1 x 1000
+// 12.7 / 17.2, 128 x 1000 28.1 / 43.3.
+bool count_in_place(const RouteArgs& a, long long workgroups) {
+    const long long rows = a.Hm == a.Hq ? a.G : 1, bytes = rows * a.T;
+    if (bytes > 32768) return false;
+    return rows == 1 ? workgroups * bytes <= (128ll << 20) : rows < 8 && workgroups * rows <= 4096;
+}
 
 __global__ __launch_bounds__(kThreads) void route_count_kernel(RouteArgs a) {
     __shared__ int lds4[4];
@@ -227,7 +236,7 @@ int route_compact(const l2a_params& p, const uint8_t* mask, int32_t* row_idx, in
     a.nkb = (p.T + 63) / 64;
     if (a.G > kMaxG) return L2A_ERR_UNSUPPORTED;
     const dim3 grid(a.nchunks, p.B * p.Hkv);
-    if ((long long)a.T * (a.Hm == a.Hq ? a.G : 1) <= kSelfCountBytes) {
+    if (count_in_place(a, (long long)a.nchunks * p.B * p.Hkv)) {
         a.chunk_cnt = nullptr;
     } else {
         KernelTimer kt("route_count", st);
