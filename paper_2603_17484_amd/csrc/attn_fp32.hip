@@ -17,8 +17,12 @@
 //
 // What bounds them: the fp32 matrix rate, 157 TFLOP/s, and every vector instruction beside it -- unlike the bf16
 // ones, these matrix instructions leave no room under them (microbenchmark, two wavefronts per SIMD: 13.7 ns
-// alone, 19.0 with one vector instruction behind each, 24.1 with four).  So addresses are kept out of the loops
-// and masks in code of their own.  A workgroup owns one small tile (16 or 32 query rows, 16 keys) and its NW
+// alone, 19.0 with one vector instruction behind each, 24.1 with four).  So addresses are kept out of the loops and, in
+// the forward and dQ, masks in code of their own (dK/dV tests every pair: a uniform branch there gained nothing).  With
+// D = 128 the registers are all taken: 9 (dK/dV), 16 and 18 (forward and dQ, 32-row tiles) are spilled, none of them inside
+// a matrix loop.  (dK/dV with its second computation inlined in the tile loop and a branch for each of the four stores
+// of a row's data spilled 221, four of which came back from scratch on every row tile: 4096 tokens, Hq = 8, Hkv = 2, W =
+// 1024, whole step 1174 us, now 1129; 3000 tokens, Hq = Hkv = 8, W = 256 942, now 870.)  A workgroup owns one small tile (16 or 32 query rows, 16 keys) and its NW
 // wavefronts share the *other* axis, each with a partial result of its own, and these meet in LDS at the end:
 // with 16-row tiles a sequence of a few thousand tokens gives a few hundred workgroups, and a serial walk of a
 // whole prefix by one wavefront would set the kernel's time.
@@ -47,6 +51,11 @@ __device__ __forceinline__ float max_k(float x) {
     return fmaxf(x, __shfl_xor(x, 32));
 }
 __device__ __forceinline__ f32x4 ld4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
+
+// Tiles a launch covers directly; beyond that its workgroups take several (keeps the grid within the limit of 2^32
+// threads at every length), at most 2^27 / 2^20: a tile is 16 of fewer than 2^31 rows or keys.
+constexpr long long kMaxTiles = 1 << 20;
+constexpr int kMaxPerGroup = 128;
 
 // code of the r-th row of one (b, KV head) (device data: clamped into the valid range)
 __device__ __forceinline__ int row_code(const RowSet& rs, const Geom& gm, int bh, int r) {
@@ -490,8 +499,9 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_bwd_dkdv_kernel(Geom gm, Dkdv
     float(*const sk)[D + 4] = lds;
     float(*const sv)[D + 4] = lds + 16;
     float(*const so)[2][16][D + 4] = reinterpret_cast<float(*)[2][16][D + 4]>(lds);
-    __shared__ __attribute__((aligned(16))) float sL[NW][16], sd[NW][16];  // statistics of a wavefront's row tile
-    __shared__ __attribute__((aligned(16))) int sp[NW][16], si[NW][16];    // position (-1: no row), row index within the batch
+    // of a wavefront's row tile: position (-1: no row), row index within the batch, log-sum-exp, delta
+    __shared__ __attribute__((aligned(16))) uint32_t row_data[NW][4][16];
+    __shared__ uint32_t redo[kMaxPerGroup / 32];  // tiles of this workgroup to be computed again
     const int bh = blockIdx.y, b = bh / gm.Hkv, hk = bh - b * gm.Hkv;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 15, kq = lane >> 4;
@@ -548,16 +558,16 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_bwd_dkdv_kernel(Geom gm, Dkdv
             f32x4 Ln, dn;
             auto fetch_tile = [&]() __attribute__((always_inline)) {
                 __builtin_amdgcn_wave_barrier();
-                if (kq == 0) sp[wave][n] = pos;
-                if (kq == 1) si[wave][n] = idx;
-                if (kq == 2) sL[wave][n] = L;
-                if (kq == 3) sd[wave][n] = dl;
+                // one store, each quarter of the wavefront its own of the four (a branch per quarter took a jump each)
+                const uint32_t a = kq & 1 ? (uint32_t)idx : (uint32_t)pos;
+                const uint32_t c = kq & 1 ? __builtin_bit_cast(uint32_t, dl) : __builtin_bit_cast(uint32_t, L);
+                row_data[wave][kq][n] = kq & 2 ? c : a;
                 asm volatile("" ::: "memory");
                 __builtin_amdgcn_wave_barrier();
-                pn = *reinterpret_cast<const i32x4*>(&sp[wave][4 * kq]);
-                const i32x4 ir = *reinterpret_cast<const i32x4*>(&si[wave][4 * kq]);
-                Ln = ld4(&sL[wave][4 * kq]);
-                dn = ld4(&sd[wave][4 * kq]);
+                pn = *reinterpret_cast<const i32x4*>(&row_data[wave][0][4 * kq]);
+                const i32x4 ir = *reinterpret_cast<const i32x4*>(&row_data[wave][1][4 * kq]);
+                Ln = *reinterpret_cast<const f32x4*>(&row_data[wave][2][4 * kq]);
+                dn = *reinterpret_cast<const f32x4*>(&row_data[wave][3][4 * kq]);
                 asm volatile("" ::: "memory");
                 __builtin_amdgcn_wave_barrier();
                 const float *qrow[4], *grow[4];
@@ -601,11 +611,13 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_bwd_dkdv_kernel(Geom gm, Dkdv
                 ak.add(qc, s[0]);
             }
         }
-        if (__syncthreads_or(ak.check() + av.check() != 0.f)) {  // as in the forward: rows that do not see a key
-            if (threadIdx.x < 64)
-                simple_dkdv_key<float, D / 4>(gm, sets, q, k, v, dO, dk, dv, bh, k0 + (threadIdx.x >> 2), threadIdx.x & 3);
-            continue;
-        }
+        // As in the forward, for rows that do not see a key; but behind the loop, where the registers that the second
+        // computation takes do not cost the first its own.
+        const int turn = tile / (int)gridDim.x;
+        const bool again = __syncthreads_or(ak.check() + av.check() != 0.f);
+        if (threadIdx.x == 0 && (turn & 31) == 0) redo[turn >> 5] = 0;
+        if (threadIdx.x == 0 && again) redo[turn >> 5] |= 1u << (turn & 31);
+        if (again) continue;
         ak.store(&so[wave][0][n][0], kq);
         av.store(&so[wave][1][n][0], kq);
         __syncthreads();
@@ -621,11 +633,12 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_bwd_dkdv_kernel(Geom gm, Dkdv
         }
         __syncthreads();
     }
+    __syncthreads();
+    for (int tile = blockIdx.x, turn = 0; tile < n_tiles; tile += gridDim.x, ++turn)
+        if ((redo[turn >> 5] >> (turn & 31) & 1u) && threadIdx.x < 64)
+            simple_dkdv_key<float, D / 4>(gm, sets, q, k, v, dO, dk, dv, bh, tile * 16 + (threadIdx.x >> 2), threadIdx.x & 3);
 }
 
-// tiles a launch covers directly; beyond that its workgroups take several (keeps the grid within the limit
-// of 2^32 threads at every length)
-constexpr long long kMaxTiles = 1 << 20;
 inline dim3 tile_grid(long long tiles, const Geom& g) {
     return dim3((unsigned)(tiles < kMaxTiles ? tiles : kMaxTiles), g.B * g.Hkv);
 }

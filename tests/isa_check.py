@@ -111,6 +111,34 @@ def scan(text):
     return list(found.values())
 
 
+def loop_spills(text):
+    """{(kernel, loop header): scratch instructions} of the innermost loops that hold matrix instructions: registers that
+    were spilled and are fetched again on every step.  Blocks are assigned to loops by the compiler's own comments."""
+    kernel, own, head = None, None, None      # kernel, label of the block, header of its innermost loop
+    inner, matrix, spills = set(), set(), {}
+    for line in text.splitlines():
+        m = re.match(r"^(_Z\w+):", line)
+        if m:
+            kernel, own, head = m.group(1), None, None
+        m = re.match(r"^\.L(BB\d+_\d+):", line)
+        if m or re.match(r"^; %bb\.\d+:", line):
+            own, head = (m.group(1) if m else None), None
+        m = re.search(r"in Loop: Header=(BB\d+_\d+)", line)
+        if m:
+            head = m.group(1)
+        if re.search(r"=>\s*This (Inner )?Loop Header", line) and own:
+            head = own
+            if "Inner" in line:
+                inner.add((kernel, own))
+        op = line.split(";")[0].split()
+        if op and head:
+            if op[0].startswith("v_mfma"):
+                matrix.add((kernel, head))
+            elif op[0].startswith("scratch_"):
+                spills[kernel, head] = spills.get((kernel, head), 0) + 1
+    return {k: spills.get(k, 0) for k in inner & matrix}
+
+
 def assembly(src):
     with tempfile.TemporaryDirectory() as tmp:
         out = os.path.join(tmp, "k.s")

@@ -93,3 +93,34 @@ def test_scanner_accepts_padded_code_and_accumulation_chains():
 def test_compiled_kernels_are_clean():
     for src, hits in isa_check.check_all().items():
         assert not hits, (src, hits)
+
+
+LOOPS = """
+_Z6kernelv:
+	scratch_store_dword off, v2, off
+.LBB0_1:                                ; =>This Loop Header: Depth=1
+                                        ;     Child Loop BB0_2 Depth 2
+	scratch_load_dword v2, off, off
+.LBB0_2:                                ;   Parent Loop BB0_1 Depth=1
+                                        ; =>  This Inner Loop Header: Depth=2
+	v_mfma_f32_16x16x4_f32 v[0:3], v4, v5, v[0:3]
+	s_cbranch_vccnz .LBB0_4
+; %bb.3:                                ;   in Loop: Header=BB0_2 Depth=2
+	scratch_load_dword v6, off, off
+.LBB0_4:                                ;   in Loop: Header=BB0_2 Depth=2
+	s_cbranch_scc1 .LBB0_2
+; %bb.5:                                ;   in Loop: Header=BB0_1 Depth=1
+	scratch_load_dword v7, off, off
+	s_endpgm
+"""
+
+
+def test_spills_are_counted_in_the_innermost_matrix_loop_only():
+    assert isa_check.loop_spills(LOOPS) == {("_Z6kernelv", "BB0_2"): 1}
+
+
+def test_fp32_matrix_loops_hold_no_spills():
+    """The D = 128 dK/dV kernel once fetched four addresses from scratch on every row tile, behind its loads."""
+    found = isa_check.loop_spills(isa_check.assembly("attn_fp32.hip"))
+    assert len(found) >= 10      # forward and dQ in two tile widths, dK/dV, both head sizes
+    assert not any(found.values()), found
