@@ -8,8 +8,10 @@ wave-uniform `if` per score element in the decode kernel: 3 wait states, wrong s
 script compiles the matrix-core kernels to assembly and walks every path of up to a dozen
 instructions behind each matrix instruction, through branches and their targets; a reader reached
 across a branch in fewer than 11 wait states is reported.  Matrix instructions whose result tile
-lies in VGPRs are the kernels' own inline assembly, which the compiler does not pad at all: for
-them a reader in fewer than 11 wait states is reported on straight-line paths as well.
+lies in VGPRs are the bf16 attention kernels' own inline assembly, which the compiler does not pad at all: for
+them a reader in fewer than 11 wait states is reported on straight-line paths as well.  Sources whose
+matrix instructions are all the compiler's (ASM_FREE_SOURCES) are scanned for readers across a branch only;
+the fp32 instruction there, v_mfma_f32_16x16x4_f32 (8 passes, another unit), needs 10 wait states.
 
 A following matrix instruction counts as a reader through any of its operands: SrcA, SrcB, and
 SrcC or a destination that overlaps the tile, unless it is the accumulation form (destination and
@@ -29,8 +31,10 @@ import tempfile
 
 from paper_2603_17484_amd.build import CSRC, FLAGS, HIPCC
 
-KERNEL_SOURCES = ["attn_fwd_bf16.hip", "attn_bwd_dq_bf16.hip", "attn_bwd_dkdv_bf16.hip", "attn_decode_bf16.hip"]
+ASM_FREE_SOURCES = ["attn_fp32.hip", "util.hip"]
+KERNEL_SOURCES = ["attn_fwd_bf16.hip", "attn_bwd_dq_bf16.hip", "attn_bwd_dkdv_bf16.hip", "attn_decode_bf16.hip"] + ASM_FREE_SOURCES
 WAIT_STATES = 11      # 8-pass matrix instruction -> read of its result by another unit
+WAIT_STATES_F32 = 10  # the same for v_mfma_f32_*_f32
 MAX_BRANCH_DEPTH = 6
 DEPTH_LIMIT = "<branch depth limit reached inside the hazard window>"
 
@@ -53,9 +57,9 @@ def _instructions(text):
     return ins
 
 
-def scan(text):
-    """[(matrix instruction, reader, wait states)] for readers reached too early: across a branch, or
-    anywhere behind a matrix instruction with a VGPR destination (inline assembly)."""
+def scan(text, inline_asm=True):
+    """[(matrix instruction, reader, wait states)] for readers reached too early: across a branch, or, with
+    inline_asm, anywhere behind a matrix instruction with a VGPR destination."""
     ins = _instructions(text)
     label = {}
     for i, s in enumerate(ins):
@@ -65,10 +69,11 @@ def scan(text):
     found = {}
 
     def walk(j, ws, dst, crossed, depth, origin):
-        if depth >= MAX_BRANCH_DEPTH and ws < WAIT_STATES and j < len(ins):
+        need = WAIT_STATES_F32 if re.match(r"v_mfma_f32_\w+_f32\b", ins[origin]) else WAIT_STATES
+        if depth >= MAX_BRANCH_DEPTH and ws < need and j < len(ins):
             found.setdefault(origin, (ins[origin], DEPTH_LIMIT, ws))
             return
-        while j < len(ins) and ws < WAIT_STATES:
+        while j < len(ins) and ws < need:
             t = ins[j]
             if t.startswith(".LBB"):
                 j += 1
@@ -97,7 +102,7 @@ def scan(text):
                     stores = op.startswith(("ds_write", "global_store", "scratch_store", "buffer_store"))
                     srcs = set().union(*[_regs(x) for k, x in enumerate(toks) if k > 0 or stores] or [set()])
                 if srcs & dst:
-                    if crossed or any(r[0] == "v" for r in dst):
+                    if crossed or (inline_asm and any(r[0] == "v" for r in dst)):
                         found.setdefault(origin, (ins[origin], t, ws))
                     return
                 if toks and _regs(toks[0]) & dst and op.startswith("v_") and not op.startswith("v_mfma"):
@@ -150,7 +155,7 @@ def assembly(src):
 
 
 def check_all():
-    return {src: scan(assembly(src)) for src in KERNEL_SOURCES}
+    return {src: scan(assembly(src), src not in ASM_FREE_SOURCES) for src in KERNEL_SOURCES}
 
 
 if __name__ == "__main__":

@@ -124,3 +124,33 @@ def test_fp32_matrix_loops_hold_no_spills():
     found = isa_check.loop_spills(isa_check.assembly("attn_fp32.hip"))
     assert len(found) >= 10      # forward and dQ in two tile widths, dK/dV, both head sizes
     assert not any(found.values()), found
+
+
+FP32 = """
+	v_mfma_f32_16x16x4_f32 v[8:11], v4, v5, v[8:11]
+	v_mov_b32_e32 v1, 0
+	s_cbranch_vccnz .LBB0_2
+	s_nop 15
+.LBB0_2:
+	s_nop %d
+	v_mul_f32_e32 v2, v3, v9
+	s_endpgm
+"""
+
+
+def test_scanner_knows_the_fp32_instruction():
+    """Two instructions and the branch, then 7 or 6 of s_nop: 10 wait states are enough, 9 are not; what the compiler
+    schedules on a straight path is left to it where there is no inline assembly."""
+    assert isa_check.scan(FP32 % 7, inline_asm=False) == []
+    hits = isa_check.scan(FP32 % 6, inline_asm=False)
+    assert len(hits) == 1 and hits[0][2] == 9
+    straight = "\n\tv_mfma_f32_16x16x4_f32 v[8:11], v4, v5, v[8:11]\n\tv_mul_f32_e32 v2, v3, v9\n\ts_endpgm\n"
+    assert isa_check.scan(straight, inline_asm=False) == [] and len(isa_check.scan(straight)) == 1
+
+
+def test_every_source_with_matrix_instructions_is_scanned():
+    import os
+    import re
+    for f in os.listdir(isa_check.CSRC):
+        if f.endswith(".hip") and re.search(r"mfma32\w*\(|__builtin_amdgcn_mfma", open(os.path.join(isa_check.CSRC, f)).read()):
+            assert f in isa_check.KERNEL_SOURCES, f
