@@ -1,6 +1,6 @@
 """dQ of both branches in one launch (short sequences) against the sequential order: the same tiles of 32 rows per
-wavefront, one rounding of the sum -- the branches' own gradients agree bit for bit where both orders give a row the
-same key blocks, and everything agrees with the oracle in the parity tests, which run both orders."""
+wavefront, one rounding of the sum -- all gradients and delta agree bit for bit, for shared and separate modules and
+both tile widths, and everything agrees with the oracle in the parity tests, which run both orders."""
 import numpy as np
 import pytest
 import torch
@@ -41,3 +41,24 @@ def test_pair_with_tiles_of_256_rows(oracle, T, W, f):
     # 8 tiles of 256 rows x 40 (batch, KV head): beyond the 256 that workgroups of 128 rows take
     x = make_case(B_=2, T=T, Hq=20, Hkv=20, W=W, Hm=20, f=f, seed=78)
     run_and_check(oracle, x, kv_heads=(0, 19), twice=True)
+
+
+@pytest.mark.parametrize("separate", [False, True])
+@pytest.mark.parametrize("T,Hq,Hkv,W,Hm,f", [(1500, 14, 2, 300, 14, 0.1), (1700, 20, 20, 300, 20, 0.3), (1601, 20, 20, 1601, 1, 0.02)])
+def test_pair_and_sequential_give_the_same_bits(T, Hq, Hkv, W, Hm, f, separate):
+    """128 and 256 rows per workgroup (4 and 8 wavefronts; the sequential order always has 8): what differs are key blocks
+    in which a row sees nothing, whose weights are zero."""
+    x = make_case(B_=2, T=T, Hq=Hq, Hkv=Hkv, W=W, Hm=Hm, f=f, seed=79)
+    y = make_case(B_=2, T=T, Hq=Hq, Hkv=Hkv, W=W, Hm=Hm, f=f, seed=80) if separate else None
+    got = {}
+    for flags in (0, B.L2A_FLAG_SEQUENTIAL):
+        lay = layer_from_numpy(x.q, x.k, x.v, x.mask, W, "bf16", flags, **(dict(qg=y.q, kg=y.k, vg=y.v) if separate else {}))
+        lay.route()
+        lay.forward()
+        lay.backward(to_device(x.dO, "bf16"), separate=separate, want_delta=True)
+        torch.cuda.synchronize()
+        got[flags] = {n: getattr(lay, n) for n in ("dq", "dk", "dv", "delta_g") + (("dqg", "dkg", "dvg") if separate else ())}
+    for n, a in got[0].items():
+        b = got[B.L2A_FLAG_SEQUENTIAL][n]
+        print(n, "elements that differ:", int((a != b).sum()), "of", a.numel(), "largest", float((a.float() - b.float()).abs().max()))
+        assert torch.equal(a, b), n

@@ -1,6 +1,6 @@
 """l2a_route_compact_static -- the routing compaction for callers that cannot allocate or hand over a
 workspace (its chunk counters live in a fixed array in the library's device image) -- against
-l2a_route_compact on the same masks, bit for bit, on two calls in a row that share the array, the
+l2a_route_compact on the same masks, bit for bit, on calls in a row that share the array, the
 second with a smaller input; and against the oracle.  Collected last, so that a failure here hides
 no other test."""
 import numpy as np
@@ -12,8 +12,9 @@ from paper_2603_17484_amd import binding as B
 pytestmark = pytest.mark.gpu
 
 # (B, T, Hq, Hkv, mask heads, routed fraction): a long input (chunks of 2048 positions, ragged last chunk),
-# then a smaller one (chunks of 256), then one that uses a single counter
-CALLS = [(2, 70001, 14, 2, 14, 0.3), (1, 3000, 8, 2, 1, 0.6), (1, 5, 4, 4, 4, 0.5)]
+# then a smaller one (chunks of 256; 16 mask rows, so that it uses the counters), then two whose workgroups count for
+# themselves and leave them alone, then the first again
+CALLS = [(2, 70001, 14, 2, 14, 0.3), (1, 3000, 16, 1, 16, 0.6), (1, 3000, 8, 2, 1, 0.6), (1, 5, 4, 4, 4, 0.5), (2, 70001, 14, 2, 14, 0.3)]
 
 
 def test_static_scratch_route_compact_matches_the_workspace_entry_point(oracle):
