@@ -6,7 +6,7 @@
 // rounding of the saved bf16 output; the dK/dV kernel uses that value.
 //
 // Same decomposition as the forward: a workgroup owns a tile of consecutive rows (8 wavefronts
-// x 32 rows), a lane owns a row, everything is computed transposed:
+// x 32 rows; 4 in the shortest sequences, see mfma_bwd_dq_pair), a lane owns a row, everything is computed transposed:
 //   S^T  = K Q^T        A = K block (LDS),            B = Q  (registers)
 //   dP^T = V dO^T       A = V block (LDS),            B = dO (registers)
 //   dQ^T += K^T dS^T    A = K block read transposed (LDS), B = dS^T = the accumulators above

@@ -21,10 +21,10 @@
 //
 // Which sequences are routed and how long they are is device data, so every workgroup plans the batch, a lane per
 // sequence, and takes its units from that.  Whole step, us, a grid over all chunks with one wavefront each (the same
-// bits) / chunks of a length derived from the whole call (other bits) / now: 1 x 32K tokens, routed 33 / 22 / 23; 8 x 128K, 2
-// routed 136 / 113 / 121, none 40 / 24 / 22, all 409 / 377 / 393; 64 x 8K, 16 routed 203 / 133 / 134; 32 ring caches of 4K
-// 125 / 108 / 113; 130 x 4K, 32 routed 324 / 350 / 194; 512 x 1K 271 / 322 / 194; per-head decisions, 28 heads, 8 x 32K
-// 62 / 58 / 70, 32 heads, 32 x 16K 316 / 246 / 253.
+// bits) / chunks of a length derived from the whole call (other bits) / now: 1 x 32K tokens, routed 33 / 22 / 22; 8 x 128K, 2
+// routed 135 / 114 / 118, none 40 / 24 / 22, all 411 / 378 / 389; 64 x 8K, 16 routed 203 / 133 / 135; 32 ring caches of 4K
+// 126 / 108 / 113; 130 x 4K, 32 routed 324 / 350 / 195; 512 x 1K 272 / 322 / 196; per-head decisions, 28 heads, 8 x 32K
+// 62 / 58 / 66, 32 heads, 32 x 16K 317 / 246 / 253.
 #include "decode_units.hpp"
 #include "tiles.hpp"
 
@@ -483,12 +483,12 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_partial_kernel(DecodeAr
     }
 }
 
-// Thread = (branch, slice, four channels): slice i takes every nslices-th chunk of its branch with a running
-// maximum, the loads of kInFlight chunks in flight together; the slices meet in LDS, where a thread is a channel.
-// How many slices there are follows from the capacity alone: the order of the sums, and so the bits, are the
-// same in every batch.
-constexpr int kInFlight = 8;
+// Thread = (branch, slice, four channels): slice i takes every nslices-th chunk of its branch with a
+// running maximum; the slices meet in LDS, where a thread is a channel.  What it spends its time on is waiting for
+// partials that other XCDs wrote: 16 chunks' loads in flight together, 32 with MANY (184 registers), whole step against 8,
+// us: 1 x 32K 23.6 / 22.2 / 22.2, 8 x 128K, 2 routed 122.0 / 119.6 / 117.4, but 256 x 4K 374 / 374 / 389.
 constexpr int kSlices = 8;
+template <bool MANY>
 __global__ __launch_bounds__(2 * kSlices * 32) void decode_combine_kernel(DecodeArgs a) {
     const int nslices = blockDim.x >> 6;
     __shared__ __attribute__((aligned(16))) float so[2][kSlices][kD];
@@ -504,32 +504,39 @@ __global__ __launch_bounds__(2 * kSlices * 32) void decode_combine_kernel(Decode
         const float* base = a.part + ((size_t)(b * gm.Hkv + hk) * a.units * gm.G + g) * kPart;
         float m = -INFINITY, l = 0.f;
         f32x4 o = {0.f, 0.f, 0.f, 0.f};
-        if (on[branch])
-            for (int ch0 = c_lo + slice; ch0 <= c_hi; ch0 += kInFlight * nslices) {
-                f32x2 ml[kInFlight];
-                f32x4 x[kInFlight];
+        auto batch = [&](auto kc, int ch0) __attribute__((always_inline)) {
+            constexpr int K = decltype(kc)::value;
+            f32x2 ml[K];
+            f32x4 x[K];
 #pragma unroll
-                for (int j = 0; j < kInFlight; ++j) {  // past the end the first is read again, for nobody
-                    const int ch = ch0 + j * nslices, at = ch <= c_hi ? ch : ch0;
-                    const int unit = at == c_lo && lo % kChunk ? a.nchunks : at;
-                    const float* part = base + (size_t)unit * gm.G * kPart;
-                    ml[j] = *reinterpret_cast<const f32x2*>(part);
-                    x[j] = *reinterpret_cast<const f32x4*>(part + 4 + c4);
-                }
-#pragma unroll
-                for (int j = 0; j < kInFlight; ++j) {
-                    if (ch0 + j * nslices > c_hi) break;
-                    const float mn = fmaxf(m, ml[j][0]);
-                    // exp2(-inf) = 0 on the first chunk; a chunk of a ring may have no slot in the window (its
-                    // maximum is -inf): while nothing has been seen the reference is 0 and both factors are 0
-                    const float ref = mn == -INFINITY ? 0.f : mn;
-                    const float s0 = fast_exp2(m - ref), s1 = fast_exp2(ml[j][0] - ref);
-                    l = fmaf(l, s0, ml[j][1] * s1);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) o[e] = fmaf(o[e], s0, x[j][e] * s1);
-                    m = mn;
-                }
+            for (int j = 0; j < K; ++j) {  // past the end the first is read again, for nobody
+                const int ch = ch0 + j * nslices, at = ch <= c_hi ? ch : ch0;
+                const int unit = at == c_lo && lo % kChunk ? a.nchunks : at;
+                const float* part = base + (size_t)unit * gm.G * kPart;
+                ml[j] = *reinterpret_cast<const f32x2*>(part);
+                x[j] = *reinterpret_cast<const f32x4*>(part + 4 + c4);
             }
+#pragma unroll
+            for (int j = 0; j < K; ++j) {
+                if (ch0 + j * nslices > c_hi) break;
+                const float mn = fmaxf(m, ml[j][0]);
+                // exp2(-inf) = 0 on the first chunk; a chunk of a ring may have no slot in the window (its
+                // maximum is -inf): while nothing has been seen the reference is 0 and both factors are 0
+                const float ref = mn == -INFINITY ? 0.f : mn;
+                const float s0 = fast_exp2(m - ref), s1 = fast_exp2(ml[j][0] - ref);
+                l = fmaf(l, s0, ml[j][1] * s1);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[e] = fmaf(o[e], s0, x[j][e] * s1);
+                m = mn;
+            }
+        };
+        if (on[branch]) {
+            int ch0 = c_lo + slice;
+            if (MANY)
+                for (; ch0 + 16 * nslices <= c_hi; ch0 += 32 * nslices) batch(std::integral_constant<int, 32>{}, ch0);
+            for (; ch0 + 4 * nslices <= c_hi; ch0 += 16 * nslices) batch(std::integral_constant<int, 16>{}, ch0);
+            for (; ch0 <= c_hi; ch0 += 4 * nslices) batch(std::integral_constant<int, 4>{}, ch0);
+        }
         *reinterpret_cast<f32x4*>(&so[branch][slice][c4]) = o;
         if (c4 == 0) sm[branch][slice] = m, sl[branch][slice] = l;
     }
@@ -606,7 +613,11 @@ int mfma_decode(const Geom& g, const void* q, const void* k, const void* v, cons
         KernelTimer kt("decode_combine", st);
         // from the capacity alone: the order of the merge decides the bits
         const int slices = a.nchunks >= 128 ? kSlices : (a.nchunks >= 32 ? 4 : 2);
-        hipLaunchKernelGGL(decode_combine_kernel, dim3(g.B * g.Hq), dim3(2 * slices * 32), 0, st, a);
+        // long lists, and no more workgroups than two per CU
+        if (slices == kSlices && g.B * g.Hq <= 512)
+            hipLaunchKernelGGL(decode_combine_kernel<true>, dim3(g.B * g.Hq), dim3(2 * slices * 32), 0, st, a);
+        else
+            hipLaunchKernelGGL(decode_combine_kernel<false>, dim3(g.B * g.Hq), dim3(2 * slices * 32), 0, st, a);
     }
     return launch_status();
 }

@@ -11,7 +11,8 @@
 // a tile reads the same K/V.  K and the token-minor copy of V are streamed through LDS in blocks
 // of 64 keys by direct global->LDS loads (three and two buffers, one barrier per block).  With 32 rows
 // a wavefront needs 256 registers, so two share a SIMD (measured 2-5 % faster than 4 wavefronts of 64
-// rows at 500 registers, which the kernel template still covers).
+// rows at 500 registers, which the kernel template still covers).  Short sequences (half_tiles) have workgroups of 4
+// wavefronts and 128 rows, half a tile each, and both branches in one launch.
 //
 // Everything is computed transposed so that a lane owns a query row:
 //   S^T[key, row]  = K Q^T     A = K block (LDS), B = Q (registers, loaded once)

@@ -61,7 +61,7 @@ L2A_UNITS_FN int last_key(const Keys& s, int lo) {
 // may be a half); the others are for whole workgroups.  A unit takes a wavefront 14 us, a workgroup 4; but while the chip
 // streams, wavefronts that never wait for each other keep more loads on their way.  Whole step, us, all by workgroups /
 // by this rule: 8 x 128K tokens, all routed 460 / 393, 2 routed 141 / 121, none 21 / 22 (by wavefronts alone 27); 1 x
-// 32K 23 / 23 (31); 16 x 32K, 4 routed (2.9 units per workgroup) 88 / 81.
+// 32K 23 / 23 (31); 16 x 32K, 4 routed (2.9 units per workgroup) 88 / 81 (with a merge that took 2-4 us longer).
 L2A_UNITS_FN int by_wave(int all, int wgs) { return (all + 2 * wgs) / (kWaves * wgs) * (kWaves * wgs); }
 
 }  // namespace units
