@@ -20,11 +20,11 @@
 // with the batch is only who computes a unit, and how (two walks, same bits).
 //
 // Which sequences are routed and how long they are is device data, so every workgroup plans the batch, a lane per
-// sequence, and takes its units from that.  Whole step, us, a grid over all chunks with one wavefront each (the same
+// sequence, and takes its units from that (large batches: a wavefront for every unit there may be).  Whole step, us, a grid over all chunks with one wavefront each (the same
 // bits) / chunks of a length derived from the whole call (other bits) / now: 1 x 32K tokens, routed 33 / 22 / 22; 8 x 128K, 2
 // routed 135 / 114 / 118, none 40 / 24 / 22, all 411 / 378 / 389; 64 x 8K, 16 routed 203 / 133 / 135; 32 ring caches of 4K
-// 126 / 108 / 113; 130 x 4K, 32 routed 324 / 350 / 195; 512 x 1K 272 / 322 / 196; per-head decisions, 28 heads, 8 x 32K
-// 62 / 58 / 66, 32 heads, 32 x 16K 317 / 246 / 253.
+// 126 / 108 / 113; 130 x 4K, 32 routed 324 / 350 / 195; 512 x 1K 272 / 322 / 186; 16384 x 256 312 / 469 / 278; per-head
+// decisions, 28 heads, 8 x 32K 63 / 58 / 68 (the whole cache stays in the last-level cache there), 32 heads, 32 x 16K 314 / 246 / 253.
 #include "decode_units.hpp"
 #include "tiles.hpp"
 
@@ -50,6 +50,7 @@ struct DecodeArgs {
     float* part;        // [B, Hkv][units][G][kPart]
     int nchunks;        // chunks of the cache, = ceil(T / kChunk)
     int units;          // partials per (b, KV head): the chunks and, where a window may begin inside one, the Local one's
+    int planned;        // units::planned
     __bf16* O;          // [B, Hq, D]
     __bf16* S;
     __bf16* A;
@@ -108,12 +109,23 @@ __device__ __forceinline__ SeqPlan seq_plan(const DecodeArgs& a, int b) {
     return s;
 }
 
+// A unit: the keys lo..hi of one (b, KV head).
 struct Unit {
     int b, hk, slot;  // slot: where the partial goes
     int lo, hi;       // its keys
     int sb, pos;      // next sub-block to be computed; position of the new token
     __device__ __forceinline__ int ke() const { return hi / kSub; }
 };
+__device__ __forceinline__ Unit make_unit(const DecodeArgs& a, int b, int hk, const SeqPlan& s, int c) {
+    Unit u;
+    u.b = b, u.hk = hk;
+    u.slot = c == units::kEdge ? a.nchunks : c;
+    u.lo = units::first_key(s.keys, c);
+    u.hi = units::last_key(s.keys, u.lo);
+    u.sb = u.lo / kSub;
+    u.pos = s.pos;
+    return u;
+}
 // The i-th unit of sequence b on the XCD with residue r.
 __device__ __forceinline__ Unit find_unit(const DecodeArgs& a, int b, const SeqPlan& s, int i, int r) {
     const int lane = threadIdx.x & 63, hkv = a.gm.Hkv;
@@ -132,14 +144,7 @@ __device__ __forceinline__ Unit find_unit(const DecodeArgs& a, int b, const SeqP
         for (; rank > 0; --rank) set &= set - 1;
         hk = min(max(hk + __ffsll((long long)set) - 1, 0), hkv - 1);  // (decisions that changed meanwhile must not lead outside)
     }
-    Unit u;
-    u.b = b, u.hk = __builtin_amdgcn_readfirstlane(hk);
-    u.slot = at.c == units::kEdge ? a.nchunks : at.c;
-    u.lo = units::first_key(s.keys, at.c);
-    u.hi = units::last_key(s.keys, u.lo);
-    u.sb = u.lo / kSub;
-    u.pos = s.pos;
-    return u;
+    return make_unit(a, b, __builtin_amdgcn_readfirstlane(hk), s, at.c);
 }
 
 // An address that is the same in all lanes, in scalar registers.
@@ -354,6 +359,17 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_partial_kernel(DecodeAr
     const int tr_i = lane & 15;
     const lds_cptr vread = (lds_cptr)(uintptr_t)(lds_offset(&lds.v[wave][0]) + (4 * h + (tr_i >> 2)) * 64 + (16 * ((lane >> 4) & 1) + 4 * (tr_i & 3)) * 2);
 
+    if (!a.planned) {
+        const long long at = (long long)blockIdx.x * kWaves + wave;
+        const int per = gm.Hkv * a.units, b = (int)(at / per);
+        if (b >= gm.B) return;
+        const int i = (int)(at - (long long)b * per), hk = i / a.units, slot = i - hk * a.units;
+        const SeqPlan s = seq_plan(a, b);
+        const int c = slot == a.nchunks ? units::kEdge : slot;
+        if (units::needed(s.keys, c, false) || (a.do_global && c != units::kEdge && kv_routed(a, b, hk) && units::needed(s.keys, c, true)))
+            unit_by_wave<RING>(a, make_unit(a, b, hk, s, c), koff, &lds.k[wave][0], &lds.v[wave][0]);
+        return;
+    }
     // ---- the units for single wavefronts
     {
         while (plan_next()) {}
@@ -603,7 +619,9 @@ int mfma_decode(const Geom& g, const void* q, const void* k, const void* v, cons
         KernelTimer kt("decode_partial", st);
         // no more workgroups than an XCD can have units
         const long long most = 8ll * g.B * g.Hkv * ((a.units + 7) / 8);
-        const dim3 grid((unsigned)(most < kMostGroups ? most : kMostGroups));
+        a.planned = units::planned(g.B, do_global && mask && mask_heads > 1);
+        const long long places = (long long)g.B * g.Hkv * a.units;
+        const dim3 grid((unsigned)(!a.planned ? (places + kWaves - 1) / kWaves : most < kMostGroups ? most : kMostGroups));
         if (ring)
             hipLaunchKernelGGL(decode_partial_kernel<true>, grid, dim3(64 * kWaves), 0, st, a);
         else

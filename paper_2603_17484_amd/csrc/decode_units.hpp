@@ -51,11 +51,23 @@ L2A_UNITS_FN Place place(const Keys& s, int heads, int routed, int i, int r) {
     if (prefix) return Place{1, j - v8 * of, v < s.chunks() ? v : kEdge};
     return Place{0, j - v8 * of, v < s.edge() ? kEdge : s.first() + v - s.edge()};
 }
+// Whether a head needs chunk c at all.
+L2A_UNITS_FN bool needed(const Keys& s, int c, bool prefix) {
+    if (c == kEdge) return s.edge() != 0;
+    return c < s.chunks() && (prefix || (s.local && c >= s.first()));
+}
 L2A_UNITS_FN int first_key(const Keys& s, int c) { return c == kEdge ? s.win : c * kChunk; }
 L2A_UNITS_FN int last_key(const Keys& s, int lo) {
     const int end = lo / kChunk * kChunk + kChunk - 1;
     return end < s.t ? end : s.t;
 }
+
+// Whether the workgroups plan the batch, each going through all its sequences, 64 at a time, or a wavefront is launched for every
+// place where a partial may go and finds out whether it is needed.  Whole step, us, planned / not: 8 x 128K tokens, 2 routed
+// 118 / 130, none routed 22 / 32; 64 x 8K 134 / 135; 256 x 4K, W = 1024 90 / 97, 256 x 1K 37 / 34; 512 x 1K 58 / 55, 4K 198 / 192; 4096 x
+// 512 194 / 138; 16384 x 256 494 / 278.  With decisions of its own for every head a sequence takes longer to plan: 65 x 1K
+// 30 / 24, 128 x 1K 39 / 28, but 8 x 128K, 2 % routed 78 / 98.
+inline bool planned(long long batch, bool per_head) { return batch <= (per_head ? 64 : 256); }
 
 // How many of an XCD's units its `wgs` workgroups work on with a wavefront each (full rounds of kWaves wgs; the last one
 // may be a half); the others are for whole workgroups.  A unit takes a wavefront 14 us, a workgroup 4; but while the chip

@@ -61,6 +61,11 @@ int units_check(int B, int heads, int local, const int* t, const int* win, const
                     for (int c = win[b] / 512 + (win[b] % 512 != 0); c <= t[b] / 512; ++c) need.push_back(c);
                 if (local && win[b] % 512 != 0) need.push_back(kEdge);
                 want += need.size();
+                for (int c = kEdge; c < t[b] / 512 + 3; ++c) {  // without a plan: every place where a partial may go
+                    int in = 0;
+                    for (int x : need) in += x == c;
+                    if (in != (kind || local ? needed(s, c, kind != 0) : 0)) return fail(msg, len, "sequence %d, chunk %d: needed or not?", b, c);
+                }
                 for (int c : need) {
                     if (seen[std::make_tuple(b, kind, rank, c)] != 1)
                         return fail(msg, len, "sequence %d, %s head %d, chunk %d: %d times", b, kind ? "routed" : "unrouted", rank, c, seen[std::make_tuple(b, kind, rank, c)]);

@@ -20,11 +20,13 @@ def step(p, q, k, v, pos, mask):
 
 
 # units by workgroups alone (few), by both, by single wavefronts (many); batches of one and of several groups of 64
-# sequences; more KV heads than 64
+# sequences, and so large that they are not planned (64 with decisions per head, 256 otherwise); more KV heads than 64
 @pytest.mark.parametrize("Bn,T,Hq,Hkv,Hm,W,f,flags", [
     (2, 3000, 28, 4, 1, 700, 0.5, 0), (6, 9000, 14, 2, 14, 1024, 0.3, 0), (12, 8191, 32, 8, 1, 4096, 1.0, 0),
     (70, 4000, 32, 8, 8, 1000, 0.4, 0), (150, 1025, 16, 8, 16, 100, 0.2, 0), (5, 2000, 40, 40, 40, 300, 0.5, 0), (3, 1500, 70, 70, 70, 300, 0.4, 0),
-    (9, 5000, 8, 4, 1, 64, 0.5, B.L2A_FLAG_SKIP_LOCAL), (9, 5000, 8, 4, 1, 600, 0.5, B.L2A_FLAG_SKIP_GLOBAL),
+    (256, 1100, 8, 2, 1, 130, 0.4, 0), (257, 1100, 8, 2, 1, 130, 0.4, 0), (64, 700, 8, 2, 8, 512, 0.4, 0),
+    (257, 700, 8, 2, 1, 130, 0.4, B.L2A_FLAG_SKIP_LOCAL), (260, 1056, 8, 2, 1, 700, 0.4, B.L2A_FLAG_SKIP_GLOBAL | B.L2A_FLAG_RING_CACHE),
+    (300, 700, 8, 2, 1, 0, 0.4, B.L2A_FLAG_SKIP_GLOBAL), (9, 5000, 8, 4, 1, 64, 0.5, B.L2A_FLAG_SKIP_LOCAL), (9, 5000, 8, 4, 1, 600, 0.5, B.L2A_FLAG_SKIP_GLOBAL),
     (40, 2080, 8, 8, 1, 2000, 0.5, B.L2A_FLAG_SKIP_GLOBAL | B.L2A_FLAG_RING_CACHE)])
 def test_bits_do_not_depend_on_the_batch(Bn, T, Hq, Hkv, Hm, W, f, flags):
     g = torch.Generator(device="cuda").manual_seed(Bn + T)
