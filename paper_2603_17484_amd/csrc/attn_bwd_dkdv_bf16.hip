@@ -115,8 +115,9 @@ __global__ __launch_bounds__(64 * kPairWaves) void bwd_dkdv_kernel(PairArgs a) {
             const int32_t* first = rs.kblk_first_row + (size_t)bh * (nkb + 1);
             kind = walk::kListRows;
             rows = rows_total(rs, gm, bh);  // clamped like the entries of `first`: device data
-            f_lo = first[k0 >> 6];
-            f_hi = first[min((k0 + kKeysPerWg) >> 6, nkb)];
+            const walk::ListBounds at = walk::list_bounds(k0, rs.shift, nkb);
+            f_lo = first[at.lo];
+            f_hi = first[at.hi];
         }
         return walk::tile_runs(kind, k0, gm.T, gm.G, gm.W, f_lo, f_hi, rows, a.nsplit, job.z);
     };

@@ -22,6 +22,7 @@ struct RowSet {
     const int32_t* count;    // [B,Hkv]     or nullptr = T*G rows
     const int32_t* kblk_first_row;  // [B,Hkv,ceil(T/64)+1] or nullptr (identity: 64*k*G)
     int local;               // 1: sliding-window branch
+    int shift = 0;           // GLOBAL: keys 0..pos - shift only (what a shared-input backward leaves to this pass: W + 1)
 };
 
 constexpr float kLog2e = 1.4426950408889634f;
@@ -90,8 +91,13 @@ int router_decide(const l2a_params& p, int C, const void* x, const float* w, flo
                   float* dhat, uint8_t* mask, hipStream_t st);
 
 // ---- util.hip
+// share_zero: optional, [B,Hq,T] set to zero on the way
 int row_deltas(const Geom& g, int dtype, const void* dO, const void* S, const void* A, float* delta_l,
-               float* delta_g, hipStream_t st);
+               float* delta_g, float* share_zero, hipStream_t st);
+// Backward of a layer whose branches share their inputs: the two branches of a routed row in its window as one row.
+// share[b,h,t] = a = exp(lse_local - lse_global) (1e-30 at least; 0 on rows not in rs) and delta_l = (delta_l + a delta_g) / (1 + a) on the rows of rs.
+int fold_rows(const Geom& g, const RowSet& rs, const float* lse_l, const float* lse_g, float* delta_l, const float* delta_g,
+              float* share, hipStream_t st);
 // bf16: delta of the first 64 tokens of every sequence recomputed from its definition, one or two branches
 struct HeadDeltas {
     const void *q, *k, *v;
@@ -129,16 +135,21 @@ struct Fill {  // n 32-bit words of one value
 // one or two V tensors; up to three buffers are filled by the same launch
 int pack_kv(const Geom& g, int n, const void* const* x, void* const* xt, int cap, const Fill* fills, int nfills,
             hipStream_t st);
-// O += A on the rows of rs (O bf16, A fp32, D = 128)
-int merge_rows(const Geom& g, const RowSet& rs, const float* A, void* O, hipStream_t st);
+// O += A on the rows of rs (O bf16, A fp32, D = 128), or O = S + A with S in fp32, where S is given
+// (rows that see a key: those at positions below rs.shift are left as they are)
+int merge_rows(const Geom& g, const RowSet& rs, const float* S, const float* A, void* O, hipStream_t st);
+// share (see fold_rows), with the Local rows: their statistics are those of the folded rows, and delta_g is completed
 int pack_rows(const Geom& g, const RowSet& rs, const void* q, const void* dO, const float* lse, const float* delta,
-              void* qc, void* gc, float* lse2_c, float* delta_c, int32_t* pos_c, int cap, hipStream_t st);
+              void* qc, void* gc, float* lse2_c, float* delta_c, int32_t* pos_c, int cap, const float* share, float* delta_g,
+              hipStream_t st);
+// wide (with share): the parts of rows that both passes visit, in fp32 -- written by the Local pass, added by the Global one;
+// share: see fold_rows; delta on return: Local rows delta_l, Global rows (keys 0..pos - shift only) their part of delta_g
 int mfma_bwd_dq(const Geom& g, const RowSet& rs, const void* q, const void* k, const void* v, const void* dO,
-                const float* lse, float* delta, void* dq, int accumulate, hipStream_t st);
+                const float* lse, float* delta, const float* share, void* dq, int accumulate, float* wide, hipStream_t st);
 int mfma_bwd_dq_pair(const Geom& g, const RowSet& rs_l, const void* q_l, const void* k_l, const void* v_l,
                      const float* lse_l, float* delta_l, void* dq_l, const RowSet& rs_g, const void* q_g,
-                     const void* k_g, const void* v_g, const float* lse_g, float* delta_g, void* dq_g, float* wide_g,
-                     const void* dO, hipStream_t st);
+                     const void* k_g, const void* v_g, const float* lse_g, float* delta_g, const float* share, void* dq_g,
+                     float* wide_l, float* wide_g, const void* dO, hipStream_t st);
 // packed[s]: the five outputs of pack_rows for set s (qc, gc, lse2_c, delta_c, pos_c)
 // part: scratch for dkdv_splits(g) x 2 x (B T Hkv D) floats when dkdv_splits(g) > 1 (short sequences)
 int dkdv_splits(const Geom& g);

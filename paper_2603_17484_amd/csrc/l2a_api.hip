@@ -84,11 +84,13 @@ size_t dkdv_part_bytes(const l2a_params& p) {
     const int z = dkdv_splits(make_geom(p));
     return z > 1 ? (size_t)z * 2 * p.B * p.T * p.Hkv * p.D * sizeof(float) : 0;
 }
+// backward with shared inputs: the branches of a routed row are folded (fold_rows)
+bool may_fold(const l2a_params& p) {
+    return use_mfma(p) && !(p.flags & (L2A_FLAG_DENSE | L2A_FLAG_SKIP_LOCAL | L2A_FLAG_SKIP_GLOBAL));
+}
 size_t bwd_workspace_bytes(const l2a_params& p) {
     return 2 * delta_bytes(p) + (use_mfma(p) ? 2 * packed_set_bytes(p) + dkdv_part_bytes(p) : 0);
 }
-
-
 
 }  // namespace
 
@@ -242,7 +244,7 @@ int l2a_attn_fwd(const l2a_params* p, const void* q_loc, const void* k_loc, cons
         if ((r = mfma_fwd_pair(g, rs_l, q_loc, k_loc, v_loc, vt_loc, out_l, rs_g, q_glb, k_glb, v_glb, vt_glb, out_g,
                                kv_cap(*p), (int32_t*)after_v, st)) != L2A_OK)
             return r;
-        return merge_rows(g, rs_g, A32, O, st);
+        return merge_rows(g, rs_g, nullptr, A32, O, st);
     }
     auto fwd_branch = [&](const RowSet& rs, const void* q, const void* k, const void* v, const void* vt,
                           const FwdOut& out) {
@@ -307,13 +309,24 @@ int l2a_attn_bwd(const l2a_params* p, const void* dO, const void* q_loc, const v
     float* delta_l = (float*)workspace;
     float* delta_g = delta_glb_opt ? delta_glb_opt : (float*)((char*)workspace + delta_bytes(*p));
     const bool mfma = use_mfma(*p), fp32 = p->dtype == L2A_FP32;
+    // Shared inputs and summed gradients: the window of a routed row counts once for both branches, and the Global pass
+    // only takes the keys before it (none at all while the window spans the sequence).
+    const bool fold = may_fold(*p) && out_alias;
+    char* packed_base = (char*)workspace + 2 * delta_bytes(*p);
+    // Until the rows are packed their place is free.  dQ of a folded row is the sum of two passes' parts, kept in fp32 where
+    // its branch's rows will lie and rounded once; the rows' shares lie where the second set's statistics will.
+    float* wide_l = fold ? (float*)packed_base : nullptr;
+    float* wide_g = fold ? (float*)(packed_base + packed_set_bytes(*p)) : nullptr;
+    float* share = fold ? (float*)(packed_base + packed_set_bytes(*p) + 2 * rows_copy_bytes(*p)) : nullptr;
+    const int far_shift = fold ? g.W + 1 : 0;
+    const bool far_rows = !fold || g.T > far_shift;
     auto bwd_dq = [&](const RowSet& rs, const void* q, const void* k, const void* v, const float* lse, float* delta,
                       void* dq, int acc) {
-        if (mfma) return mfma_bwd_dq(g, rs, q, k, v, dO, lse, delta, dq, acc, st);
+        if (mfma) return mfma_bwd_dq(g, rs, q, k, v, dO, lse, delta, share, dq, acc, far_rows ? wide_l : nullptr, st);
         return fp32 ? fp32_bwd_dq(g, rs, q, k, v, dO, lse, delta, dq, acc, st)
                     : simple_bwd_dq(g, rs, q, k, v, dO, lse, delta, dq, acc, st);
     };
-    if ((r = row_deltas(g, p->dtype, dO, do_local ? S : nullptr, do_global ? A : nullptr, delta_l, delta_g, st)) !=
+    if ((r = row_deltas(g, p->dtype, dO, do_local ? S : nullptr, do_global ? A : nullptr, delta_l, delta_g, share, st)) !=
         L2A_OK)
         return r;
     if (p->dtype == L2A_BF16) {  // outputs saved in bf16: the first tokens' deltas come from the definition instead
@@ -323,22 +336,19 @@ int l2a_attn_bwd(const l2a_params* p, const void* dO, const void* q_loc, const v
     }
 
     const RowSet rs_l{nullptr, nullptr, nullptr, 1};
-    const RowSet rs_g = dense ? RowSet{nullptr, nullptr, nullptr, 0} : RowSet{row_idx, count, kblk_first_row, 0};
+    const RowSet rs_g = dense ? RowSet{nullptr, nullptr, nullptr, 0} : RowSet{row_idx, count, kblk_first_row, 0, far_shift};
+    if (fold && (r = fold_rows(g, rs_g, lse_local, lse_global, delta_l, delta_g, share, st)) != L2A_OK) return r;
 
-    // dQ: one pass per branch over that branch's rows; short sequences: both in one launch, the Global branch's
-    // share of a summed dQ in fp32 first (where the packed rows go afterwards) and added with the one rounding
-    // the sequential order has
-    char* packed_base = (char*)workspace + 2 * delta_bytes(*p);
-    if (pair_bwd(*p)) {
+    // dQ: one pass per branch over that branch's rows; short sequences: both in one launch
+    if (pair_bwd(*p) && far_rows) {
         if (!out_alias && (r = fill_zero(dq_glb, q_elems(*p) * elem_bytes(*p), st)) != L2A_OK) return r;
-        float* wide = out_alias ? (float*)packed_base : nullptr;
         if ((r = mfma_bwd_dq_pair(g, rs_l, q_loc, k_loc, v_loc, lse_local, delta_l, dq_loc, rs_g, q_glb, k_glb, v_glb,
-                                  lse_global, delta_g, dq_glb, wide, dO, st)) != L2A_OK)
+                                  lse_global, delta_g, share, dq_glb, wide_l, wide_g, dO, st)) != L2A_OK)
             return r;
-        if (wide && (r = merge_rows(g, rs_g, wide, dq_loc, st)) != L2A_OK) return r;
+        if (fold && (r = merge_rows(g, rs_g, wide_l, wide_g, dq_loc, st)) != L2A_OK) return r;
     } else {
         if (do_local && (r = bwd_dq(rs_l, q_loc, k_loc, v_loc, lse_local, delta_l, dq_loc, 0)) != L2A_OK) return r;
-        if (do_global) {
+        if (do_global && far_rows) {
             if (!out_alias && !dense && (r = fill_zero(dq_glb, q_elems(*p) * elem_bytes(*p), st)) != L2A_OK) return r;
             if ((r = bwd_dq(rs_g, q_glb, k_glb, v_glb, lse_global, delta_g, dq_glb, out_alias ? 1 : 0)) != L2A_OK)
                 return r;
@@ -358,7 +368,7 @@ int l2a_attn_bwd(const l2a_params* p, const void* dO, const void* q_loc, const v
             void* out[5] = {base, base + rows_copy_bytes(*p), stat, stat + rows_stat_bytes(*p),
                             stat + 2 * rows_stat_bytes(*p)};
             const int rc2 = pack_rows(g, sets[i], qs[i], dO, lses[i], deltas[i], out[0], out[1], (float*)out[2],
-                                      (float*)out[3], (int32_t*)out[4], cap, st);
+                                      (float*)out[3], (int32_t*)out[4], cap, sets[i].local ? share : nullptr, delta_g, st);
             if (rc2 != L2A_OK) return rc2;
             for (int j = 0; j < 5; ++j) packed[i][j] = out[j];
         }
@@ -370,7 +380,7 @@ int l2a_attn_bwd(const l2a_params* p, const void* dO, const void* q_loc, const v
         const void* qs[2] = {q_loc, q_loc};
         const float* lses[2] = {lse_local, lse_global};
         const float* deltas[2] = {delta_l, delta_g};
-        return dkdv(sets, 2, qs, lses, deltas, k_loc, v_loc, dk_loc, dv_loc);
+        return dkdv(sets, far_rows ? 2 : 1, qs, lses, deltas, k_loc, v_loc, dk_loc, dv_loc);
     }
     if (do_local) {
         const void* qs[1] = {q_loc};

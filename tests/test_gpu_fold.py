@@ -1,0 +1,47 @@
+"""The backward of a layer with shared inputs, where a routed row's window counts once for both branches and the Global pass
+takes the keys before it: windows around the edges at which a row, a tile of rows or a block of keys has keys before the
+window at all (tiles of 32 and 256 rows, blocks of 64 and 128 keys), both tile widths, both orders, batches, every mask
+granularity, and scores so uneven that one branch's share of a row vanishes."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2603_17484_amd import binding as B
+from paper_2603_17484_amd.runner import layer_from_numpy, to_device
+from tests.gpu_helpers import make_case, run_and_check
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("order", [0, B.L2A_FLAG_SEQUENTIAL])
+@pytest.mark.parametrize("T,W,Hq,Hkv,Hm,f", [(300, 298, 4, 2, 1, 0.5), (300, 299, 4, 2, 1, 0.5), (300, 300, 4, 2, 4, 0.5),
+                                             (321, 63, 7, 1, 7, 0.3), (321, 64, 7, 1, 1, 1.0), (449, 127, 2, 2, 2, 0.04),
+                                             (641, 0, 4, 1, 4, 0.2), (1700, 190, 20, 20, 20, 0.1)])
+def test_window_edges(oracle, T, W, Hq, Hkv, Hm, f, order):
+    run_and_check(oracle, make_case(B_=2, T=T, Hq=Hq, Hkv=Hkv, W=W, Hm=Hm, f=f, seed=T + W), order, twice=True,
+                  kv_heads=(0, Hkv - 1) if Hkv > 2 else None)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+def test_a_key_before_the_window_takes_all_the_weight(oracle, dtype):
+    # one early key whose score with every later query is about 60 above the rest: exp(lse_local - lse_global) ~ e^-60, and
+    # rows before the window's end where it is 1
+    x = make_case(T=400, Hq=4, Hkv=2, W=50, f=0.4, dtype=dtype, seed=3)
+    x.q[..., 0], x.k[..., 0] = 8.0, 0.0
+    x.k[:, 5, :, 0] = 85.0
+    lay = layer_from_numpy(x.q, x.k, x.v, x.mask, x.w.W, dtype)
+    lay.route()
+    lay.forward()
+    lay.backward(to_device(x.dO, dtype), want_delta=True)
+    torch.cuda.synchronize()
+    pr = oracle.Problem(x.q, x.k, x.v, x.mask, x.w.W)
+    ref = oracle.layer_fwd(pr)
+    g = oracle.layer_bwd(pr, x.dO, ref)
+    # relative to the tensors' size: half an ulp of bf16 outputs and of the weights and dS on the way (2^-9 each, a few of
+    # them), 2^-22 times the largest score in fp32
+    tol = 2e-2 if dtype == "bf16" else 1e-4
+    for name, got, want in (("O", lay.O, ref["S"] + ref["A"]), ("dq", lay.dq, g["dq_l"] + g["dq_g"]),
+                            ("dk", lay.dk, g["dk_l"] + g["dk_g"]), ("dv", lay.dv, g["dv_l"] + g["dv_g"])):
+        err = np.linalg.norm(got.double().cpu().numpy() - want) / np.linalg.norm(want)
+        print(name, "relative error", err, flush=True)
+        assert err <= tol, name
