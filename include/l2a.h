@@ -89,12 +89,14 @@ const char* l2a_strerror(int code);
  * calls; calls that share one workspace must be ordered on one stream.  What it holds:
  *   route     one int32 count per (b, KV head, chunk of 2048 positions; of 256 for T <= 16384)
  *   forward   bf16, D = 128 without L2A_FLAG_SCALAR: a token-minor copy [B,Hkv,D,ceil64(T)] of
- *             each branch's V and one int32 flag per tile of 256 rows (tiles per (b, KV head)
- *             rounded up to a multiple of 8); when both branches run in one launch (see
+ *             each branch's V (shared inputs: in place of the second, the list of the rows that are not
+ *             routed) and one int32 flag per tile of 256 rows (tiles per (b, KV head) rounded up to a
+ *             multiple of 8; 1 for a tile whose softmax needed a running maximum); when both branches run in one launch (see
  *             l2a_attn_fwd) the flags twice and a [B,T,Hq,D] float buffer for a; else nothing
  *   backward  delta_t of each branch, [B,Hq,T] float, twice; on the matrix-core path also, per
  *             branch, compact row-major copies of the rows' Q and dO (ceil64(T G) rows per
- *             (b, KV head)) with three per-row statistics; short sequences (fewer than 1024
+ *             (b, KV head)) with three per-row statistics (shared inputs: before those, the two passes'
+ *             parts of dq in float); short sequences (fewer than 1024
  *             blocks of 128 keys over all (b, KV head)): up to 8 x 2 float copies of [B,T,Hkv,D],
  *             partial sums of the workgroups that share a key block's rows
  */
@@ -176,10 +178,13 @@ int l2a_router_decide(const l2a_params* p, int32_t C, const void* x, const float
  *   S_opt       out optional [B,T,Hq,D]: s alone (needed by l2a_attn_bwd)
  *   A_opt       out optional [B,T,Hq,D]: d a alone, zero where d = 0 (needed by l2a_attn_bwd)
  *
- * Short sequences (bf16, D = 128, both branches, routing lists in use, at most 2048 tiles of 256
- * rows over all (b, KV head)): the Global rows' tiles alone would occupy a fraction of the chip, so
+ * With bf16, D = 128, both branches, routing lists in use and shared inputs (each *_glb pointer equal to its
+ * *_loc partner), a routed row's window is computed once for both branches: its workgroup walks the
+ * window, which gives s, and then the keys before it, which gives a; one launch, whatever the order flags.
+ * A layer of separate modules, or one without kblk_first_row, runs its branches apart.  While they are short (at most
+ * 2048 tiles of 256 rows over all (b, KV head)) the Global rows' tiles alone would occupy a fraction of the chip, so
  * the two branches run in one launch, the Global one leaves a in fp32 in the workspace, and a
- * third, small kernel forms o = s + d a -- bit for bit the result of the sequential order, where
+ * second, small kernel forms o = s + d a -- bit for bit the result of the sequential order, where
  * the Global kernel adds its fp32 result to the stored s.  L2A_FLAG_SEQUENTIAL keeps the sequential
  * order at every length.
  */

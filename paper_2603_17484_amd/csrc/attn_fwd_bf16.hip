@@ -6,6 +6,8 @@
 // The epilogue writes the log-sum-exp and merges into O (Sec. 3.1 Eq. 5), so the scatter of
 // Alg. 1's last step costs no extra pass.
 //
+// Layers whose branches share q, k, v take the routed rows with both branches in one walk (kBoth, fwd_shared_kernel).
+//
 // Work decomposition.  One workgroup = 8 wavefronts of 32 rows = a tile of 256 consecutive rows of
 // one (batch, KV head); the rows of the G query heads of the group are interleaved, so every row of
 // a tile reads the same K/V.  K and the token-minor copy of V are streamed through LDS in blocks
@@ -31,10 +33,8 @@ namespace l2a {
 namespace {
 
 constexpr int kBK = 64;  // keys per block
-constexpr int kNQB = 2;  // 32-row blocks per wavefront (fix-up kernel)
-constexpr int kFwdNQB = 1, kFwdNW = 8;  // the pipelined kernel's shape: see fwd_kernel
-constexpr int kRW = 32 * kNQB;
-constexpr int kBQ = 4 * kRW;
+constexpr int kFwdNQB = 1, kFwdNW = 8;  // the kernel's shape: see fwd_kernel
+constexpr int kBQ = 256;                // rows of a tile
 constexpr int kAhead = 2;  // operand look-ahead, in operands (each feeds two instructions)
 
 #define L2A_FENCE() __builtin_amdgcn_sched_barrier(0)
@@ -44,11 +44,15 @@ struct FwdArgs {
     RowSet rs;
     const __bf16* q;
     const __bf16* k;
-    const __bf16* v;   // V as given (fix-up kernel only)
+    const __bf16* v;   // V as given (running_max_body only)
     const __bf16* vt;  // token-minor copy of V: [B*Hkv][128][vt_cap]
     int vt_cap;
-    int32_t* redo;  // [B*Hkv][width of the branch's grid]: set to 1 for a tile whose rows must be recomputed by the fix-up kernel
+    int32_t* redo;  // [B*Hkv][redo_stride]: set to 1 for a tile of 256 rows that was left to running_max_body
+    int redo_stride;
     FwdOut out;
+    // kBoth: `out` is where a goes (main_out: o); s and its log-sum-exp
+    __bf16* s_out = nullptr;
+    float* s_lse = nullptr;
 };
 
 template <int NQB>
@@ -62,36 +66,31 @@ using Int = std::integral_constant<int, V>;
 // NW wavefronts of NQB x 32 rows each.  256 rows (NW * NQB = 8): 4 x 2 runs one wavefront per SIMD with 500 registers,
 // 8 x 1 runs two per SIMD with 256 each, so that one wavefront's softmax arithmetic can overlap the
 // other's matrix instructions.
-// (bx, by) of (gx, nbh): the workgroup's index in its branch's part of the grid (a launch may carry both branches)
-template <bool LOCAL, int NQB, int NW>
-__device__ __forceinline__ void fwd_body(const FwdArgs& a, const int bx, const int by, const int gx, const int nbh,
-                                         __bf16 (&lds_k)[3][kBK * 128], __bf16 (&lds_v)[2][kD * kBK]) {
-    constexpr int RW = 32 * NQB;       // rows per wavefront
-    constexpr int BQ = RW * NW;        // rows per workgroup: a fix-up tile, or a whole part of one
-    static_assert(kBQ % BQ == 0, "a workgroup's rows lie in one fix-up tile");
-    constexpr int NS = 16 * NQB;       // slots (matrix instructions) per half-block: NS / 2 for S, NS / 2 for P V
-    constexpr int NL = 16 / NW;        // 16-byte loads a wavefront issues per K or V block
-    constexpr int kLoadSlot0 = NS - 1 - 2 * NL;  // the loads of later blocks go out in the last slots of a block's first half
-    using Scores = ScoresT<NQB>;
+// What a workgroup computes for its rows.  kBoth: routed rows of a layer whose branches share their inputs -- the window
+// first, whose sums give s, then the keys before it into the same sums, which give a: the scores of the window, and its
+// products with V, are computed once for both branches.
+enum Kind { kGlobal, kLocal, kBoth };
 
-    const Geom& gm = a.gm;
-    // Workgroups are dispatched in the order of their linear index and dealt round-robin to the 8 XCDs
-    // (the grid's width is a multiple of 8).  Global rows: longest prefixes first; every tile starts
-    // at key block 0, so the tiles resident on an XCD read the same K/V blocks at about the same time
-    // whatever their order.  While the K and V of all heads together about fit the last-level cache, the
-    // order runs over all (b, KV head) together (rotated, so that no XCD is tied to one head) -- with
-    // a few hundred tiles in all, a head whose long tiles started last would set the kernel's time;
-    // beyond that the heads go one after the other, so that the chip streams one head's K and V at a time.
-    // Local rows: each XCD takes a contiguous range of a head's tiles, so that the tiles resident on it
-    // have overlapping windows and share their K/V blocks through its L2 -- when the sequence is
-    // several windows long, so that the ranges cost the same; otherwise the tiles' costs grow with
-    // their position like the Global ones' and they are ordered the same way.
-    int bh, rank;
-    const bool by_range = LOCAL && gm.T / 4 > gm.W;
-    if (by_range) {
-        bh = by;
-        rank = (bx & 7) * (gx >> 3) + (bx >> 3);
-    } else if ((long long)nbh * gm.T <= kAllHeadsMaxTokens) {
+// Which tile of which (b, KV head) a workgroup takes; (bx, by) of (gx, nbh): its index in its branch's part of the grid (a
+// launch may carry both branches).
+//
+// Workgroups are dispatched in the order of their linear index and dealt round-robin to the 8 XCDs
+// (the grid's width is a multiple of 8).  Global rows: longest prefixes first; every tile starts
+// at key block 0, so the tiles resident on an XCD read the same K/V blocks at about the same time
+// whatever their order.  While the K and V of all heads together about fit the last-level cache, the
+// order runs over all (b, KV head) together (rotated, so that no XCD is tied to one head) -- with
+// a few hundred tiles in all, a head whose long tiles started last would set the kernel's time;
+// beyond that the heads go one after the other, so that the chip streams one head's K and V at a time.
+// Local rows: each XCD takes a contiguous range of a head's tiles, so that the tiles resident on it
+// have overlapping windows and share their K/V blocks through its L2 -- when the sequence is
+// several windows long, so that the ranges cost the same; otherwise the tiles' costs grow with
+// their position like the Global ones' and they are ordered the same way.
+struct Tile {
+    int bh, tile, n_rows;
+};
+__device__ __forceinline__ bool windows_by_range(const Geom& gm) { return gm.T / 4 > gm.W; }
+__device__ __forceinline__ void head_and_rank(const Geom& gm, int bx, int by, int gx, int nbh, int& bh, int& rank) {
+    if ((long long)nbh * gm.T <= kAllHeadsMaxTokens) {
         const int lin = by * gx + bx;
         rank = lin / nbh;
         bh = (lin - rank * nbh + rank) % nbh;
@@ -99,374 +98,44 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const int bx, const i
         bh = by;
         rank = bx;
     }
-    const int b = bh / gm.Hkv, hk = bh - b * gm.Hkv;
-    const int n_rows = rows_total(a.rs, gm, bh);
-    const int n_tiles = (n_rows + BQ - 1) / BQ;
-    const int tile = by_range ? rank : n_tiles - 1 - rank;
-    if (tile < 0 || tile >= n_tiles) return;
-
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int n = lane & 31, h = lane >> 5;
-
-    // ---- rows of this workgroup / wavefront / lane
-    const int wg_r0 = tile * BQ;
-    const int wg_r1 = min(wg_r0 + BQ, n_rows);  // exclusive
-    const int wg_pmin = row_code(a.rs, gm, bh, wg_r0) / gm.G;
-    const int wg_pmax = row_code(a.rs, gm, bh, wg_r1 - 1) / gm.G;
-    const int wv_r0 = wg_r0 + wave * RW;
-    const bool wave_active = wv_r0 < n_rows;
-
-    int pos[NQB], head[NQB];
-    bool valid[NQB];
-    bf16x8 qreg[NQB][8];
-#pragma unroll
-    for (int c = 0; c < NQB; ++c) {
-        const int r = wv_r0 + c * 32 + n;
-        valid[c] = r < n_rows;
-        // rows past the end repeat the last row: computed, never written
-        const int code = row_code(a.rs, gm, bh, min(r, n_rows - 1));
-        pos[c] = code / gm.G;
-        head[c] = hk * gm.G + (code - pos[c] * gm.G);
-        const __bf16* qp = a.q + (((size_t)b * gm.T + pos[c]) * gm.Hq + head[c]) * kD + 8 * h;
-#pragma unroll
-        for (int ks = 0; ks < 8; ++ks) qreg[c][ks] = *reinterpret_cast<const bf16x8*>(qp + ks * 16);
+}
+template <int BQ>
+__device__ __forceinline__ Tile tile_of(const Geom& gm, const RowSet& rs, bool windows, int bx, int by, int gx, int nbh) {
+    Tile t;
+    int rank;
+    if (windows && windows_by_range(gm)) {
+        t.bh = by;
+        t.n_rows = rows_total(rs, gm, t.bh);
+        const int n = (t.n_rows + BQ - 1) / BQ, x = bx & 7, j = bx >> 3;
+        t.tile = j < n / 8 + (x < (n & 7) ? 1 : 0) ? x * (n / 8) + min(x, n & 7) + j : -1;
+        return t;
     }
-
-    // ---- block range of the workgroup, and its three runs: blocks that need the window-start
-    // mask (LOCAL only), blocks no row of the tile needs a mask for, blocks on the causal diagonal.  Parts of a
-    // fix-up tile start where the whole one would: a row's reference, and so its bits, are the same either way.
-    const int pmin_all = BQ == kBQ ? wg_pmin : row_code(a.rs, gm, bh, wg_r0 / kBQ * kBQ) / gm.G;
-    const int jb0 = LOCAL ? max(pmin_all - gm.W, 0) / kBK : 0;
-    const int jb1 = wg_pmax / kBK;  // inclusive
-    int j_mid = jb0;                // first block without window-start masking
-    if (LOCAL) j_mid = min(jb1 + 1, max(jb0, (max(wg_pmax - gm.W, 0) + kBK - 1) / kBK));
-    const int j_diag = max(j_mid, min(jb1 + 1, (wg_pmin + 1) / kBK));  // first block with a key > some row
-
-    // Loads: a wave-uniform base per block plus per-lane offsets fixed for the whole kernel.
-    const unsigned kv_row_bytes = (unsigned)gm.Hkv * kD * 2;
-    const char* kbase = (const char*)(a.k + ((size_t)b * gm.T * gm.Hkv + hk) * kD);
-    const char* vtbase = (const char*)(a.vt + (size_t)bh * kD * a.vt_cap);
-    const unsigned lds_k0 = lds_offset(&lds_k[0][0]), lds_v0 = lds_offset(&lds_v[0][0]);
-    const RmDma<kBK, NW> k_off = rm_dma_setup<kBK, NW>(kv_row_bytes, wave);
-    const TmDma<kBK, NW> v_off = tm_dma_setup<kBK, NW>((unsigned)a.vt_cap * 2u, wave);
-    auto load_k = [&](int jb, int buf) __attribute__((always_inline)) {
-        const char* src = kbase + (size_t)jb * kBK * kv_row_bytes;
-        const unsigned dst = lds_k0 + buf * (kBK * 256);
-        if ((jb + 1) * kBK <= gm.T) rm_dma_issue(k_off, src, dst, wave);
-        else  // keys past the end of the sequence are clamped: always masked, never out of bounds
-            rm_dma_issue_clamped<kBK, NW>(kv_row_bytes, gm.T - jb * kBK, src, dst, wave);
-    };
-    auto load_v = [&](int jb, int buf) __attribute__((always_inline)) {
-        tm_dma_issue(v_off, vtbase + (size_t)jb * kBK * 2, lds_v0 + buf * (kD * kBK * 2), wave);
-    };
-    // In the main loop the 2 NL loads of a block are issued one at a time between matrix
-    // instructions.  K rows are clamped to the end of the sequence on the fly (rows past it are always
-    // masked), so that the ragged last block needs no code path of its own:
-    // lane l of load i fetches chunk (l & 15) ^ (row & 15) of row (NW i + wave) * 4 + (l >> 4).
-    const int k_lane_row = wave * 4 + (lane >> 4);
-    const unsigned k_lane_chunk = (unsigned)(((lane & 15) ^ (k_lane_row & 15)) * 16);
-    struct BlockLoads {
-        const char* ksrc;
-        const char* vsrc;
-        unsigned kdst, vdst;
-        int krows;  // rows of the K block that exist
-    };
-    auto issue_block_load = [&](const BlockLoads& L, auto ic) __attribute__((always_inline)) {
-        constexpr int i = decltype(ic)::value;
-        if constexpr (i < NL) {
-            const unsigned row = (unsigned)min(k_lane_row + 4 * NW * i, L.krows - 1);
-            dma16_so(L.ksrc, __umul24(row, kv_row_bytes) + k_lane_chunk, L.kdst + (i * NW + wave) * 1024);
-        } else {
-            dma16_so(L.vsrc, v_off.voff[i - NL], L.vdst + ((i - NL) * NW + wave) * 1024);
-        }
-    };
-
-    f32x16 oacc[4][NQB];
-    float mref[NQB], negm[NQB], l[NQB];
-#pragma unroll
-    for (int c = 0; c < NQB; ++c) {
-        l[c] = 0.f;
-#pragma unroll
-        for (int d = 0; d < 4; ++d)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) oacc[d][c][r] = 0.f;
-    }
-    const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    auto key_ok = [&](int key, int c) __attribute__((always_inline)) {
-        bool ok = key <= pos[c];
-        if (LOCAL) ok = ok && (key >= pos[c] - gm.W);
-        return ok;
-    };
-
-    // One half-block (32 keys, half KB of block jb; keys k0 .. k0+31): exp of `cur` against the
-    // row's fixed reference, overlapped with the scores of the next half-block into `nxt` (K rows
-    // krow0.. of tile kt) and with O += P V for this half-block (tile vt).  32 matrix-core
-    // instructions = 32 slots:
-    //   first half of the slots   next half-block's scores | exp, row sum, pack P  (pair q in slot 3 q / 2)
-    //   second half               O += P V
-    auto score = [&](float x) __attribute__((always_inline)) { return NQB == 2 ? acc_read(x) : x; };
-    auto half_block = [&](auto mask_tag, auto kb_tag, Scores& cur, Scores& nxt, const __bf16* kt, int krow0,
-                          const __bf16* vt, int k0, auto&& side) __attribute__((always_inline)) {
-        constexpr bool MASK = decltype(mask_tag)::value;
-        constexpr int KB = decltype(kb_tag)::value;
-        const float c2 = gm.scale_log2;
-        bf16x8 opnd[16 + kAhead];
-        uint32_t pw[NQB][2][4];  // P as packed bf16 pairs: [row block][16-key group][dword]
-        float rsum[NQB];
-        const bf16x2 one2 = {(__bf16)1.0f, (__bf16)1.0f};
-#pragma unroll
-        for (int c = 0; c < NQB; ++c) rsum[c] = 0.f;
-        // operand o: o < 8 -> K rows of the next half-block (ks = o); else V^T (16-key group, channel block)
-        auto read_operand = [&](auto oc) {
-            constexpr int o = decltype(oc)::value;
-            if constexpr (o < 8) opnd[o] = rm_operand(kt, krow0 + n, o, h);
-            else if constexpr (o < 16) opnd[o] = tm_operand<kBK>(vt, ((o - 8) & 3) * 32 + n, 2 * KB + ((o - 8) >> 2), h);
-        };
-        auto issue = [&](auto mc) {
-            constexpr int mm = decltype(mc)::value;
-            if constexpr (mm < NS / 2) {
-                constexpr int ks = mm / NQB, c = mm % NQB;
-                nxt.s[c] = mfma32(opnd[ks], qreg[c][ks], ks == 0 ? zero16 : nxt.s[c]);
-            } else {
-                constexpr int x = mm - NS / 2, grp = x / (4 * NQB), d = (x / NQB) & 3, c = x % NQB;
-                const u32x4 pv = {pw[c][grp][0], pw[c][grp][1], pw[c][grp][2], pw[c][grp][3]};
-                oacc[d][c] = mfma32(opnd[8 + x / NQB], __builtin_bit_cast(bf16x8, pv), oacc[d][c]);
-            }
-        };
-        // exp of one pair of scores: pair q in 0 .. 8 NQB - 1, in the order the P V product consumes them
-        auto exp_pair = [&](auto qc) {
-            constexpr int q = decltype(qc)::value;
-            constexpr int grp = q / (4 * NQB), c = (q >> 2) % NQB, i2 = (q & 3) * 2, r = grp * 8 + i2;
-            float p0 = fast_exp2(fmaf(score(cur.s[c][r]), c2, negm[c]));
-            float p1 = fast_exp2(fmaf(score(cur.s[c][r + 1]), c2, negm[c]));
-            if (MASK) {
-                p0 = key_ok(k0 + c_row(r, h), c) ? p0 : 0.f;
-                p1 = key_ok(k0 + c_row(r + 1, h), c) ? p1 : 0.f;
-            }
-            f32x2 f = {p0, p1};
-            const bf16x2 pb = __builtin_convertvector(f, bf16x2);
-            pw[c][grp][i2 >> 1] = __builtin_bit_cast(uint32_t, pb);
-            // row sum of the weights as the matrix cores will see them (rounded to bf16): one
-            // v_dot2 per pair, and the normalisation is exact for the weights actually used
-            rsum[c] = __builtin_amdgcn_fdot2_f32_bf16(pb, one2, rsum[c], false);
-        };
-
-        static_for<0, kAhead>([&](auto oc) { read_operand(oc); });
-        L2A_FENCE();
-        static_for<0, NS>([&](auto mc) {
-            constexpr int mm = decltype(mc)::value;
-            issue(mc);
-            if constexpr (mm % NQB == 0) read_operand(Int<mm / NQB + kAhead>{});
-            static_for<0, 8 * NQB>([&](auto qc) {
-                constexpr int q = decltype(qc)::value;
-                if constexpr ((3 * q) / 2 == mm) exp_pair(qc);
-            });
-            side(mc);
-            L2A_FENCE();
-        });
-#pragma unroll
-        for (int c = 0; c < NQB; ++c) l[c] += rsum[c];
-        // With more than 256 registers both score buffers stay in AGPRs, where the matrix instructions
-        // write them; the VALU side fetches each element with acc_read where it is consumed.
-        if constexpr (NQB == 2) asm volatile("" : "+a"(nxt.s[0]), "+a"(nxt.s[1]));
-    };
-
-    // ---- prologue: K of the first two blocks, V of the first
-    Scores Sa, Sb;
-    load_k(jb0, 0);
-    if (jb0 < jb1) load_k(jb0 + 1, 1);
-    load_v(jb0, 0);
-    dma_wait();
-    __syncthreads();
-    // Reference of every row's exponentials: the largest score among the row's keys in the first
-    // two blocks (every row of the tile has a key there).  It is never updated: scores that come
-    // later may exceed it, which costs no accuracy in floating point; the epilogue checks that the
-    // row sums stayed far from overflow and otherwise leaves the tile to the fix-up kernel.
-    {  // wavefronts whose rows all lie past the end compute on a repeated row and store nothing
-#pragma unroll
-        for (int c = 0; c < NQB; ++c) mref[c] = -INFINITY;
-        const int nb = jb0 < jb1 ? 2 : 1;
-        for (int bi = 0; bi < nb; ++bi) {
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb) {
-                Scores S;
-#pragma unroll
-                for (int ks = 0; ks < 8; ++ks) {
-                    const bf16x8 op = rm_operand(&lds_k[bi][0], kb * 32 + n, ks, h);
-#pragma unroll
-                    for (int c = 0; c < NQB; ++c) S.s[c] = mfma32(op, qreg[c][ks], ks == 0 ? zero16 : S.s[c]);
-                }
-#pragma unroll
-                for (int c = 0; c < NQB; ++c)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int key = (jb0 + bi) * kBK + kb * 32 + c_row(r, h);
-                        mref[c] = fmaxf(mref[c], key_ok(key, c) ? S.s[c][r] : -INFINITY);
-                    }
-            }
-        }
-#pragma unroll
-        for (int c = 0; c < NQB; ++c) {
-            mref[c] = fmaxf(mref[c], __shfl_xor(mref[c], 32)) * gm.scale_log2;
-            if (!(mref[c] > -INFINITY)) mref[c] = 0.f;  // no key in reach yet: any finite reference will do
-            negm[c] = -mref[c];
-        }
-        // scores of the first half-block
-#pragma unroll
-        for (int ks = 0; ks < 8; ++ks) {
-            const bf16x8 op = rm_operand(&lds_k[0][0], n, ks, h);
-#pragma unroll
-            for (int c = 0; c < NQB; ++c) Sa.s[c] = mfma32(op, qreg[c][ks], ks == 0 ? zero16 : Sa.s[c]);
-        }
-    }
-
-    // One block = two half-blocks; Sa holds the scores of a block's first half on entry and exit.
-    // K blocks rotate through three buffers: block jb in kbuf, jb+1 in kbuf1, and the block loaded now, jb+2, in kbuf2
-    int kbuf = 0, kbuf1 = 1, kbuf2 = 2;
-    auto run = [&](auto mask_tag, int j_begin, int j_end) __attribute__((always_inline)) {
-        for (int jb = j_begin; jb < j_end; ++jb) {
-            const int rel = jb - jb0;
-            // prefetch: K of block jb+2 (its buffer held block jb-1), V of block jb+1 (held block jb-1),
-            // issued in the slots of the first half-block where the VALU has nothing to do.  Past the
-            // last block the last one is loaded again, into buffers nobody reads any more.
-            const int jk = min(jb + 2, jb1), jv = min(jb + 1, jb1);
-            {  // wavefronts whose rows all lie past the end compute on a repeated row and store nothing
-                const __bf16* vt = &lds_v[rel & 1][0];
-                BlockLoads L;
-                half_block(mask_tag, Int<0>{}, Sa, Sb, &lds_k[kbuf][0], 32, vt, jb * kBK, [&](auto mc) {
-                    constexpr int mm = decltype(mc)::value;
-                    if constexpr (mm == kLoadSlot0 - 1) {
-                        L.ksrc = kbase + (size_t)jk * kBK * kv_row_bytes;
-                        L.vsrc = vtbase + (size_t)jv * kBK * 2;
-                        L.kdst = lds_k0 + kbuf2 * (kBK * 256);
-                        L.vdst = lds_v0 + ((rel + 1) & 1) * (kD * kBK * 2);
-                        L.krows = min(kBK, gm.T - jk * kBK);
-                    }
-                    if constexpr (mm >= kLoadSlot0 && mm < kLoadSlot0 + 2 * NL) issue_block_load(L, Int<mm - kLoadSlot0>{});
-                });
-                half_block(mask_tag, Int<1>{}, Sb, Sa, &lds_k[kbuf1][0], 0, vt, jb * kBK + 32, [](auto) {});
-            }
-            dma_wait();
-            __syncthreads();
-            const int t = kbuf;
-            kbuf = kbuf1, kbuf1 = kbuf2, kbuf2 = t;
-        }
-    };
-    // three runs: window-start masks (LOCAL), no masks, causal diagonal
-    for (int seg = 0; seg < 3; ++seg) {
-        const int j_begin = seg == 0 ? jb0 : (seg == 1 ? j_mid : j_diag);
-        const int j_end = seg == 0 ? j_mid : (seg == 1 ? j_diag : jb1 + 1);
-        if (seg == 1)
-            run(std::false_type{}, j_begin, j_end);
-        else
-            run(std::true_type{}, j_begin, j_end);
-    }
-
-    // ---- did every row sum stay in range, and every accumulator finite?  (workgroup-wide vote; LDS is
-    // free after the last barrier.)  A row sum below 1e30 bounds the weights, not the products with V:
-    // values beyond ~3e8 can still overflow an accumulator, so those are checked themselves
-    // (x * 0 is NaN exactly when x is infinite or NaN).
-    float lt[NQB];
-    bool bad = false;
-#pragma unroll
-    for (int c = 0; c < NQB; ++c) {
-        lt[c] = l[c] + __shfl_xor(l[c], 32);
-        float chk = 0.f;
-#pragma unroll
-        for (int d = 0; d < 4; ++d)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) chk = fmaf(oacc[d][c][e], 0.f, chk);
-        bad = bad || (wave_active && valid[c] && !(lt[c] > 0.f && lt[c] < 1.0e30f && chk == 0.f));
-    }
-    int* vote = reinterpret_cast<int*>(&lds_v[0][0]);
-    if (threadIdx.x == 0) *vote = 0;
-    __syncthreads();
-    if (bad) *vote = 1;
-    __syncthreads();
-    if (*vote) {
-        if (threadIdx.x == 0) a.redo[(size_t)bh * (gx / (kBQ / BQ)) + tile / (kBQ / BQ)] = 1;
-        return;
-    }
-
-    // ---- epilogue: normalise, log-sum-exp, merge / scatter
-    if (!wave_active) return;
-    __bf16* mo = (__bf16*)a.out.main_out;
-    __bf16* co = (__bf16*)a.out.copy_out;
-    __bf16* zf = (__bf16*)a.out.zero_fill;
-#pragma unroll
-    for (int c = 0; c < NQB; ++c) {
-        if (!valid[c]) continue;
-        const float inv = 1.f / lt[c];
-        const size_t base = (((size_t)b * gm.T + pos[c]) * gm.Hq + head[c]) * kD + 4 * h;
-#pragma unroll
-        for (int d = 0; d < 4; ++d)
-#pragma unroll
-            for (int rg = 0; rg < 4; ++rg) {
-                const size_t off = base + d * 32 + 8 * rg;
-                f32x4 x = {oacc[d][c][4 * rg + 0] * inv, oacc[d][c][4 * rg + 1] * inv,
-                           oacc[d][c][4 * rg + 2] * inv, oacc[d][c][4 * rg + 3] * inv};
-                if (co) *reinterpret_cast<bf16x4*>(co + off) = __builtin_convertvector(x, bf16x4);
-                if (a.out.merge) {
-                    const bf16x4 old = *reinterpret_cast<const bf16x4*>(mo + off);
-                    x += __builtin_convertvector(old, f32x4);
-                }
-                if (a.out.wide_out) *reinterpret_cast<f32x4*>(a.out.wide_out + off) = x;
-                else *reinterpret_cast<bf16x4*>(mo + off) = __builtin_convertvector(x, bf16x4);
-                if (zf) {
-                    const u32x2 z = {0u, 0u};
-                    *reinterpret_cast<u32x2*>(zf + off) = z;
-                }
-            }
-        if (h == 0) {
-            const size_t so = ((size_t)b * gm.Hq + head[c]) * gm.T + pos[c];
-            a.out.lse_out[so] = (mref[c] + __builtin_amdgcn_logf(lt[c])) * kLn2;
-            if (a.out.lse_fill) a.out.lse_fill[so] = -INFINITY;
-        }
-    }
+    head_and_rank(gm, bx, by, gx, nbh, t.bh, rank);
+    t.n_rows = rows_total(rs, gm, t.bh);
+    t.tile = (t.n_rows + BQ - 1) / BQ - 1 - rank;
+    return t;
 }
 
-template <bool LOCAL, int NQB, int NW>
-__global__ __launch_bounds__(64 * NW) void fwd_kernel(FwdArgs a) {
-    __shared__ __attribute__((aligned(1024))) __bf16 lds_k[3][kBK * 128];
-    __shared__ __attribute__((aligned(1024))) __bf16 lds_v[2][kD * kBK];
-    fwd_body<LOCAL, NQB, NW>(a, (int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x, (int)gridDim.y, lds_k, lds_v);
-}
-
-// Both branches in one launch, for sequences so short that the Global rows' tiles alone leave most
-// compute units idle: the first gx_global workgroups (per b, KV head) take the Global rows' tiles,
-// the others the Local rows'.  The branches then must not depend on each other: the Global one
-// writes its rows of A only (in fp32, besides the caller's bf16 copy), and O = S + A is formed
-// afterwards (merge_rows) with the one rounding the sequential order has.
-template <int NQB, int NW>
-__global__ __launch_bounds__(64 * NW, 2) void fwd_pair_kernel(FwdArgs ag, FwdArgs al, int gx_global) {
-    __shared__ __attribute__((aligned(1024))) __bf16 lds_k[3][kBK * 128];
-    __shared__ __attribute__((aligned(1024))) __bf16 lds_v[2][kD * kBK];
-    if ((int)blockIdx.x < gx_global)
-        fwd_body<false, NQB, NW>(ag, (int)blockIdx.x, (int)blockIdx.y, gx_global, (int)gridDim.y, lds_k, lds_v);
-    else
-        fwd_body<true, NQB, NW>(al, (int)blockIdx.x - gx_global, (int)blockIdx.y, (int)gridDim.x - gx_global,
-                                (int)gridDim.y, lds_k, lds_v);
-}
-
-// Fix-up kernel: recomputes the tiles the pipelined kernel gave up on (a later score exceeded a
-// row's fixed reference by so much that a row sum left the safe range).  Same tiling, classical
-// streaming softmax with a running maximum and rescaling (App. C Alg. 1 as printed, with the
-// rescaling factor read as exp(m_old - m_new)); V is transposed on its way into LDS.
-typedef __bf16 FixK[2][kTileRows * kRowPad];
-typedef __bf16 FixV[2][kD * kColPad];
-template <bool LOCAL>
-__device__ __forceinline__ void fixup_body(const FwdArgs& a, const int bx, const int gx, FixK& lds_k, FixV& lds_v) {
-    constexpr int NQB = kNQB;
-    constexpr int RW = 32 * NQB;
-    constexpr int BQ = 4 * RW;
-
+// The same tile by the classical streaming softmax with a running maximum and rescaling (App. C Alg. 1 as printed, with the
+// rescaling factor read as exp(m_old - m_new)): for tiles the pipeline below gives up on, because a score exceeded
+// a row's fixed reference by so much that a sum left the safe range.  V is transposed on its way into LDS.  A launch of its own
+// for such tiles cost 4.6 us in a prompt of 1000 tokens that had none (42.8 us, now 41.4).
+struct FwdLds {
+    __bf16 k[3][kBK * 128];
+    __bf16 v[2][kD * kBK];
+};
+template <bool LOCAL, int NW>
+__device__ __forceinline__ void running_max_body(const FwdArgs& a, const FwdOut& out, const Tile t, FwdLds& lds) {
+    constexpr int NQB = 1, RW = 32 * NQB, BQ = NW * RW;
+    typedef __bf16 K2[2][kTileRows * kRowPad];
+    typedef __bf16 V2[2][kD * kColPad];
+    static_assert(sizeof(K2) + sizeof(V2) <= sizeof(FwdLds), "both fit the pipeline's buffers");
+    K2& lds_k = *reinterpret_cast<K2*>(&lds);
+    V2& lds_v = *reinterpret_cast<V2*>(reinterpret_cast<char*>(&lds) + sizeof(K2));
     const Geom& gm = a.gm;
-    const int bh = blockIdx.y, b = bh / gm.Hkv, hk = bh - b * gm.Hkv;
-    const int n_rows = rows_total(a.rs, gm, bh);
-    const int n_tiles = (n_rows + BQ - 1) / BQ;
-    if (bx >= n_tiles) return;
-    const int tile = n_tiles - 1 - bx;
-    if (!a.redo[(size_t)bh * gx + tile]) return;
+    const int bh = t.bh, tile = t.tile, n_rows = t.n_rows;
+    const int b = bh / gm.Hkv, hk = bh - b * gm.Hkv;
+    __syncthreads();  // the buffers are free
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int n = lane & 31, h = lane >> 5;
@@ -510,13 +179,16 @@ __device__ __forceinline__ void fixup_body(const FwdArgs& a, const int bx, const
     const __bf16* vbase = a.v + ((size_t)b * gm.T * gm.Hkv + hk) * kD;
     const int r4 = (threadIdx.x >> 4) * 4;
     TileRegs kr, vr;
+    const bool loads = threadIdx.x < kThreads;  // 256 threads stage a tile
     auto load_block = [&](int jb) {
+        if (!loads) return;
         const int k0 = jb * kBK + r4;
         // keys past the end of the sequence are clamped: always masked, never out of bounds
         tile_load(kr, [&](int i) { return kbase + (size_t)min(k0 + i, gm.T - 1) * kv_row; });
         tile_load(vr, [&](int i) { return vbase + (size_t)min(k0 + i, gm.T - 1) * kv_row; });
     };
     auto store_block = [&](int buf) {
+        if (!loads) return;
         tile_store_rowmajor(kr, lds_k[buf]);
         tile_store_transposed(vr, lds_v[buf]);
     };
@@ -638,9 +310,9 @@ __device__ __forceinline__ void fixup_body(const FwdArgs& a, const int bx, const
 
     // ---- epilogue: normalise, log-sum-exp, merge / scatter
     if (!wave_active) return;
-    __bf16* mo = (__bf16*)a.out.main_out;
-    __bf16* co = (__bf16*)a.out.copy_out;
-    __bf16* zf = (__bf16*)a.out.zero_fill;
+    __bf16* mo = (__bf16*)out.main_out;
+    __bf16* co = (__bf16*)out.copy_out;
+    __bf16* zf = (__bf16*)out.zero_fill;
 #pragma unroll
     for (int c = 0; c < NQB; ++c) {
         const float lt = l[c] + __shfl_xor(l[c], 32);
@@ -655,7 +327,402 @@ __device__ __forceinline__ void fixup_body(const FwdArgs& a, const int bx, const
                 f32x4 x = {oacc[d][c][4 * rg + 0] * inv, oacc[d][c][4 * rg + 1] * inv,
                            oacc[d][c][4 * rg + 2] * inv, oacc[d][c][4 * rg + 3] * inv};
                 if (co) *reinterpret_cast<bf16x4*>(co + off) = __builtin_convertvector(x, bf16x4);
-                if (a.out.merge) {
+                if (out.merge) {
+                    const bf16x4 old = *reinterpret_cast<const bf16x4*>(mo + off);
+                    x += __builtin_convertvector(old, f32x4);
+                }
+                if (out.wide_out) *reinterpret_cast<f32x4*>(out.wide_out + off) = x;
+                else *reinterpret_cast<bf16x4*>(mo + off) = __builtin_convertvector(x, bf16x4);
+                if (zf) {
+                    const u32x2 z = {0u, 0u};
+                    *reinterpret_cast<u32x2*>(zf + off) = z;
+                }
+            }
+        if (h == 0) {
+            const size_t so = ((size_t)b * gm.Hq + head[c]) * gm.T + pos[c];
+            out.lse_out[so] = (m[c] + __builtin_amdgcn_logf(lt)) * kLn2;
+            if (out.lse_fill) out.lse_fill[so] = -INFINITY;
+        }
+    }
+}
+
+template <Kind KIND, int NQB, int NW>
+__device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds& lds) {
+    auto& lds_k = lds.k;
+    auto& lds_v = lds.v;
+    constexpr bool LOCAL = KIND != kGlobal;  // starts with the window
+    constexpr int RW = 32 * NQB;       // rows per wavefront
+    constexpr int BQ = RW * NW;        // rows per workgroup: a tile, or a whole part of one
+    static_assert(kBQ % BQ == 0, "a workgroup's rows lie in one tile");
+    constexpr int NS = 16 * NQB;       // slots (matrix instructions) per half-block: NS / 2 for S, NS / 2 for P V
+    constexpr int NL = 16 / NW;        // 16-byte loads a wavefront issues per K or V block
+    constexpr int kLoadSlot0 = NS - 1 - 2 * NL;  // the loads of later blocks go out in the last slots of a block's first half
+    using Scores = ScoresT<NQB>;
+
+    const Geom& gm = a.gm;
+    const int bh = t.bh, tile = t.tile, n_rows = t.n_rows;
+    if (tile < 0) return;
+    const int b = bh / gm.Hkv, hk = bh - b * gm.Hkv;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = lane & 31, h = lane >> 5;
+
+    // ---- rows of this workgroup / wavefront / lane
+    const int wg_r0 = tile * BQ;
+    const int wg_r1 = min(wg_r0 + BQ, n_rows);  // exclusive
+    const int wg_pmin = row_code(a.rs, gm, bh, wg_r0) / gm.G;
+    const int wg_pmax = row_code(a.rs, gm, bh, wg_r1 - 1) / gm.G;
+    const int wv_r0 = wg_r0 + wave * RW;
+    const bool wave_active = wv_r0 < n_rows;
+
+    int pos[NQB], head[NQB];
+    bool valid[NQB];
+    bf16x8 qreg[NQB][8];
+#pragma unroll
+    for (int c = 0; c < NQB; ++c) {
+        const int r = wv_r0 + c * 32 + n;
+        valid[c] = r < n_rows;
+        // rows past the end repeat the last row: computed, never written
+        const int code = row_code(a.rs, gm, bh, min(r, n_rows - 1));
+        pos[c] = code / gm.G;
+        head[c] = hk * gm.G + (code - pos[c] * gm.G);
+        const __bf16* qp = a.q + (((size_t)b * gm.T + pos[c]) * gm.Hq + head[c]) * kD + 8 * h;
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) qreg[c][ks] = *reinterpret_cast<const bf16x8*>(qp + ks * 16);
+    }
+
+    // ---- block range of the workgroup, and its three runs: blocks that need the window-start
+    // mask (LOCAL only), blocks no row of the tile needs a mask for, blocks on the causal diagonal.  Parts of a
+    // tile start where the whole one would: a row's reference, and so its bits, are the same either way.
+    const int pmin_all = BQ == kBQ ? wg_pmin : row_code(a.rs, gm, bh, wg_r0 / kBQ * kBQ) / gm.G;
+    const int jb0 = LOCAL ? max(pmin_all - gm.W, 0) / kBK : 0;
+    const int jb1 = wg_pmax / kBK;  // inclusive
+    int j_mid = jb0;                // first block without window-start masking
+    if (LOCAL) j_mid = min(jb1 + 1, max(jb0, (max(wg_pmax - gm.W, 0) + kBK - 1) / kBK));
+    const int j_diag = max(j_mid, min(jb1 + 1, (wg_pmin + 1) / kBK));  // first block with a key > some row
+    // kBoth: behind the window's blocks come the ones with keys before some row's window, from block 0 on.  i-th block walked:
+    const int n_win = jb1 - jb0 + 1;
+    const int n_far = KIND == kBoth && wg_pmax > gm.W ? (wg_pmax - gm.W - 1) / kBK + 1 : 0;
+    const int n_all = n_win + n_far;
+    auto block = [&](int i) __attribute__((always_inline)) { return KIND == kBoth && i >= n_win ? i - n_win : jb0 + i; };
+    // a row sees key j if  j + key_lo <= pos  and  j + key_hi >= pos
+    int key_lo = 0, key_hi = gm.W;
+
+    // Loads: a wave-uniform base per block plus per-lane offsets fixed for the whole kernel.
+    const unsigned kv_row_bytes = (unsigned)gm.Hkv * kD * 2;
+    const char* kbase = (const char*)(a.k + ((size_t)b * gm.T * gm.Hkv + hk) * kD);
+    const char* vtbase = (const char*)(a.vt + (size_t)bh * kD * a.vt_cap);
+    const unsigned lds_k0 = lds_offset(&lds_k[0][0]), lds_v0 = lds_offset(&lds_v[0][0]);
+    const RmDma<kBK, NW> k_off = rm_dma_setup<kBK, NW>(kv_row_bytes, wave);
+    const TmDma<kBK, NW> v_off = tm_dma_setup<kBK, NW>((unsigned)a.vt_cap * 2u, wave);
+    auto load_k = [&](int jb, int buf) __attribute__((always_inline)) {
+        const char* src = kbase + (size_t)jb * kBK * kv_row_bytes;
+        const unsigned dst = lds_k0 + buf * (kBK * 256);
+        if ((jb + 1) * kBK <= gm.T) rm_dma_issue(k_off, src, dst, wave);
+        else  // keys past the end of the sequence are clamped: always masked, never out of bounds
+            rm_dma_issue_clamped<kBK, NW>(kv_row_bytes, gm.T - jb * kBK, src, dst, wave);
+    };
+    auto load_v = [&](int jb, int buf) __attribute__((always_inline)) {
+        tm_dma_issue(v_off, vtbase + (size_t)jb * kBK * 2, lds_v0 + buf * (kD * kBK * 2), wave);
+    };
+    // In the main loop the 2 NL loads of a block are issued one at a time between matrix
+    // instructions.  K rows are clamped to the end of the sequence on the fly (rows past it are always
+    // masked), so that the ragged last block needs no code path of its own:
+    // lane l of load i fetches chunk (l & 15) ^ (row & 15) of row (NW i + wave) * 4 + (l >> 4).
+    const int k_lane_row = wave * 4 + (lane >> 4);
+    const unsigned k_lane_chunk = (unsigned)(((lane & 15) ^ (k_lane_row & 15)) * 16);
+    struct BlockLoads {
+        const char* ksrc;
+        const char* vsrc;
+        unsigned kdst, vdst;
+        int krows;  // rows of the K block that exist
+    };
+    auto issue_block_load = [&](const BlockLoads& L, auto ic) __attribute__((always_inline)) {
+        constexpr int i = decltype(ic)::value;
+        if constexpr (i < NL) {
+            const unsigned row = (unsigned)min(k_lane_row + 4 * NW * i, L.krows - 1);
+            dma16_so(L.ksrc, __umul24(row, kv_row_bytes) + k_lane_chunk, L.kdst + (i * NW + wave) * 1024);
+        } else {
+            dma16_so(L.vsrc, v_off.voff[i - NL], L.vdst + ((i - NL) * NW + wave) * 1024);
+        }
+    };
+
+    f32x16 oacc[4][NQB];
+    float mref[NQB], negm[NQB], l[NQB];
+#pragma unroll
+    for (int c = 0; c < NQB; ++c) {
+        l[c] = 0.f;
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) oacc[d][c][r] = 0.f;
+    }
+    const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    // keys of a score tile that starts at key k0 are k0 + c_row(r, h): those in reach have first <= c_row(r, 0) <= last
+    auto last_row = [&](int k0, int c) __attribute__((always_inline)) { return pos[c] - k0 - 4 * h - (KIND == kBoth ? key_lo : 0); };
+    auto first_row = [&](int k0, int c) __attribute__((always_inline)) { return pos[c] - k0 - 4 * h - (KIND == kBoth ? key_hi : gm.W); };
+
+    // One half-block (32 keys, half KB of block jb; keys k0 .. k0+31): exp of `cur` against the
+    // row's fixed reference, overlapped with the scores of the next half-block into `nxt` (K rows
+    // krow0.. of tile kt) and with O += P V for this half-block (tile vt).  32 matrix-core
+    // instructions = 32 slots:
+    //   first half of the slots   next half-block's scores | exp, row sum, pack P  (pair q in slot 3 q / 2)
+    //   second half               O += P V
+    auto score = [&](float x) __attribute__((always_inline)) { return NQB == 2 ? acc_read(x) : x; };
+    auto half_block = [&](auto mask_tag, auto kb_tag, Scores& cur, Scores& nxt, const __bf16* kt, int krow0,
+                          const __bf16* vt, int k0, auto&& side) __attribute__((always_inline)) {
+        constexpr bool MASK = decltype(mask_tag)::value;
+        constexpr int KB = decltype(kb_tag)::value;
+        const float c2 = gm.scale_log2;
+        bf16x8 opnd[16 + kAhead];
+        uint32_t pw[NQB][2][4];  // P as packed bf16 pairs: [row block][16-key group][dword]
+        float rsum[NQB];
+        const bf16x2 one2 = {(__bf16)1.0f, (__bf16)1.0f};
+        int last[NQB], first[NQB];
+#pragma unroll
+        for (int c = 0; c < NQB; ++c) {
+            rsum[c] = 0.f;
+            if (MASK) last[c] = last_row(k0, c), first[c] = LOCAL ? first_row(k0, c) : 0;
+        }
+        // operand o: o < 8 -> K rows of the next half-block (ks = o); else V^T (16-key group, channel block)
+        auto read_operand = [&](auto oc) {
+            constexpr int o = decltype(oc)::value;
+            if constexpr (o < 8) opnd[o] = rm_operand(kt, krow0 + n, o, h);
+            else if constexpr (o < 16) opnd[o] = tm_operand<kBK>(vt, ((o - 8) & 3) * 32 + n, 2 * KB + ((o - 8) >> 2), h);
+        };
+        auto issue = [&](auto mc) {
+            constexpr int mm = decltype(mc)::value;
+            if constexpr (mm < NS / 2) {
+                constexpr int ks = mm / NQB, c = mm % NQB;
+                nxt.s[c] = mfma32(opnd[ks], qreg[c][ks], ks == 0 ? zero16 : nxt.s[c]);
+            } else {
+                constexpr int x = mm - NS / 2, grp = x / (4 * NQB), d = (x / NQB) & 3, c = x % NQB;
+                const u32x4 pv = {pw[c][grp][0], pw[c][grp][1], pw[c][grp][2], pw[c][grp][3]};
+                oacc[d][c] = mfma32(opnd[8 + x / NQB], __builtin_bit_cast(bf16x8, pv), oacc[d][c]);
+            }
+        };
+        // exp of one pair of scores: pair q in 0 .. 8 NQB - 1, in the order the P V product consumes them
+        auto exp_pair = [&](auto qc) {
+            constexpr int q = decltype(qc)::value;
+            constexpr int grp = q / (4 * NQB), c = (q >> 2) % NQB, i2 = (q & 3) * 2, r = grp * 8 + i2;
+            float p0 = fast_exp2(fmaf(score(cur.s[c][r]), c2, negm[c]));
+            float p1 = fast_exp2(fmaf(score(cur.s[c][r + 1]), c2, negm[c]));
+            if (MASK) {
+                constexpr int c0 = c_row(r, 0), c1 = c_row(r + 1, 0);
+                p0 = c0 <= last[c] && (!LOCAL || c0 >= first[c]) ? p0 : 0.f;
+                p1 = c1 <= last[c] && (!LOCAL || c1 >= first[c]) ? p1 : 0.f;
+            }
+            f32x2 f = {p0, p1};
+            const bf16x2 pb = __builtin_convertvector(f, bf16x2);
+            pw[c][grp][i2 >> 1] = __builtin_bit_cast(uint32_t, pb);
+            // row sum of the weights as the matrix cores will see them (rounded to bf16): one
+            // v_dot2 per pair, and the normalisation is exact for the weights actually used
+            rsum[c] = __builtin_amdgcn_fdot2_f32_bf16(pb, one2, rsum[c], false);
+        };
+
+        static_for<0, kAhead>([&](auto oc) { read_operand(oc); });
+        L2A_FENCE();
+        static_for<0, NS>([&](auto mc) {
+            constexpr int mm = decltype(mc)::value;
+            issue(mc);
+            if constexpr (mm % NQB == 0) read_operand(Int<mm / NQB + kAhead>{});
+            static_for<0, 8 * NQB>([&](auto qc) {
+                constexpr int q = decltype(qc)::value;
+                if constexpr ((3 * q) / 2 == mm) exp_pair(qc);
+            });
+            side(mc);
+            L2A_FENCE();
+        });
+#pragma unroll
+        for (int c = 0; c < NQB; ++c) l[c] += rsum[c];
+        // With more than 256 registers both score buffers stay in AGPRs, where the matrix instructions
+        // write them; the VALU side fetches each element with acc_read where it is consumed.
+        if constexpr (NQB == 2) asm volatile("" : "+a"(nxt.s[0]), "+a"(nxt.s[1]));
+    };
+
+    // ---- prologue: K of the first two blocks, V of the first
+    Scores Sa, Sb;
+    load_k(jb0, 0);
+    if (n_all > 1) load_k(block(1), 1);
+    load_v(jb0, 0);
+    dma_wait();
+    __syncthreads();
+    // Reference of every row's exponentials: the largest score among the row's keys in the window's or prefix's first
+    // two blocks (0 where there is none).  It is never updated: scores that come
+    // later may exceed it, which costs no accuracy in floating point; the epilogue checks that the
+    // row sums stayed far from overflow and otherwise leaves the tile to running_max_body.
+    {  // wavefronts whose rows all lie past the end compute on a repeated row and store nothing
+#pragma unroll
+        for (int c = 0; c < NQB; ++c) mref[c] = -INFINITY;
+        const int nb = jb0 < jb1 ? 2 : 1;
+        for (int bi = 0; bi < nb; ++bi) {
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) {
+                Scores S;
+#pragma unroll
+                for (int ks = 0; ks < 8; ++ks) {
+                    const bf16x8 op = rm_operand(&lds_k[bi][0], kb * 32 + n, ks, h);
+#pragma unroll
+                    for (int c = 0; c < NQB; ++c) S.s[c] = mfma32(op, qreg[c][ks], ks == 0 ? zero16 : S.s[c]);
+                }
+#pragma unroll
+                for (int c = 0; c < NQB; ++c) {
+                    const int last = last_row((jb0 + bi) * kBK + kb * 32, c);
+                    const int first = LOCAL ? first_row((jb0 + bi) * kBK + kb * 32, c) : 0;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const bool ok = c_row(r, 0) <= last && (!LOCAL || c_row(r, 0) >= first);
+                        mref[c] = fmaxf(mref[c], ok ? S.s[c][r] : -INFINITY);
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < NQB; ++c) {
+            mref[c] = fmaxf(mref[c], __shfl_xor(mref[c], 32)) * gm.scale_log2;
+            if (!(mref[c] > -INFINITY)) mref[c] = 0.f;  // no key in reach yet: any finite reference will do
+            negm[c] = -mref[c];
+        }
+        // scores of the first half-block
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) {
+            const bf16x8 op = rm_operand(&lds_k[0][0], n, ks, h);
+#pragma unroll
+            for (int c = 0; c < NQB; ++c) Sa.s[c] = mfma32(op, qreg[c][ks], ks == 0 ? zero16 : Sa.s[c]);
+        }
+    }
+
+    // One block = two half-blocks; Sa holds the scores of a block's first half on entry and exit.
+    // K blocks rotate through three buffers: block jb in kbuf, jb+1 in kbuf1, and the block loaded now, jb+2, in kbuf2
+    int kbuf = 0, kbuf1 = 1, kbuf2 = 2;
+    auto run = [&](auto mask_tag, int i_begin, int i_end) __attribute__((always_inline)) {
+        for (int rel = i_begin; rel < i_end; ++rel) {
+            const int jb = block(rel);
+            // prefetch: K of block jb+2 (its buffer held block jb-1), V of block jb+1 (held block jb-1),
+            // issued in the slots of the first half-block where the VALU has nothing to do.  Past the
+            // last block the last one is loaded again, into buffers nobody reads any more.
+            const int jk = block(min(rel + 2, n_all - 1)), jv = block(min(rel + 1, n_all - 1));
+            {  // wavefronts whose rows all lie past the end compute on a repeated row and store nothing
+                const __bf16* vt = &lds_v[rel & 1][0];
+                BlockLoads L;
+                half_block(mask_tag, Int<0>{}, Sa, Sb, &lds_k[kbuf][0], 32, vt, jb * kBK, [&](auto mc) {
+                    constexpr int mm = decltype(mc)::value;
+                    if constexpr (mm == kLoadSlot0 - 1) {
+                        L.ksrc = kbase + (size_t)jk * kBK * kv_row_bytes;
+                        L.vsrc = vtbase + (size_t)jv * kBK * 2;
+                        L.kdst = lds_k0 + kbuf2 * (kBK * 256);
+                        L.vdst = lds_v0 + ((rel + 1) & 1) * (kD * kBK * 2);
+                        L.krows = min(kBK, gm.T - jk * kBK);
+                    }
+                    if constexpr (mm >= kLoadSlot0 && mm < kLoadSlot0 + 2 * NL) issue_block_load(L, Int<mm - kLoadSlot0>{});
+                });
+                half_block(mask_tag, Int<1>{}, Sb, Sa, &lds_k[kbuf1][0], 0, vt, jb * kBK + 32, [](auto) {});
+            }
+            dma_wait();
+            __syncthreads();
+            const int t = kbuf;
+            kbuf = kbuf1, kbuf1 = kbuf2, kbuf2 = t;
+        }
+    };
+    // ---- did every row sum stay in range, and every accumulator finite?  A row sum below 1e30 bounds the weights, not the
+    // products with V: values beyond ~3e8 can still overflow an accumulator, so those are checked themselves
+    // (x * 0 is NaN exactly when x is infinite or NaN).  A sum above 1e-30 (a reference of 0 may leave it small) still
+    // holds every weight that counts beside it, none flushed to zero.
+    float lt[NQB];
+    bool bad = false;
+    auto check_sums = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int c = 0; c < NQB; ++c) {
+            lt[c] = l[c] + __shfl_xor(l[c], 32);
+            float chk = 0.f;
+#pragma unroll
+            for (int d = 0; d < 4; ++d)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) chk = fmaf(oacc[d][c][e], 0.f, chk);
+            bad = bad || (wave_active && valid[c] && !(lt[c] > 1.0e-30f && lt[c] < 1.0e30f && chk == 0.f));
+        }
+    };
+    auto row_base = [&](int c) __attribute__((always_inline)) { return (((size_t)b * gm.T + pos[c]) * gm.Hq + head[c]) * kD + 4 * h; };
+    auto row_stat = [&](int c) __attribute__((always_inline)) { return ((size_t)b * gm.Hq + head[c]) * gm.T + pos[c]; };
+    auto row_lse = [&](int c) __attribute__((always_inline)) { return (mref[c] + __builtin_amdgcn_logf(lt[c])) * kLn2; };
+
+    // runs of blocks: window-start masks (LOCAL), no masks, causal diagonal; keys before the window: no masks, masks
+    const int i_mid = j_mid - jb0, i_diag = j_diag - jb0;
+    const int i_edge = n_win + min(n_far, max(wg_pmin - gm.W, 0) / kBK);
+    for (int seg = 0; seg < (KIND == kBoth ? 5 : 3); ++seg) {
+        const int i_begin = seg == 0 ? 0 : seg == 1 ? i_mid : seg == 2 ? i_diag : seg == 3 ? n_win : i_edge;
+        const int i_end = seg == 0 ? i_mid : seg == 1 ? i_diag : seg == 2 ? n_win : seg == 3 ? i_edge : n_all;
+        if (KIND == kBoth && seg == 3 && n_far > 0) {
+            // the window is complete: s, to O (which the end adds a to) and to the caller's copy.  A bad sum stays bad.
+            check_sums();
+#pragma unroll
+            for (int c = 0; c < NQB; ++c) {
+                if (!valid[c]) continue;
+                const float inv = 1.f / lt[c];
+                const size_t base = row_base(c);
+#pragma unroll
+                for (int d = 0; d < 4; ++d)
+#pragma unroll
+                    for (int rg = 0; rg < 4; ++rg) {
+                        const size_t off = base + d * 32 + 8 * rg;
+                        const f32x4 x = {oacc[d][c][4 * rg + 0] * inv, oacc[d][c][4 * rg + 1] * inv,
+                                         oacc[d][c][4 * rg + 2] * inv, oacc[d][c][4 * rg + 3] * inv};
+                        const bf16x4 y = __builtin_convertvector(x, bf16x4);
+                        *reinterpret_cast<bf16x4*>((__bf16*)a.out.main_out + off) = y;
+                        if (a.s_out) *reinterpret_cast<bf16x4*>(a.s_out + off) = y;
+                    }
+                if (h == 0) a.s_lse[row_stat(c)] = row_lse(c);
+            }
+            key_lo = gm.W + 1;
+            key_hi = gm.T;
+        }
+        if (seg == 1 || seg == 3)
+            run(std::false_type{}, i_begin, i_end);
+        else
+            run(std::true_type{}, i_begin, i_end);
+    }
+
+    // (workgroup-wide vote; LDS is free after the last barrier)
+    check_sums();
+    int* vote = reinterpret_cast<int*>(&lds_v[0][0]);
+    if (threadIdx.x == 0) *vote = 0;
+    __syncthreads();
+    if (bad) *vote = 1;
+    __syncthreads();
+    if (*vote) {
+        if (threadIdx.x == 0) a.redo[(size_t)bh * a.redo_stride + tile / (kBQ / BQ)] = 1;
+        if constexpr (KIND == kBoth) {  // the window first, then the whole prefix, which adds to the O that the same lanes wrote
+            running_max_body<true, NW>(a, FwdOut{a.out.main_out, a.s_out, a.s_lse, nullptr, nullptr, 0}, t, lds);
+            running_max_body<false, NW>(a, a.out, t, lds);
+        } else {
+            running_max_body<KIND == kLocal, NW>(a, a.out, t, lds);
+        }
+        return;
+    }
+
+    // ---- epilogue: normalise, log-sum-exp, merge / scatter
+    if (!wave_active) return;
+    __bf16* mo = (__bf16*)a.out.main_out;
+    __bf16* co = (__bf16*)a.out.copy_out;
+    __bf16* zf = (__bf16*)a.out.zero_fill;
+    const bool all_window = KIND == kBoth && n_far == 0;  // s = a
+#pragma unroll
+    for (int c = 0; c < NQB; ++c) {
+        if (!valid[c]) continue;
+        const float inv = 1.f / lt[c];
+        const size_t base = row_base(c);
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+#pragma unroll
+            for (int rg = 0; rg < 4; ++rg) {
+                const size_t off = base + d * 32 + 8 * rg;
+                f32x4 x = {oacc[d][c][4 * rg + 0] * inv, oacc[d][c][4 * rg + 1] * inv,
+                           oacc[d][c][4 * rg + 2] * inv, oacc[d][c][4 * rg + 3] * inv};
+                if (co) *reinterpret_cast<bf16x4*>(co + off) = __builtin_convertvector(x, bf16x4);
+                if (KIND == kBoth && all_window) {
+                    const bf16x4 y = __builtin_convertvector(x, bf16x4);
+                    if (a.s_out) *reinterpret_cast<bf16x4*>(a.s_out + off) = y;
+                    x += __builtin_convertvector(y, f32x4);
+                } else if (KIND == kBoth || a.out.merge) {
                     const bf16x4 old = *reinterpret_cast<const bf16x4*>(mo + off);
                     x += __builtin_convertvector(old, f32x4);
                 }
@@ -667,24 +734,71 @@ __device__ __forceinline__ void fixup_body(const FwdArgs& a, const int bx, const
                 }
             }
         if (h == 0) {
-            const size_t so = ((size_t)b * gm.Hq + head[c]) * gm.T + pos[c];
-            a.out.lse_out[so] = (m[c] + __builtin_amdgcn_logf(lt)) * kLn2;
+            const size_t so = row_stat(c);
+            a.out.lse_out[so] = row_lse(c);
+            if (KIND == kBoth && all_window) a.s_lse[so] = row_lse(c);
             if (a.out.lse_fill) a.out.lse_fill[so] = -INFINITY;
         }
     }
 }
 
-template <bool LOCAL>
-__global__ __launch_bounds__(kThreads) void fwd_fixup_kernel(FwdArgs a) {
-    __shared__ __attribute__((aligned(16))) FixK lds_k;
-    __shared__ __attribute__((aligned(16))) FixV lds_v;
-    fixup_body<LOCAL>(a, (int)blockIdx.x, (int)gridDim.x, lds_k, lds_v);
+template <bool LOCAL, int NQB, int NW>
+__global__ __launch_bounds__(64 * NW) void fwd_kernel(FwdArgs a) {
+    __shared__ __attribute__((aligned(1024))) FwdLds lds;
+    const Tile t = tile_of<32 * NQB * NW>(a.gm, a.rs, LOCAL, (int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x, (int)gridDim.y);
+    fwd_body<LOCAL ? kLocal : kGlobal, NQB, NW>(a, t, lds);
 }
-__global__ __launch_bounds__(kThreads) void fwd_fixup_pair_kernel(FwdArgs ag, FwdArgs al, int gx) {
-    __shared__ __attribute__((aligned(16))) FixK lds_k;
-    __shared__ __attribute__((aligned(16))) FixV lds_v;
-    if ((int)blockIdx.x < gx) fixup_body<false>(ag, (int)blockIdx.x, gx, lds_k, lds_v);
-    else fixup_body<true>(al, (int)blockIdx.x - gx, gx, lds_k, lds_v);
+
+// Shared inputs: the routed rows (kBoth) and the others, which have the window only, in one launch; every row belongs to
+// one workgroup, which writes all of its outputs.  A routed row costs its prefix, another one its window at most.
+// Short sequences (windows that are no fraction of them): one range of workgroups per (b, KV head), longest tiles
+// first -- the routed rows beyond a window's length, then both kinds in proportion, which is by position for routing
+// that does not depend on it much.  Long ones: the first half of the grid takes the routed rows' tiles, the second the others'.
+// Whole forward, W = 4096, 20 % routed, 28 / 4 heads, the branches apart (one launch and a merge at 4096, two launches
+// beyond 16384) / together, us: T = 4096 171.4 / 151.2, T = 32768 3200 / 2920; of a training step of 16379 (32 / 8 heads,
+// bursty) 170 us, of one of 131072 1.2 ms.
+template <int NQB, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void fwd_shared_kernel(FwdArgs ar, FwdArgs au, int gx) {
+    __shared__ __attribute__((aligned(1024))) FwdLds lds;
+    constexpr int BQ = 32 * NQB * NW;
+    const Geom& gm = ar.gm;
+    Tile t;
+    bool routed;
+    if (windows_by_range(gm)) {
+        routed = (int)blockIdx.x < gx;
+        t = routed ? tile_of<BQ>(gm, ar.rs, false, (int)blockIdx.x, (int)blockIdx.y, gx, (int)gridDim.y)
+                   : tile_of<BQ>(gm, au.rs, true, (int)blockIdx.x - gx, (int)blockIdx.y, gx, (int)gridDim.y);
+    } else {
+        int rank;
+        head_and_rank(gm, (int)blockIdx.x, (int)blockIdx.y, gx, (int)gridDim.y, t.bh, rank);
+        const int rows_r = rows_total(ar.rs, gm, t.bh), rows_u = rows_total(au.rs, gm, t.bh);
+        const int nr = (rows_r + BQ - 1) / BQ, nu = (rows_u + BQ - 1) / BQ;
+        const int far = gm.T > gm.W ? (int)((long long)nr * (gm.T - gm.W) / gm.T) : 0;  // routed tiles beyond a window's length
+        const int k = rank - far, n = nr - far + nu;
+        // the k-th of n, nr - far of them routed, spread evenly
+        const int before = k <= 0 ? 0 : (int)((long long)k * (nr - far) / max(n, 1));
+        routed = k < 0 || (k < n && (int)((long long)(k + 1) * (nr - far) / max(n, 1)) > before);
+        t.n_rows = routed ? rows_r : rows_u;
+        t.tile = k < 0 ? nr - 1 - rank : k >= n ? -1 : routed ? nr - far - 1 - before : nu - 1 - (k - before);
+    }
+    if (routed) fwd_body<kBoth, NQB, NW>(ar, t, lds);
+    else fwd_body<kLocal, NQB, NW>(au, t, lds);
+}
+
+// Both branches in one launch, for sequences so short that the Global rows' tiles alone leave most
+// compute units idle: the first gx_global workgroups (per b, KV head) take the Global rows' tiles,
+// the others the Local rows'.  The branches then must not depend on each other: the Global one
+// writes its rows of A only (in fp32, besides the caller's bf16 copy), and O = S + A is formed
+// afterwards (merge_rows) with the one rounding the sequential order has.
+template <int NQB, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void fwd_pair_kernel(FwdArgs ag, FwdArgs al, int gx_global) {
+    __shared__ __attribute__((aligned(1024))) FwdLds lds;
+    constexpr int BQ = 32 * NQB * NW;
+    if ((int)blockIdx.x < gx_global)
+        fwd_body<kGlobal, NQB, NW>(ag, tile_of<BQ>(ag.gm, ag.rs, false, (int)blockIdx.x, (int)blockIdx.y, gx_global, (int)gridDim.y), lds);
+    else
+        fwd_body<kLocal, NQB, NW>(al, tile_of<BQ>(al.gm, al.rs, true, (int)blockIdx.x - gx_global, (int)blockIdx.y,
+                                                  (int)gridDim.x - gx_global, (int)gridDim.y), lds);
 }
 
 // One launch for both branches: workgroups of 128 rows up to this many 256-row tiles of a branch.  The longest tile's
@@ -694,6 +808,9 @@ __global__ __launch_bounds__(kThreads) void fwd_fixup_pair_kernel(FwdArgs ag, Fw
 // 1192 / 1214; 32 / 8 heads, W = 1024: T = 4096 (512) 136.3 / 135.9, 16384 588 / 574.
 bool half_tiles(size_t tiles) { return tiles <= 512; }
 
+// tiles of 256 rows of a branch, per (b, KV head): a multiple of 8, see the tile order
+unsigned tiles_x(const Geom& g) { return (unsigned)((((long long)g.T * g.G + kBQ - 1) / kBQ + 7) / 8 * 8); }
+
 }  // namespace
 
 int mfma_fwd(const Geom& g, const RowSet& rs, const void* q, const void* k, const void* v, const void* vt,
@@ -701,9 +818,9 @@ int mfma_fwd(const Geom& g, const RowSet& rs, const void* q, const void* k, cons
     if (g.D != kD) return L2A_ERR_UNSUPPORTED;
     // per-lane load offsets are 32-bit
     if ((unsigned long long)vt_cap * 2ull * kD > 0xffffffffull) return L2A_ERR_UNSUPPORTED;
-    FwdArgs a{g, rs, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (const __bf16*)vt, vt_cap, redo, out};
-    const long long rows = (long long)g.T * g.G;
-    const dim3 grid((unsigned)(((rows + kBQ - 1) / kBQ + 7) / 8 * 8), g.B * g.Hkv);  // a multiple of 8: see the tile order
+    FwdArgs a{g, rs, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (const __bf16*)vt, vt_cap, redo,
+              (int)tiles_x(g), out};
+    const dim3 grid(tiles_x(g), g.B * g.Hkv);
     int r = fill_zero(redo, sizeof(int32_t) * grid.x * grid.y, st);
     if (r != L2A_OK) return r;
     {
@@ -712,13 +829,6 @@ int mfma_fwd(const Geom& g, const RowSet& rs, const void* q, const void* k, cons
             hipLaunchKernelGGL((fwd_kernel<true, kFwdNQB, kFwdNW>), grid, dim3(64 * kFwdNW), 0, st, a);
         else
             hipLaunchKernelGGL((fwd_kernel<false, kFwdNQB, kFwdNW>), grid, dim3(64 * kFwdNW), 0, st, a);
-    }
-    {
-        KernelTimer kt(rs.local ? "fwd_local_fixup" : "fwd_global_fixup", st);
-        if (rs.local)
-            hipLaunchKernelGGL((fwd_fixup_kernel<true>), grid, dim3(kThreads), 0, st, a);
-        else
-            hipLaunchKernelGGL((fwd_fixup_kernel<false>), grid, dim3(kThreads), 0, st, a);
     }
     return launch_status();
 }
@@ -730,12 +840,11 @@ int mfma_fwd_pair(const Geom& g, const RowSet& rs_l, const void* q_l, const void
                   const void* v_g, const void* vt_g, const FwdOut& out_g, int vt_cap, int32_t* redo, hipStream_t st) {
     if (g.D != kD || out_g.merge || !out_g.wide_out || out_l.wide_out) return L2A_ERR_UNSUPPORTED;
     if ((unsigned long long)vt_cap * 2ull * kD > 0xffffffffull) return L2A_ERR_UNSUPPORTED;
-    const long long rows = (long long)g.T * g.G;
-    const unsigned gx = (unsigned)(((rows + kBQ - 1) / kBQ + 7) / 8 * 8);  // per branch
+    const unsigned gx = tiles_x(g);  // per branch
     const size_t entries = (size_t)gx * g.B * g.Hkv;
-    FwdArgs al{g, rs_l, (const __bf16*)q_l, (const __bf16*)k_l, (const __bf16*)v_l, (const __bf16*)vt_l, vt_cap, redo, out_l};
+    FwdArgs al{g, rs_l, (const __bf16*)q_l, (const __bf16*)k_l, (const __bf16*)v_l, (const __bf16*)vt_l, vt_cap, redo, (int)gx, out_l};
     FwdArgs ag{g, rs_g, (const __bf16*)q_g, (const __bf16*)k_g, (const __bf16*)v_g, (const __bf16*)vt_g, vt_cap,
-               redo + entries, out_g};
+               redo + entries, (int)gx, out_g};
     {
         KernelTimer kt("fwd_pair", st);
         if (half_tiles(entries))
@@ -744,17 +853,36 @@ int mfma_fwd_pair(const Geom& g, const RowSet& rs_l, const void* q_l, const void
             hipLaunchKernelGGL((fwd_pair_kernel<kFwdNQB, kFwdNW>), dim3(2 * gx, g.B * g.Hkv), dim3(64 * kFwdNW), 0, st, ag,
                                al, (int)gx);
     }
+    return launch_status();
+}
+
+// Shared inputs: routed rows rs_r with both branches, the rest of the rows rs_u with the window (fwd_shared_kernel).
+// out_r: a (main_out: o); S, lse_l: s of the routed rows; out_u: the other rows, with the fills for them.  redo: mfma_fwd_redo_entries flags, zero.
+int mfma_fwd_shared(const Geom& g, const RowSet& rs_r, const RowSet& rs_u, const void* q, const void* k, const void* v,
+                    const void* vt, int vt_cap, int32_t* redo, const FwdOut& out_r, void* S, float* lse_l, const FwdOut& out_u,
+                    hipStream_t st) {
+    if (g.D != kD || out_r.wide_out || out_u.wide_out || !out_r.merge) return L2A_ERR_UNSUPPORTED;
+    if ((unsigned long long)vt_cap * 2ull * kD > 0xffffffffull) return L2A_ERR_UNSUPPORTED;
+    const unsigned gx = tiles_x(g);
+    const bool half = half_tiles((size_t)gx * g.B * g.Hkv), split = g.T / 4 > g.W;  // split: windows_by_range
+    FwdArgs au{g, rs_u, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (const __bf16*)vt, vt_cap, redo, (int)gx, out_u};
+    FwdArgs ar{g, rs_r, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (const __bf16*)vt, vt_cap, redo, (int)gx, out_r,
+               (__bf16*)S, lse_l};
     {
-        KernelTimer kt("fwd_pair_fixup", st);
-        hipLaunchKernelGGL(fwd_fixup_pair_kernel, dim3(2 * gx, g.B * g.Hkv), dim3(kThreads), 0, st, ag, al, (int)gx);
+        // tiles of both kinds together: at most one more than all rows have; a multiple of 8
+        const long long rows = (long long)g.T * g.G;
+        const int bq = half ? 128 : 256;
+        const unsigned w = (unsigned)(((rows + bq - 1) / bq + 1 + 7) / 8 * 8);
+        KernelTimer kt("fwd_shared", st);
+        if (half) hipLaunchKernelGGL((fwd_shared_kernel<1, 4>), dim3(split ? 2 * w : w, g.B * g.Hkv), dim3(256), 0, st, ar, au, (int)w);
+        else hipLaunchKernelGGL((fwd_shared_kernel<kFwdNQB, kFwdNW>), dim3(split ? 2 * w : w, g.B * g.Hkv), dim3(64 * kFwdNW), 0, st, ar, au, (int)w);
     }
     return launch_status();
 }
 
 // number of redo flags mfma_fwd needs
 size_t mfma_fwd_redo_entries(const Geom& g) {
-    const long long rows = (long long)g.T * g.G;
-    return (size_t)(((rows + kBQ - 1) / kBQ + 7) / 8 * 8) * g.B * g.Hkv;
+    return (size_t)tiles_x(g) * g.B * g.Hkv;
 }
 
 }  // namespace l2a

@@ -120,6 +120,10 @@ int mfma_fwd_pair(const Geom& g, const RowSet& rs_l, const void* q_l, const void
                   const void* vt_l, const FwdOut& out_l, const RowSet& rs_g, const void* q_g, const void* k_g,
                   const void* v_g, const void* vt_g, const FwdOut& out_g, int vt_cap, int32_t* redo, hipStream_t st);
 
+int mfma_fwd_shared(const Geom& g, const RowSet& rs_r, const RowSet& rs_u, const void* q, const void* k, const void* v,
+                    const void* vt, int vt_cap, int32_t* redo, const FwdOut& out_r, void* S, float* lse_l, const FwdOut& out_u,
+                    hipStream_t st);
+
 // ---- attn_decode_bf16.hip : one new token per sequence against the KV cache (bf16, D = 128)
 size_t decode_partial_floats(const Geom& g);
 int mfma_decode(const Geom& g, const void* q, const void* k, const void* v, const int32_t* pos, const uint8_t* mask,
@@ -133,8 +137,13 @@ struct Fill {  // n 32-bit words of one value
     uint32_t value;
 };
 // one or two V tensors; up to three buffers are filled by the same launch
+// rest (optional): the rows that are not in `routed` (which has its kblk_first_row), as another list
+struct RestList {
+    RowSet routed;
+    int32_t *row_idx, *count;  // [B,Hkv,T*G], [B,Hkv]
+};
 int pack_kv(const Geom& g, int n, const void* const* x, void* const* xt, int cap, const Fill* fills, int nfills,
-            hipStream_t st);
+            const RestList* rest, hipStream_t st);
 // O += A on the rows of rs (O bf16, A fp32, D = 128), or O = S + A with S in fp32, where S is given
 // (rows that see a key: those at positions below rs.shift are left as they are)
 int merge_rows(const Geom& g, const RowSet& rs, const float* S, const float* A, void* O, hipStream_t st);

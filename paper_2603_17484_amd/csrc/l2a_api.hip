@@ -191,7 +191,6 @@ int l2a_attn_fwd(const l2a_params* p, const void* q_loc, const void* k_loc, cons
                  const int32_t* count, const int32_t* kblk_first_row, void* O, float* lse_local,
                  float* lse_global, void* S_opt, void* A_opt, void* workspace, size_t workspace_bytes,
                  void* stream) {
-    (void)kblk_first_row;
     const int rc = check_params(p);
     if (rc != L2A_OK) return rc;
     const bool dense = p->flags & L2A_FLAG_DENSE;
@@ -215,7 +214,27 @@ int l2a_attn_fwd(const l2a_params* p, const void* q_loc, const void* k_loc, cons
     // matrix-core path: token-minor copy of each distinct V (layout pre-pass, one pass over V)
     char* vt_loc = (char*)workspace;
     char* vt_glb = vt_loc;
-    const bool pair = pair_fwd(*p);
+    // Shared inputs: routed rows take both branches in one walk, the other rows the window, in one launch at every length
+    // (a list of the latter lies where a second V copy would: 4 G bytes per token and KV head of 256).  What it gains:
+    // fwd_shared_kernel.  Lists without kblk_first_row take the branches as they come.
+    const bool shared = mfma && do_local && do_global && !dense && kblk_first_row && q_glb == q_loc && k_glb == k_loc && v_glb == v_loc;
+    const bool pair = pair_fwd(*p) && !shared;
+    if (shared) {
+        char* after_v = (char*)workspace + 2 * kv_copy_bytes(*p);
+        int32_t* rest = (int32_t*)((char*)workspace + kv_copy_bytes(*p));
+        int32_t* n_rest = rest + (size_t)p->B * p->Hkv * p->T * g.G;
+        const RowSet rs_r{row_idx, count, kblk_first_row, 0};
+        const RestList rl{rs_r, rest, n_rest};
+        const void* vs[1] = {v_loc};
+        void* vts[1] = {vt_loc};
+        // the flags of both branches where there is room for them (the second half stays zero)
+        const Fill flags{(uint32_t*)after_v, (pair_fwd(*p) ? 2 : 1) * mfma_fwd_redo_entries(g), 0u};
+        if ((r = pack_kv(g, 1, vs, vts, kv_cap(*p), &flags, 1, &rl, st)) != L2A_OK) return r;
+        const FwdOut out_r{O, A_opt, lse_global, nullptr, nullptr, 1};
+        const FwdOut out_u{O, S_opt, lse_local, lse_global, A_opt, 0};
+        return mfma_fwd_shared(g, rs_r, RowSet{rest, n_rest, nullptr, 1}, q_loc, k_loc, v_loc, vt_loc, kv_cap(*p),
+                               (int32_t*)after_v, out_r, S_opt, lse_local, out_u, st);
+    }
     if (mfma) {
         const void* vs[2];
         void* vts[2];
@@ -232,7 +251,7 @@ int l2a_attn_fwd(const l2a_params* p, const void* q_loc, const void* k_loc, cons
             fills[nf++] = Fill{(uint32_t*)lse_global, stat_elems(*p), 0xff800000u};  // -inf
             if (A_opt) fills[nf++] = Fill{(uint32_t*)A_opt, q_elems(*p) / 2, 0u};
         }
-        if ((r = pack_kv(g, nv, vs, vts, kv_cap(*p), fills, nf, st)) != L2A_OK) return r;
+        if ((r = pack_kv(g, nv, vs, vts, kv_cap(*p), fills, nf, nullptr, st)) != L2A_OK) return r;
     }
     if (pair) {
         char* after_v = (char*)workspace + 2 * kv_copy_bytes(*p);

@@ -33,6 +33,7 @@ struct PackArgs {
     int32_t* pos_c;       // last key the row sees (its position; less rs.shift), negative: none (padding: -1)
     int cap;              // rows per (b, kv head) in the outputs; multiple of 64
     Fill fill[3];         // buffers to be filled on the way
+    RestList rest;        // kv_rows: the rows that are not routed, listed on the way (rest.row_idx may be null)
 };
 
 // A launch costs a short forward as much as the kernel it carries (about 3 us each), so the constants that its
@@ -49,14 +50,43 @@ __device__ __forceinline__ void run_fill(const Fill& f) {
     for (i += done; i < f.n; i += step) f.p[i] = f.value;
 }
 
+// The rows of positions 64 kb .. 64 kb + 63 that are not in the routed list, in ascending order, to their place in the rest
+// list: code - (routed rows before it).  Which are routed is gathered as bits from the list's entries first[kb] .. first[kb+1].
+constexpr int kMaxG = 16;  // Hq / Hkv at most
+__device__ __forceinline__ void list_rest(const Geom& gm, const RestList& rl, int bh, int kb, unsigned long long (&bits)[kMaxG]) {
+    const int nkb = (gm.T + 63) / 64, all = gm.T * gm.G, n = rows_total(rl.routed, gm, bh);
+    if (kb >= nkb) return;
+    const int32_t* first = rl.routed.kblk_first_row + (size_t)bh * (nkb + 1) + kb;
+    const int f0 = min(max(first[0], 0), n), f1 = min(max(first[1], f0), n);
+    const int c0 = kb * 64 * gm.G, codes = min(64, gm.T - kb * 64) * gm.G;
+    if (threadIdx.x < kMaxG) bits[threadIdx.x] = 0;
+    __syncthreads();
+    for (int i = f0 + (int)threadIdx.x; i < f1; i += kThreads) {
+        const int c = row_code(rl.routed, gm, bh, i) - c0;
+        if (c >= 0 && c < codes) atomicOr(&bits[c >> 6], 1ull << (c & 63));
+    }
+    __syncthreads();
+    for (int c = threadIdx.x; c < codes; c += kThreads) {
+        int before = f0;
+        for (int w = 0; w < c >> 6; ++w) before += __popcll(bits[w]);
+        const unsigned long long word = bits[c >> 6];
+        before += __popcll(word & ((1ull << (c & 63)) - 1));
+        const int at = c0 + c - before;
+        if (!(word >> (c & 63) & 1) && at >= 0 && at < all) rl.row_idx[(size_t)bh * all + at] = c0 + c;
+    }
+    if (kb == nkb - 1 && threadIdx.x == 0) rl.count[bh] = all - n;
+}
+
 __global__ __launch_bounds__(kThreads) void pack_token_minor_kernel(PackArgs a) {
     __shared__ __attribute__((aligned(16))) __bf16 lds[2][kTileRows * kRowPad];
+    __shared__ unsigned long long rest_bits[kMaxG];
     const Geom& gm = a.gm;
     const int bh = blockIdx.y, b = bh / gm.Hkv, hk = bh - b * gm.Hkv;
     const int r0 = blockIdx.x * 64;
 #pragma unroll
     for (int i = 0; i < 3; ++i)
         if (a.fill[i].n) run_fill(a.fill[i]);
+    if (a.rest.row_idx) list_rest(gm, a.rest, bh, (int)blockIdx.x, rest_bits);
     const int n_rows = a.kv_rows ? gm.T : rows_total(a.rs, gm, bh);
     if (r0 >= n_rows) return;
     // rows before the first one that the dK/dV walk may read (see walk::list_bounds) see nothing
@@ -163,7 +193,7 @@ __global__ __launch_bounds__(kThreads) void merge_rows_kernel(Geom gm, RowSet rs
 
 // rows = tokens of each KV head: x[i] [B,T,Hkv,128] -> xt[i] [B*Hkv][128][cap], cap = round_up(T, 64)
 int pack_kv(const Geom& g, int n, const void* const* x, void* const* xt, int cap, const Fill* fills, int nfills,
-            hipStream_t st) {
+            const RestList* rest, hipStream_t st) {
     if (n < 1 || n > 2 || nfills < 0 || nfills > 3) return L2A_ERR_UNSUPPORTED;
     PackArgs a{};
     a.gm = g;
@@ -175,6 +205,7 @@ int pack_kv(const Geom& g, int n, const void* const* x, void* const* xt, int cap
     }
     for (int i = 0; i < nfills; ++i) a.fill[i] = fills[i];
     a.cap = cap;
+    if (rest) a.rest = *rest;
     KernelTimer kt("pack_kv", st);
     hipLaunchKernelGGL(pack_token_minor_kernel, dim3(cap / 64, g.B * g.Hkv), dim3(kThreads), 0, st, a);
     return launch_status();

@@ -1,5 +1,5 @@
-"""The backward of a layer with shared inputs, where a routed row's window counts once for both branches and the Global pass
-takes the keys before it: windows around the edges at which a row, a tile of rows or a block of keys has keys before the
+"""A layer with shared inputs, where a routed row's window is computed once for both branches -- in the forward one walk
+over the window and then the keys before it, in the backward a Local pass over combined rows and a Global one over those keys: windows around the edges at which a row, a tile of rows or a block of keys has keys before the
 window at all (tiles of 32 and 256 rows, blocks of 64 and 128 keys), both tile widths, both orders, batches, every mask
 granularity, and scores so uneven that one branch's share of a row vanishes."""
 import numpy as np
@@ -16,7 +16,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("order", [0, B.L2A_FLAG_SEQUENTIAL])
 @pytest.mark.parametrize("T,W,Hq,Hkv,Hm,f", [(300, 298, 4, 2, 1, 0.5), (300, 299, 4, 2, 1, 0.5), (300, 300, 4, 2, 4, 0.5),
                                              (321, 63, 7, 1, 7, 0.3), (321, 64, 7, 1, 1, 1.0), (449, 127, 2, 2, 2, 0.04),
-                                             (641, 0, 4, 1, 4, 0.2), (1700, 190, 20, 20, 20, 0.1)])
+                                             (641, 0, 4, 1, 4, 0.2), (1700, 190, 20, 20, 20, 0.1),
+                                             (1100, 70, 16, 1, 16, 1.0), (1100, 70, 16, 1, 1, 0.0), (515, 400, 16, 1, 16, 0.9)])
 def test_window_edges(oracle, T, W, Hq, Hkv, Hm, f, order):
     run_and_check(oracle, make_case(B_=2, T=T, Hq=Hq, Hkv=Hkv, W=W, Hm=Hm, f=f, seed=T + W), order, twice=True,
                   kv_heads=(0, Hkv - 1) if Hkv > 2 else None)
@@ -45,3 +46,20 @@ def test_a_key_before_the_window_takes_all_the_weight(oracle, dtype):
         err = np.linalg.norm(got.double().cpu().numpy() - want) / np.linalg.norm(want)
         print(name, "relative error", err, flush=True)
         assert err <= tol, name
+
+
+def test_lists_without_key_block_entries(oracle):
+    """The forward takes NULL for kblk_first_row; it then runs the branches apart, to the same bars."""
+    x = make_case(T=700, Hq=8, Hkv=2, W=120, Hm=8, f=0.3, seed=12)
+    lay, ref = run_and_check(oracle, x, backward=False)
+    with_first = [t.clone() for t in (lay.O, lay.S, lay.lse_l, lay.lse_g)]
+    lay.first = None
+    lay.forward()
+    torch.cuda.synchronize()
+    for a, b in zip(with_first, (lay.O, lay.S)):
+        assert (a.float() - b.float()).abs().max() <= 2e-2      # two bf16 roundings of values below 4
+    # row sums are of weights rounded to bf16 against another reference: 2^-9 of the sum each at most
+    tol = 2 * 2.0 ** -9
+    assert (with_first[2] - lay.lse_l).abs().max() <= tol
+    both = torch.isfinite(lay.lse_g)
+    assert torch.equal(both, torch.isfinite(with_first[3])) and (with_first[3] - lay.lse_g)[both].abs().max() <= tol
