@@ -38,7 +38,7 @@ struct DqArgs {
     const __bf16* dO;
     const float* lse;
     float* delta;  // in: <dO, saved out>; out: sum_j P dP
-    const float* share;  // optional: see fold_rows.  LOCAL: the rows are folded ones; else delta gets the far keys' part
+    const float* share;  // optional: see row_stats.  LOCAL: the rows are folded ones; else delta gets the far keys' part
     __bf16* dq;
     int accumulate;
     // The rows' results in fp32 go here instead of to dq.  LOCAL: those of folded rows that also have keys before the window,

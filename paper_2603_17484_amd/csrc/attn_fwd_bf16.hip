@@ -50,9 +50,10 @@ struct FwdArgs {
     int32_t* redo;  // [B*Hkv][redo_stride]: set to 1 for a tile of 256 rows that was left to running_max_body
     int redo_stride;
     FwdOut out;
-    // kBoth: `out` is where a goes (main_out: o); s and its log-sum-exp
+    // kBoth, kWhole: `out` is where a goes (main_out: o); s and its log-sum-exp
     __bf16* s_out = nullptr;
     float* s_lse = nullptr;
+    const unsigned char* routed = nullptr;  // kWhole: [B*Hkv][T*G], by row code
 };
 
 template <int NQB>
@@ -68,8 +69,9 @@ using Int = std::integral_constant<int, V>;
 // other's matrix instructions.
 // What a workgroup computes for its rows.  kBoth: routed rows of a layer whose branches share their inputs -- the window
 // first, whose sums give s, then the keys before it into the same sums, which give a: the scores of the window, and its
-// products with V, are computed once for both branches.
-enum Kind { kGlobal, kLocal, kBoth };
+// products with V, are computed once for both branches.  kWhole: all rows of such a layer while the window spans the
+// sequence: s = a, and which rows are routed only matters to what is written.
+enum Kind { kGlobal, kLocal, kBoth, kWhole };
 
 // Which tile of which (b, KV head) a workgroup takes; (bx, by) of (gx, nbh): its index in its branch's part of the grid (a
 // launch may carry both branches).
@@ -124,8 +126,21 @@ struct FwdLds {
     __bf16 k[3][kBK * 128];
     __bf16 v[2][kD * kBK];
 };
+// kWhole: four channels x of s, which is a where the row is routed; the row's log-sum-exp
+__device__ __forceinline__ void store_whole(const FwdArgs& a, size_t off, const f32x4& x, bool routed) {
+    const bf16x4 y = __builtin_convertvector(x, bf16x4), z = {(__bf16)0.f, (__bf16)0.f, (__bf16)0.f, (__bf16)0.f};
+    if (a.s_out) *reinterpret_cast<bf16x4*>(a.s_out + off) = y;
+    if (a.out.copy_out) *reinterpret_cast<bf16x4*>((__bf16*)a.out.copy_out + off) = routed ? y : z;
+    const f32x4 both = __builtin_convertvector(y, f32x4) + x;
+    *reinterpret_cast<bf16x4*>((__bf16*)a.out.main_out + off) = routed ? __builtin_convertvector(both, bf16x4) : y;
+}
+__device__ __forceinline__ void store_whole_lse(const FwdArgs& a, size_t so, float lse, bool routed) {
+    a.s_lse[so] = lse;
+    a.out.lse_out[so] = routed ? lse : -INFINITY;
+}
+
 template <bool LOCAL, int NW>
-__device__ __forceinline__ void running_max_body(const FwdArgs& a, const FwdOut& out, const Tile t, FwdLds& lds) {
+__device__ __forceinline__ void running_max_body(const FwdArgs& a, const FwdOut& out, const Tile t, FwdLds& lds, bool whole = false) {
     constexpr int NQB = 1, RW = 32 * NQB, BQ = NW * RW;
     typedef __bf16 K2[2][kTileRows * kRowPad];
     typedef __bf16 V2[2][kD * kColPad];
@@ -319,6 +334,7 @@ __device__ __forceinline__ void running_max_body(const FwdArgs& a, const FwdOut&
         if (!valid[c]) continue;
         const float inv = 1.f / lt;
         const size_t base = (((size_t)b * gm.T + pos[c]) * gm.Hq + head[c]) * kD + 4 * h;
+        const bool routed = whole && a.routed[(size_t)bh * gm.T * gm.G + wv_r0 + c * 32 + n];
 #pragma unroll
         for (int d = 0; d < 4; ++d)
 #pragma unroll
@@ -326,6 +342,10 @@ __device__ __forceinline__ void running_max_body(const FwdArgs& a, const FwdOut&
                 const size_t off = base + d * 32 + 8 * rg;
                 f32x4 x = {oacc[d][c][4 * rg + 0] * inv, oacc[d][c][4 * rg + 1] * inv,
                            oacc[d][c][4 * rg + 2] * inv, oacc[d][c][4 * rg + 3] * inv};
+                if (whole) {
+                    store_whole(a, off, x, routed);
+                    continue;
+                }
                 if (co) *reinterpret_cast<bf16x4*>(co + off) = __builtin_convertvector(x, bf16x4);
                 if (out.merge) {
                     const bf16x4 old = *reinterpret_cast<const bf16x4*>(mo + off);
@@ -340,6 +360,10 @@ __device__ __forceinline__ void running_max_body(const FwdArgs& a, const FwdOut&
             }
         if (h == 0) {
             const size_t so = ((size_t)b * gm.Hq + head[c]) * gm.T + pos[c];
+            if (whole) {
+                store_whole_lse(a, so, (m[c] + __builtin_amdgcn_logf(lt)) * kLn2, routed);
+                continue;
+            }
             out.lse_out[so] = (m[c] + __builtin_amdgcn_logf(lt)) * kLn2;
             if (out.lse_fill) out.lse_fill[so] = -INFINITY;
         }
@@ -350,7 +374,7 @@ template <Kind KIND, int NQB, int NW>
 __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds& lds) {
     auto& lds_k = lds.k;
     auto& lds_v = lds.v;
-    constexpr bool LOCAL = KIND != kGlobal;  // starts with the window
+    constexpr bool LOCAL = KIND == kLocal || KIND == kBoth;  // starts with the window
     constexpr int RW = 32 * NQB;       // rows per wavefront
     constexpr int BQ = RW * NW;        // rows per workgroup: a tile, or a whole part of one
     static_assert(kBQ % BQ == 0, "a workgroup's rows lie in one tile");
@@ -375,7 +399,7 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds&
     const bool wave_active = wv_r0 < n_rows;
 
     int pos[NQB], head[NQB];
-    bool valid[NQB];
+    bool valid[NQB], routed[NQB];
     bf16x8 qreg[NQB][8];
 #pragma unroll
     for (int c = 0; c < NQB; ++c) {
@@ -388,6 +412,7 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds&
         const __bf16* qp = a.q + (((size_t)b * gm.T + pos[c]) * gm.Hq + head[c]) * kD + 8 * h;
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks) qreg[c][ks] = *reinterpret_cast<const bf16x8*>(qp + ks * 16);
+        routed[c] = KIND == kWhole && a.routed[(size_t)bh * gm.T * gm.G + code] != 0;
     }
 
     // ---- block range of the workgroup, and its three runs: blocks that need the window-start
@@ -594,6 +619,16 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds&
     // One block = two half-blocks; Sa holds the scores of a block's first half on entry and exit.
     // K blocks rotate through three buffers: block jb in kbuf, jb+1 in kbuf1, and the block loaded now, jb+2, in kbuf2
     int kbuf = 0, kbuf1 = 1, kbuf2 = 2;
+    // Routed rows lie far apart where few are routed: the masked blocks of a tile are then out of reach of some wavefronts'
+    // rows altogether, and those skip the arithmetic (but not the loads, which are shared).  Blocks wanted: [w0, w1) and [n_win, w3).
+    int w0 = 0, w1 = n_all, w3 = 0;
+    if (KIND == kBoth) {
+        const int pmin = row_code(a.rs, gm, bh, min(wv_r0, n_rows - 1)) / gm.G;
+        const int pmax = row_code(a.rs, gm, bh, min(wv_r0 + RW, n_rows) - 1) / gm.G;
+        w0 = __builtin_amdgcn_readfirstlane(max(pmin - gm.W, 0) / kBK - jb0), w1 = __builtin_amdgcn_readfirstlane(pmax / kBK + 1 - jb0);
+        w3 = __builtin_amdgcn_readfirstlane(pmax > gm.W ? n_win + (pmax - gm.W - 1) / kBK + 1 : 0);
+    }
+    auto wanted = [&](int i) __attribute__((always_inline)) { return (i >= w0 && i < w1) || (i >= n_win && i < w3); };
     auto run = [&](auto mask_tag, int i_begin, int i_end) __attribute__((always_inline)) {
         for (int rel = i_begin; rel < i_end; ++rel) {
             const int jb = block(rel);
@@ -601,18 +636,30 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds&
             // issued in the slots of the first half-block where the VALU has nothing to do.  Past the
             // last block the last one is loaded again, into buffers nobody reads any more.
             const int jk = block(min(rel + 2, n_all - 1)), jv = block(min(rel + 1, n_all - 1));
-            {  // wavefronts whose rows all lie past the end compute on a repeated row and store nothing
+            BlockLoads L;
+            auto stage = [&]() __attribute__((always_inline)) {
+                L.ksrc = kbase + (size_t)jk * kBK * kv_row_bytes;
+                L.vsrc = vtbase + (size_t)jv * kBK * 2;
+                L.kdst = lds_k0 + kbuf2 * (kBK * 256);
+                L.vdst = lds_v0 + ((rel + 1) & 1) * (kD * kBK * 2);
+                L.krows = min(kBK, gm.T - jk * kBK);
+            };
+            if (KIND == kBoth && decltype(mask_tag)::value && !wanted(rel)) {
+                stage();
+                static_for<0, 2 * NL>([&](auto ic) { issue_block_load(L, ic); });
+                if (wanted(rel + 1)) {  // (past the end: of a tile that nobody reads)
+#pragma unroll
+                    for (int ks = 0; ks < 8; ++ks) {
+                        const bf16x8 op = rm_operand(&lds_k[kbuf1][0], n, ks, h);
+#pragma unroll
+                        for (int c = 0; c < NQB; ++c) Sa.s[c] = mfma32(op, qreg[c][ks], ks == 0 ? zero16 : Sa.s[c]);
+                    }
+                }
+            } else {  // wavefronts whose rows all lie past the end compute on a repeated row and store nothing
                 const __bf16* vt = &lds_v[rel & 1][0];
-                BlockLoads L;
                 half_block(mask_tag, Int<0>{}, Sa, Sb, &lds_k[kbuf][0], 32, vt, jb * kBK, [&](auto mc) {
                     constexpr int mm = decltype(mc)::value;
-                    if constexpr (mm == kLoadSlot0 - 1) {
-                        L.ksrc = kbase + (size_t)jk * kBK * kv_row_bytes;
-                        L.vsrc = vtbase + (size_t)jv * kBK * 2;
-                        L.kdst = lds_k0 + kbuf2 * (kBK * 256);
-                        L.vdst = lds_v0 + ((rel + 1) & 1) * (kD * kBK * 2);
-                        L.krows = min(kBK, gm.T - jk * kBK);
-                    }
+                    if constexpr (mm == kLoadSlot0 - 1) stage();
                     if constexpr (mm >= kLoadSlot0 && mm < kLoadSlot0 + 2 * NL) issue_block_load(L, Int<mm - kLoadSlot0>{});
                 });
                 half_block(mask_tag, Int<1>{}, Sb, Sa, &lds_k[kbuf1][0], 0, vt, jb * kBK + 32, [](auto) {});
@@ -694,7 +741,7 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds&
             running_max_body<true, NW>(a, FwdOut{a.out.main_out, a.s_out, a.s_lse, nullptr, nullptr, 0}, t, lds);
             running_max_body<false, NW>(a, a.out, t, lds);
         } else {
-            running_max_body<KIND == kLocal, NW>(a, a.out, t, lds);
+            running_max_body<KIND == kLocal, NW>(a, a.out, t, lds, KIND == kWhole);
         }
         return;
     }
@@ -710,6 +757,17 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds&
         if (!valid[c]) continue;
         const float inv = 1.f / lt[c];
         const size_t base = row_base(c);
+        if constexpr (KIND == kWhole) {
+#pragma unroll
+            for (int d = 0; d < 4; ++d)
+#pragma unroll
+                for (int rg = 0; rg < 4; ++rg)
+                    store_whole(a, base + d * 32 + 8 * rg,
+                                f32x4{oacc[d][c][4 * rg + 0] * inv, oacc[d][c][4 * rg + 1] * inv,
+                                      oacc[d][c][4 * rg + 2] * inv, oacc[d][c][4 * rg + 3] * inv}, routed[c]);
+            if (h == 0) store_whole_lse(a, row_stat(c), row_lse(c), routed[c]);
+            continue;
+        }
 #pragma unroll
         for (int d = 0; d < 4; ++d)
 #pragma unroll
@@ -749,40 +807,21 @@ __global__ __launch_bounds__(64 * NW) void fwd_kernel(FwdArgs a) {
     fwd_body<LOCAL ? kLocal : kGlobal, NQB, NW>(a, t, lds);
 }
 
-// Shared inputs: the routed rows (kBoth) and the others, which have the window only, in one launch; every row belongs to
-// one workgroup, which writes all of its outputs.  A routed row costs its prefix, another one its window at most.
-// Short sequences (windows that are no fraction of them): one range of workgroups per (b, KV head), longest tiles
-// first -- the routed rows beyond a window's length, then both kinds in proportion, which is by position for routing
-// that does not depend on it much.  Long ones: the first half of the grid takes the routed rows' tiles, the second the others'.
-// Whole forward, W = 4096, 20 % routed, 28 / 4 heads, the branches apart (one launch and a merge at 4096, two launches
-// beyond 16384) / together, us: T = 4096 171.4 / 151.2, T = 32768 3200 / 2920; of a training step of 16379 (32 / 8 heads,
-// bursty) 170 us, of one of 131072 1.2 ms.
-template <int NQB, int NW>
-__global__ __launch_bounds__(64 * NW, 2) void fwd_shared_kernel(FwdArgs ar, FwdArgs au, int gx) {
+// Shared inputs, the window spans the sequence: every row once.
+template <int NW>
+__global__ __launch_bounds__(64 * NW, 2) void fwd_whole_kernel(FwdArgs a) {
     __shared__ __attribute__((aligned(1024))) FwdLds lds;
-    constexpr int BQ = 32 * NQB * NW;
-    const Geom& gm = ar.gm;
-    Tile t;
-    bool routed;
-    if (windows_by_range(gm)) {
-        routed = (int)blockIdx.x < gx;
-        t = routed ? tile_of<BQ>(gm, ar.rs, false, (int)blockIdx.x, (int)blockIdx.y, gx, (int)gridDim.y)
-                   : tile_of<BQ>(gm, au.rs, true, (int)blockIdx.x - gx, (int)blockIdx.y, gx, (int)gridDim.y);
-    } else {
-        int rank;
-        head_and_rank(gm, (int)blockIdx.x, (int)blockIdx.y, gx, (int)gridDim.y, t.bh, rank);
-        const int rows_r = rows_total(ar.rs, gm, t.bh), rows_u = rows_total(au.rs, gm, t.bh);
-        const int nr = (rows_r + BQ - 1) / BQ, nu = (rows_u + BQ - 1) / BQ;
-        const int far = gm.T > gm.W ? (int)((long long)nr * (gm.T - gm.W) / gm.T) : 0;  // routed tiles beyond a window's length
-        const int k = rank - far, n = nr - far + nu;
-        // the k-th of n, nr - far of them routed, spread evenly
-        const int before = k <= 0 ? 0 : (int)((long long)k * (nr - far) / max(n, 1));
-        routed = k < 0 || (k < n && (int)((long long)(k + 1) * (nr - far) / max(n, 1)) > before);
-        t.n_rows = routed ? rows_r : rows_u;
-        t.tile = k < 0 ? nr - 1 - rank : k >= n ? -1 : routed ? nr - far - 1 - before : nu - 1 - (k - before);
-    }
-    if (routed) fwd_body<kBoth, NQB, NW>(ar, t, lds);
-    else fwd_body<kLocal, NQB, NW>(au, t, lds);
+    fwd_body<kWhole, 1, NW>(a, tile_of<32 * NW>(a.gm, a.rs, false, (int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x, (int)gridDim.y), lds);
+}
+
+// Shared inputs, long sequences: the routed rows (kBoth; the first half of the grid) and the others, which have the window
+// only, in one launch; every row belongs to one workgroup, which writes all of its outputs.
+__global__ __launch_bounds__(64 * kFwdNW, 2) void fwd_shared_kernel(FwdArgs ar, FwdArgs au, int gx) {
+    __shared__ __attribute__((aligned(1024))) FwdLds lds;
+    if ((int)blockIdx.x < gx)
+        fwd_body<kBoth, 1, kFwdNW>(ar, tile_of<kBQ>(ar.gm, ar.rs, false, (int)blockIdx.x, (int)blockIdx.y, gx, (int)gridDim.y), lds);
+    else
+        fwd_body<kLocal, 1, kFwdNW>(au, tile_of<kBQ>(au.gm, au.rs, true, (int)blockIdx.x - gx, (int)blockIdx.y, gx, (int)gridDim.y), lds);
 }
 
 // Both branches in one launch, for sequences so short that the Global rows' tiles alone leave most
@@ -864,23 +903,28 @@ int mfma_fwd_shared(const Geom& g, const RowSet& rs_r, const RowSet& rs_u, const
     if (g.D != kD || out_r.wide_out || out_u.wide_out || !out_r.merge) return L2A_ERR_UNSUPPORTED;
     if ((unsigned long long)vt_cap * 2ull * kD > 0xffffffffull) return L2A_ERR_UNSUPPORTED;
     const unsigned gx = tiles_x(g);
-    const bool half = half_tiles((size_t)gx * g.B * g.Hkv), split = g.T / 4 > g.W;  // split: windows_by_range
     FwdArgs au{g, rs_u, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (const __bf16*)vt, vt_cap, redo, (int)gx, out_u};
     FwdArgs ar{g, rs_r, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (const __bf16*)vt, vt_cap, redo, (int)gx, out_r,
                (__bf16*)S, lse_l};
-    {
-        // tiles of both kinds together: at most one more than all rows have; a multiple of 8
-        const long long rows = (long long)g.T * g.G;
-        const int bq = half ? 128 : 256;
-        const unsigned w = (unsigned)(((rows + bq - 1) / bq + 1 + 7) / 8 * 8);
-        KernelTimer kt("fwd_shared", st);
-        if (half) hipLaunchKernelGGL((fwd_shared_kernel<1, 4>), dim3(split ? 2 * w : w, g.B * g.Hkv), dim3(256), 0, st, ar, au, (int)w);
-        else hipLaunchKernelGGL((fwd_shared_kernel<kFwdNQB, kFwdNW>), dim3(split ? 2 * w : w, g.B * g.Hkv), dim3(64 * kFwdNW), 0, st, ar, au, (int)w);
-    }
+    KernelTimer kt("fwd_shared", st);
+    hipLaunchKernelGGL(fwd_shared_kernel, dim3(2 * gx, g.B * g.Hkv), dim3(64 * kFwdNW), 0, st, ar, au, (int)gx);
     return launch_status();
 }
 
-// number of redo flags mfma_fwd needs
+// Shared inputs while the window spans the sequence (fwd_whole_kernel): routed [B*Hkv][T*G] bytes by row code; out: a (main_out: o)
+int mfma_fwd_whole(const Geom& g, const void* q, const void* k, const void* v, const void* vt, int vt_cap, int32_t* redo,
+                   const unsigned char* routed, const FwdOut& out, void* S, float* lse_l, hipStream_t st) {
+    if (g.D != kD || g.T > g.W + 1LL) return L2A_ERR_UNSUPPORTED;
+    if ((unsigned long long)vt_cap * 2ull * kD > 0xffffffffull) return L2A_ERR_UNSUPPORTED;
+    const unsigned gx = tiles_x(g);
+    FwdArgs a{g, RowSet{nullptr, nullptr, nullptr, 0}, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (const __bf16*)vt, vt_cap,
+              redo, (int)gx, out, (__bf16*)S, lse_l, routed};
+    KernelTimer kt("fwd_whole", st);
+    if (half_tiles((size_t)gx * g.B * g.Hkv)) hipLaunchKernelGGL((fwd_whole_kernel<4>), dim3(2 * gx, g.B * g.Hkv), dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((fwd_whole_kernel<8>), dim3(gx, g.B * g.Hkv), dim3(512), 0, st, a);
+    return launch_status();
+}
+
 size_t mfma_fwd_redo_entries(const Geom& g) {
     return (size_t)tiles_x(g) * g.B * g.Hkv;
 }

@@ -91,21 +91,17 @@ int router_decide(const l2a_params& p, int C, const void* x, const float* w, flo
                   float* dhat, uint8_t* mask, hipStream_t st);
 
 // ---- util.hip
-// share_zero: optional, [B,Hq,T] set to zero on the way
-int row_deltas(const Geom& g, int dtype, const void* dO, const void* S, const void* A, float* delta_l,
-               float* delta_g, float* share_zero, hipStream_t st);
-// Backward of a layer whose branches share their inputs: the two branches of a routed row in its window as one row.
-// share[b,h,t] = a = exp(lse_local - lse_global) (1e-30 at least; 0 on rows not in rs) and delta_l = (delta_l + a delta_g) / (1 + a) on the rows of rs.
-int fold_rows(const Geom& g, const RowSet& rs, const float* lse_l, const float* lse_g, float* delta_l, const float* delta_g,
-              float* share, hipStream_t st);
-// bf16: delta of the first 64 tokens of every sequence recomputed from its definition, one or two branches
-struct HeadDeltas {
-    const void *q, *k, *v;
+// The backward's per-row statistics: delta of the branches that are run (bf16: the first 64 tokens' from the definition).
+// share (optional, both branches with the same q, k, v): the two branches of a routed row in its window become one row:
+// share[b,h,t] = a = exp(lse_local - lse_global) (1e-30 at least; 0 on rows not in `routed`) and the Local delta is that
+// of the folded row, (delta_l + a delta_g) / (1 + a)
+struct RowStats {
+    const void *q, *k, *v, *out;  // out: the saved s or a
     const float* lse;
     float* delta;
-    int local;
 };
-int head_deltas(const Geom& g, const HeadDeltas* branches, int n, const void* dO, hipStream_t st);
+int row_stats(const Geom& g, int dtype, const void* dO, const RowStats* local, const RowStats* global, const RowSet& routed,
+              float* share, hipStream_t st);
 int fill_zero(void* ptr, size_t bytes, hipStream_t st);
 int fill_f32(float* ptr, size_t n, float value, hipStream_t st);
 
@@ -123,6 +119,8 @@ int mfma_fwd_pair(const Geom& g, const RowSet& rs_l, const void* q_l, const void
 int mfma_fwd_shared(const Geom& g, const RowSet& rs_r, const RowSet& rs_u, const void* q, const void* k, const void* v,
                     const void* vt, int vt_cap, int32_t* redo, const FwdOut& out_r, void* S, float* lse_l, const FwdOut& out_u,
                     hipStream_t st);
+int mfma_fwd_whole(const Geom& g, const void* q, const void* k, const void* v, const void* vt, int vt_cap, int32_t* redo,
+                   const unsigned char* routed, const FwdOut& out, void* S, float* lse_l, hipStream_t st);
 
 // ---- attn_decode_bf16.hip : one new token per sequence against the KV cache (bf16, D = 128)
 size_t decode_partial_floats(const Geom& g);
@@ -141,18 +139,19 @@ struct Fill {  // n 32-bit words of one value
 struct RestList {
     RowSet routed;
     int32_t *row_idx, *count;  // [B,Hkv,T*G], [B,Hkv]
+    unsigned char* flags;      // instead of the list: [B,Hkv,T*G], 1 where the row is routed
 };
 int pack_kv(const Geom& g, int n, const void* const* x, void* const* xt, int cap, const Fill* fills, int nfills,
             const RestList* rest, hipStream_t st);
 // O += A on the rows of rs (O bf16, A fp32, D = 128), or O = S + A with S in fp32, where S is given
 // (rows that see a key: those at positions below rs.shift are left as they are)
 int merge_rows(const Geom& g, const RowSet& rs, const float* S, const float* A, void* O, hipStream_t st);
-// share (see fold_rows), with the Local rows: their statistics are those of the folded rows, and delta_g is completed
+// share (see row_stats), with the Local rows: their statistics are those of the folded rows, and delta_g is completed
 int pack_rows(const Geom& g, const RowSet& rs, const void* q, const void* dO, const float* lse, const float* delta,
               void* qc, void* gc, float* lse2_c, float* delta_c, int32_t* pos_c, int cap, const float* share, float* delta_g,
               hipStream_t st);
 // wide (with share): the parts of rows that both passes visit, in fp32 -- written by the Local pass, added by the Global one;
-// share: see fold_rows; delta on return: Local rows delta_l, Global rows (keys 0..pos - shift only) their part of delta_g
+// share: see row_stats; delta on return: Local rows delta_l, Global rows (keys 0..pos - shift only) their part of delta_g
 int mfma_bwd_dq(const Geom& g, const RowSet& rs, const void* q, const void* k, const void* v, const void* dO,
                 const float* lse, float* delta, const float* share, void* dq, int accumulate, float* wide, hipStream_t st);
 int mfma_bwd_dq_pair(const Geom& g, const RowSet& rs_l, const void* q_l, const void* k_l, const void* v_l,

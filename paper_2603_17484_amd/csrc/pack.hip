@@ -26,7 +26,7 @@ struct PackArgs {
     __bf16* xc[2];        // optional compact row-major copies [B*Hkv][cap][128]
     const float* lse;     // optional per-row statistics of the row set, [B,Hq,T]
     const float* delta;
-    const float* share;   // optional, with the Local rows: the folded rows' a (fold_rows)
+    const float* share;   // optional, with the Local rows: the folded rows' a (row_stats)
     float* delta_g;       // share: in the far keys' part of the routed rows' delta_g, out delta_g
     float* lse2_c;        // [B*Hkv][cap]: lse * log2(e)
     float* delta_c;
@@ -66,6 +66,10 @@ __device__ __forceinline__ void list_rest(const Geom& gm, const RestList& rl, in
         if (c >= 0 && c < codes) atomicOr(&bits[c >> 6], 1ull << (c & 63));
     }
     __syncthreads();
+    if (rl.flags) {
+        for (int c = threadIdx.x; c < codes; c += kThreads) rl.flags[(size_t)bh * all + c0 + c] = bits[c >> 6] >> (c & 63) & 1;
+        return;
+    }
     for (int c = threadIdx.x; c < codes; c += kThreads) {
         int before = f0;
         for (int w = 0; w < c >> 6; ++w) before += __popcll(bits[w]);
@@ -86,7 +90,7 @@ __global__ __launch_bounds__(kThreads) void pack_token_minor_kernel(PackArgs a) 
 #pragma unroll
     for (int i = 0; i < 3; ++i)
         if (a.fill[i].n) run_fill(a.fill[i]);
-    if (a.rest.row_idx) list_rest(gm, a.rest, bh, (int)blockIdx.x, rest_bits);
+    if (a.rest.row_idx || a.rest.flags) list_rest(gm, a.rest, bh, (int)blockIdx.x, rest_bits);
     const int n_rows = a.kv_rows ? gm.T : rows_total(a.rs, gm, bh);
     if (r0 >= n_rows) return;
     // rows before the first one that the dK/dV walk may read (see walk::list_bounds) see nothing

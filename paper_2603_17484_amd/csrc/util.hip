@@ -6,63 +6,12 @@
 namespace l2a {
 namespace {
 
-// delta_l[b,h,t] = <dO, S>, delta_g[b,h,t] = <dO, A>  (the "D" vector of the FlashAttention
-// backward, one per branch; delta_g is also the task-loss part of the router-score gradient,
-// Sec. 3.3 Eq. 7).  A workgroup takes `tok` consecutive tokens of one sequence -- a contiguous
-// stretch of [t, h, D] rows, sixteen lanes per row -- and transposes its results through LDS, so
-// that the [b, h, t] outputs are written in runs of consecutive t instead of one scattered float
-// per row.
-template <typename E, int DL>
-__global__ __launch_bounds__(kThreads) void row_deltas_kernel(Geom gm, const E* __restrict__ dO,
-                                                              const E* __restrict__ S, const E* __restrict__ A,
-                                                              float* __restrict__ delta_l,
-                                                              float* __restrict__ delta_g,
-                                                              float* __restrict__ share_zero, int tok) {
-    extern __shared__ float stage[];  // [2][Hq][tok]
-    const int b = blockIdx.y, t0 = blockIdx.x * tok;
-    const int ntok = min(tok, gm.T - t0);
-    const int part = threadIdx.x & 15;
-    float* sa = stage;
-    float* sc = stage + gm.Hq * tok;
-    const size_t row0 = ((size_t)b * gm.T + t0) * gm.Hq;
-    for (int r = threadIdx.x >> 4; r < ntok * gm.Hq; r += kThreads / 16) {
-        const size_t off = (row0 + r) * gm.D + part * DL;
-        float a = 0.f, c = 0.f;
-        // one 16- or 32-byte load per array and lane
-        typedef E Vec __attribute__((ext_vector_type(DL)));
-        const Vec gv = *reinterpret_cast<const Vec*>(dO + off);
-        if (S) {
-            const Vec sv = *reinterpret_cast<const Vec*>(S + off);
-#pragma unroll
-            for (int i = 0; i < DL; ++i) a += (float)gv[i] * (float)sv[i];
-        }
-        if (A) {
-            const Vec av = *reinterpret_cast<const Vec*>(A + off);
-#pragma unroll
-            for (int i = 0; i < DL; ++i) c += (float)gv[i] * (float)av[i];
-        }
-        for (int o = 8; o > 0; o >>= 1) {
-            a += __shfl_xor(a, o);
-            c += __shfl_xor(c, o);
-        }
-        if (part == 0) {
-            const int tt = r / gm.Hq, h = r - tt * gm.Hq;
-            sa[h * tok + tt] = a;
-            sc[h * tok + tt] = c;
-        }
-    }
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < gm.Hq * tok; idx += kThreads) {
-        const int h = idx / tok, tt = idx - h * tok;
-        if (tt >= ntok) continue;
-        const size_t so = ((size_t)b * gm.Hq + h) * gm.T + t0 + tt;
-        if (delta_l) delta_l[so] = sa[idx];
-        if (delta_g) delta_g[so] = sc[idx];
-        if (share_zero) share_zero[so] = 0.f;
-    }
-}
-
-// Shared inputs: in its window a routed row's two branches have the same scores, so that their weights differ by a
+// The per-row statistics of the backward, one launch:
+//     delta_l[b,h,t] = <dO, S>, delta_g[b,h,t] = <dO, A>  (the "D" vector of the FlashAttention backward, one per branch;
+//     delta_g is also the task-loss part of the router-score gradient, Sec. 3.3 Eq. 7),
+// for bf16 those of the first tokens from their definition, and for shared inputs the fold of the routed rows.
+//
+// Fold.  In its window a routed row's two branches have the same scores, so that their weights differ by a
 // constant, p_g = a p_l with a = exp(lse_l - lse_g) <= 1, and what they add up to there is one row's gradient:
 //     p_l + p_g = p',   p_l (dP - delta_l) + p_g (dP - delta_g) = p' (dP - delta'),
 //     p' = exp(s - lse_l + log(1 + a)),   delta' = (delta_l + a delta_g) / (1 + a).
@@ -71,19 +20,52 @@ __global__ __launch_bounds__(kThreads) void row_deltas_kernel(Geom gm, const E* 
 // (32 / 8 heads) 6389 / 5740 us, T = 131072 (28 / 4 heads) 125.9 / 121.2 ms.  dK and dV take one rounding of the sum of
 // two weights where they took two independent ones: their error against 64 bits at T = 16379 is 1.4 % and 0.9 % larger
 // (2.83e-3 -> 2.87e-3, 2.31e-3 -> 2.33e-3 of the norm); dQ, whose two parts are now added in fp32, 2.381e-3 -> 2.380e-3.
-// One thread per routed row.
-__global__ __launch_bounds__(kThreads) void fold_rows_kernel(Geom gm, RowSet rs, const float* __restrict__ lse_l,
-                                                             const float* __restrict__ lse_g, float* __restrict__ delta_l,
-                                                             const float* __restrict__ delta_g, float* __restrict__ share) {
-    const int bh = blockIdx.y, b = bh / gm.Hkv, hk = bh - b * gm.Hkv;
-    const int r = blockIdx.x * kThreads + threadIdx.x;
-    if (r >= rows_total(rs, gm, bh)) return;
-    const int code = row_code(rs, gm, bh, r), p = code / gm.G;
-    const size_t so = ((size_t)b * gm.Hq + hk * gm.G + (code - p * gm.G)) * gm.T + p;
-    float a = expf(lse_l[so] - lse_g[so]);
-    a = a < 1e-30f ? 1e-30f : a;  // not zero: that marks the rows that are not folded (a NaN stays one)
-    share[so] = a;
-    delta_l[so] = (delta_l[so] + a * delta_g[so]) / (1.f + a);
+//
+// Memory-bound: a workgroup takes `tok` consecutive tokens of one sequence -- a contiguous
+// stretch of [t, h, D] rows, sixteen lanes per row, four rows of each in flight -- and transposes its results through
+// LDS, so that the [b, h, t] outputs are written in runs of consecutive t instead of one scattered float
+// per row.  Which rows are routed comes from the lists: the entries of the 64 positions around.  As three launches
+// (products, first tokens, fold) with one row in flight this took 36 us at 1000 tokens of 28 heads, now 15; 2 x 4000 tokens
+// of separate modules (two launches) 51, now 43 (172 MB).
+struct StatsBranch {
+    const void *q, *k, *v, *out;  // out: the saved s or a (null: the branch is not run)
+    const float* lse;
+    float* delta;
+    int local;
+};
+struct StatsArgs {
+    Geom gm;
+    StatsBranch br[2];
+    const void* dO;
+    int tok;         // tokens per workgroup, a power of two up to 64
+    int row_blocks;  // workgroups per sequence that take rows; the ones behind them the first tokens, one head each
+    RowSet routed;   // share: the routed rows and kblk_first_row
+    float* share;    // fold: a, 0 on rows that are not routed (null: no fold)
+};
+
+// marks the routed rows of positions t0 .. t0 + n - 1 (inside one block of 64) of KV head hk: flags[g * n + t - t0]
+__device__ __forceinline__ void mark_routed(const Geom& gm, const RowSet& rs, int b, int hk, int t0, int n, unsigned char* flags) {
+    const int bh = b * gm.Hkv + hk, total = rows_total(rs, gm, bh);
+    const int32_t* first = rs.kblk_first_row + (size_t)bh * ((gm.T + 63) / 64 + 1) + (t0 >> 6);
+    const int f0 = min(max(first[0], 0), total), f1 = min(max(first[1], f0), total);
+    for (int i = f0 + (int)threadIdx.x; i < f1; i += kThreads) {
+        const int code = row_code(rs, gm, bh, i), p = code / gm.G, t = p - t0;
+        if (t >= 0 && t < n) flags[(code - p * gm.G) * n + t] = 1;
+    }
+}
+
+__device__ __forceinline__ void store_stats(const StatsArgs& a, size_t so, float dl, float dg, bool routed) {
+    if (a.share) {
+        float f = 0.f;
+        if (routed) {
+            f = expf(a.br[0].lse[so] - a.br[1].lse[so]);
+            f = f < 1e-30f ? 1e-30f : f;  // not zero: that marks the rows that are not folded (a NaN stays one)
+            dl = (dl + f * dg) / (1.f + f);
+        }
+        a.share[so] = f;
+    }
+    if (a.br[0].out) a.br[0].delta[so] = dl;
+    if (a.br[1].out) a.br[1].delta[so] = dg;
 }
 
 // delta of the first tokens of a sequence, from its definition instead of from the saved outputs:
@@ -93,29 +75,19 @@ __global__ __launch_bounds__(kThreads) void fold_rows_kernel(Geom gm, RowSet rs,
 // rows that average many keys, but for the first few tokens they do not (token 2 with N(0,1) inputs:
 // up to 1.2e-2 per branch, twice that when both branches read the same tensors, since s_t = a_t
 // there), so the first kHeadTokens deltas are recomputed exactly.  A row whose log-sum-exp is -inf (not routed: a_t = 0)
-// gets delta = 0.  Workgroup = (branch, head, sequence), wavefront = 32 tokens, on the matrix cores: S^T = K Q^T and dP^T
-// = V dO^T of 32 keys at a time, a lane owns a token.  With a wavefront per token and a lane per key the 64 separate cache
-// lines of every load set the time: 30 us for two sequences of 28 heads, both branches, now 12.
+// gets delta = 0.  Workgroup = (head, sequence), wavefront = 32 tokens of a branch, on the matrix cores: S^T = K Q^T and
+// dP^T = V dO^T of 32 keys at a time, a lane owns a token.  With a wavefront per token and a lane per key the 64 separate
+// cache lines of every load set the time: 30 us for two sequences of 28 heads, both branches, now 12.
 constexpr int kHeadTokens = 64;
 
-struct HeadBranch {
-    const __bf16 *q, *k, *v;
-    const float* lse;
-    float* delta;
-    int local;
-};
-
-__global__ __launch_bounds__(128) void head_deltas_kernel(Geom gm, HeadBranch br0, HeadBranch br1,
-                                                          const __bf16* __restrict__ dO) {
-    const HeadBranch br = blockIdx.x ? br1 : br0;
-    const int h = blockIdx.y, b = blockIdx.z, hk = h / gm.G;
-    const int lane = threadIdx.x & 63, n = lane & 31, half = lane >> 5;
-    const int t0 = (int)(threadIdx.x >> 6) * 32, nt = min(gm.T, kHeadTokens);
-    if (t0 >= nt) return;
+__device__ __forceinline__ void head_deltas(const StatsArgs& a, const StatsBranch& br, int b, int h, int t0, float* out) {
+    const Geom& gm = a.gm;
+    const int hk = h / gm.G, lane = threadIdx.x & 63, n = lane & 31, half = lane >> 5;
+    const int nt = min(gm.T, kHeadTokens);
     const int t = min(t0 + n, nt - 1);  // lanes past the end repeat the last token and write nothing
     const size_t row = (((size_t)b * gm.T + t) * gm.Hq + h) * gm.D + 8 * half;
-    const size_t so = ((size_t)b * gm.Hq + h) * gm.T + t;
-    const float l = br.lse[so];
+    const float l = br.lse[((size_t)b * gm.Hq + h) * gm.T + t];
+    const __bf16 *q = (const __bf16*)br.q, *k = (const __bf16*)br.k, *v = (const __bf16*)br.v, *dO = (const __bf16*)a.dO;
     float sum = 0.f;
     for (int k0 = 0; k0 <= min(t0 + 31, nt - 1); k0 += 32) {
         const int j = min(k0 + n, gm.T - 1);  // keys past the end: out of every token's reach
@@ -128,8 +100,8 @@ __global__ __launch_bounds__(128) void head_deltas_kernel(Geom gm, HeadBranch br
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int c = c0 + 16 * i;
-                q8[i] = *reinterpret_cast<const bf16x8*>(br.q + row + c), k8[i] = *reinterpret_cast<const bf16x8*>(br.k + key + c);
-                g8[i] = *reinterpret_cast<const bf16x8*>(dO + row + c), v8[i] = *reinterpret_cast<const bf16x8*>(br.v + key + c);
+                q8[i] = *reinterpret_cast<const bf16x8*>(q + row + c), k8[i] = *reinterpret_cast<const bf16x8*>(k + key + c);
+                g8[i] = *reinterpret_cast<const bf16x8*>(dO + row + c), v8[i] = *reinterpret_cast<const bf16x8*>(v + key + c);
             }
 #pragma unroll
             for (int i = 0; i < 4; ++i) s = mfma32(k8[i], q8[i], s), dp = mfma32(v8[i], g8[i], dp);
@@ -142,7 +114,86 @@ __global__ __launch_bounds__(128) void head_deltas_kernel(Geom gm, HeadBranch br
         }
     }
     sum += __shfl_xor(sum, 32);
-    if (half == 0 && t0 + n < nt) br.delta[so] = sum;
+    if (half == 0) out[t0 + n] = sum;
+}
+
+constexpr int kFlight = 4;  // rows of sixteen lanes whose loads are in flight together
+template <typename E, int DL>
+__global__ __launch_bounds__(kThreads) void row_stats_kernel(StatsArgs a) {
+    extern __shared__ float stage[];  // [2][Hq][tok] products, then one byte per row: routed
+    const Geom& gm = a.gm;
+    const int b = blockIdx.y;
+    if constexpr (sizeof(E) == 2) {
+        if ((int)blockIdx.x >= a.row_blocks) {  // the first tokens of one head
+            const int h = (int)blockIdx.x - a.row_blocks, hk = h / gm.G, nt = min(gm.T, kHeadTokens);
+            unsigned char* flags = reinterpret_cast<unsigned char*>(stage + 2 * kHeadTokens);  // [G][nt]
+            const int which = (int)threadIdx.x >> 7, t0 = (int)(threadIdx.x >> 6 & 1) * 32;
+            if (a.share)
+                for (int i = threadIdx.x; i < gm.G * nt; i += kThreads) flags[i] = 0;
+            if (a.br[which].out && t0 < nt) head_deltas(a, a.br[which], b, h, t0, stage + which * kHeadTokens);
+            __syncthreads();
+            if (a.share) {
+                mark_routed(gm, a.routed, b, hk, 0, nt, flags);
+                __syncthreads();
+            }
+            const int t = threadIdx.x;
+            if (t < nt)
+                store_stats(a, ((size_t)b * gm.Hq + h) * gm.T + t, stage[t], stage[kHeadTokens + t],
+                            a.share && flags[(h - hk * gm.G) * nt + t]);
+            return;
+        }
+    }
+    const int tok = a.tok, t0 = blockIdx.x * tok;
+    const int ntok = min(tok, gm.T - t0), rows = ntok * gm.Hq;
+    const int part = threadIdx.x & 15;
+    float* sa = stage;
+    float* sc = stage + gm.Hq * tok;
+    unsigned char* flags = reinterpret_cast<unsigned char*>(stage + 2 * gm.Hq * tok);  // [Hq][ntok]
+    if (a.share) {
+        for (int i = threadIdx.x; i < rows; i += kThreads) flags[i] = 0;
+        __syncthreads();
+        for (int hk = 0; hk < gm.Hkv; ++hk) mark_routed(gm, a.routed, b, hk, t0, ntok, flags + hk * gm.G * ntok);
+    }
+    const size_t row0 = ((size_t)b * gm.T + t0) * gm.Hq;
+    typedef E Vec __attribute__((ext_vector_type(DL)));  // one 16- or 32-byte load per array and lane
+    const E* dO = (const E*)a.dO;
+    const E *S = (const E*)a.br[0].out, *A = (const E*)a.br[1].out;
+    for (int rr = threadIdx.x >> 4; rr < rows; rr += kFlight * (kThreads / 16)) {
+        Vec gv[kFlight], sv[kFlight], av[kFlight];
+#pragma unroll
+        for (int j = 0; j < kFlight; ++j) {
+            const size_t off = (row0 + min(rr + j * (kThreads / 16), rows - 1)) * gm.D + part * DL;
+            gv[j] = *reinterpret_cast<const Vec*>(dO + off);
+            if (S) sv[j] = *reinterpret_cast<const Vec*>(S + off);
+            if (A) av[j] = *reinterpret_cast<const Vec*>(A + off);
+        }
+#pragma unroll
+        for (int j = 0; j < kFlight; ++j) {
+            float x = 0.f, y = 0.f;
+            if (S)
+#pragma unroll
+                for (int i = 0; i < DL; ++i) x += (float)gv[j][i] * (float)sv[j][i];
+            if (A)
+#pragma unroll
+                for (int i = 0; i < DL; ++i) y += (float)gv[j][i] * (float)av[j][i];
+            for (int o = 8; o > 0; o >>= 1) {
+                x += __shfl_xor(x, o);
+                y += __shfl_xor(y, o);
+            }
+            const int r = rr + j * (kThreads / 16);
+            if (part == 0 && r < rows) {
+                const int tt = r / gm.Hq, h = r - tt * gm.Hq;
+                sa[h * tok + tt] = x;
+                sc[h * tok + tt] = y;
+            }
+        }
+    }
+    __syncthreads();
+    for (int idx = threadIdx.x; idx < gm.Hq * tok; idx += kThreads) {
+        const int h = idx / tok, tt = idx - h * tok;
+        if (tt >= ntok || (sizeof(E) == 2 && t0 + tt < kHeadTokens)) continue;
+        store_stats(a, ((size_t)b * gm.Hq + h) * gm.T + t0 + tt, sa[idx], sc[idx], a.share && flags[h * ntok + tt]);
+    }
 }
 
 // 16-byte stores from an aligned address, a few per thread (57 MB with a 4-byte store per thread 18 us, now 11)
@@ -159,47 +210,33 @@ __global__ __launch_bounds__(kThreads) void fill_u32_kernel(uint32_t* p, size_t 
 
 }  // namespace
 
-int row_deltas(const Geom& g, int dtype, const void* dO, const void* S, const void* A, float* delta_l,
-               float* delta_g, float* share_zero, hipStream_t st) {
-    int tok = 64;  // tokens per workgroup: as many as fit 64 KB of LDS with Hq heads
-    while (tok > 1 && sizeof(float) * 2 * g.Hq * tok > 64 * 1024) tok /= 2;
-    // short sequences: fewer tokens per workgroup rather than a grid that leaves most of the chip idle
-    while (tok > 8 && (long long)((g.T + tok - 1) / tok) * g.B < 2048) tok /= 2;
-    const size_t lds = sizeof(float) * 2 * g.Hq * tok;
-    if (lds > 64 * 1024) return L2A_ERR_UNSUPPORTED;
-    const dim3 grid((unsigned)((g.T + tok - 1) / tok), (unsigned)g.B);
-    KernelTimer kt("row_deltas", st);
-    if (dtype == L2A_FP32 && g.D == 64)
-        hipLaunchKernelGGL((row_deltas_kernel<float, 4>), grid, dim3(kThreads), lds, st, g, (const float*)dO, (const float*)S, (const float*)A, delta_l, delta_g, share_zero, tok);
-    else if (dtype == L2A_FP32 && g.D == 128)
-        hipLaunchKernelGGL((row_deltas_kernel<float, 8>), grid, dim3(kThreads), lds, st, g, (const float*)dO, (const float*)S, (const float*)A, delta_l, delta_g, share_zero, tok);
-    else if (dtype == L2A_BF16 && g.D == 64)
-        hipLaunchKernelGGL((row_deltas_kernel<__bf16, 4>), grid, dim3(kThreads), lds, st, g, (const __bf16*)dO, (const __bf16*)S, (const __bf16*)A, delta_l, delta_g, share_zero, tok);
-    else if (dtype == L2A_BF16 && g.D == 128)
-        hipLaunchKernelGGL((row_deltas_kernel<__bf16, 8>), grid, dim3(kThreads), lds, st, g, (const __bf16*)dO, (const __bf16*)S, (const __bf16*)A, delta_l, delta_g, share_zero, tok);
-    else
-        return L2A_ERR_UNSUPPORTED;
-    return launch_status();
-}
-
-int fold_rows(const Geom& g, const RowSet& rs, const float* lse_l, const float* lse_g, float* delta_l, const float* delta_g,
+int row_stats(const Geom& g, int dtype, const void* dO, const RowStats* local, const RowStats* global, const RowSet& routed,
               float* share, hipStream_t st) {
-    const long long rows = (long long)g.T * g.G;
-    KernelTimer kt("fold_rows", st);
-    hipLaunchKernelGGL(fold_rows_kernel, dim3((unsigned)((rows + kThreads - 1) / kThreads), g.B * g.Hkv), dim3(kThreads), 0, st, g,
-                       rs, lse_l, lse_g, delta_l, delta_g, share);
-    return launch_status();
-}
-
-int head_deltas(const Geom& g, const HeadDeltas* branches, int n, const void* dO, hipStream_t st) {
-    static_assert(kHeadTokens <= 64, "two wavefronts of 32 tokens");
-    HeadBranch br[2] = {};
-    for (int i = 0; i < n; ++i)
-        br[i] = HeadBranch{(const __bf16*)branches[i].q, (const __bf16*)branches[i].k, (const __bf16*)branches[i].v,
-                           branches[i].lse, branches[i].delta, branches[i].local};
-    KernelTimer kt("head_deltas", st);
-    hipLaunchKernelGGL(head_deltas_kernel, dim3((unsigned)n, (unsigned)g.Hq, (unsigned)g.B), dim3(128), 0, st, g, br[0], br[1],
-                       (const __bf16*)dO);
+    auto lds_bytes = [&](int tok) { return (size_t)g.Hq * tok * 9; };
+    int tok = 64;  // tokens per workgroup: as many as fit 64 KB of LDS with Hq heads
+    while (tok > 1 && lds_bytes(tok) > 64 * 1024) tok /= 2;
+    // short sequences: fewer tokens per workgroup rather than a grid that leaves most of the chip idle
+    while (tok > 2 && tok * g.Hq > kFlight * (kThreads / 16) && (long long)((g.T + tok - 1) / tok) * g.B < 1024) tok /= 2;
+    if (lds_bytes(tok) > 64 * 1024) return L2A_ERR_UNSUPPORTED;
+    StatsArgs a{};
+    a.gm = g;
+    a.dO = dO;
+    a.tok = tok;
+    a.row_blocks = (g.T + tok - 1) / tok;
+    a.routed = routed;
+    a.share = share;
+    if (local) a.br[0] = StatsBranch{local->q, local->k, local->v, local->out, local->lse, local->delta, 1};
+    if (global) a.br[1] = StatsBranch{global->q, global->k, global->v, global->out, global->lse, global->delta, 0};
+    // bf16: the first tokens of a head need 2 x 64 floats and 64 G bytes
+    const size_t head_lds = (2 * sizeof(float) + g.G) * kHeadTokens, row_lds = lds_bytes(tok);
+    const size_t lds = dtype == L2A_BF16 && head_lds > row_lds ? head_lds : row_lds;
+    const dim3 grid((unsigned)(a.row_blocks + (dtype == L2A_BF16 ? g.Hq : 0)), (unsigned)g.B);
+    KernelTimer kt("row_stats", st);
+    if (dtype == L2A_FP32 && g.D == 64) hipLaunchKernelGGL((row_stats_kernel<float, 4>), grid, dim3(kThreads), lds, st, a);
+    else if (dtype == L2A_FP32 && g.D == 128) hipLaunchKernelGGL((row_stats_kernel<float, 8>), grid, dim3(kThreads), lds, st, a);
+    else if (dtype == L2A_BF16 && g.D == 64) hipLaunchKernelGGL((row_stats_kernel<__bf16, 4>), grid, dim3(kThreads), lds, st, a);
+    else if (dtype == L2A_BF16 && g.D == 128) hipLaunchKernelGGL((row_stats_kernel<__bf16, 8>), grid, dim3(kThreads), lds, st, a);
+    else return L2A_ERR_UNSUPPORTED;
     return launch_status();
 }
 
