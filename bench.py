@@ -241,7 +241,8 @@ def main() -> int:
     pf = pairs_before_window(mask_np, w.Hq, T, w.W)
     alg = {  # FLOPs per launch, the window's pairs of a routed row once; the backward's 10 D per pair = 8 D (S, dP, dV, dK) + 2 D (dQ)
         "bwd_dq_local": 2.0 * D * pl, "bwd_dq_global": 2.0 * D * pf, "bwd_dq_pair": 2.0 * D * (pl + pf),
-        "bwd_dkdv": 8.0 * D * (pl + pf), "fwd_shared": 4.0 * D * (pl + pf),
+        "bwd_dkdv": 8.0 * D * (pl + pf), "fwd_shared": 4.0 * D * (pl + pf), "fwd_whole": 4.0 * D * pl, "fwd_pair": 4.0 * D * (pl + pg),
+        "fwd_local": 4.0 * D * pl, "fwd_global": 4.0 * D * pg,
     }
     dom = max((n for n in kern if n in alg), key=lambda n: kern[n])
     achieved = alg[dom] / (kern[dom] * 1e-3) / 1e12

@@ -179,9 +179,10 @@ int l2a_router_decide(const l2a_params* p, int32_t C, const void* x, const float
  *   A_opt       out optional [B,T,Hq,D]: d a alone, zero where d = 0 (needed by l2a_attn_bwd)
  *
  * With bf16, D = 128, both branches, routing lists in use and shared inputs (each *_glb pointer equal to its
- * *_loc partner), a routed row's window is computed once for both branches: its workgroup walks the
- * window, which gives s, and then the keys before it, which gives a; one launch, whatever the order flags.
- * A layer of separate modules, or one without kblk_first_row, runs its branches apart.  While they are short (at most
+ * *_loc partner), a routed row's window need not be computed twice.  While W >= T - 1 (s = a for routed rows) every row
+ * is computed once; in long sequences a routed row's workgroup walks the window, which gives s, and then the keys
+ * before it, which gives a.  Either is one launch, whatever the order flags.
+ * Otherwise (and without kblk_first_row) the branches run apart.  While they are short (at most
  * 2048 tiles of 256 rows over all (b, KV head)) the Global rows' tiles alone would occupy a fraction of the chip, so
  * the two branches run in one launch, the Global one leaves a in fp32 in the workspace, and a
  * second, small kernel forms o = s + d a -- bit for bit the result of the sequential order, where
