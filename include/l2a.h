@@ -92,13 +92,16 @@ const char* l2a_strerror(int code);
  *             each branch's V (shared inputs: in place of the second, the list of the rows that are not
  *             routed) and one int32 flag per tile of 256 rows (tiles per (b, KV head) rounded up to a
  *             multiple of 8; 1 for a tile whose softmax needed a running maximum); when both branches run in one launch (see
- *             l2a_attn_fwd) the flags twice and a [B,T,Hq,D] float buffer for a; else nothing
+ *             l2a_attn_fwd) the flags twice and a [B,T,Hq,D] float buffer for a; L2A_FP32, both branches with
+ *             routing lists, T > 256: optional room (at most 8 [B,T,Hq,D] float buffers and statistics) for the partial sums that
+ *             layers with shared inputs use; without it the branches run one after the other; else nothing
  *   backward  delta_t of each branch, [B,Hq,T] float, twice; on the matrix-core path also, per
  *             branch, compact row-major copies of the rows' Q and dO (ceil64(T G) rows per
  *             (b, KV head)) with three per-row statistics (shared inputs: before those, the two passes'
  *             parts of dq in float); short sequences (fewer than 1024
  *             blocks of 128 keys over all (b, KV head)): up to 8 x 2 float copies of [B,T,Hkv,D],
- *             partial sums of the workgroups that share a key block's rows
+ *             partial sums of the workgroups that share a key block's rows; L2A_FP32, both branches with
+ *             routing lists, T > 256: room as for the forward, of which only the two deltas are required
  */
 size_t l2a_route_workspace_bytes(const l2a_params* p);
 size_t l2a_attn_workspace_bytes(const l2a_params* p, int backward);

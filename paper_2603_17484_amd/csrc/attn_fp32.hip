@@ -26,12 +26,16 @@
 // wavefronts share the *other* axis, each with a partial result of its own, and these meet in LDS at the end:
 // with 16-row tiles a sequence of a few thousand tokens gives a few hundred workgroups, and a serial walk of a
 // whole prefix by one wavefront would set the kernel's time.
-// Measured (T = 4096, Hq = 8, Hkv = 2, D = 128, W = 1024, 20 % routed): forward Local / Global 183 / 100 us, dQ
-// 234 / 129, dK/dV 540 (82 TFLOP/s); the scalar kernels these replace took 9.2 ms per forward branch, 8.8 ms
-// per dQ and 14.7 ms for dK/dV.
+// Layers whose branches share q, k, v compute a routed row's window once for both (row_stats explains the backward's
+// rows), and the keys before it in parts (Parts) in the Local rows' launch: the few routed tiles of a short sequence walked their
+// prefixes alone on a tenth of the chip.  Training step, us, the branches one after the other / this: T = 2048, 1 head, D = 64, W = 256,
+// 20 % routed 109.6 / 70.0 (forward 8.5 + 29 -> 15 + 6, dQ 9.5 + 35 -> 16 + 4); T = 3000, 1 head, D = 128, W = 1024, 5 % 290 / 155; T = 4096,
+// Hq = 8, Hkv = 2, D = 128, W = 1024, 20 % 1135 / 990 (forward 307 -> 252 + 7, dQ 388 -> 318 + 6, dK/dV 523 -> 467).
+// Errors against 64 bits there, dK / dV: 7.6e-7 / 7.3e-7 -> 5.9e-7 / 5.2e-7 of the norm, because rows are walked downwards.
 #include "attn_simple.hpp"
 
 
+#include <algorithm>
 #include <type_traits>
 
 namespace l2a {
@@ -195,18 +199,45 @@ struct TileRange {
     int pmin, pmax;   // positions of the tile's first and last row
     int key0, nblk;   // first key (a multiple of 16) and number of 16-key blocks any of the rows can see
 };
+// part z of nz of the blocks: key0 and nblk are that part's
 template <int RB>
-__device__ __forceinline__ TileRange tile_range(const Geom& gm, const RowSet& rs, int bh, int tile, int n_rows) {
+__device__ __forceinline__ TileRange tile_range(const Geom& gm, const RowSet& rs, int bh, int tile, int n_rows, int z, int nz) {
     TileRange t;
     t.r0 = tile * 16 * RB;
     t.n_rows = n_rows;
-    t.pmin = __builtin_amdgcn_readfirstlane(row_code(rs, gm, bh, t.r0) / gm.G);
-    t.pmax = __builtin_amdgcn_readfirstlane(row_code(rs, gm, bh, min(t.r0 + 16 * RB, n_rows) - 1) / gm.G);
-    t.key0 = (rs.local ? max(t.pmin - gm.W, 0) : 0) & ~15;
-    t.nblk = max(t.pmax - t.key0, 0) / 16 + 1;
+    t.pmin = __builtin_amdgcn_readfirstlane(row_code(rs, gm, bh, t.r0) / gm.G) - rs.shift;  // the last keys its rows see
+    t.pmax = __builtin_amdgcn_readfirstlane(row_code(rs, gm, bh, min(t.r0 + 16 * RB, n_rows) - 1) / gm.G) - rs.shift;
+    const int first = (rs.local ? max(t.pmin - gm.W, 0) : 0) & ~15, all = t.pmax < 0 ? 0 : max(t.pmax - first, 0) / 16 + 1;
+    const int b0 = all * z / nz;
+    t.key0 = first + 16 * b0;
+    t.nblk = all * (z + 1) / nz - b0;
     return t;
 }
-// which of the keys k0 + 4 k + r (r = bit) the row at position pos sees
+// Keys before the window, for rows whose branches share their inputs: a tile's blocks are shared between nz workgroups, and
+// what each finds goes to its rows' places in x ([bh][z][row of the list][D]) and s ([bh][z][row][2]), which are added up
+// (combine kernels) together with the window's part.
+struct Parts {
+    float *x, *s;
+    int nz;
+    int groups;     // the first `groups` workgroups of the grid take these tiles (nz each), the others the tiles of the main set
+    float* main_s;  // forward: reference and row sum of the main set's rows, [bh][row][2]
+};
+// Which tile a workgroup starts with, how far the next one is, and which part it takes
+struct Role {
+    bool far;
+    int it, step, z, nz;
+};
+template <bool SHARED>  // false: a launch of one set's tiles
+__device__ __forceinline__ Role role_of(const Parts& p) {
+    const int x = blockIdx.x;
+    if (!SHARED) return Role{false, x, (int)gridDim.x, 0, 1};
+    if (x < p.groups) return Role{true, x / p.nz, p.groups / p.nz, x % p.nz, p.nz};
+    return Role{false, x - p.groups, (int)gridDim.x - p.groups, 0, 1};
+}
+__device__ __forceinline__ size_t part_row(const Geom& gm, const Role& ro, int bh, int r) {
+    return ((size_t)bh * ro.nz + ro.z) * gm.T * gm.G + r;
+}
+// which of the keys k0 + 4 k + r (r = bit) the row whose last key is pos sees
 __device__ __forceinline__ unsigned keys_seen(const Geom& gm, const RowSet& rs, int first_key, int pos) {
     unsigned ok = 0;
 #pragma unroll
@@ -216,14 +247,30 @@ __device__ __forceinline__ unsigned keys_seen(const Geom& gm, const RowSet& rs, 
 }
 __device__ __forceinline__ float exp2_(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// The backward's weights exp(scale s - L) as exp2(c2 s - hi) f: hi = L log2(e) rounded, f what the rounding left out.  One
+// instruction and one rounding less than (scale s - L) log2(e).  (dK and dV, whose error is that of their long sums, keep
+// the latter: there the row's factor would be one more product, 2.5 % of the kernel.)
+struct RowScale {
+    float hi, f;
+};
+__device__ __forceinline__ RowScale row_scale(float L) {
+    constexpr float kLog2eLo = 1.925963033500e-8f;  // log2(e) - kLog2e
+    RowScale r;
+    r.hi = L * kLog2e;
+    const float lo = fmaf(L, kLog2e, -r.hi) + L * kLog2eLo;
+    r.f = 1.f - lo * kLn2;  // |lo| < 2^-24 |hi|
+    if (!(fabsf(lo) < 1.f)) r.f = 1.f;  // infinite or NaN: hi says it
+    return r;
+}
+
 // ---------------------------------------------------------------------------------------
 // Forward.  Workgroup = 16 RB rows, wavefront w takes the 16-key blocks w, w + NW, ... of the rows' keys with
 // a streaming softmax of its own (Alg. 1, running maximum per row); the partials are merged in LDS.
 // ---------------------------------------------------------------------------------------
-template <int D, int RB, int NW>
-__global__ __launch_bounds__(64 * NW, 2) void fp32_fwd_kernel(Geom gm, RowSet rs, const float* __restrict__ q,
+template <int D, int RB, int NW, bool SHARED>
+__global__ __launch_bounds__(64 * NW, 2) void fp32_fwd_kernel(Geom gm, RowSet rs_main, RowSet rs_far, const float* __restrict__ q,
                                                               const float* __restrict__ k, const float* __restrict__ v,
-                                                              FwdOut out) {
+                                                              FwdOut out, Parts parts) {
     constexpr int R = 16 * RB;
     // first the Q rows and the wavefronts' K tiles, then the partial results
     constexpr int kFirst = R + 16 * NW, kRows = kFirst > R * NW ? kFirst : R * NW;
@@ -234,6 +281,8 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_fwd_kernel(Geom gm, RowSet rs
     const int bh = blockIdx.y, b = bh / gm.Hkv, hk = bh - b * gm.Hkv;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 15, kq = lane >> 4;
+    const Role ro = role_of<SHARED>(parts);
+    const RowSet rs = ro.far ? rs_far : rs_main;
     const int n_rows = num_rows(rs, gm, bh), n_tiles = (n_rows + R - 1) / R;
     const size_t kv_row = (size_t)gm.Hkv * D;
     const size_t kv0 = ((size_t)b * gm.T * gm.Hkv + hk) * D;
@@ -243,8 +292,8 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_fwd_kernel(Geom gm, RowSet rs
     keys.init(gm.T, kv_row * sizeof(float), n, kq);
     const float c2 = gm.scale_log2;
 
-    for (int it = blockIdx.x; it < n_tiles; it += gridDim.x) {  // longest prefixes first
-        const TileRange tr = tile_range<RB>(gm, rs, bh, n_tiles - 1 - it, n_rows);
+    for (int it = ro.it; it < n_tiles; it += ro.step) {  // longest prefixes first
+        const TileRange tr = tile_range<RB>(gm, rs, bh, n_tiles - 1 - it, n_rows, ro.z, ro.nz);
         auto q_row = [&](int r) {  // rows past the end repeat the last one
             const int code = row_code(rs, gm, bh, min(tr.r0 + r, n_rows - 1)), p = code / gm.G;
             return q + (((size_t)b * gm.T + p) * gm.Hq + hk * gm.G + (code - p * gm.G)) * D;
@@ -255,14 +304,14 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_fwd_kernel(Geom gm, RowSet rs
         float m[RB], l[RB];
 #pragma unroll
         for (int c = 0; c < RB; ++c) {
-            pos[c] = row_code(rs, gm, bh, min(tr.r0 + 16 * c + n, n_rows - 1)) / gm.G;
+            pos[c] = row_code(rs, gm, bh, min(tr.r0 + 16 * c + n, n_rows - 1)) / gm.G - rs.shift;
             o[c].zero();
             m[c] = -INFINITY;
             l[c] = 0.f;
         }
         float(*const sk)[D + 4] = lds + R + 16 * wave;
         ColOperand<D> kc;
-        const int k_last = tr.key0 + 16 * (tr.nblk - 1);  // past the last block it is loaded again, for nobody
+        const int k_last = tr.key0 + 16 * max(tr.nblk - 1, 0);  // past the last block it is loaded again, for nobody
         keys.load(kc, kbase, min(tr.key0 + 16 * wave, k_last));
         __syncthreads();
         for (int blk = wave; blk < tr.nblk; blk += NW) {
@@ -313,7 +362,18 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_fwd_kernel(Geom gm, RowSet rs
 #pragma unroll
         for (int c = 0; c < RB; ++c) chk = fmaf(l[c], 0.f, chk + o[c].check());
         if (__syncthreads_or(chk != 0.f)) {
-            if (threadIdx.x < 4 * R) simple_fwd_row<float, D / 4>(gm, rs, q, k, v, out, bh, tr.r0 + (threadIdx.x >> 2), threadIdx.x & 3);
+            const int r = tr.r0 + (int)(threadIdx.x >> 2), part = threadIdx.x & 3;
+            if (threadIdx.x < 4 * R && !ro.far) {
+                simple_fwd_row<float, D / 4>(gm, rs, q, k, v, out, bh, r, part, parts.main_s);
+            } else if (threadIdx.x < 4 * R && r < n_rows) {
+                const Row row = get_row(rs, gm, bh, r);
+                float m_, l_, acc[D / 4];
+                simple_fwd_keys<float, D / 4>(gm, q, k, v, b, hk, (((size_t)b * gm.T + row.pos) * gm.Hq + hk * gm.G + row.g) * D + part * (D / 4),
+                                              part, tr.key0, min(tr.key0 + 16 * tr.nblk - 1, row.pos - rs.shift), m_, l_, acc);
+                const size_t at = part_row(gm, ro, bh, r);
+                for (int i = 0; i < D / 4; ++i) parts.x[at * D + part * (D / 4) + i] = acc[i];
+                if (part == 0) parts.s[2 * at] = m_ / gm.scale, parts.s[2 * at + 1] = l_;
+            }
             continue;
         }
 #pragma unroll
@@ -340,6 +400,12 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_fwd_kernel(Geom gm, RowSet rs
                 lt += f * sl[w][row];
                 x += f * ld4(&so[w][row][ch]);
             }
+            if (ro.far) {
+                const size_t at = part_row(gm, ro, bh, tr.r0 + row);
+                *reinterpret_cast<f32x4*>(parts.x + at * D + ch) = x;
+                if (ch == 0) parts.s[2 * at] = mm, parts.s[2 * at + 1] = lt;
+                continue;
+            }
             const int code = row_code(rs, gm, bh, tr.r0 + row), p = code / gm.G, h = hk * gm.G + (code - p * gm.G);
             const size_t off = (((size_t)b * gm.T + p) * gm.Hq + h) * D + ch;
             x *= 1.f / lt;
@@ -350,6 +416,10 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_fwd_kernel(Geom gm, RowSet rs
             if (ch == 0) {
                 const size_t st = ((size_t)b * gm.Hq + h) * gm.T + p;
                 out.lse_out[st] = fmaf(mm, gm.scale, logf(lt));
+                if (SHARED && parts.main_s) {
+                    float* ms = parts.main_s + 2 * ((size_t)bh * gm.T * gm.G + tr.r0 + row);
+                    ms[0] = mm, ms[1] = lt;
+                }
                 if (out.lse_fill) out.lse_fill[st] = -INFINITY;
             }
         }
@@ -357,16 +427,52 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_fwd_kernel(Geom gm, RowSet rs
     }
 }
 
+// a of the routed rows: the window's sums (S lies in O, its reference and row sum in main_s) and those of the parts before
+// it; o = s + a.  D / 4 lanes per row.
+template <int D>
+__global__ __launch_bounds__(256) void fp32_fwd_combine_kernel(Geom gm, RowSet rs, Parts parts, FwdOut out) {
+    const int bh = blockIdx.y, b = bh / gm.Hkv, hk = bh - b * gm.Hkv;
+    const int n_rows = num_rows(rs, gm, bh), ch = (threadIdx.x % (D / 4)) * 4;
+    for (int r = blockIdx.x * (1024 / D) + threadIdx.x / (D / 4); r < n_rows; r += gridDim.x * (1024 / D)) {
+        const int code = row_code(rs, gm, bh, r), p = code / gm.G, h = hk * gm.G + (code - p * gm.G);
+        const size_t off = (((size_t)b * gm.T + p) * gm.Hq + h) * D + ch;
+        const float* ms = parts.main_s + 2 * ((size_t)bh * gm.T * gm.G + code);
+        const f32x4 sx = ld4((const float*)out.main_out + off);
+        float top = ms[0], sum = ms[1];
+        f32x4 x = sx * sum;
+        const int nz = p >= rs.shift ? parts.nz : 0;
+        for (int z = 0; z < nz; ++z) {
+            const size_t at = ((size_t)bh * parts.nz + z) * gm.T * gm.G + r;
+            const float m = parts.s[2 * at], l = parts.s[2 * at + 1];
+            const f32x4 px = ld4(parts.x + at * D + ch);
+            if (!(l > 0.f || l != l)) continue;  // no key in reach there
+            const float up = fmaxf(top, m), f0 = exp2_((top - up) * gm.scale_log2), f1 = exp2_((m - up) * gm.scale_log2);
+            x = x * f0 + px * f1;
+            sum = sum * f0 + l * f1;
+            top = up;
+        }
+        x *= 1.f / sum;
+        if (nz == 0) x = sx;
+        if (out.copy_out) *reinterpret_cast<f32x4*>((float*)out.copy_out + off) = x;
+        *reinterpret_cast<f32x4*>((float*)out.main_out + off) = sx + x;
+        if (ch == 0) out.lse_out[((size_t)b * gm.Hq + h) * gm.T + p] = fmaf(top, gm.scale, logf(sum));
+    }
+}
+
 // ---------------------------------------------------------------------------------------
 // dQ.  Tiles and key split as in the forward; the exact delta = sum_j p dp replaces the one from the saved output.
 // ---------------------------------------------------------------------------------------
-template <int D, int RB, int NW>
-__global__ __launch_bounds__(64 * NW, 2) void fp32_bwd_dq_kernel(Geom gm, RowSet rs, const float* __restrict__ q,
+template <int D, int RB, int NW, bool SHARED>
+__global__ __launch_bounds__(64 * NW, 2) void fp32_bwd_dq_kernel(Geom gm, RowSet rs_main, RowSet rs_far,
+                                                                 const float* __restrict__ q,
                                                                  const float* __restrict__ k,
                                                                  const float* __restrict__ v,
                                                                  const float* __restrict__ dO,
-                                                                 const float* __restrict__ lse, float* delta, float* dq,
-                                                                 int accumulate) {
+                                                                 const float* __restrict__ lse_main,
+                                                                 const float* __restrict__ lse_far, float* delta_main,
+                                                                 const float* __restrict__ delta_far,
+                                                                 const float* __restrict__ share, float* dq, int accumulate,
+                                                                 Parts parts) {
     constexpr int R = 16 * RB;
     // first the Q and dO rows and the wavefronts' K, V tiles, then the partial results
     constexpr int kFirst = 2 * R + 16 * NW, kRows = kFirst > R * NW ? kFirst : R * NW;
@@ -378,6 +484,9 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_bwd_dq_kernel(Geom gm, RowSet
     const int bh = blockIdx.y, b = bh / gm.Hkv, hk = bh - b * gm.Hkv;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 15, kq = lane >> 4;
+    const Role ro = role_of<SHARED>(parts);
+    const RowSet rs = ro.far ? rs_far : rs_main;
+    const float *lse = ro.far ? lse_far : lse_main, *delta = ro.far ? delta_far : delta_main;
     const int n_rows = num_rows(rs, gm, bh), n_tiles = (n_rows + R - 1) / R;
     const size_t kv_row = (size_t)gm.Hkv * D;
     const size_t kv0 = ((size_t)b * gm.T * gm.Hkv + hk) * D;
@@ -386,8 +495,8 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_bwd_dq_kernel(Geom gm, RowSet
     KeyRows keys;
     keys.init(gm.T, kv_row * sizeof(float), n, kq);
 
-    for (int it = blockIdx.x; it < n_tiles; it += gridDim.x) {
-        const TileRange tr = tile_range<RB>(gm, rs, bh, n_tiles - 1 - it, n_rows);
+    for (int it = ro.it; it < n_tiles; it += ro.step) {
+        const TileRange tr = tile_range<RB>(gm, rs, bh, n_tiles - 1 - it, n_rows, ro.z, ro.nz);
         auto row_at = [&](const float* base) {
             return [&, base](int r) {
                 const int code = row_code(rs, gm, bh, min(tr.r0 + r, n_rows - 1)), p = code / gm.G;
@@ -404,14 +513,15 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_bwd_dq_kernel(Geom gm, RowSet
             const int code = row_code(rs, gm, bh, min(tr.r0 + 16 * c + n, n_rows - 1));
             pos[c] = code / gm.G;
             const size_t st = ((size_t)b * gm.Hq + hk * gm.G + (code - pos[c] * gm.G)) * gm.T + pos[c];
-            L[c] = lse[st];
+            L[c] = -row_scale(lse[st]).hi;
             dl[c] = delta[st];
+            pos[c] -= rs.shift;
             dx[c] = 0.f;
             acc[c].zero();
         }
         float(*const st)[D + 4] = lds + 2 * R + 16 * wave;
         ColOperand<D> kn, vn;  // the next block's
-        const int k_last = tr.key0 + 16 * (tr.nblk - 1);
+        const int k_last = tr.key0 + 16 * max(tr.nblk - 1, 0);
         keys.load(kn, kbase, min(tr.key0 + 16 * wave, k_last));
         keys.load(vn, vbase, min(tr.key0 + 16 * wave, k_last));
         __syncthreads();
@@ -438,7 +548,7 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_bwd_dq_kernel(Geom gm, RowSet
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         const bool in = !MASK || ((ok >> r) & 1u);
-                        const float p = exp2_(fmaf(s[c][r], gm.scale, -L[c]) * kLog2e);
+                        const float p = exp2_(fmaf(s[c][r], gm.scale_log2, L[c]));  // times the row's f: in the epilogue
                         dx[c] += in ? p * dp[c][r] : 0.f;
                         s[c][r] = in ? p * (dp[c][r] - dl[c]) : 0.f;  // dS
                     }
@@ -453,8 +563,20 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_bwd_dq_kernel(Geom gm, RowSet
 #pragma unroll
         for (int c = 0; c < RB; ++c) chk += acc[c].check();
         if (__syncthreads_or(chk != 0.f)) {
-            if (threadIdx.x < 4 * R)
-                simple_dq_row<float, D / 4>(gm, rs, q, k, v, dO, lse, delta, dq, accumulate, bh, tr.r0 + (threadIdx.x >> 2), threadIdx.x & 3);
+            const int r = tr.r0 + (int)(threadIdx.x >> 2), part = threadIdx.x & 3;
+            if (threadIdx.x < 4 * R && !ro.far) {
+                simple_dq_row<float, D / 4>(gm, rs, q, k, v, dO, lse, delta_main, dq, accumulate, bh, r, part, share);
+            } else if (threadIdx.x < 4 * R && r < n_rows) {
+                const Row row = get_row(rs, gm, bh, r);
+                const int h = hk * gm.G + row.g;
+                const size_t so = ((size_t)b * gm.Hq + h) * gm.T + row.pos;
+                float dx_, acc_[D / 4];
+                simple_dq_keys<float, D / 4>(gm, q, k, v, dO, b, hk, (((size_t)b * gm.T + row.pos) * gm.Hq + h) * D + part * (D / 4), part,
+                                             tr.key0, min(tr.key0 + 16 * tr.nblk - 1, row.pos - rs.shift), lse[so], delta[so], dx_, acc_);
+                const size_t at = part_row(gm, ro, bh, r);
+                for (int i = 0; i < D / 4; ++i) parts.x[at * D + part * (D / 4) + i] = acc_[i];
+                if (part == 0) parts.s[at] = dx_;
+            }
             continue;
         }
 #pragma unroll
@@ -471,24 +593,64 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_bwd_dq_kernel(Geom gm, RowSet
 #pragma unroll
             for (int w = 0; w < NW; ++w) x += ld4(&so[w][row][ch]);
             const int code = row_code(rs, gm, bh, tr.r0 + row), p = code / gm.G, h = hk * gm.G + (code - p * gm.G);
+            const float f = row_scale(lse[((size_t)b * gm.Hq + h) * gm.T + p]).f;
+            x *= f;
+            if (ro.far) {
+                const size_t at = part_row(gm, ro, bh, tr.r0 + row);
+                *reinterpret_cast<f32x4*>(parts.x + at * D + ch) = x;
+                if (ch == 0) {
+                    float d = 0.f;
+#pragma unroll
+                    for (int w = 0; w < NW; ++w) d += sd[w][row];
+                    parts.s[at] = d * f;
+                }
+                continue;
+            }
             float* dst = dq + (((size_t)b * gm.T + p) * gm.Hq + h) * D + ch;
-            x *= gm.scale;
+            x *= SHARED && share ? gm.scale * (1.f + share[((size_t)b * gm.Hq + h) * gm.T + p]) : gm.scale;
             *reinterpret_cast<f32x4*>(dst) = accumulate ? ld4(dst) + x : x;
             if (ch == 0) {
                 float d = 0.f;
 #pragma unroll
                 for (int w = 0; w < NW; ++w) d += sd[w][row];
-                delta[((size_t)b * gm.Hq + h) * gm.T + p] = d;
+                delta_main[((size_t)b * gm.Hq + h) * gm.T + p] = d * f;
             }
         }
         __syncthreads();
     }
 }
 
+// dQ of the routed rows: the parts before the window are added; their exact deltas, and the delta of the row that
+// both branches' rows make in the window (row_stats), which the dK/dV kernel takes.
+template <int D>
+__global__ __launch_bounds__(256) void fp32_dq_combine_kernel(Geom gm, RowSet rs, Parts parts, const float* __restrict__ share,
+                                                              float* delta_l, float* delta_g, float* dq) {
+    const int bh = blockIdx.y, b = bh / gm.Hkv, hk = bh - b * gm.Hkv;
+    const int n_rows = num_rows(rs, gm, bh), ch = (threadIdx.x % (D / 4)) * 4;
+    for (int r = blockIdx.x * (1024 / D) + threadIdx.x / (D / 4); r < n_rows; r += gridDim.x * (1024 / D)) {
+        const int code = row_code(rs, gm, bh, r), p = code / gm.G, h = hk * gm.G + (code - p * gm.G);
+        const size_t off = (((size_t)b * gm.T + p) * gm.Hq + h) * D + ch, so = ((size_t)b * gm.Hq + h) * gm.T + p;
+        f32x4 x = {0.f, 0.f, 0.f, 0.f};
+        float d = 0.f;
+        const int nz = p >= rs.shift ? parts.nz : 0;
+        for (int z = 0; z < nz; ++z) {
+            const size_t at = ((size_t)bh * parts.nz + z) * gm.T * gm.G + r;
+            x += ld4(parts.x + at * D + ch);
+            d += parts.s[at];
+        }
+        if (nz) *reinterpret_cast<f32x4*>(dq + off) = ld4(dq + off) + x * gm.scale;
+        if (ch == 0) {
+            const float a = share[so], dl = delta_l[so], dg = a * dl + d;
+            delta_g[so] = dg;
+            delta_l[so] = (dl + a * dg) / (1.f + a);
+        }
+    }
+}
+
 // ---------------------------------------------------------------------------------------
 // dK, dV.  Workgroup = 16 keys, wavefront w takes the 16-row tiles w, w + NW, ... of the rows that can see them.
 // ---------------------------------------------------------------------------------------
-template <int D, int NW>
+template <int D, int NW, bool SHARE>
 __global__ __launch_bounds__(64 * NW, 2) void fp32_bwd_dkdv_kernel(Geom gm, DkdvSets sets, const float* __restrict__ q,
                                                                    const float* __restrict__ k,
                                                                    const float* __restrict__ v,
@@ -499,8 +661,11 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_bwd_dkdv_kernel(Geom gm, Dkdv
     float(*const sk)[D + 4] = lds;
     float(*const sv)[D + 4] = lds + 16;
     float(*const so)[2][16][D + 4] = reinterpret_cast<float(*)[2][16][D + 4]>(lds);
-    // of a wavefront's row tile: position (-1: no row), row index within the batch, log-sum-exp, delta
+    // of a wavefront's row tile: last key its row sees (-1: no row), row index within the batch, log-sum-exp, delta
     __shared__ __attribute__((aligned(16))) uint32_t row_data[NW][4][16];
+    // log2 of what the row's weights count (1 + share); of this tile and the next: read where it is used, which costs
+    // the matrix loop no registers
+    __shared__ __attribute__((aligned(16))) float row_weight[NW][2][16];
     __shared__ uint32_t redo[kMaxPerGroup / 32];  // tiles of this workgroup to be computed again
     const int bh = blockIdx.y, b = bh / gm.Hkv, hk = bh - b * gm.Hkv;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -521,38 +686,44 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_bwd_dkdv_kernel(Geom gm, Dkdv
         Acc<D> ak, av;
         ak.zero();
         av.zero();
-        for (int s_i = 0; s_i < sets.n; ++s_i) {
+        // The rows that weigh most for a key are the first ones that see it, and an early large sum is what later small terms are
+        // rounded against: so the last rows come first, and the keys-before-the-window rows before the Local ones.
+        for (int s_i = sets.n - 1; s_i >= 0; --s_i) {
             const RowSet rs = sets.rs[s_i];
             const float* lse = sets.lse[s_i];
             const float* delta = sets.delta[s_i];
+            const float* share = sets.share[s_i];
             int r0, r1;  // candidate rows [r0, r1)
             if (rs.local) {
                 r0 = k0 * gm.G;
                 r1 = (int)min((long long)k0 + 15 + gm.W, (long long)gm.T - 1) * gm.G + gm.G;
             } else {
-                r0 = rs.kblk_first_row ? max(rs.kblk_first_row[(size_t)bh * (nkb + 1) + (k0 >> 6)], 0) : k0 * gm.G;
+                r0 = rs.kblk_first_row ? max(rs.kblk_first_row[(size_t)bh * (nkb + 1) + min((k0 + rs.shift) >> 6, nkb)], 0) : k0 * gm.G;
                 r1 = num_rows(rs, gm, bh);
             }
-            int rt = r0 + 16 * wave;
-            if (rt >= r1) continue;
+            const int rt0 = r0 + 16 * wave;
+            if (rt0 >= r1) continue;
+            int rt = rt0 + (r1 - 1 - rt0) / (16 * NW) * (16 * NW);
             // Of the next tile: position (-1: no row), row index within the batch and statistics of lane n's row,
             // passed through LDS to the lanes whose weights and operands are rows 4 kq + r (one wavefront, in order);
             // then those rows of dO and Q.
             typedef int i32x4 __attribute__((ext_vector_type(4)));
             i32x4 pr;
             f32x4 Lr, dr;
+            int par = 0;
             ColOperand<D> gn, qn;
             int pos, idx;
-            float L, dl;
+            float L, dl, wt;
             auto fetch_row = [&](int t) __attribute__((always_inline)) {
-                const int code = row_code(rs, gm, bh, min(t + n, r1 - 1));
+                const int code = row_code(rs, gm, bh, max(min(t + n, r1 - 1), r0));
                 pos = code / gm.G;
                 const int h = hk * gm.G + (code - pos * gm.G);
                 idx = pos * gm.Hq + h;
                 const size_t so_ = ((size_t)b * gm.Hq + h) * gm.T + pos;
                 L = lse[so_];
                 dl = delta[so_];
-                if (t + n >= r1) pos = -1;
+                if (SHARE) wt = share ? __builtin_amdgcn_logf(1.f + share[so_]) : 0.f;
+                pos = t + n >= r1 ? -1 : pos - rs.shift;  // the last key the row sees
             };
             i32x4 pn;
             f32x4 Ln, dn;
@@ -562,6 +733,7 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_bwd_dkdv_kernel(Geom gm, Dkdv
                 const uint32_t a = kq & 1 ? (uint32_t)idx : (uint32_t)pos;
                 const uint32_t c = kq & 1 ? __builtin_bit_cast(uint32_t, dl) : __builtin_bit_cast(uint32_t, L);
                 row_data[wave][kq][n] = kq & 2 ? c : a;
+                if (SHARE) row_weight[wave][par][n] = wt;
                 asm volatile("" ::: "memory");
                 __builtin_amdgcn_wave_barrier();
                 pn = *reinterpret_cast<const i32x4*>(&row_data[wave][0][4 * kq]);
@@ -581,8 +753,8 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_bwd_dkdv_kernel(Geom gm, Dkdv
             };
             fetch_row(rt);
             fetch_tile();
-            fetch_row(rt + 16 * NW);
-            for (; rt < r1; rt += 16 * NW) {
+            fetch_row(rt - 16 * NW);
+            for (; rt >= rt0; rt -= 16 * NW) {
                 const ColOperand<D> gc = gn, qc = qn;
                 pr = pn, Lr = Ln, dr = dn;
                 f32x4 s[1], dp[1];
@@ -590,11 +762,14 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_bwd_dkdv_kernel(Geom gm, Dkdv
                 dot_tile<D, 1>(st, sv, n, kq, dp);
                 __builtin_amdgcn_sched_barrier(0);
                 put_tile<D>(st, qc, n, kq);
-                fetch_tile();  // (past the end the last row is fetched again, for nobody)
-                fetch_row(rt + 32 * NW);
+                par ^= 1;
+                fetch_tile();  // (past the first tile rows are fetched again, for nobody)
+                fetch_row(rt - 32 * NW);
                 __builtin_amdgcn_sched_barrier(0);
                 dot_tile<D, 1>(st, sk, n, kq, s);
                 __builtin_amdgcn_sched_barrier(0);
+                f32x4 wr;
+                if (SHARE) wr = ld4(&row_weight[wave][par ^ 1][4 * kq]);
                 unsigned ok = 0;
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
@@ -603,7 +778,8 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_bwd_dkdv_kernel(Geom gm, Dkdv
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const bool in = (ok >> r) & 1u;
-                    const float x = exp2_(fmaf(s[0][r], gm.scale, -Lr[r]) * kLog2e);
+                    const float x = exp2_(SHARE ? fmaf(fmaf(s[0][r], gm.scale, -Lr[r]), kLog2e, wr[r])
+                                                : fmaf(s[0][r], gm.scale, -Lr[r]) * kLog2e);
                     p[r] = in ? x : 0.f;
                     s[0][r] = in ? x * (dp[0][r] - dr[r]) : 0.f;  // dS
                 }
@@ -656,62 +832,149 @@ bool wide_tiles(const Geom& g, const RowSet& rs) {
     return (rs.row_idx ? tiles / 4 : tiles) >= 1024;
 }
 
-template <int D, int RB, int NW>
-void launch_fwd(const Geom& g, const RowSet& rs, const void* q, const void* k, const void* v, const FwdOut& out,
-                hipStream_t st) {
-    const long long tiles = ((long long)g.T * g.G + 16 * RB - 1) / (16 * RB);
-    hipLaunchKernelGGL((fp32_fwd_kernel<D, RB, NW>), tile_grid(tiles, g), dim3(64 * NW), 0, st, g, rs, cf(q), cf(k), cf(v), out);
+// Workgroups that share a routed tile's keys before the window (none if no row has such keys): until there are two workgroups
+// per CU if a quarter of all rows is routed, and until none takes more than about 1024 keys, so that they end with the Local
+// rows' (fewer where their partial sums would be many times the tensors); at least 256 keys each.
+int far_parts(const Geom& g) {
+    const long long tiles = std::max(1LL, (long long)g.T * g.G / 64 * g.B * g.Hkv), keys = (long long)g.T - g.W - 1;
+    if (keys <= 0) return 0;
+    const long long want = std::max((512 + tiles - 1) / tiles, std::min((keys + 512) / 1024, std::max(1LL, 8192 / tiles)));
+    return (int)std::min(std::min(want, 8LL), std::max(1LL, keys / 256));
 }
+size_t round256(size_t n) { return (n + 255) / 256 * 256; }
+size_t all_rows(const Geom& g) { return (size_t)g.B * g.Hkv * g.T * g.G; }
+Parts place_parts(const Geom& g, char* ws, int stats, bool main_s) {  // stats: floats per row and part
+    Parts p{};
+    p.nz = far_parts(g);
+    p.x = (float*)ws;
+    p.s = (float*)(ws + round256(all_rows(g) * p.nz * g.D * sizeof(float)));
+    if (main_s) p.main_s = (float*)((char*)p.s + round256(all_rows(g) * p.nz * stats * sizeof(float)));
+    return p;
+}
+size_t parts_bytes(const Geom& g, int stats, bool main_s) {
+    const int nz = far_parts(g);
+    return round256(all_rows(g) * nz * g.D * sizeof(float)) + round256(all_rows(g) * nz * stats * sizeof(float)) +
+           (main_s ? round256(all_rows(g) * 2 * sizeof(float)) : 0);
+}
+// The grid of tiles of 16 RB rows: those of the main set, behind parts.nz workgroups for each tile of the far set
+dim3 role_grid(const Geom& g, int rows, Parts& parts) {
+    const long long tiles = std::min(((long long)g.T * g.G + rows - 1) / rows, kMaxTiles / 16);
+    parts.groups = (int)tiles * parts.nz;
+    return dim3((unsigned)tiles + parts.groups, g.B * g.Hkv);
+}
+
+struct FwdCall {
+    RowSet main, far;
+    const void *q, *k, *v;
+    FwdOut out;
+    Parts parts;
+};
 template <int D, int RB, int NW>
-void launch_dq(const Geom& g, const RowSet& rs, const void* q, const void* k, const void* v, const void* dO,
-               const float* lse, float* delta, void* dq, int accumulate, hipStream_t st) {
-    const long long tiles = ((long long)g.T * g.G + 16 * RB - 1) / (16 * RB);
-    hipLaunchKernelGGL((fp32_bwd_dq_kernel<D, RB, NW>), tile_grid(tiles, g), dim3(64 * NW), 0, st, g, rs, cf(q), cf(k), cf(v),
-                       cf(dO), lse, delta, (float*)dq, accumulate);
+void launch_fwd(const Geom& g, FwdCall c, hipStream_t st) {
+    const dim3 grid = role_grid(g, 16 * RB, c.parts);
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(64 * NW), 0, st, g, c.main, c.far, cf(c.q), cf(c.k), cf(c.v), c.out, c.parts); };
+    c.parts.main_s ? launch(fp32_fwd_kernel<D, RB, NW, true>) : launch(fp32_fwd_kernel<D, RB, NW, false>);
+}
+void run_fwd(const Geom& g, const FwdCall& c, bool wide, hipStream_t st) {
+    if (g.D == 64) wide ? launch_fwd<64, 2, 4>(g, c, st) : launch_fwd<64, 1, 8>(g, c, st);
+    else wide ? launch_fwd<128, 2, 4>(g, c, st) : launch_fwd<128, 1, 8>(g, c, st);
+}
+struct DqCall {
+    RowSet main, far;
+    const void *q, *k, *v, *dO;
+    const float *lse_main, *lse_far;
+    float *delta_main, *delta_far;
+    const float* share;
+    void* dq;
+    int accumulate;
+    Parts parts;
+};
+template <int D, int RB, int NW>
+void launch_dq(const Geom& g, DqCall c, hipStream_t st) {
+    const dim3 grid = role_grid(g, 16 * RB, c.parts);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(64 * NW), 0, st, g, c.main, c.far, cf(c.q), cf(c.k), cf(c.v), cf(c.dO), c.lse_main, c.lse_far,
+                           c.delta_main, c.delta_far, c.share, (float*)c.dq, c.accumulate, c.parts);
+    };
+    c.share ? launch(fp32_bwd_dq_kernel<D, RB, NW, true>) : launch(fp32_bwd_dq_kernel<D, RB, NW, false>);
+}
+void run_dq(const Geom& g, const DqCall& c, bool wide, hipStream_t st) {
+    if (g.D == 64) wide ? launch_dq<64, 2, 4>(g, c, st) : launch_dq<64, 1, 8>(g, c, st);
+    else wide ? launch_dq<128, 2, 4>(g, c, st) : launch_dq<128, 1, 8>(g, c, st);
+}
+dim3 row_grid(const Geom& g) {
+    return dim3((unsigned)std::min(((long long)g.T * g.G * g.D + 1023) / 1024, 65536LL), g.B * g.Hkv);
 }
 
 }  // namespace
 
 int fp32_fwd(const Geom& g, const RowSet& rs, const void* q, const void* k, const void* v, const FwdOut& out,
              hipStream_t st) {
+    if (g.D != 64 && g.D != 128) return L2A_ERR_UNSUPPORTED;
     KernelTimer kt(rs.local ? "fp32_fwd_local" : "fp32_fwd_global", st);
-    const bool wide = wide_tiles(g, rs);
-    if (g.D == 64) wide ? launch_fwd<64, 2, 4>(g, rs, q, k, v, out, st) : launch_fwd<64, 1, 8>(g, rs, q, k, v, out, st);
-    else if (g.D == 128) wide ? launch_fwd<128, 2, 4>(g, rs, q, k, v, out, st) : launch_fwd<128, 1, 8>(g, rs, q, k, v, out, st);
-    else return L2A_ERR_UNSUPPORTED;
+    run_fwd(g, FwdCall{rs, rs, q, k, v, out, Parts{}}, wide_tiles(g, rs), st);
+    return launch_status();
+}
+
+size_t fp32_fwd_shared_bytes(const Geom& g) { return parts_bytes(g, 2, true); }
+
+int fp32_fwd_shared(const Geom& g, const RowSet& rs_l, const RowSet& rs_g, const void* q, const void* k, const void* v,
+                    const FwdOut& out_l, const FwdOut& out_g, void* ws, hipStream_t st) {
+    if (g.D != 64 && g.D != 128) return L2A_ERR_UNSUPPORTED;
+    const Parts parts = place_parts(g, (char*)ws, 2, true);
+    {
+        KernelTimer kt("fp32_fwd_shared", st);
+        run_fwd(g, FwdCall{rs_l, rs_g, q, k, v, out_l, parts}, wide_tiles(g, rs_l), st);
+    }
+    KernelTimer kt("fp32_fwd_combine", st);
+    if (g.D == 64) hipLaunchKernelGGL(fp32_fwd_combine_kernel<64>, row_grid(g), dim3(256), 0, st, g, rs_g, parts, out_g);
+    else hipLaunchKernelGGL(fp32_fwd_combine_kernel<128>, row_grid(g), dim3(256), 0, st, g, rs_g, parts, out_g);
     return launch_status();
 }
 
 int fp32_bwd_dq(const Geom& g, const RowSet& rs, const void* q, const void* k, const void* v, const void* dO,
                 const float* lse, float* delta, void* dq, int accumulate, hipStream_t st) {
+    if (g.D != 64 && g.D != 128) return L2A_ERR_UNSUPPORTED;
     KernelTimer kt(rs.local ? "fp32_bwd_dq_local" : "fp32_bwd_dq_global", st);
-    const bool wide = wide_tiles(g, rs);
-    if (g.D == 64) wide ? launch_dq<64, 2, 4>(g, rs, q, k, v, dO, lse, delta, dq, accumulate, st)
-                        : launch_dq<64, 1, 8>(g, rs, q, k, v, dO, lse, delta, dq, accumulate, st);
-    else if (g.D == 128) wide ? launch_dq<128, 2, 4>(g, rs, q, k, v, dO, lse, delta, dq, accumulate, st)
-                              : launch_dq<128, 1, 8>(g, rs, q, k, v, dO, lse, delta, dq, accumulate, st);
-    else return L2A_ERR_UNSUPPORTED;
+    run_dq(g, DqCall{rs, rs, q, k, v, dO, lse, lse, delta, delta, nullptr, dq, accumulate, Parts{}}, wide_tiles(g, rs), st);
+    return launch_status();
+}
+
+size_t fp32_dq_shared_bytes(const Geom& g) { return parts_bytes(g, 1, false); }
+
+int fp32_bwd_dq_shared(const Geom& g, const RowSet& rs_l, const RowSet& rs_g, const void* q, const void* k, const void* v,
+                       const void* dO, const float* lse_l, const float* lse_g, float* delta_l, float* delta_g, const float* share,
+                       void* dq, void* ws, hipStream_t st) {
+    if (g.D != 64 && g.D != 128) return L2A_ERR_UNSUPPORTED;
+    const Parts parts = place_parts(g, (char*)ws, 1, false);
+    {
+        KernelTimer kt("fp32_bwd_dq_shared", st);
+        run_dq(g, DqCall{rs_l, rs_g, q, k, v, dO, lse_l, lse_g, delta_l, delta_g, share, dq, 0, parts}, wide_tiles(g, rs_l), st);
+    }
+    KernelTimer kt("fp32_dq_combine", st);
+    if (g.D == 64) hipLaunchKernelGGL(fp32_dq_combine_kernel<64>, row_grid(g), dim3(256), 0, st, g, rs_g, parts, share, delta_l, delta_g, (float*)dq);
+    else hipLaunchKernelGGL(fp32_dq_combine_kernel<128>, row_grid(g), dim3(256), 0, st, g, rs_g, parts, share, delta_l, delta_g, (float*)dq);
     return launch_status();
 }
 
 int fp32_bwd_dkdv(const Geom& g, const RowSet* sets, int nsets, const void* q, const void* k, const void* v,
-                  const void* dO, const float* const* lse, const float* const* delta, void* dk, void* dv,
-                  hipStream_t st) {
+                  const void* dO, const float* const* lse, const float* const* delta, const float* const* share, void* dk,
+                  void* dv, hipStream_t st) {
     DkdvSets s;
     s.n = nsets;
     for (int i = 0; i < nsets; ++i) {
         s.rs[i] = sets[i];
         s.lse[i] = lse[i];
         s.delta[i] = delta[i];
+        s.share[i] = share[i];
     }
     KernelTimer kt("fp32_bwd_dkdv", st);
     const dim3 grid = tile_grid(((long long)g.T + 15) / 16, g);
-    if (g.D == 64)
-        hipLaunchKernelGGL((fp32_bwd_dkdv_kernel<64, 8>), grid, dim3(512), 0, st, g, s, cf(q), cf(k), cf(v), cf(dO), (float*)dk, (float*)dv);
-    else if (g.D == 128)
-        hipLaunchKernelGGL((fp32_bwd_dkdv_kernel<128, 8>), grid, dim3(512), 0, st, g, s, cf(q), cf(k), cf(v), cf(dO), (float*)dk, (float*)dv);
-    else
-        return L2A_ERR_UNSUPPORTED;
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(512), 0, st, g, s, cf(q), cf(k), cf(v), cf(dO), (float*)dk, (float*)dv); };
+    const bool folded = s.share[0] || s.share[1];
+    if (g.D == 64) folded ? launch(fp32_bwd_dkdv_kernel<64, 8, true>) : launch(fp32_bwd_dkdv_kernel<64, 8, false>);
+    else if (g.D == 128) folded ? launch(fp32_bwd_dkdv_kernel<128, 8, true>) : launch(fp32_bwd_dkdv_kernel<128, 8, false>);
+    else return L2A_ERR_UNSUPPORTED;
     return launch_status();
 }
 

@@ -43,26 +43,19 @@ __device__ __forceinline__ Row get_row(const RowSet& rs, const Geom& gm, int bh,
     return x;
 }
 
-// Forward of row r of (b, KV head) bh, channels part * DL ..
+// Running sums of a row over the keys j0 .. j1 (inclusive; none if j1 < j0): m, l and acc as in the streaming softmax
 template <typename E, int DL>
-__device__ __forceinline__ void simple_fwd_row(const Geom& gm, const RowSet& rs, const E* __restrict__ q,
-                                               const E* __restrict__ k, const E* __restrict__ v, const FwdOut& out,
-                                               int bh, int r, int part) {
-    const int b = bh / gm.Hkv, hk = bh % gm.Hkv;
-    if (r >= num_rows(rs, gm, bh)) return;
-    const Row row = get_row(rs, gm, bh, r);
-    const int h = hk * gm.G + row.g;
-    const size_t qoff = (((size_t)b * gm.T + row.pos) * gm.Hq + h) * gm.D + part * DL;
-
-    float qr[DL], acc[DL];
+__device__ __forceinline__ void simple_fwd_keys(const Geom& gm, const E* __restrict__ q, const E* __restrict__ k,
+                                                const E* __restrict__ v, int b, int hk, size_t qoff, int part, int j0, int j1,
+                                                float& m, float& l, float (&acc)[DL]) {
+    float qr[DL];
 #pragma unroll
     for (int i = 0; i < DL; ++i) {
         qr[i] = ld(q + qoff + i);
         acc[i] = 0.f;
     }
-    float m = -INFINITY, l = 0.f;
-    const int j0 = rs.local ? (row.pos - gm.W > 0 ? row.pos - gm.W : 0) : 0;
-    for (int j = j0; j <= row.pos; ++j) {
+    m = -INFINITY, l = 0.f;
+    for (int j = j0; j <= j1; ++j) {
         const size_t koff = (((size_t)b * gm.T + j) * gm.Hkv + hk) * gm.D + part * DL;
         float s = 0.f;
 #pragma unroll
@@ -76,6 +69,21 @@ __device__ __forceinline__ void simple_fwd_row(const Geom& gm, const RowSet& rs,
         for (int i = 0; i < DL; ++i) acc[i] = acc[i] * alpha + p * ld(v + koff + i);
         m = mn;
     }
+}
+
+// Forward of row r of (b, KV head) bh, channels part * DL ..
+template <typename E, int DL>
+__device__ __forceinline__ void simple_fwd_row(const Geom& gm, const RowSet& rs, const E* __restrict__ q,
+                                               const E* __restrict__ k, const E* __restrict__ v, const FwdOut& out,
+                                               int bh, int r, int part, float* row_s = nullptr) {
+    const int b = bh / gm.Hkv, hk = bh % gm.Hkv;
+    if (r >= num_rows(rs, gm, bh)) return;
+    const Row row = get_row(rs, gm, bh, r);
+    const int h = hk * gm.G + row.g;
+    const size_t qoff = (((size_t)b * gm.T + row.pos) * gm.Hq + h) * gm.D + part * DL;
+
+    float acc[DL], m, l;
+    simple_fwd_keys<E, DL>(gm, q, k, v, b, hk, qoff, part, rs.local ? max(row.pos - gm.W, 0) : 0, row.pos, m, l, acc);
     const float inv = 1.f / l;
     E* mo = (E*)out.main_out;
     E* co = (E*)out.copy_out;
@@ -91,34 +99,28 @@ __device__ __forceinline__ void simple_fwd_row(const Geom& gm, const RowSet& rs,
     if (part == 0) {
         const size_t so = ((size_t)b * gm.Hq + h) * gm.T + row.pos;
         out.lse_out[so] = m + logf(l);
+        if (row_s) {  // reference (of the unscaled scores) and row sum, by row
+            float* rs_ = row_s + 2 * ((size_t)bh * gm.T * gm.G + r);
+            rs_[0] = m / gm.scale, rs_[1] = l;
+        }
         if (out.lse_fill) out.lse_fill[so] = -INFINITY;
     }
 }
 
-// dQ and the exact delta of that row
+// dQ (not scaled) and sum_j p_j dp_j of a row over the keys j0 .. j1
 template <typename E, int DL>
-__device__ __forceinline__ void simple_dq_row(const Geom& gm, const RowSet& rs, const E* __restrict__ q,
-                                              const E* __restrict__ k, const E* __restrict__ v,
-                                              const E* __restrict__ dO, const float* __restrict__ lse, float* delta,
-                                              E* dq, int accumulate, int bh, int r, int part) {
-    const int b = bh / gm.Hkv, hk = bh % gm.Hkv;
-    if (r >= num_rows(rs, gm, bh)) return;
-    const Row row = get_row(rs, gm, bh, r);
-    const int h = hk * gm.G + row.g;
-    const size_t qoff = (((size_t)b * gm.T + row.pos) * gm.Hq + h) * gm.D + part * DL;
-    const size_t so = ((size_t)b * gm.Hq + h) * gm.T + row.pos;
-
-    float qr[DL], gr[DL], acc[DL];
+__device__ __forceinline__ void simple_dq_keys(const Geom& gm, const E* __restrict__ q, const E* __restrict__ k,
+                                               const E* __restrict__ v, const E* __restrict__ dO, int b, int hk, size_t qoff,
+                                               int part, int j0, int j1, float L, float dl, float& dx, float (&acc)[DL]) {
+    float qr[DL], gr[DL];
 #pragma unroll
     for (int i = 0; i < DL; ++i) {
         qr[i] = ld(q + qoff + i);
         gr[i] = ld(dO + qoff + i);
         acc[i] = 0.f;
     }
-    const float L = lse[so], dl = delta[so];
-    float dl_exact = 0.f;  // sum_j p_j dp_j: the same quantity without the rounding of the saved output
-    const int j0 = rs.local ? (row.pos - gm.W > 0 ? row.pos - gm.W : 0) : 0;
-    for (int j = j0; j <= row.pos; ++j) {
+    dx = 0.f;  // the delta of the row without the rounding of the saved output
+    for (int j = j0; j <= j1; ++j) {
         const size_t koff = (((size_t)b * gm.T + j) * gm.Hkv + hk) * gm.D + part * DL;
         float s = 0.f, dp = 0.f;
 #pragma unroll
@@ -130,14 +132,33 @@ __device__ __forceinline__ void simple_dq_row(const Geom& gm, const RowSet& rs, 
         dp = quad_sum(dp);
         const float p = expf(s - L);
         const float ds = p * (dp - dl);
-        dl_exact += p * dp;
+        dx += p * dp;
 #pragma unroll
         for (int i = 0; i < DL; ++i) acc[i] += ds * ld(k + koff + i);
     }
+}
+
+// dQ and the exact delta of that row
+template <typename E, int DL>
+__device__ __forceinline__ void simple_dq_row(const Geom& gm, const RowSet& rs, const E* __restrict__ q,
+                                              const E* __restrict__ k, const E* __restrict__ v,
+                                              const E* __restrict__ dO, const float* __restrict__ lse, float* delta,
+                                              E* dq, int accumulate, int bh, int r, int part,
+                                              const float* __restrict__ share = nullptr) {
+    const int b = bh / gm.Hkv, hk = bh % gm.Hkv;
+    if (r >= num_rows(rs, gm, bh)) return;
+    const Row row = get_row(rs, gm, bh, r);
+    const int h = hk * gm.G + row.g;
+    const size_t qoff = (((size_t)b * gm.T + row.pos) * gm.Hq + h) * gm.D + part * DL;
+    const size_t so = ((size_t)b * gm.Hq + h) * gm.T + row.pos;
+
+    float acc[DL], dl_exact;
+    simple_dq_keys<E, DL>(gm, q, k, v, dO, b, hk, qoff, part, rs.local ? max(row.pos - gm.W, 0) : 0, row.pos, lse[so], delta[so],
+                          dl_exact, acc);
     if (part == 0) delta[so] = dl_exact;
 #pragma unroll
     for (int i = 0; i < DL; ++i) {
-        float x = acc[i] * gm.scale;
+        float x = acc[i] * gm.scale * (share ? 1.f + share[so] : 1.f);
         if (accumulate) x += ld(dq + qoff + i);
         st(dq + qoff + i, x);
     }
@@ -147,6 +168,7 @@ struct DkdvSets {
     RowSet rs[2];
     const float* lse[2];
     const float* delta[2];
+    const float* share[2] = {nullptr, nullptr};  // optional: the rows' weights count 1 + share times (see row_stats)
     int n;
 };
 
@@ -175,12 +197,12 @@ __device__ __forceinline__ void simple_dkdv_key(const Geom& gm, const DkdvSets& 
             r0 = j * gm.G;
             r1 = (last + 1) * gm.G;
         } else {
-            r0 = rs.kblk_first_row ? max(rs.kblk_first_row[(size_t)bh * (nkb + 1) + (j >> 6)], 0) : (j >> 6) * 64 * gm.G;
+            r0 = rs.kblk_first_row ? max(rs.kblk_first_row[(size_t)bh * (nkb + 1) + min((j + rs.shift) >> 6, nkb)], 0) : (j >> 6) * 64 * gm.G;
             r1 = num_rows(rs, gm, bh);
         }
         for (int r = r0; r < r1; ++r) {
             const Row row = get_row(rs, gm, bh, r);
-            if (row.pos < j) continue;
+            if (row.pos - rs.shift < j) continue;
             const int h = hk * gm.G + row.g;
             const size_t qoff = (((size_t)b * gm.T + row.pos) * gm.Hq + h) * gm.D + part * DL;
             const size_t so = ((size_t)b * gm.Hq + h) * gm.T + row.pos;
@@ -192,7 +214,7 @@ __device__ __forceinline__ void simple_dkdv_key(const Geom& gm, const DkdvSets& 
             }
             sc = quad_sum(sc) * gm.scale;
             dp = quad_sum(dp);
-            const float p = expf(sc - sets.lse[s][so]);
+            const float p = expf(sc - sets.lse[s][so]) * (sets.share[s] ? 1.f + sets.share[s][so] : 1.f);
             const float ds = p * (dp - sets.delta[s][so]);
 #pragma unroll
             for (int i = 0; i < DL; ++i) {

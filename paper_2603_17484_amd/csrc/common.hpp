@@ -72,10 +72,20 @@ int fp32_fwd(const Geom& g, const RowSet& rs, const void* q, const void* k, cons
              hipStream_t st);
 int fp32_bwd_dq(const Geom& g, const RowSet& rs, const void* q, const void* k, const void* v, const void* dO,
                 const float* lse, float* delta, void* dq, int accumulate, hipStream_t st);
-// dk, dv of every key token; `sets` (1 or 2 row sets: local and/or global) accumulate into the same outputs
+// dk, dv of every key token; `sets` (1 or 2 row sets: local and/or global) accumulate into the same outputs; share: see row_stats
 int fp32_bwd_dkdv(const Geom& g, const RowSet* sets, int nsets, const void* q, const void* k, const void* v,
-                  const void* dO, const float* const* lse, const float* const* delta, void* dk, void* dv,
-                  hipStream_t st);
+                  const void* dO, const float* const* lse, const float* const* delta, const float* const* share, void* dk,
+                  void* dv, hipStream_t st);
+// Shared inputs: a routed row's window once for both branches (rs_l), and the keys before it (rs_g, shift = W + 1), in one launch and
+// a combine.  out_l: s of all rows, in O; out_g: a, added to O.  dq: on return delta_l is that of the rows folded by `share`
+// (row_stats), delta_g complete, both exact.
+size_t fp32_fwd_shared_bytes(const Geom& g);
+int fp32_fwd_shared(const Geom& g, const RowSet& rs_l, const RowSet& rs_g, const void* q, const void* k, const void* v,
+                    const FwdOut& out_l, const FwdOut& out_g, void* ws, hipStream_t st);
+size_t fp32_dq_shared_bytes(const Geom& g);
+int fp32_bwd_dq_shared(const Geom& g, const RowSet& rs_l, const RowSet& rs_g, const void* q, const void* k, const void* v,
+                       const void* dO, const float* lse_l, const float* lse_g, float* delta_l, float* delta_g, const float* share,
+                       void* dq, void* ws, hipStream_t st);
 
 // ---- attn_simple.hip : straightforward scalar-FMA kernels (bf16 storage, fp32 arithmetic, D = 64 or 128)
 int simple_fwd(const Geom& g, const RowSet& rs, const void* q, const void* k, const void* v, const FwdOut& out,

@@ -80,7 +80,13 @@ bool one_walk_pays(const l2a_params& p) {
 bool pair_bwd(const l2a_params& p) { return pair_fwd(p); }
 // two token-minor copies of V (one per branch) and the forward kernels' redo flags; short sequences:
 // flags for both branches at once and room for A in fp32
+// fp32 with shared inputs: the parts that a routed row's keys before the window are found in (an option: without room for
+// them the branches run one after the other)
+bool both_routed(const l2a_params& p) { return !(p.flags & (L2A_FLAG_DENSE | L2A_FLAG_SKIP_LOCAL | L2A_FLAG_SKIP_GLOBAL)); }
+// (Up to 256 tokens a launch for each branch and one for the parts with a combine behind it take the same few us.)
+bool fp32_parts(const l2a_params& p) { return p.dtype == L2A_FP32 && both_routed(p) && p.T > 256; }
 size_t fwd_workspace_bytes(const l2a_params& p) {
+    if (fp32_parts(p)) return fp32_fwd_shared_bytes(make_geom(p));
     if (!use_mfma(p)) return 0;
     if (pair_fwd(p)) return 2 * kv_copy_bytes(p) + 2 * redo_bytes(p) + q_elems(p) * sizeof(float);
     return 2 * kv_copy_bytes(p) + redo_bytes(p);
@@ -98,10 +104,9 @@ size_t dkdv_part_bytes(const l2a_params& p) {
     return z > 1 ? (size_t)z * 2 * p.B * p.T * p.Hkv * p.D * sizeof(float) : 0;
 }
 // backward with shared inputs: the branches of a routed row are folded (row_stats)
-bool may_fold(const l2a_params& p) {
-    return use_mfma(p) && !(p.flags & (L2A_FLAG_DENSE | L2A_FLAG_SKIP_LOCAL | L2A_FLAG_SKIP_GLOBAL));
-}
+bool may_fold(const l2a_params& p) { return (use_mfma(p) && both_routed(p)) || fp32_parts(p); }
 size_t bwd_workspace_bytes(const l2a_params& p) {
+    if (fp32_parts(p)) return 3 * delta_bytes(p) + fp32_dq_shared_bytes(make_geom(p));
     return 2 * delta_bytes(p) + (use_mfma(p) ? 2 * packed_set_bytes(p) + dkdv_part_bytes(p) : 0);
 }
 
@@ -216,7 +221,7 @@ int l2a_attn_fwd(const l2a_params* p, const void* q_loc, const void* k_loc, cons
     const void* ptrs[] = {q_loc, k_loc, v_loc, q_glb, k_glb, v_glb, O, S_opt, A_opt};
     for (const void* x : ptrs)
         if (x && misaligned(x)) return L2A_ERR_ALIGN;
-    const size_t need = fwd_workspace_bytes(*p);
+    const size_t need = use_mfma(*p) ? fwd_workspace_bytes(*p) : 0;
     if (need && (!workspace || workspace_bytes < need)) return L2A_ERR_WORKSPACE;
     if (need && misaligned(workspace)) return L2A_ERR_ALIGN;
 
@@ -283,6 +288,12 @@ int l2a_attn_fwd(const l2a_params* p, const void* q_loc, const void* k_loc, cons
             return r;
         return merge_rows(g, rs_g, nullptr, A32, O, st);
     }
+    if (fp32_parts(*p) && kblk_first_row && q_glb == q_loc && k_glb == k_loc && v_glb == v_loc && workspace &&
+        workspace_bytes >= fwd_workspace_bytes(*p) && !misaligned(workspace)) {
+        const FwdOut out_l{O, S_opt, lse_local, lse_global, A_opt, 0}, out_g{O, A_opt, lse_global, nullptr, nullptr, 1};
+        return fp32_fwd_shared(g, RowSet{nullptr, nullptr, nullptr, 1}, RowSet{row_idx, count, kblk_first_row, 0, g.W + 1}, q_loc, k_loc,
+                               v_loc, out_l, out_g, workspace, st);
+    }
     auto fwd_branch = [&](const RowSet& rs, const void* q, const void* k, const void* v, const void* vt,
                           const FwdOut& out) {
         int32_t* redo = (int32_t*)((char*)workspace + 2 * kv_copy_bytes(*p));
@@ -328,7 +339,8 @@ int l2a_attn_bwd(const l2a_params* p, const void* dO, const void* q_loc, const v
     if (do_global && (!q_glb || !k_glb || !v_glb || !A || !lse_global || !dq_glb || !dk_glb || !dv_glb))
         return L2A_ERR_NULL;
     if (do_global && !dense && (!row_idx || !count || !kblk_first_row)) return L2A_ERR_NULL;
-    if (!workspace || workspace_bytes < l2a_attn_workspace_bytes(p, 1)) return L2A_ERR_WORKSPACE;
+    // fp32 makes do with the two deltas (the branches then run one after the other)
+    if (!workspace || workspace_bytes < (p->dtype == L2A_FP32 ? 2 * delta_bytes(*p) : bwd_workspace_bytes(*p))) return L2A_ERR_WORKSPACE;
     const void* ptrs[] = {dO, q_loc, k_loc, v_loc, q_glb, k_glb, v_glb, S, A, dq_loc, dk_loc, dv_loc,
                           dq_glb, dk_glb, dv_glb, workspace};
     for (const void* x : ptrs)
@@ -348,13 +360,14 @@ int l2a_attn_bwd(const l2a_params* p, const void* dO, const void* q_loc, const v
     const bool mfma = use_mfma(*p), fp32 = p->dtype == L2A_FP32;
     // Shared inputs and summed gradients: the window of a routed row counts once for both branches, and the Global pass
     // only takes the keys before it (none at all while the window spans the sequence).
-    const bool fold = may_fold(*p) && out_alias;
+    const bool fold = may_fold(*p) && out_alias && workspace_bytes >= bwd_workspace_bytes(*p);
     char* packed_base = (char*)workspace + 2 * delta_bytes(*p);
     // Until the rows are packed their place is free.  dQ of a folded row is the sum of two passes' parts, kept in fp32 where
     // its branch's rows will lie and rounded once; the rows' shares lie where the second set's statistics will.
-    float* wide_l = fold ? (float*)packed_base : nullptr;
-    float* wide_g = fold ? (float*)(packed_base + packed_set_bytes(*p)) : nullptr;
-    float* share = fold ? (float*)(packed_base + packed_set_bytes(*p) + 2 * rows_copy_bytes(*p)) : nullptr;
+    // (fp32: the shares behind the deltas, then the parts of dQ.)
+    float* wide_l = fold && mfma ? (float*)packed_base : nullptr;
+    float* wide_g = fold && mfma ? (float*)(packed_base + packed_set_bytes(*p)) : nullptr;
+    float* share = !fold ? nullptr : mfma ? (float*)(packed_base + packed_set_bytes(*p) + 2 * rows_copy_bytes(*p)) : (float*)packed_base;
     const int far_shift = fold ? g.W + 1 : 0;
     const bool far_rows = !fold || g.T > far_shift;
     auto bwd_dq = [&](const RowSet& rs, const void* q, const void* k, const void* v, const float* lse, float* delta,
@@ -370,7 +383,11 @@ int l2a_attn_bwd(const l2a_params* p, const void* dO, const void* q_loc, const v
         return r;
 
     // dQ: one pass per branch over that branch's rows; short sequences: both in one launch
-    if (pair_bwd(*p) && far_rows) {
+    if (fp32 && fold) {
+        if ((r = fp32_bwd_dq_shared(g, rs_l, rs_g, q_loc, k_loc, v_loc, dO, lse_local, lse_global, delta_l, delta_g, share, dq_loc,
+                                    packed_base + delta_bytes(*p), st)) != L2A_OK)
+            return r;
+    } else if (pair_bwd(*p) && far_rows) {
         if (!out_alias && (r = fill_zero(dq_glb, q_elems(*p) * elem_bytes(*p), st)) != L2A_OK) return r;
         if ((r = mfma_bwd_dq_pair(g, rs_l, q_loc, k_loc, v_loc, lse_local, delta_l, dq_loc, rs_g, q_glb, k_glb, v_glb,
                                   lse_global, delta_g, share, dq_glb, wide_l, wide_g, dO, st)) != L2A_OK)
@@ -389,7 +406,10 @@ int l2a_attn_bwd(const l2a_params* p, const void* dO, const void* q_loc, const v
     const int cap = rows_cap(*p);
     auto dkdv = [&](const RowSet* sets, int n, const void* const* qs, const float* const* lses,
                     const float* const* deltas, const void* k, const void* v, void* dk, void* dv) -> int {
-        if (fp32) return fp32_bwd_dkdv(g, sets, n, qs[0], k, v, dO, lses, deltas, dk, dv, st);
+        if (fp32) {
+            const float* shares[2] = {share, nullptr};
+            return fp32_bwd_dkdv(g, sets, n, qs[0], k, v, dO, lses, deltas, shares, dk, dv, st);
+        }
         if (!mfma) return simple_bwd_dkdv(g, sets, n, qs[0], k, v, dO, lses, deltas, dk, dv, st);
         const void* packed[2][5];
         for (int i = 0; i < n; ++i) {

@@ -63,3 +63,28 @@ def test_lists_without_key_block_entries(oracle):
     assert (with_first[2] - lay.lse_l).abs().max() <= tol
     both = torch.isfinite(lay.lse_g)
     assert torch.equal(both, torch.isfinite(with_first[3])) and (with_first[3] - lay.lse_g)[both].abs().max() <= tol
+
+
+@pytest.mark.parametrize("T,W,Hq,Hkv,Hm,f,D", [(1, 0, 1, 1, 1, 1.0, 64), (300, 299, 4, 2, 4, 0.5, 128), (300, 300, 4, 2, 1, 0.5, 64),
+                                               (273, 255, 3, 1, 3, 0.7, 128), (600, 79, 2, 2, 2, 0.02, 64), (600, 80, 4, 1, 1, 1.0, 128),
+                                               (2100, 100, 1, 1, 1, 0.2, 64),     # 7 workgroups share a tile's keys before the window
+                                               (1200, 40, 8, 2, 8, 0.3, 128),     # 4 of them
+                                               (531, 70, 32, 4, 32, 0.3, 128)])   # Local rows in wide tiles, a launch of their own
+def test_fp32_window_edges(oracle, T, W, Hq, Hkv, Hm, f, D):
+    run_and_check(oracle, make_case(B_=2, T=T, Hq=Hq, Hkv=Hkv, D=D, W=W, dtype="fp32", Hm=Hm, f=f, seed=T + W), twice=True)
+
+
+def test_fp32_without_room_for_the_parts(oracle):
+    """The forward takes no workspace and the backward the two deltas alone, as before there were parts."""
+    x = make_case(T=500, Hq=4, Hkv=2, D=64, W=90, dtype="fp32", Hm=4, f=0.3, seed=4)
+    lay, ref = run_and_check(oracle, x, check_branches=False)
+    want = [t.clone() for t in (lay.O, lay.A, lay.lse_g, lay.dq, lay.dk, lay.dv, lay.delta_g)]
+    p = lay.p
+    lay.fwd_ws, lay.bwd_ws = None, torch.empty(2 * ((4 * p.B * p.Hq * p.T + 255) // 256 * 256), dtype=torch.uint8, device="cuda")
+    lay.forward()
+    lay.backward(to_device(x.dO, "fp32"), want_delta=True)
+    torch.cuda.synchronize()
+    for a, b in zip(want, (lay.O, lay.A, lay.lse_g, lay.dq, lay.dk, lay.dv, lay.delta_g)):
+        fin = torch.isfinite(a)
+        assert torch.equal(fin, torch.isfinite(b))
+        assert (a - b)[fin].abs().max() <= 1e-4     # the bar of every fp32 result
