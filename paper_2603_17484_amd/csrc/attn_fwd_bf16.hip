@@ -571,32 +571,54 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds&
     load_v(jb0, 0);
     dma_wait();
     __syncthreads();
-    // Reference of every row's exponentials: the largest score among the row's keys in the window's or prefix's first
-    // two blocks (0 where there is none).  It is never updated: scores that come
+    // Reference of every row's exponentials: the largest score among the keys of the first two blocks that all rows of the
+    // 256-row tile see (by 32, no masks), or else (beginning of the sequence, routed rows far apart) among the row's own keys in
+    // these two blocks, 0 where there is none.  It is never updated: scores that come
     // later may exceed it, which costs no accuracy in floating point; the epilogue checks that the
-    // row sums stayed far from overflow and otherwise leaves the tile to running_max_body.
+    // row sums stayed far from overflow and otherwise leaves the tile to running_max_body.  (Masks for every tile's two blocks took it to
+    // 5200 cycles of a tile's 57000 at 1001 tokens.  The first 32 keys alone would do, but the weights next to a row's largest
+    // are rounded best: error against 64 bits 1.2-1.6 % larger.)
     {  // wavefronts whose rows all lie past the end compute on a repeated row and store nothing
 #pragma unroll
         for (int c = 0; c < NQB; ++c) mref[c] = -INFINITY;
-        const int nb = jb0 < jb1 ? 2 : 1;
-        for (int bi = 0; bi < nb; ++bi) {
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb) {
+        const int pmax_all = BQ == kBQ ? wg_pmax : row_code(a.rs, gm, bh, min(wg_r0 / kBQ * kBQ + kBQ, n_rows) - 1) / gm.G;
+        const int seen = LOCAL ? (max(pmax_all - gm.W, 0) + 31) / 32 * 32 - jb0 * kBK : 0;  // behind the first block's first key
+        if (seen <= 2 * kBK - 32 && (jb0 + 2) * kBK - 1 <= pmin_all) {
+#pragma unroll 1
+            for (int at = seen; at <= 2 * kBK - 32; at += 32) {
                 Scores S;
 #pragma unroll
                 for (int ks = 0; ks < 8; ++ks) {
-                    const bf16x8 op = rm_operand(&lds_k[bi][0], kb * 32 + n, ks, h);
+                    const bf16x8 op = rm_operand(&lds_k[at / kBK][0], at % kBK + n, ks, h);
 #pragma unroll
                     for (int c = 0; c < NQB; ++c) S.s[c] = mfma32(op, qreg[c][ks], ks == 0 ? zero16 : S.s[c]);
                 }
 #pragma unroll
-                for (int c = 0; c < NQB; ++c) {
-                    const int last = last_row((jb0 + bi) * kBK + kb * 32, c);
-                    const int first = LOCAL ? first_row((jb0 + bi) * kBK + kb * 32, c) : 0;
+                for (int c = 0; c < NQB; ++c)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const bool ok = c_row(r, 0) <= last && (!LOCAL || c_row(r, 0) >= first);
-                        mref[c] = fmaxf(mref[c], ok ? S.s[c][r] : -INFINITY);
+                    for (int r = 0; r < 16; ++r) mref[c] = fmaxf(mref[c], S.s[c][r]);
+            }
+        } else {
+            const int nb = jb0 < jb1 ? 2 : 1;
+            for (int bi = 0; bi < nb; ++bi) {
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb) {
+                    Scores S;
+#pragma unroll
+                    for (int ks = 0; ks < 8; ++ks) {
+                        const bf16x8 op = rm_operand(&lds_k[bi][0], kb * 32 + n, ks, h);
+#pragma unroll
+                        for (int c = 0; c < NQB; ++c) S.s[c] = mfma32(op, qreg[c][ks], ks == 0 ? zero16 : S.s[c]);
+                    }
+#pragma unroll
+                    for (int c = 0; c < NQB; ++c) {
+                        const int last = last_row((jb0 + bi) * kBK + kb * 32, c);
+                        const int first = LOCAL ? first_row((jb0 + bi) * kBK + kb * 32, c) : 0;
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) {
+                            const bool ok = c_row(r, 0) <= last && (!LOCAL || c_row(r, 0) >= first);
+                            mref[c] = fmaxf(mref[c], ok ? S.s[c][r] : -INFINITY);
+                        }
                     }
                 }
             }
@@ -688,7 +710,7 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds&
             bad = bad || (wave_active && valid[c] && !(lt[c] > 1.0e-30f && lt[c] < 1.0e30f && chk == 0.f));
         }
     };
-    auto row_base = [&](int c) __attribute__((always_inline)) { return (((size_t)b * gm.T + pos[c]) * gm.Hq + head[c]) * kD + 4 * h; };
+    auto row_base = [&](int c) __attribute__((always_inline)) { return (((size_t)b * gm.T + pos[c]) * gm.Hq + head[c]) * kD; };
     auto row_stat = [&](int c) __attribute__((always_inline)) { return ((size_t)b * gm.Hq + head[c]) * gm.T + pos[c]; };
     auto row_lse = [&](int c) __attribute__((always_inline)) { return (mref[c] + __builtin_amdgcn_logf(lt[c])) * kLn2; };
 
@@ -705,7 +727,7 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds&
             for (int c = 0; c < NQB; ++c) {
                 if (!valid[c]) continue;
                 const float inv = 1.f / lt[c];
-                const size_t base = row_base(c);
+                const size_t base = row_base(c) + 4 * h;
 #pragma unroll
                 for (int d = 0; d < 4; ++d)
 #pragma unroll
@@ -730,7 +752,7 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds&
 
     // (workgroup-wide vote; LDS is free after the last barrier)
     check_sums();
-    int* vote = reinterpret_cast<int*>(&lds_v[0][0]);
+    int* vote = reinterpret_cast<int*>(&lds_v[1][kD * kBK - 2]);
     if (threadIdx.x == 0) *vote = 0;
     __syncthreads();
     if (bad) *vote = 1;
@@ -748,6 +770,70 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds&
 
     // ---- epilogue: normalise, log-sum-exp, merge / scatter
     if (!wave_active) return;
+    if constexpr (KIND == kLocal || KIND == kWhole) {
+        // Through LDS, where a lane's 8 bytes of its own row become 16 bytes of rows that sixteen lanes write whole: written
+        // straight from the accumulators a store touched 32 rows, and a tile's outputs took 4700 to 9300 cycles.  A wavefront's
+        // rows lie 272 bytes apart; behind a row's 256 bytes, where it goes (elements) and what it is (-1: nowhere, else routed).
+        static_assert(NQB == 1 && NW * 32 * 272 < sizeof(FwdLds) - 16, "below the vote");
+        char* const st = reinterpret_cast<char*>(&lds) + wave * (32 * 272);
+        const float inv = 1.f / lt[0];
+        auto put = [&](bool sum) __attribute__((always_inline)) {  // s, or o where it differs
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int d = 0; d < 4; ++d)
+#pragma unroll
+                for (int rg = 0; rg < 4; ++rg) {
+                    f32x4 x = {oacc[d][0][4 * rg + 0] * inv, oacc[d][0][4 * rg + 1] * inv, oacc[d][0][4 * rg + 2] * inv,
+                               oacc[d][0][4 * rg + 3] * inv};
+                    bf16x4 y = __builtin_convertvector(x, bf16x4);
+                    if (KIND == kWhole && sum && routed[0]) y = __builtin_convertvector(x + __builtin_convertvector(y, f32x4), bf16x4);
+                    *reinterpret_cast<bf16x4*>(st + n * 272 + d * 64 + rg * 16 + h * 8) = y;
+                }
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_wave_barrier();
+        };
+        if (h == 0) {
+            *reinterpret_cast<size_t*>(st + n * 272 + 256) = row_base(0);
+            *reinterpret_cast<int*>(st + n * 272 + 264) = valid[0] ? (KIND == kWhole && routed[0] ? 1 : 0) : -1;
+        }
+        auto rows_out = [&](auto f) __attribute__((always_inline)) {  // f(16 bytes, element offset, routed)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const char* row = st + (4 * i + (lane >> 4)) * 272;
+                const u32x4 x = *reinterpret_cast<const u32x4*>(row + (lane & 15) * 16);
+                const size_t off = *reinterpret_cast<const size_t*>(row + 256) + (lane & 15) * 8;
+                const int what = *reinterpret_cast<const int*>(row + 264);
+                if (what >= 0) f(x, off, what);
+            }
+        };
+        __bf16* mo = (__bf16*)a.out.main_out;
+        if constexpr (KIND == kWhole) {
+            __bf16* ao = (__bf16*)a.out.copy_out;
+            if (a.s_out || ao) {
+                put(false);
+                rows_out([&](const u32x4& x, size_t off, int r) __attribute__((always_inline)) {
+                    if (a.s_out) *reinterpret_cast<u32x4*>(a.s_out + off) = x;
+                    if (ao) *reinterpret_cast<u32x4*>(ao + off) = r ? x : u32x4{0u, 0u, 0u, 0u};
+                });
+            }
+            put(true);
+            rows_out([&](const u32x4& x, size_t off, int) __attribute__((always_inline)) { *reinterpret_cast<u32x4*>(mo + off) = x; });
+            if (h == 0 && valid[0]) store_whole_lse(a, row_stat(0), row_lse(0), routed[0]);
+        } else {
+            __bf16 *co = (__bf16*)a.out.copy_out, *zf = (__bf16*)a.out.zero_fill;
+            put(false);
+            rows_out([&](const u32x4& x, size_t off, int) __attribute__((always_inline)) {
+                *reinterpret_cast<u32x4*>(mo + off) = x;
+                if (co) *reinterpret_cast<u32x4*>(co + off) = x;
+                if (zf) *reinterpret_cast<u32x4*>(zf + off) = u32x4{0u, 0u, 0u, 0u};
+            });
+            if (h == 0 && valid[0]) {
+                a.out.lse_out[row_stat(0)] = row_lse(0);
+                if (a.out.lse_fill) a.out.lse_fill[row_stat(0)] = -INFINITY;
+            }
+        }
+        return;
+    }
     __bf16* mo = (__bf16*)a.out.main_out;
     __bf16* co = (__bf16*)a.out.copy_out;
     __bf16* zf = (__bf16*)a.out.zero_fill;
@@ -756,18 +842,7 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds&
     for (int c = 0; c < NQB; ++c) {
         if (!valid[c]) continue;
         const float inv = 1.f / lt[c];
-        const size_t base = row_base(c);
-        if constexpr (KIND == kWhole) {
-#pragma unroll
-            for (int d = 0; d < 4; ++d)
-#pragma unroll
-                for (int rg = 0; rg < 4; ++rg)
-                    store_whole(a, base + d * 32 + 8 * rg,
-                                f32x4{oacc[d][c][4 * rg + 0] * inv, oacc[d][c][4 * rg + 1] * inv,
-                                      oacc[d][c][4 * rg + 2] * inv, oacc[d][c][4 * rg + 3] * inv}, routed[c]);
-            if (h == 0) store_whole_lse(a, row_stat(c), row_lse(c), routed[c]);
-            continue;
-        }
+        const size_t base = row_base(c) + 4 * h;
 #pragma unroll
         for (int d = 0; d < 4; ++d)
 #pragma unroll
