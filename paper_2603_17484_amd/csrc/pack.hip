@@ -87,14 +87,10 @@ __global__ __launch_bounds__(kThreads) void pack_token_minor_kernel(PackArgs a) 
     const Geom& gm = a.gm;
     const int bh = blockIdx.y, b = bh / gm.Hkv, hk = bh - b * gm.Hkv;
     const int r0 = blockIdx.x * 64;
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-        if (a.fill[i].n) run_fill(a.fill[i]);
-    if (a.rest.row_idx || a.rest.flags) list_rest(gm, a.rest, bh, (int)blockIdx.x, rest_bits);
     const int n_rows = a.kv_rows ? gm.T : rows_total(a.rs, gm, bh);
-    if (r0 >= n_rows) return;
     // rows before the first one that the dK/dV walk may read (see walk::list_bounds) see nothing
-    if (a.rs.shift && row_code(a.rs, gm, bh, min(r0 + 64, n_rows) - 1) / gm.G < (a.rs.shift & ~63)) return;
+    const bool unread =
+        r0 >= n_rows || (a.rs.shift && row_code(a.rs, gm, bh, min(r0 + 64, n_rows) - 1) / gm.G < (a.rs.shift & ~63));
 
     // global element offset of row r's channel 0, or -1 for padding
     auto row_offset = [&](int r, int* pos_out, size_t* stat_out) -> long long {
@@ -108,21 +104,35 @@ __global__ __launch_bounds__(kThreads) void pack_token_minor_kernel(PackArgs a) 
         return (((long long)b * gm.T + p) * gm.Hq + head) * kD;
     };
 
-    // ---- 64 rows -> LDS (row-major, padded), and the compact row-major copy
+    // ---- 64 rows, on their way while the constants and the list are written: a workgroup's time is the chain of its dependent
+    // loads (list bounds, list, then the rows), T = 1001 with 4 KV heads 6.9 -> 5.7 us; the rows of two tensors in flight
+    // together, 2 x 4000 tokens with 4 KV heads 47.2 + 19.3 -> 42.0 + 17.1 us (5.4 TB/s).
     const int r4 = (threadIdx.x >> 4) * 4, c8 = (threadIdx.x & 15) * 8;
     long long offs[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) offs[i] = row_offset(r0 + r4 + i, nullptr, nullptr);
+    for (int i = 0; i < 4; ++i) offs[i] = unread ? -1 : row_offset(r0 + r4 + i, nullptr, nullptr);
+    u32x4 v[2][4] = {};
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (a.x[t] && offs[i] >= 0) v[t][i] = *reinterpret_cast<const u32x4*>(a.x[t] + offs[i] + c8);
+
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+        if (a.fill[i].n) run_fill(a.fill[i]);
+    if (a.rest.row_idx || a.rest.flags) list_rest(gm, a.rest, bh, (int)blockIdx.x, rest_bits);
+    if (unread) return;
+
+    // ---- -> LDS (row-major, padded), and the compact row-major copy
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
         if (!a.x[t]) continue;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            u32x4 v = {0u, 0u, 0u, 0u};
-            if (offs[i] >= 0) v = *reinterpret_cast<const u32x4*>(a.x[t] + offs[i] + c8);
-            if (a.xt[t]) *reinterpret_cast<u32x4*>(&lds[t][(r4 + i) * kRowPad + c8]) = v;
+            if (a.xt[t]) *reinterpret_cast<u32x4*>(&lds[t][(r4 + i) * kRowPad + c8]) = v[t][i];
             if (a.xc[t])
-                *reinterpret_cast<u32x4*>(a.xc[t] + ((size_t)bh * a.cap + r0 + r4 + i) * kD + c8) = v;
+                *reinterpret_cast<u32x4*>(a.xc[t] + ((size_t)bh * a.cap + r0 + r4 + i) * kD + c8) = v[t][i];
         }
     }
     if (a.lse2_c && threadIdx.x < 64) {
