@@ -29,7 +29,7 @@ PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA peak
 # committed profile are repeated here; they are reported only for exactly that workload.
 TRAFFIC_SOURCE = ("NOT measured in this run: constant copied from profiles/all_kernels_train_128k_hbm_bytes.md, two "
                   "rocprofv3 --pmc runs of `bench.py --sparse-only --calibrate-copy` on the same workload")
-MEASURED_TRAFFIC_BYTES = {"bwd_dkdv": 1.573e10, "bwd_dq_global": 2.508e10, "bwd_dq_local": 4.26e9,
+MEASURED_TRAFFIC_BYTES = {"bwd_dkdv": 1.564e10, "bwd_dq_global": 2.966e10, "bwd_dq_local": 4.25e9,
                           "fwd_shared": 3.577e10}
 
 
@@ -239,9 +239,9 @@ def main() -> int:
 
     # ---- roofline of the dominant kernel (live HIP-event durations over the timed region)
     pf = pairs_before_window(mask_np, w.Hq, T, w.W)
-    alg = {  # FLOPs per launch, the window's pairs of a routed row once; the backward's 10 D per pair = 8 D (S, dP, dV, dK) + 2 D (dQ)
-        "bwd_dq_local": 2.0 * D * pl, "bwd_dq_global": 2.0 * D * pf, "bwd_dq_pair": 2.0 * D * (pl + pf),
-        "bwd_dkdv": 8.0 * D * (pl + pf), "fwd_shared": 4.0 * D * (pl + pf), "fwd_whole": 4.0 * D * pl, "fwd_pair": 4.0 * D * (pl + pg),
+    alg = {  # algorithmic FLOPs per launch; the backward's 10 D per pair = 8 D (S, dP, dV, dK) + 2 D (dQ)
+        "bwd_dq_local": 2.0 * D * pl, "bwd_dq_global": 2.0 * D * pg, "bwd_dq_pair": 2.0 * D * (pl + pg),
+        "bwd_dkdv": 8.0 * D * (pl + pg), "fwd_shared": 4.0 * D * (pl + pf), "fwd_whole": 4.0 * D * pl, "fwd_pair": 4.0 * D * (pl + pg),
         "fwd_local": 4.0 * D * pl, "fwd_global": 4.0 * D * pg,
     }
     dom = max((n for n in kern if n in alg), key=lambda n: kern[n])
@@ -281,7 +281,7 @@ def main() -> int:
             "ms_layer": round(ms_dense, 3),
             "ms_layer_graph_replay": None if ms_dense_graph is None else round(ms_dense_graph, 3),
             "speedup_sparse_vs_dense": round((ms_dense_graph or ms_dense) / ms_sparse, 3),
-            # the kernel that runs on Global rows only (in the sparse mode on the keys before the window)
+            # the kernel that runs on Global rows only (the dK/dV kernel walks both row sets in one launch)
             "speedup_global_kernels": {k: round(kern_dense[k] / kern[k], 3) for k in ("bwd_dq_global",)
                                        if kern.get(k) and kern_dense.get(k)},
             "tflops_layer": round(mult * D * (pl + pg_dense) / (ms_dense * 1e-3) / 1e12, 2),

@@ -97,8 +97,8 @@ const char* l2a_strerror(int code);
  *             layers with shared inputs use; without it the branches run one after the other; else nothing
  *   backward  delta_t of each branch, [B,Hq,T] float, twice; on the matrix-core path also, per
  *             branch, compact row-major copies of the rows' Q and dO (ceil64(T G) rows per
- *             (b, KV head)) with three per-row statistics (shared inputs: before those, the two passes'
- *             parts of dq in float); short sequences (fewer than 1024
+ *             (b, KV head)) with three per-row statistics (summed dq of short sequences: before those, the
+ *             Global branch's part in float); short sequences (fewer than 1024
  *             blocks of 128 keys over all (b, KV head)): up to 8 x 2 float copies of [B,T,Hkv,D],
  *             partial sums of the workgroups that share a key block's rows; L2A_FP32, both branches with
  *             routing lists, T > 256: room as for the forward, of which only the two deltas are required

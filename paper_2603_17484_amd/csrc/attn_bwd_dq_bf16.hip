@@ -38,13 +38,9 @@ struct DqArgs {
     const __bf16* dO;
     const float* lse;
     float* delta;  // in: <dO, saved out>; out: sum_j P dP
-    const float* share;  // optional: see row_stats.  LOCAL: the rows are folded ones; else delta gets the far keys' part
     __bf16* dq;
     int accumulate;
-    // The rows' results in fp32 go here instead of to dq.  LOCAL: those of folded rows that also have keys before the window,
-    // whose parts are added (wide_add, or merge_rows) before they are rounded
-    float* wide_out = nullptr;
-    const float* wide_add = nullptr;  // fp32 parts to be added
+    float* wide_out = nullptr;  // the rows' results in fp32 go here instead of to dq
 };
 
 struct SdP {
@@ -105,10 +101,8 @@ __device__ __forceinline__ void dq_body(const DqArgs& a, const int bx, const int
 
     const int wg_r0 = tile * kBQ;
     const int wg_r1 = min(wg_r0 + kBQ, n_rows);
-    const int shift = LOCAL ? 0 : a.rs.shift;
-    const int wg_pmin = row_code(a.rs, gm, bh, wg_r0) / gm.G - shift;  // last keys the tile's rows see
-    const int wg_pmax = row_code(a.rs, gm, bh, wg_r1 - 1) / gm.G - shift;
-    if (wg_pmax < 0) return;  // none sees any
+    const int wg_pmin = row_code(a.rs, gm, bh, wg_r0) / gm.G;
+    const int wg_pmax = row_code(a.rs, gm, bh, wg_r1 - 1) / gm.G;
     const int wv_r0 = wg_r0 + wave * kRW;
     const bool wave_active = wv_r0 < n_rows;
 
@@ -126,9 +120,7 @@ __device__ __forceinline__ void dq_body(const DqArgs& a, const int bx, const int
         qreg[ks] = *reinterpret_cast<const bf16x8*>(a.q + row_off + 8 * h + ks * 16);
         greg[ks] = *reinterpret_cast<const bf16x8*>(a.dO + row_off + 8 * h + ks * 16);
     }
-    const int mpos = pos - shift;  // the last key this row sees
-    float neg_lse2 = -a.lse[so] * kLog2e;
-    if (LOCAL && a.share) neg_lse2 += __builtin_amdgcn_logf(1.f + a.share[so]);
+    const float neg_lse2 = -a.lse[so] * kLog2e;
     // The dP accumulators start from -delta (delta = <dO, saved out>), so dS = P o dP' needs no
     // subtraction, and since every row's P sums to one, sum_j dS_j = (sum_j P dP) - delta: the
     // exact delta is the saved one plus the row sum of dS.
@@ -244,7 +236,7 @@ __device__ __forceinline__ void dq_body(const DqArgs& a, const int bx, const int
         // Masks before the slots and not among them, behind a uniform branch: scores out of reach become -inf, and the slots
         // are the same for masked and unmasked blocks.  Key k0 + c_row(e, h) lies in [pos - W, pos], or in [0, pos]: one comparison.
         if (masked) {
-            const int at = LOCAL ? k0 + 4 * h - mpos + gm.W : mpos - k0 - 4 * h;
+            const int at = LOCAL ? k0 + 4 * h - pos + gm.W : pos - k0 - 4 * h;
             static_for<0, 16>([&](auto ec) {
                 constexpr int e = decltype(ec)::value, ce = c_row(e, 0);
                 const bool ok = LOCAL ? (unsigned)(at + ce) <= (unsigned)gm.W : ce <= at;
@@ -337,13 +329,8 @@ __device__ __forceinline__ void dq_body(const DqArgs& a, const int bx, const int
 
     // ---- epilogue
     if (!wave_active) return;
-    const float ds_sum = dlt_exact + __shfl_xor(dlt_exact, 32);
+    const float de = dlt + dlt_exact + __shfl_xor(dlt_exact, 32);
     if (!valid) return;
-    // sum_j dS = sum_j P dP - delta sum_j P.  Folded rows: sum_j P = 1 + a, and delta_l is wanted; far keys: 1 - a.
-    const float f = a.share ? a.share[so] : 0.f;
-    const float de = LOCAL ? dlt + ds_sum / (1.f + f) : dlt * (1.f - f) + ds_sum;
-    const bool wide = a.wide_out && (!LOCAL || (f != 0.f && mpos > gm.W));
-    if (!LOCAL && mpos < 0) return;
 #pragma unroll
     for (int d = 0; d < 4; ++d)
 #pragma unroll
@@ -351,13 +338,11 @@ __device__ __forceinline__ void dq_body(const DqArgs& a, const int bx, const int
             const size_t off = row_off + 4 * h + d * 32 + 8 * rg;
             f32x4 x = {acc[d][4 * rg + 0] * gm.scale, acc[d][4 * rg + 1] * gm.scale, acc[d][4 * rg + 2] * gm.scale,
                        acc[d][4 * rg + 3] * gm.scale};
-            if (wide) {
+            if (PAIR && a.wide_out) {
                 *reinterpret_cast<f32x4*>(a.wide_out + off) = x;
                 continue;
             }
-            if (!PAIR && a.wide_add) {
-                x += *reinterpret_cast<const f32x4*>(a.wide_add + off);
-            } else if (!PAIR && a.accumulate) {
+            if (!PAIR && a.accumulate) {
                 const bf16x4 old = *reinterpret_cast<const bf16x4*>(a.dq + off);
                 x += __builtin_convertvector(old, f32x4);
             }
@@ -394,14 +379,12 @@ unsigned tiles_x(const Geom& g, int bq) { return (unsigned)((((long long)g.T * g
 }  // namespace
 
 int mfma_bwd_dq(const Geom& g, const RowSet& rs, const void* q, const void* k, const void* v, const void* dO,
-                const float* lse, float* delta, const float* share, void* dq, int accumulate, float* wide, hipStream_t st) {
+                const float* lse, float* delta, void* dq, int accumulate, hipStream_t st) {
     if (g.D != kD) return L2A_ERR_UNSUPPORTED;
     // per-lane load offsets are 32-bit: 64 rows of K or V
     if (64ull * g.Hkv * kD * 2ull > 0xffffffffull) return L2A_ERR_UNSUPPORTED;
-    DqArgs a{g, rs, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (const __bf16*)dO, lse, delta, share,
+    DqArgs a{g, rs, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (const __bf16*)dO, lse, delta,
              (__bf16*)dq, accumulate};
-    if (wide && rs.local) a.wide_out = wide;
-    else a.wide_add = wide;
     const bool half = half_tiles(g);
     const dim3 grid(tiles_x(g, half ? 128 : 256), g.B * g.Hkv);
     KernelTimer kt_(rs.local ? "bwd_dq_local" : "bwd_dq_global", st);
@@ -412,15 +395,15 @@ int mfma_bwd_dq(const Geom& g, const RowSet& rs, const void* q, const void* k, c
     return launch_status();
 }
 
-// Both branches at once (bwd_dq_pair_kernel); wide_l, wide_g: the parts of the rows that both have, in fp32, instead of to dq
+// Both branches at once (bwd_dq_pair_kernel); wide_g: the Global rows' dQ in fp32 instead of to dq_g
 int mfma_bwd_dq_pair(const Geom& g, const RowSet& rs_l, const void* q_l, const void* k_l, const void* v_l,
                      const float* lse_l, float* delta_l, void* dq_l, const RowSet& rs_g, const void* q_g,
-                     const void* k_g, const void* v_g, const float* lse_g, float* delta_g, const float* share, void* dq_g,
-                     float* wide_l, float* wide_g, const void* dO, hipStream_t st) {
+                     const void* k_g, const void* v_g, const float* lse_g, float* delta_g, void* dq_g, float* wide_g,
+                     const void* dO, hipStream_t st) {
     if (g.D != kD) return L2A_ERR_UNSUPPORTED;
     if (64ull * g.Hkv * kD * 2ull > 0xffffffffull) return L2A_ERR_UNSUPPORTED;
-    DqArgs al{g, rs_l, (const __bf16*)q_l, (const __bf16*)k_l, (const __bf16*)v_l, (const __bf16*)dO, lse_l, delta_l, share, (__bf16*)dq_l, 0, wide_l};
-    DqArgs ag{g, rs_g, (const __bf16*)q_g, (const __bf16*)k_g, (const __bf16*)v_g, (const __bf16*)dO, lse_g, delta_g, share, (__bf16*)dq_g, 0, wide_g};
+    DqArgs al{g, rs_l, (const __bf16*)q_l, (const __bf16*)k_l, (const __bf16*)v_l, (const __bf16*)dO, lse_l, delta_l, (__bf16*)dq_l, 0};
+    DqArgs ag{g, rs_g, (const __bf16*)q_g, (const __bf16*)k_g, (const __bf16*)v_g, (const __bf16*)dO, lse_g, delta_g, (__bf16*)dq_g, 0, wide_g};
     KernelTimer kt("bwd_dq_pair", st);
     const unsigned w = tiles_x(g, half_tiles(g) ? 128 : 256);  // per branch
     if (half_tiles(g)) hipLaunchKernelGGL((bwd_dq_pair_kernel<4>), dim3(2 * w, g.B * g.Hkv), dim3(256), 0, st, ag, al, (int)w);

@@ -22,7 +22,7 @@ struct RowSet {
     const int32_t* count;    // [B,Hkv]     or nullptr = T*G rows
     const int32_t* kblk_first_row;  // [B,Hkv,ceil(T/64)+1] or nullptr (identity: 64*k*G)
     int local;               // 1: sliding-window branch
-    int shift = 0;           // GLOBAL: keys 0..pos - shift only (what a shared-input backward leaves to this pass: W + 1)
+    int shift = 0;           // GLOBAL, fp32: keys 0..pos - shift only (what the fp32 kernels leave to this set with shared inputs: W + 1)
 };
 
 constexpr float kLog2e = 1.4426950408889634f;
@@ -102,8 +102,8 @@ int router_decide(const l2a_params& p, int C, const void* x, const float* w, flo
 
 // ---- util.hip
 // The backward's per-row statistics: delta of the branches that are run (bf16: the first 64 tokens' from the definition).
-// share (optional, both branches with the same q, k, v): the two branches of a routed row in its window become one row:
-// share[b,h,t] = a = exp(lse_local - lse_global) (1e-30 at least; 0 on rows not in `routed`) and the Local delta is that
+// share (optional; fp32, both branches with the same q, k, v): the two branches of a routed row in its window become one row:
+// share[b,h,t] = a = exp(lse_local - lse_global) (0 on rows not in `routed`) and the Local delta is that
 // of the folded row, (delta_l + a delta_g) / (1 + a)
 struct RowStats {
     const void *q, *k, *v, *out;  // out: the saved s or a
@@ -153,21 +153,16 @@ struct RestList {
 };
 int pack_kv(const Geom& g, int n, const void* const* x, void* const* xt, int cap, const Fill* fills, int nfills,
             const RestList* rest, hipStream_t st);
-// O += A on the rows of rs (O bf16, A fp32, D = 128), or O = S + A with S in fp32, where S is given
-// (rows that see a key: those at positions below rs.shift are left as they are)
-int merge_rows(const Geom& g, const RowSet& rs, const float* S, const float* A, void* O, hipStream_t st);
-// share (see row_stats), with the Local rows: their statistics are those of the folded rows, and delta_g is completed
+// O += A on the rows of rs (O bf16, A fp32, D = 128)
+int merge_rows(const Geom& g, const RowSet& rs, const float* A, void* O, hipStream_t st);
 int pack_rows(const Geom& g, const RowSet& rs, const void* q, const void* dO, const float* lse, const float* delta,
-              void* qc, void* gc, float* lse2_c, float* delta_c, int32_t* pos_c, int cap, const float* share, float* delta_g,
-              hipStream_t st);
-// wide (with share): the parts of rows that both passes visit, in fp32 -- written by the Local pass, added by the Global one;
-// share: see row_stats; delta on return: Local rows delta_l, Global rows (keys 0..pos - shift only) their part of delta_g
+              void* qc, void* gc, float* lse2_c, float* delta_c, int32_t* pos_c, int cap, hipStream_t st);
 int mfma_bwd_dq(const Geom& g, const RowSet& rs, const void* q, const void* k, const void* v, const void* dO,
-                const float* lse, float* delta, const float* share, void* dq, int accumulate, float* wide, hipStream_t st);
+                const float* lse, float* delta, void* dq, int accumulate, hipStream_t st);
 int mfma_bwd_dq_pair(const Geom& g, const RowSet& rs_l, const void* q_l, const void* k_l, const void* v_l,
                      const float* lse_l, float* delta_l, void* dq_l, const RowSet& rs_g, const void* q_g,
-                     const void* k_g, const void* v_g, const float* lse_g, float* delta_g, const float* share, void* dq_g,
-                     float* wide_l, float* wide_g, const void* dO, hipStream_t st);
+                     const void* k_g, const void* v_g, const float* lse_g, float* delta_g, void* dq_g, float* wide_g,
+                     const void* dO, hipStream_t st);
 // packed[s]: the five outputs of pack_rows for set s (qc, gc, lse2_c, delta_c, pos_c)
 // part: scratch for dkdv_splits(g) x 2 x (B T Hkv D) floats when dkdv_splits(g) > 1 (short sequences)
 int dkdv_splits(const Geom& g);

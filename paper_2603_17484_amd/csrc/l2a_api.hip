@@ -103,8 +103,6 @@ size_t dkdv_part_bytes(const l2a_params& p) {
     const int z = dkdv_splits(make_geom(p));
     return z > 1 ? (size_t)z * 2 * p.B * p.T * p.Hkv * p.D * sizeof(float) : 0;
 }
-// backward with shared inputs: the branches of a routed row are folded (row_stats)
-bool may_fold(const l2a_params& p) { return (use_mfma(p) && both_routed(p)) || fp32_parts(p); }
 size_t bwd_workspace_bytes(const l2a_params& p) {
     if (fp32_parts(p)) return 3 * delta_bytes(p) + fp32_dq_shared_bytes(make_geom(p));
     return 2 * delta_bytes(p) + (use_mfma(p) ? 2 * packed_set_bytes(p) + dkdv_part_bytes(p) : 0);
@@ -286,7 +284,7 @@ int l2a_attn_fwd(const l2a_params* p, const void* q_loc, const void* k_loc, cons
         if ((r = mfma_fwd_pair(g, rs_l, q_loc, k_loc, v_loc, vt_loc, out_l, rs_g, q_glb, k_glb, v_glb, vt_glb, out_g,
                                kv_cap(*p), (int32_t*)after_v, st)) != L2A_OK)
             return r;
-        return merge_rows(g, rs_g, nullptr, A32, O, st);
+        return merge_rows(g, rs_g, A32, O, st);
     }
     if (fp32_parts(*p) && kblk_first_row && q_glb == q_loc && k_glb == k_loc && v_glb == v_loc && workspace &&
         workspace_bytes >= fwd_workspace_bytes(*p) && !misaligned(workspace)) {
@@ -358,21 +356,18 @@ int l2a_attn_bwd(const l2a_params* p, const void* dO, const void* q_loc, const v
     float* delta_l = (float*)workspace;
     float* delta_g = delta_glb_opt ? delta_glb_opt : (float*)((char*)workspace + delta_bytes(*p));
     const bool mfma = use_mfma(*p), fp32 = p->dtype == L2A_FP32;
-    // Shared inputs and summed gradients: the window of a routed row counts once for both branches, and the Global pass
-    // only takes the keys before it (none at all while the window spans the sequence).
-    const bool fold = may_fold(*p) && out_alias && workspace_bytes >= bwd_workspace_bytes(*p);
     char* packed_base = (char*)workspace + 2 * delta_bytes(*p);
-    // Until the rows are packed their place is free.  dQ of a folded row is the sum of two passes' parts, kept in fp32 where
-    // its branch's rows will lie and rounded once; the rows' shares lie where the second set's statistics will.
-    // (fp32: the shares behind the deltas, then the parts of dQ.)
-    float* wide_l = fold && mfma ? (float*)packed_base : nullptr;
-    float* wide_g = fold && mfma ? (float*)(packed_base + packed_set_bytes(*p)) : nullptr;
-    float* share = !fold ? nullptr : mfma ? (float*)(packed_base + packed_set_bytes(*p) + 2 * rows_copy_bytes(*p)) : (float*)packed_base;
+    // fp32, shared inputs and summed gradients: the window of a routed row counts once for both branches, and the Global rows
+    // only take the keys before it (none at all while the window spans the sequence).  Behind the deltas the rows' shares
+    // (row_stats), then the parts of dQ.  (bf16 computes the window for each branch: one rounding of P and dS for both
+    // cost dK 1.4 % and dV 0.9 % of their error against 64 bits at 16379 tokens.)
+    const bool fold = fp32_parts(*p) && out_alias && workspace_bytes >= bwd_workspace_bytes(*p);
+    float* share = fold ? (float*)packed_base : nullptr;
     const int far_shift = fold ? g.W + 1 : 0;
     const bool far_rows = !fold || g.T > far_shift;
     auto bwd_dq = [&](const RowSet& rs, const void* q, const void* k, const void* v, const float* lse, float* delta,
                       void* dq, int acc) {
-        if (mfma) return mfma_bwd_dq(g, rs, q, k, v, dO, lse, delta, share, dq, acc, far_rows ? wide_l : nullptr, st);
+        if (mfma) return mfma_bwd_dq(g, rs, q, k, v, dO, lse, delta, dq, acc, st);
         return fp32 ? fp32_bwd_dq(g, rs, q, k, v, dO, lse, delta, dq, acc, st)
                     : simple_bwd_dq(g, rs, q, k, v, dO, lse, delta, dq, acc, st);
     };
@@ -382,20 +377,23 @@ int l2a_attn_bwd(const l2a_params* p, const void* dO, const void* q_loc, const v
     if ((r = row_stats(g, p->dtype, dO, do_local ? &stats_l : nullptr, do_global ? &stats_g : nullptr, rs_g, share, st)) != L2A_OK)
         return r;
 
-    // dQ: one pass per branch over that branch's rows; short sequences: both in one launch
-    if (fp32 && fold) {
+    // dQ: one pass per branch over that branch's rows; short sequences: both in one launch, the Global branch's
+    // share of a summed dQ in fp32 first (where the packed rows go afterwards) and added with the one rounding
+    // the sequential order has
+    if (fold) {
         if ((r = fp32_bwd_dq_shared(g, rs_l, rs_g, q_loc, k_loc, v_loc, dO, lse_local, lse_global, delta_l, delta_g, share, dq_loc,
                                     packed_base + delta_bytes(*p), st)) != L2A_OK)
             return r;
-    } else if (pair_bwd(*p) && far_rows) {
+    } else if (pair_bwd(*p)) {
         if (!out_alias && (r = fill_zero(dq_glb, q_elems(*p) * elem_bytes(*p), st)) != L2A_OK) return r;
+        float* wide = out_alias ? (float*)packed_base : nullptr;
         if ((r = mfma_bwd_dq_pair(g, rs_l, q_loc, k_loc, v_loc, lse_local, delta_l, dq_loc, rs_g, q_glb, k_glb, v_glb,
-                                  lse_global, delta_g, share, dq_glb, wide_l, wide_g, dO, st)) != L2A_OK)
+                                  lse_global, delta_g, dq_glb, wide, dO, st)) != L2A_OK)
             return r;
-        if (fold && (r = merge_rows(g, rs_g, wide_l, wide_g, dq_loc, st)) != L2A_OK) return r;
+        if (wide && (r = merge_rows(g, rs_g, wide, dq_loc, st)) != L2A_OK) return r;
     } else {
         if (do_local && (r = bwd_dq(rs_l, q_loc, k_loc, v_loc, lse_local, delta_l, dq_loc, 0)) != L2A_OK) return r;
-        if (do_global && far_rows) {
+        if (do_global) {
             if (!out_alias && !dense && (r = fill_zero(dq_glb, q_elems(*p) * elem_bytes(*p), st)) != L2A_OK) return r;
             if ((r = bwd_dq(rs_g, q_glb, k_glb, v_glb, lse_global, delta_g, dq_glb, out_alias ? 1 : 0)) != L2A_OK)
                 return r;
@@ -418,7 +416,7 @@ int l2a_attn_bwd(const l2a_params* p, const void* dO, const void* q_loc, const v
             void* out[5] = {base, base + rows_copy_bytes(*p), stat, stat + rows_stat_bytes(*p),
                             stat + 2 * rows_stat_bytes(*p)};
             const int rc2 = pack_rows(g, sets[i], qs[i], dO, lses[i], deltas[i], out[0], out[1], (float*)out[2],
-                                      (float*)out[3], (int32_t*)out[4], cap, sets[i].local ? share : nullptr, delta_g, st);
+                                      (float*)out[3], (int32_t*)out[4], cap, st);
             if (rc2 != L2A_OK) return rc2;
             for (int j = 0; j < 5; ++j) packed[i][j] = out[j];
         }

@@ -26,11 +26,9 @@ struct PackArgs {
     __bf16* xc[2];        // optional compact row-major copies [B*Hkv][cap][128]
     const float* lse;     // optional per-row statistics of the row set, [B,Hq,T]
     const float* delta;
-    const float* share;   // optional, with the Local rows: the folded rows' a (row_stats)
-    float* delta_g;       // share: in the far keys' part of the routed rows' delta_g, out delta_g
     float* lse2_c;        // [B*Hkv][cap]: lse * log2(e)
     float* delta_c;
-    int32_t* pos_c;       // last key the row sees (its position; less rs.shift), negative: none (padding: -1)
+    int32_t* pos_c;       // position, -1 for padding
     int cap;              // rows per (b, kv head) in the outputs; multiple of 64
     Fill fill[3];         // buffers to be filled on the way
     RestList rest;        // kv_rows: the rows that are not routed, listed on the way (rest.row_idx may be null)
@@ -88,9 +86,6 @@ __global__ __launch_bounds__(kThreads) void pack_token_minor_kernel(PackArgs a) 
     const int bh = blockIdx.y, b = bh / gm.Hkv, hk = bh - b * gm.Hkv;
     const int r0 = blockIdx.x * 64;
     const int n_rows = a.kv_rows ? gm.T : rows_total(a.rs, gm, bh);
-    // rows before the first one that the dK/dV walk may read (see walk::list_bounds) see nothing
-    const bool unread =
-        r0 >= n_rows || (a.rs.shift && row_code(a.rs, gm, bh, min(r0 + 64, n_rows) - 1) / gm.G < (a.rs.shift & ~63));
 
     // global element offset of row r's channel 0, or -1 for padding
     auto row_offset = [&](int r, int* pos_out, size_t* stat_out) -> long long {
@@ -110,7 +105,7 @@ __global__ __launch_bounds__(kThreads) void pack_token_minor_kernel(PackArgs a) 
     const int r4 = (threadIdx.x >> 4) * 4, c8 = (threadIdx.x & 15) * 8;
     long long offs[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) offs[i] = unread ? -1 : row_offset(r0 + r4 + i, nullptr, nullptr);
+    for (int i = 0; i < 4; ++i) offs[i] = row_offset(r0 + r4 + i, nullptr, nullptr);
     u32x4 v[2][4] = {};
 #pragma unroll
     for (int t = 0; t < 2; ++t)
@@ -122,7 +117,7 @@ __global__ __launch_bounds__(kThreads) void pack_token_minor_kernel(PackArgs a) 
     for (int i = 0; i < 3; ++i)
         if (a.fill[i].n) run_fill(a.fill[i]);
     if (a.rest.row_idx || a.rest.flags) list_rest(gm, a.rest, bh, (int)blockIdx.x, rest_bits);
-    if (unread) return;
+    if (r0 >= n_rows) return;  // the readers stop at the last row's tile
 
     // ---- -> LDS (row-major, padded), and the compact row-major copy
 #pragma unroll
@@ -140,21 +135,9 @@ __global__ __launch_bounds__(kThreads) void pack_token_minor_kernel(PackArgs a) 
         size_t so = 0;
         const long long off = row_offset(r0 + (int)threadIdx.x, &p, &so);
         const size_t o = (size_t)bh * a.cap + r0 + threadIdx.x;
-        float l2 = 0.f, dl = 0.f;
-        if (off >= 0) {
-            l2 = a.lse[so] * kLog2e;
-            dl = a.delta[so];
-            const float f = a.share ? a.share[so] : 0.f;
-            if (f != 0.f) {  // a routed row: both branches in its window as one, with the exact deltas
-                const float dg = f * dl + (p > gm.W ? a.delta_g[so] : 0.f);
-                a.delta_g[so] = dg;
-                dl = (dl + f * dg) / (1.f + f);
-                l2 -= __builtin_amdgcn_logf(1.f + f);
-            }
-        }
-        a.lse2_c[o] = l2;
-        a.delta_c[o] = -dl;  // stored negated: dP accumulators start from it
-        a.pos_c[o] = off >= 0 ? p - a.rs.shift : -1;
+        a.lse2_c[o] = off >= 0 ? a.lse[so] * kLog2e : 0.f;
+        a.delta_c[o] = off >= 0 ? -a.delta[so] : 0.f;  // stored negated: dP accumulators start from it
+        a.pos_c[o] = off >= 0 ? p : -1;
     }
     __syncthreads();
 
@@ -186,21 +169,18 @@ __global__ __launch_bounds__(kThreads) void pack_token_minor_kernel(PackArgs a) 
 // O = S + A on the rows of a set (Sec. 3.2 Eq. 5), for the forward that runs both branches in one
 // launch: O holds S, A the Global branch's rows in fp32, so that the sum is rounded once.  Sixteen
 // lanes per row, sixteen rows per workgroup.
-__global__ __launch_bounds__(kThreads) void merge_rows_kernel(Geom gm, RowSet rs, const float* __restrict__ S,
-                                                              const float* __restrict__ A,
+__global__ __launch_bounds__(kThreads) void merge_rows_kernel(Geom gm, RowSet rs, const float* __restrict__ A,
                                                               __bf16* __restrict__ O) {
     const int bh = blockIdx.y, b = bh / gm.Hkv, hk = bh - b * gm.Hkv;
     const int r = blockIdx.x * (kThreads / 16) + (threadIdx.x >> 4);
     if (r >= rows_total(rs, gm, bh)) return;
     const int code = row_code(rs, gm, bh, r);
     const int p = code / gm.G;
-    if (p < rs.shift) return;
     const int head = hk * gm.G + (code - p * gm.G);
     const size_t off = (((size_t)b * gm.T + p) * gm.Hq + head) * kD + (threadIdx.x & 15) * 8;
     const f32x8 x = *reinterpret_cast<const f32x8*>(A + off);
-    const f32x8 y = S ? *reinterpret_cast<const f32x8*>(S + off)
-                      : __builtin_convertvector(*reinterpret_cast<const bf16x8*>(O + off), f32x8);
-    *reinterpret_cast<bf16x8*>(O + off) = __builtin_convertvector(x + y, bf16x8);
+    const bf16x8 y = *reinterpret_cast<const bf16x8*>(O + off);
+    *reinterpret_cast<bf16x8*>(O + off) = __builtin_convertvector(x + __builtin_convertvector(y, f32x8), bf16x8);
 }
 
 }  // namespace
@@ -227,8 +207,7 @@ int pack_kv(const Geom& g, int n, const void* const* x, void* const* xt, int cap
 
 // rows of a branch: Q and dO -> compact row-major copies + per-row statistics
 int pack_rows(const Geom& g, const RowSet& rs, const void* q, const void* dO, const float* lse, const float* delta,
-              void* qc, void* gc, float* lse2_c, float* delta_c, int32_t* pos_c, int cap, const float* share, float* delta_g,
-              hipStream_t st) {
+              void* qc, void* gc, float* lse2_c, float* delta_c, int32_t* pos_c, int cap, hipStream_t st) {
     PackArgs a{};
     a.gm = g;
     a.rs = rs;
@@ -239,8 +218,6 @@ int pack_rows(const Geom& g, const RowSet& rs, const void* q, const void* dO, co
     a.xc[1] = (__bf16*)gc;
     a.lse = lse;
     a.delta = delta;
-    a.share = share;
-    a.delta_g = delta_g;
     a.lse2_c = lse2_c;
     a.delta_c = delta_c;
     a.pos_c = pos_c;
@@ -250,12 +227,12 @@ int pack_rows(const Geom& g, const RowSet& rs, const void* q, const void* dO, co
     return launch_status();
 }
 
-int merge_rows(const Geom& g, const RowSet& rs, const float* S, const float* A, void* O, hipStream_t st) {
+int merge_rows(const Geom& g, const RowSet& rs, const float* A, void* O, hipStream_t st) {
     if (g.D != kD) return L2A_ERR_UNSUPPORTED;
     const long long rows = (long long)g.T * g.G;
     KernelTimer kt("merge_rows", st);
     hipLaunchKernelGGL(merge_rows_kernel, dim3((unsigned)((rows + kThreads / 16 - 1) / (kThreads / 16)), g.B * g.Hkv),
-                       dim3(kThreads), 0, st, g, rs, S, A, (__bf16*)O);
+                       dim3(kThreads), 0, st, g, rs, A, (__bf16*)O);
     return launch_status();
 }
 

@@ -9,17 +9,16 @@ namespace {
 // The per-row statistics of the backward, one launch:
 //     delta_l[b,h,t] = <dO, S>, delta_g[b,h,t] = <dO, A>  (the "D" vector of the FlashAttention backward, one per branch;
 //     delta_g is also the task-loss part of the router-score gradient, Sec. 3.3 Eq. 7),
-// for bf16 those of the first tokens from their definition, and for shared inputs the fold of the routed rows.
+// for bf16 those of the first tokens from their definition, and for fp32 with shared inputs the fold of the routed rows.
 //
 // Fold.  In its window a routed row's two branches have the same scores, so that their weights differ by a
 // constant, p_g = a p_l with a = exp(lse_l - lse_g) <= 1, and what they add up to there is one row's gradient:
 //     p_l + p_g = p',   p_l (dP - delta_l) + p_g (dP - delta_g) = p' (dP - delta'),
 //     p' = exp(s - lse_l + log(1 + a)),   delta' = (delta_l + a delta_g) / (1 + a).
 // The Local pass runs over these rows, and the Global pass only over the keys before the window: the window's
-// (row, key) pairs are computed once instead of twice.  Training step, W = 4096, 20 % routed, before / after: T = 16379
-// (32 / 8 heads) 6389 / 5740 us, T = 131072 (28 / 4 heads) 125.9 / 121.2 ms.  dK and dV take one rounding of the sum of
-// two weights where they took two independent ones: their error against 64 bits at T = 16379 is 1.4 % and 0.9 % larger
-// (2.83e-3 -> 2.87e-3, 2.31e-3 -> 2.33e-3 of the norm); dQ, whose two parts are now added in fp32, 2.381e-3 -> 2.380e-3.
+// (row, key) pairs are computed once instead of twice.  fp32 only: in bf16 dK and dV would take one rounding of the sum of two
+// weights where they take two independent ones, and their error against 64 bits at 16379 tokens would be 1.4 % and 0.9 % larger
+// (2.83e-3 -> 2.87e-3, 2.31e-3 -> 2.33e-3 of the norm).
 //
 // Memory-bound: a workgroup takes `tok` consecutive tokens of one sequence -- a contiguous
 // stretch of [t, h, D] rows, sixteen lanes per row, four rows of each in flight -- and transposes its results through
@@ -59,7 +58,6 @@ __device__ __forceinline__ void store_stats(const StatsArgs& a, size_t so, float
         float f = 0.f;
         if (routed) {
             f = expf(a.br[0].lse[so] - a.br[1].lse[so]);
-            f = f < 1e-30f ? 1e-30f : f;  // not zero: that marks the rows that are not folded (a NaN stays one)
             dl = (dl + f * dg) / (1.f + f);
         }
         a.share[so] = f;
@@ -125,21 +123,12 @@ __global__ __launch_bounds__(kThreads) void row_stats_kernel(StatsArgs a) {
     const int b = blockIdx.y;
     if constexpr (sizeof(E) == 2) {
         if ((int)blockIdx.x >= a.row_blocks) {  // the first tokens of one head
-            const int h = (int)blockIdx.x - a.row_blocks, hk = h / gm.G, nt = min(gm.T, kHeadTokens);
-            unsigned char* flags = reinterpret_cast<unsigned char*>(stage + 2 * kHeadTokens);  // [G][nt]
+            const int h = (int)blockIdx.x - a.row_blocks, nt = min(gm.T, kHeadTokens);
             const int which = (int)threadIdx.x >> 7, t0 = (int)(threadIdx.x >> 6 & 1) * 32;
-            if (a.share)
-                for (int i = threadIdx.x; i < gm.G * nt; i += kThreads) flags[i] = 0;
             if (a.br[which].out && t0 < nt) head_deltas(a, a.br[which], b, h, t0, stage + which * kHeadTokens);
             __syncthreads();
-            if (a.share) {
-                mark_routed(gm, a.routed, b, hk, 0, nt, flags);
-                __syncthreads();
-            }
             const int t = threadIdx.x;
-            if (t < nt)
-                store_stats(a, ((size_t)b * gm.Hq + h) * gm.T + t, stage[t], stage[kHeadTokens + t],
-                            a.share && flags[(h - hk * gm.G) * nt + t]);
+            if (t < nt) store_stats(a, ((size_t)b * gm.Hq + h) * gm.T + t, stage[t], stage[kHeadTokens + t], false);
             return;
         }
     }
@@ -227,8 +216,8 @@ int row_stats(const Geom& g, int dtype, const void* dO, const RowStats* local, c
     a.share = share;
     if (local) a.br[0] = StatsBranch{local->q, local->k, local->v, local->out, local->lse, local->delta, 1};
     if (global) a.br[1] = StatsBranch{global->q, global->k, global->v, global->out, global->lse, global->delta, 0};
-    // bf16: the first tokens of a head need 2 x 64 floats and 64 G bytes
-    const size_t head_lds = (2 * sizeof(float) + g.G) * kHeadTokens, row_lds = lds_bytes(tok);
+    // bf16: the first tokens of a head need 2 x 64 floats
+    const size_t head_lds = 2 * sizeof(float) * kHeadTokens, row_lds = lds_bytes(tok);
     const size_t lds = dtype == L2A_BF16 && head_lds > row_lds ? head_lds : row_lds;
     const dim3 grid((unsigned)(a.row_blocks + (dtype == L2A_BF16 ? g.Hq : 0)), (unsigned)g.B);
     KernelTimer kt("row_stats", st);

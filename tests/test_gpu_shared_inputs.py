@@ -1,0 +1,41 @@
+"""Layers whose branches share q, k, v against the same layers with each branch on its own: sharing may save work, but not
+change what is computed -- neither the outputs' bits nor the roundings inside the gradients."""
+import pytest
+import torch
+
+from paper_2603_17484_amd import binding as B
+from paper_2603_17484_amd.runner import layer_from_numpy, to_device
+from tests.gpu_helpers import make_case
+
+pytestmark = pytest.mark.gpu
+
+
+def branch_gradients(lay, dO, skip):
+    """dq, dk, dv of one branch, from the outputs that the layer's forward saved."""
+    p = B.make_params(lay.p.B, lay.p.T, lay.p.Hq, lay.p.Hkv, lay.p.D, lay.p.W, lay.p.mask_heads, lay.p.dtype, skip, lay.p.softmax_scale)
+    dq, dk, dv, ws = B.alloc_bwd(p, dO.device)
+    B.l2a_attn_bwd(p, dO, lay.q, lay.k, lay.v, lay.q, lay.k, lay.v, lay.row_idx, lay.count, lay.first, lay.S, lay.A, lay.lse_l,
+                   lay.lse_g, dq, dk, dv, dq, dk, dv, None, ws)
+    return dq, dk, dv
+
+
+@pytest.mark.parametrize("order", [0, B.L2A_FLAG_SEQUENTIAL])
+@pytest.mark.parametrize("T,W,Hq,Hkv,Hm,f", [(700, 100, 8, 2, 8, 0.4), (900, 900, 7, 1, 1, 0.3), (1700, 601, 20, 20, 20, 0.2)])
+def test_gradients_are_the_sums_of_the_branches_gradients(T, W, Hq, Hkv, Hm, f, order):
+    """P and dS of each branch are rounded to bf16 for themselves, so that the summed gradients differ from the sum of the
+    branches' only by the roundings of stored results: 2^-8 of each of the three numbers, and the order of fp32 sums (2e-5:
+    of at most 2 x 1700 terms below one).  One rounding of the two branches' common weight is an error of the size of the terms,
+    which shows where they cancel."""
+    x = make_case(B_=2, T=T, Hq=Hq, Hkv=Hkv, W=W, Hm=Hm, f=f, seed=T)
+    lay = layer_from_numpy(x.q, x.k, x.v, x.mask, W, "bf16", order)
+    lay.route()
+    lay.forward()
+    dO = to_device(x.dO, "bf16")
+    lay.backward(dO)
+    local, glob = branch_gradients(lay, dO, B.L2A_FLAG_SKIP_GLOBAL), branch_gradients(lay, dO, B.L2A_FLAG_SKIP_LOCAL)
+    torch.cuda.synchronize()
+    for name, both, l, g in zip(("dq", "dk", "dv"), (lay.dq, lay.dk, lay.dv), local, glob):
+        both, l, g = both.double(), l.double(), g.double()
+        over = (both - (l + g)).abs() - (2.0 ** -8 * (both.abs() + l.abs() + g.abs()) + 2e-5)
+        print(name, "elements beyond the bound:", int((over > 0).sum()), "of", over.numel(), "worst", float(over.max()), flush=True)
+        assert over.max() <= 0, name
