@@ -30,7 +30,7 @@ PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA peak
 TRAFFIC_SOURCE = ("NOT measured in this run: constant copied from profiles/all_kernels_train_128k_hbm_bytes.md, two "
                   "rocprofv3 --pmc runs of `bench.py --sparse-only --calibrate-copy` on the same workload")
 MEASURED_TRAFFIC_BYTES = {"bwd_dkdv": 1.564e10, "bwd_dq_global": 2.966e10, "bwd_dq_local": 4.25e9,
-                          "fwd_shared": 3.577e10}
+                          "fwd_global": 2.646e10, "fwd_local": 5.44e9}
 
 
 def pair_counts(mask: np.ndarray, Hq: int, Hkv: int, T: int, W: int, dense: bool):
@@ -47,13 +47,6 @@ def pair_counts(mask: np.ndarray, Hq: int, Hkv: int, T: int, W: int, dense: bool
         glob = float(per.sum()) * rep
         frac = float((mask != 0).mean())
     return local, glob, frac
-
-
-def pairs_before_window(mask: np.ndarray, Hq: int, T: int, W: int) -> float:
-    """(row, key) pairs of the routed rows with keys before their window: the pairs that both branches have lie in the
-    window, and with shared inputs the kernels compute those once."""
-    far = np.maximum(np.arange(T, dtype=np.float64) - W, 0)
-    return float(((mask != 0).astype(np.float64) @ far).sum()) * (Hq // mask.shape[1])
 
 
 def main() -> int:
@@ -238,10 +231,9 @@ def main() -> int:
         _, pg_dense, _ = pair_counts(mask_np, w.Hq, w.Hkv, T, w.W, dense=True)
 
     # ---- roofline of the dominant kernel (live HIP-event durations over the timed region)
-    pf = pairs_before_window(mask_np, w.Hq, T, w.W)
     alg = {  # algorithmic FLOPs per launch; the backward's 10 D per pair = 8 D (S, dP, dV, dK) + 2 D (dQ)
         "bwd_dq_local": 2.0 * D * pl, "bwd_dq_global": 2.0 * D * pg, "bwd_dq_pair": 2.0 * D * (pl + pg),
-        "bwd_dkdv": 8.0 * D * (pl + pg), "fwd_shared": 4.0 * D * (pl + pf), "fwd_whole": 4.0 * D * pl, "fwd_pair": 4.0 * D * (pl + pg),
+        "bwd_dkdv": 8.0 * D * (pl + pg), "fwd_whole": 4.0 * D * pl, "fwd_pair": 4.0 * D * (pl + pg),
         "fwd_local": 4.0 * D * pl, "fwd_global": 4.0 * D * pg,
     }
     dom = max((n for n in kern if n in alg), key=lambda n: kern[n])
@@ -281,8 +273,8 @@ def main() -> int:
             "ms_layer": round(ms_dense, 3),
             "ms_layer_graph_replay": None if ms_dense_graph is None else round(ms_dense_graph, 3),
             "speedup_sparse_vs_dense": round((ms_dense_graph or ms_dense) / ms_sparse, 3),
-            # the kernel that runs on Global rows only (the dK/dV kernel walks both row sets in one launch)
-            "speedup_global_kernels": {k: round(kern_dense[k] / kern[k], 3) for k in ("bwd_dq_global",)
+            # the kernels that run on Global rows only (the dK/dV kernel walks both row sets in one launch)
+            "speedup_global_kernels": {k: round(kern_dense[k] / kern[k], 3) for k in ("fwd_global", "bwd_dq_global")
                                        if kern.get(k) and kern_dense.get(k)},
             "tflops_layer": round(mult * D * (pl + pg_dense) / (ms_dense * 1e-3) / 1e12, 2),
             "kernels_ms": {n: round(t, 3) for n, t in kern_dense.items()}},

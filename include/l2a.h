@@ -89,8 +89,7 @@ const char* l2a_strerror(int code);
  * calls; calls that share one workspace must be ordered on one stream.  What it holds:
  *   route     one int32 count per (b, KV head, chunk of 2048 positions; of 256 for T <= 16384)
  *   forward   bf16, D = 128 without L2A_FLAG_SCALAR: a token-minor copy [B,Hkv,D,ceil64(T)] of
- *             each branch's V (shared inputs: in place of the second, the list of the rows that are not
- *             routed) and one int32 flag per tile of 256 rows (tiles per (b, KV head) rounded up to a
+ *             each branch's V (shared inputs: in place of the second, a flag per row: routed) and one int32 flag per tile of 256 rows (tiles per (b, KV head) rounded up to a
  *             multiple of 8; 1 for a tile whose softmax needed a running maximum); when both branches run in one launch (see
  *             l2a_attn_fwd) the flags twice and a [B,T,Hq,D] float buffer for a; L2A_FP32, both branches with
  *             routing lists, T > 256: optional room (at most 8 [B,T,Hq,D] float buffers and statistics) for the partial sums that
@@ -182,9 +181,7 @@ int l2a_router_decide(const l2a_params* p, int32_t C, const void* x, const float
  *   A_opt       out optional [B,T,Hq,D]: d a alone, zero where d = 0 (needed by l2a_attn_bwd)
  *
  * With bf16, D = 128, both branches, routing lists in use and shared inputs (each *_glb pointer equal to its
- * *_loc partner), a routed row's window need not be computed twice.  While W >= T - 1 (s = a for routed rows) every row
- * is computed once; in long sequences a routed row's workgroup walks the window, which gives s, and then the keys
- * before it, which gives a.  Either is one launch, whatever the order flags.
+ * *_loc partner), s = a for routed rows while W >= T - 1, and every row is computed once, in one launch, whatever the order flags.
  * Otherwise (and without kblk_first_row) the branches run apart.  While they are short (at most
  * 2048 tiles of 256 rows over all (b, KV head)) the Global rows' tiles alone would occupy a fraction of the chip, so
  * the two branches run in one launch, the Global one leaves a in fp32 in the workspace, and a

@@ -6,7 +6,7 @@
 // The epilogue writes the log-sum-exp and merges into O (Sec. 3.1 Eq. 5), so the scatter of
 // Alg. 1's last step costs no extra pass.
 //
-// Layers whose branches share q, k, v take the routed rows with both branches in one walk (kBoth, fwd_shared_kernel).
+// Layers whose branches share q, k, v take every row once while the window spans the sequence (kWhole, fwd_whole_kernel).
 //
 // Work decomposition.  One workgroup = 8 wavefronts of 32 rows = a tile of 256 consecutive rows of
 // one (batch, KV head); the rows of the G query heads of the group are interleaved, so every row of
@@ -50,7 +50,7 @@ struct FwdArgs {
     int32_t* redo;  // [B*Hkv][redo_stride]: set to 1 for a tile of 256 rows that was left to running_max_body
     int redo_stride;
     FwdOut out;
-    // kBoth, kWhole: `out` is where a goes (main_out: o); s and its log-sum-exp
+    // kWhole: `out` is where a goes (main_out: o); s and its log-sum-exp
     __bf16* s_out = nullptr;
     float* s_lse = nullptr;
     const unsigned char* routed = nullptr;  // kWhole: [B*Hkv][T*G], by row code
@@ -67,11 +67,12 @@ using Int = std::integral_constant<int, V>;
 // NW wavefronts of NQB x 32 rows each.  256 rows (NW * NQB = 8): 4 x 2 runs one wavefront per SIMD with 500 registers,
 // 8 x 1 runs two per SIMD with 256 each, so that one wavefront's softmax arithmetic can overlap the
 // other's matrix instructions.
-// What a workgroup computes for its rows.  kBoth: routed rows of a layer whose branches share their inputs -- the window
-// first, whose sums give s, then the keys before it into the same sums, which give a: the scores of the window, and its
-// products with V, are computed once for both branches.  kWhole: all rows of such a layer while the window spans the
-// sequence: s = a, and which rows are routed only matters to what is written.
-enum Kind { kGlobal, kLocal, kBoth, kWhole };
+// What a workgroup computes for its rows.  kWhole: all rows of a layer whose branches share their inputs while the window
+// spans the sequence: s = a, and which rows are routed only matters to what is written.  (A shorter window is computed for each
+// branch: in one walk over the window and then the keys before it s and a share the roundings of the window's weights,
+// which their sum does not average out -- error of O against 64 bits at 32768 tokens 1.2 % larger -- and s of a token would
+// depend, in its last bits, on which other tokens are routed.)
+enum Kind { kGlobal, kLocal, kWhole };
 
 // Which tile of which (b, KV head) a workgroup takes; (bx, by) of (gx, nbh): its index in its branch's part of the grid (a
 // launch may carry both branches).
@@ -140,7 +141,8 @@ __device__ __forceinline__ void store_whole_lse(const FwdArgs& a, size_t so, flo
 }
 
 template <bool LOCAL, int NW>
-__device__ __forceinline__ void running_max_body(const FwdArgs& a, const FwdOut& out, const Tile t, FwdLds& lds, bool whole = false) {
+__device__ __forceinline__ void running_max_body(const FwdArgs& a, const Tile t, FwdLds& lds, bool whole) {
+    const FwdOut& out = a.out;
     constexpr int NQB = 1, RW = 32 * NQB, BQ = NW * RW;
     typedef __bf16 K2[2][kTileRows * kRowPad];
     typedef __bf16 V2[2][kD * kColPad];
@@ -374,7 +376,7 @@ template <Kind KIND, int NQB, int NW>
 __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds& lds) {
     auto& lds_k = lds.k;
     auto& lds_v = lds.v;
-    constexpr bool LOCAL = KIND == kLocal || KIND == kBoth;  // starts with the window
+    constexpr bool LOCAL = KIND == kLocal;
     constexpr int RW = 32 * NQB;       // rows per wavefront
     constexpr int BQ = RW * NW;        // rows per workgroup: a tile, or a whole part of one
     static_assert(kBQ % BQ == 0, "a workgroup's rows lie in one tile");
@@ -424,13 +426,7 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds&
     int j_mid = jb0;                // first block without window-start masking
     if (LOCAL) j_mid = min(jb1 + 1, max(jb0, (max(wg_pmax - gm.W, 0) + kBK - 1) / kBK));
     const int j_diag = max(j_mid, min(jb1 + 1, (wg_pmin + 1) / kBK));  // first block with a key > some row
-    // kBoth: behind the window's blocks come the ones with keys before some row's window, from block 0 on.  i-th block walked:
-    const int n_win = jb1 - jb0 + 1;
-    const int n_far = KIND == kBoth && wg_pmax > gm.W ? (wg_pmax - gm.W - 1) / kBK + 1 : 0;
-    const int n_all = n_win + n_far;
-    auto block = [&](int i) __attribute__((always_inline)) { return KIND == kBoth && i >= n_win ? i - n_win : jb0 + i; };
-    // a row sees key j if  j + key_lo <= pos  and  j + key_hi >= pos
-    int key_lo = 0, key_hi = gm.W;
+    const int n_all = jb1 - jb0 + 1;
 
     // Loads: a wave-uniform base per block plus per-lane offsets fixed for the whole kernel.
     const unsigned kv_row_bytes = (unsigned)gm.Hkv * kD * 2;
@@ -483,8 +479,8 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds&
     }
     const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     // keys of a score tile that starts at key k0 are k0 + c_row(r, h): those in reach have first <= c_row(r, 0) <= last
-    auto last_row = [&](int k0, int c) __attribute__((always_inline)) { return pos[c] - k0 - 4 * h - (KIND == kBoth ? key_lo : 0); };
-    auto first_row = [&](int k0, int c) __attribute__((always_inline)) { return pos[c] - k0 - 4 * h - (KIND == kBoth ? key_hi : gm.W); };
+    auto last_row = [&](int k0, int c) __attribute__((always_inline)) { return pos[c] - k0 - 4 * h; };
+    auto first_row = [&](int k0, int c) __attribute__((always_inline)) { return pos[c] - k0 - 4 * h - gm.W; };
 
     // One half-block (32 keys, half KB of block jb; keys k0 .. k0+31): exp of `cur` against the
     // row's fixed reference, overlapped with the scores of the next half-block into `nxt` (K rows
@@ -567,7 +563,7 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds&
     // ---- prologue: K of the first two blocks, V of the first
     Scores Sa, Sb;
     load_k(jb0, 0);
-    if (n_all > 1) load_k(block(1), 1);
+    if (n_all > 1) load_k(jb0 + 1, 1);
     load_v(jb0, 0);
     dma_wait();
     __syncthreads();
@@ -641,23 +637,13 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds&
     // One block = two half-blocks; Sa holds the scores of a block's first half on entry and exit.
     // K blocks rotate through three buffers: block jb in kbuf, jb+1 in kbuf1, and the block loaded now, jb+2, in kbuf2
     int kbuf = 0, kbuf1 = 1, kbuf2 = 2;
-    // Routed rows lie far apart where few are routed: the masked blocks of a tile are then out of reach of some wavefronts'
-    // rows altogether, and those skip the arithmetic (but not the loads, which are shared).  Blocks wanted: [w0, w1) and [n_win, w3).
-    int w0 = 0, w1 = n_all, w3 = 0;
-    if (KIND == kBoth) {
-        const int pmin = row_code(a.rs, gm, bh, min(wv_r0, n_rows - 1)) / gm.G;
-        const int pmax = row_code(a.rs, gm, bh, min(wv_r0 + RW, n_rows) - 1) / gm.G;
-        w0 = __builtin_amdgcn_readfirstlane(max(pmin - gm.W, 0) / kBK - jb0), w1 = __builtin_amdgcn_readfirstlane(pmax / kBK + 1 - jb0);
-        w3 = __builtin_amdgcn_readfirstlane(pmax > gm.W ? n_win + (pmax - gm.W - 1) / kBK + 1 : 0);
-    }
-    auto wanted = [&](int i) __attribute__((always_inline)) { return (i >= w0 && i < w1) || (i >= n_win && i < w3); };
     auto run = [&](auto mask_tag, int i_begin, int i_end) __attribute__((always_inline)) {
         for (int rel = i_begin; rel < i_end; ++rel) {
-            const int jb = block(rel);
+            const int jb = jb0 + rel;
             // prefetch: K of block jb+2 (its buffer held block jb-1), V of block jb+1 (held block jb-1),
             // issued in the slots of the first half-block where the VALU has nothing to do.  Past the
             // last block the last one is loaded again, into buffers nobody reads any more.
-            const int jk = block(min(rel + 2, n_all - 1)), jv = block(min(rel + 1, n_all - 1));
+            const int jk = min(jb + 2, jb1), jv = min(jb + 1, jb1);
             BlockLoads L;
             auto stage = [&]() __attribute__((always_inline)) {
                 L.ksrc = kbase + (size_t)jk * kBK * kv_row_bytes;
@@ -666,26 +652,14 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds&
                 L.vdst = lds_v0 + ((rel + 1) & 1) * (kD * kBK * 2);
                 L.krows = min(kBK, gm.T - jk * kBK);
             };
-            if (KIND == kBoth && decltype(mask_tag)::value && !wanted(rel)) {
-                stage();
-                static_for<0, 2 * NL>([&](auto ic) { issue_block_load(L, ic); });
-                if (wanted(rel + 1)) {  // (past the end: of a tile that nobody reads)
-#pragma unroll
-                    for (int ks = 0; ks < 8; ++ks) {
-                        const bf16x8 op = rm_operand(&lds_k[kbuf1][0], n, ks, h);
-#pragma unroll
-                        for (int c = 0; c < NQB; ++c) Sa.s[c] = mfma32(op, qreg[c][ks], ks == 0 ? zero16 : Sa.s[c]);
-                    }
-                }
-            } else {  // wavefronts whose rows all lie past the end compute on a repeated row and store nothing
-                const __bf16* vt = &lds_v[rel & 1][0];
-                half_block(mask_tag, Int<0>{}, Sa, Sb, &lds_k[kbuf][0], 32, vt, jb * kBK, [&](auto mc) {
-                    constexpr int mm = decltype(mc)::value;
-                    if constexpr (mm == kLoadSlot0 - 1) stage();
-                    if constexpr (mm >= kLoadSlot0 && mm < kLoadSlot0 + 2 * NL) issue_block_load(L, Int<mm - kLoadSlot0>{});
-                });
-                half_block(mask_tag, Int<1>{}, Sb, Sa, &lds_k[kbuf1][0], 0, vt, jb * kBK + 32, [](auto) {});
-            }
+            // wavefronts whose rows all lie past the end compute on a repeated row and store nothing
+            const __bf16* vt = &lds_v[rel & 1][0];
+            half_block(mask_tag, Int<0>{}, Sa, Sb, &lds_k[kbuf][0], 32, vt, jb * kBK, [&](auto mc) {
+                constexpr int mm = decltype(mc)::value;
+                if constexpr (mm == kLoadSlot0 - 1) stage();
+                if constexpr (mm >= kLoadSlot0 && mm < kLoadSlot0 + 2 * NL) issue_block_load(L, Int<mm - kLoadSlot0>{});
+            });
+            half_block(mask_tag, Int<1>{}, Sb, Sa, &lds_k[kbuf1][0], 0, vt, jb * kBK + 32, [](auto) {});
             dma_wait();
             __syncthreads();
             const int t = kbuf;
@@ -714,37 +688,11 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds&
     auto row_stat = [&](int c) __attribute__((always_inline)) { return ((size_t)b * gm.Hq + head[c]) * gm.T + pos[c]; };
     auto row_lse = [&](int c) __attribute__((always_inline)) { return (mref[c] + __builtin_amdgcn_logf(lt[c])) * kLn2; };
 
-    // runs of blocks: window-start masks (LOCAL), no masks, causal diagonal; keys before the window: no masks, masks
-    const int i_mid = j_mid - jb0, i_diag = j_diag - jb0;
-    const int i_edge = n_win + min(n_far, max(wg_pmin - gm.W, 0) / kBK);
-    for (int seg = 0; seg < (KIND == kBoth ? 5 : 3); ++seg) {
-        const int i_begin = seg == 0 ? 0 : seg == 1 ? i_mid : seg == 2 ? i_diag : seg == 3 ? n_win : i_edge;
-        const int i_end = seg == 0 ? i_mid : seg == 1 ? i_diag : seg == 2 ? n_win : seg == 3 ? i_edge : n_all;
-        if (KIND == kBoth && seg == 3 && n_far > 0) {
-            // the window is complete: s, to O (which the end adds a to) and to the caller's copy.  A bad sum stays bad.
-            check_sums();
-#pragma unroll
-            for (int c = 0; c < NQB; ++c) {
-                if (!valid[c]) continue;
-                const float inv = 1.f / lt[c];
-                const size_t base = row_base(c) + 4 * h;
-#pragma unroll
-                for (int d = 0; d < 4; ++d)
-#pragma unroll
-                    for (int rg = 0; rg < 4; ++rg) {
-                        const size_t off = base + d * 32 + 8 * rg;
-                        const f32x4 x = {oacc[d][c][4 * rg + 0] * inv, oacc[d][c][4 * rg + 1] * inv,
-                                         oacc[d][c][4 * rg + 2] * inv, oacc[d][c][4 * rg + 3] * inv};
-                        const bf16x4 y = __builtin_convertvector(x, bf16x4);
-                        *reinterpret_cast<bf16x4*>((__bf16*)a.out.main_out + off) = y;
-                        if (a.s_out) *reinterpret_cast<bf16x4*>(a.s_out + off) = y;
-                    }
-                if (h == 0) a.s_lse[row_stat(c)] = row_lse(c);
-            }
-            key_lo = gm.W + 1;
-            key_hi = gm.T;
-        }
-        if (seg == 1 || seg == 3)
+    // runs of blocks: window-start masks (LOCAL), no masks, causal diagonal
+    for (int seg = 0; seg < 3; ++seg) {
+        const int i_begin = seg == 0 ? 0 : seg == 1 ? j_mid - jb0 : j_diag - jb0;
+        const int i_end = seg == 0 ? j_mid - jb0 : seg == 1 ? j_diag - jb0 : n_all;
+        if (seg == 1)
             run(std::false_type{}, i_begin, i_end);
         else
             run(std::true_type{}, i_begin, i_end);
@@ -759,12 +707,7 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds&
     __syncthreads();
     if (*vote) {
         if (threadIdx.x == 0) a.redo[(size_t)bh * a.redo_stride + tile / (kBQ / BQ)] = 1;
-        if constexpr (KIND == kBoth) {  // the window first, then the whole prefix, which adds to the O that the same lanes wrote
-            running_max_body<true, NW>(a, FwdOut{a.out.main_out, a.s_out, a.s_lse, nullptr, nullptr, 0}, t, lds);
-            running_max_body<false, NW>(a, a.out, t, lds);
-        } else {
-            running_max_body<KIND == kLocal, NW>(a, a.out, t, lds, KIND == kWhole);
-        }
+        running_max_body<KIND == kLocal, NW>(a, t, lds, KIND == kWhole);
         return;
     }
 
@@ -837,7 +780,6 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds&
     __bf16* mo = (__bf16*)a.out.main_out;
     __bf16* co = (__bf16*)a.out.copy_out;
     __bf16* zf = (__bf16*)a.out.zero_fill;
-    const bool all_window = KIND == kBoth && n_far == 0;  // s = a
 #pragma unroll
     for (int c = 0; c < NQB; ++c) {
         if (!valid[c]) continue;
@@ -851,11 +793,7 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds&
                 f32x4 x = {oacc[d][c][4 * rg + 0] * inv, oacc[d][c][4 * rg + 1] * inv,
                            oacc[d][c][4 * rg + 2] * inv, oacc[d][c][4 * rg + 3] * inv};
                 if (co) *reinterpret_cast<bf16x4*>(co + off) = __builtin_convertvector(x, bf16x4);
-                if (KIND == kBoth && all_window) {
-                    const bf16x4 y = __builtin_convertvector(x, bf16x4);
-                    if (a.s_out) *reinterpret_cast<bf16x4*>(a.s_out + off) = y;
-                    x += __builtin_convertvector(y, f32x4);
-                } else if (KIND == kBoth || a.out.merge) {
+                if (a.out.merge) {
                     const bf16x4 old = *reinterpret_cast<const bf16x4*>(mo + off);
                     x += __builtin_convertvector(old, f32x4);
                 }
@@ -869,7 +807,6 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds&
         if (h == 0) {
             const size_t so = row_stat(c);
             a.out.lse_out[so] = row_lse(c);
-            if (KIND == kBoth && all_window) a.s_lse[so] = row_lse(c);
             if (a.out.lse_fill) a.out.lse_fill[so] = -INFINITY;
         }
     }
@@ -889,16 +826,6 @@ template <int NW>
 __global__ __launch_bounds__(64 * NW, 2) void fwd_whole_kernel(FwdArgs a) {
     __shared__ __attribute__((aligned(1024))) FwdLds lds;
     fwd_body<kWhole, 1, NW>(a, tile_of<32 * NW>(a.gm, a.rs, false, (int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x, (int)gridDim.y), lds);
-}
-
-// Shared inputs, long sequences: the routed rows (kBoth; the first half of the grid) and the others, which have the window
-// only, in one launch; every row belongs to one workgroup, which writes all of its outputs.
-__global__ __launch_bounds__(64 * kFwdNW, 2) void fwd_shared_kernel(FwdArgs ar, FwdArgs au, int gx) {
-    __shared__ __attribute__((aligned(1024))) FwdLds lds;
-    if ((int)blockIdx.x < gx)
-        fwd_body<kBoth, 1, kFwdNW>(ar, tile_of<kBQ>(ar.gm, ar.rs, false, (int)blockIdx.x, (int)blockIdx.y, gx, (int)gridDim.y), lds);
-    else
-        fwd_body<kLocal, 1, kFwdNW>(au, tile_of<kBQ>(au.gm, au.rs, true, (int)blockIdx.x - gx, (int)blockIdx.y, gx, (int)gridDim.y), lds);
 }
 
 // Both branches in one launch, for sequences so short that the Global rows' tiles alone leave most
@@ -969,22 +896,6 @@ int mfma_fwd_pair(const Geom& g, const RowSet& rs_l, const void* q_l, const void
             hipLaunchKernelGGL((fwd_pair_kernel<kFwdNQB, kFwdNW>), dim3(2 * gx, g.B * g.Hkv), dim3(64 * kFwdNW), 0, st, ag,
                                al, (int)gx);
     }
-    return launch_status();
-}
-
-// Shared inputs: routed rows rs_r with both branches, the rest of the rows rs_u with the window (fwd_shared_kernel).
-// out_r: a (main_out: o); S, lse_l: s of the routed rows; out_u: the other rows, with the fills for them.  redo: mfma_fwd_redo_entries flags, zero.
-int mfma_fwd_shared(const Geom& g, const RowSet& rs_r, const RowSet& rs_u, const void* q, const void* k, const void* v,
-                    const void* vt, int vt_cap, int32_t* redo, const FwdOut& out_r, void* S, float* lse_l, const FwdOut& out_u,
-                    hipStream_t st) {
-    if (g.D != kD || out_r.wide_out || out_u.wide_out || !out_r.merge) return L2A_ERR_UNSUPPORTED;
-    if ((unsigned long long)vt_cap * 2ull * kD > 0xffffffffull) return L2A_ERR_UNSUPPORTED;
-    const unsigned gx = tiles_x(g);
-    FwdArgs au{g, rs_u, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (const __bf16*)vt, vt_cap, redo, (int)gx, out_u};
-    FwdArgs ar{g, rs_r, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (const __bf16*)vt, vt_cap, redo, (int)gx, out_r,
-               (__bf16*)S, lse_l};
-    KernelTimer kt("fwd_shared", st);
-    hipLaunchKernelGGL(fwd_shared_kernel, dim3(2 * gx, g.B * g.Hkv), dim3(64 * kFwdNW), 0, st, ar, au, (int)gx);
     return launch_status();
 }
 

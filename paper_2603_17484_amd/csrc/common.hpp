@@ -126,9 +126,6 @@ int mfma_fwd_pair(const Geom& g, const RowSet& rs_l, const void* q_l, const void
                   const void* vt_l, const FwdOut& out_l, const RowSet& rs_g, const void* q_g, const void* k_g,
                   const void* v_g, const void* vt_g, const FwdOut& out_g, int vt_cap, int32_t* redo, hipStream_t st);
 
-int mfma_fwd_shared(const Geom& g, const RowSet& rs_r, const RowSet& rs_u, const void* q, const void* k, const void* v,
-                    const void* vt, int vt_cap, int32_t* redo, const FwdOut& out_r, void* S, float* lse_l, const FwdOut& out_u,
-                    hipStream_t st);
 int mfma_fwd_whole(const Geom& g, const void* q, const void* k, const void* v, const void* vt, int vt_cap, int32_t* redo,
                    const unsigned char* routed, const FwdOut& out, void* S, float* lse_l, hipStream_t st);
 
@@ -145,14 +142,13 @@ struct Fill {  // n 32-bit words of one value
     uint32_t value;
 };
 // one or two V tensors; up to three buffers are filled by the same launch
-// rest (optional): the rows that are not in `routed` (which has its kblk_first_row), as another list
-struct RestList {
+// flags (optional, [B,Hkv,T*G]): 1 where the row, by its code, is in `routed` (which has its kblk_first_row), else 0
+struct RoutedFlags {
     RowSet routed;
-    int32_t *row_idx, *count;  // [B,Hkv,T*G], [B,Hkv]
-    unsigned char* flags;      // instead of the list: [B,Hkv,T*G], 1 where the row is routed
+    unsigned char* flags;
 };
 int pack_kv(const Geom& g, int n, const void* const* x, void* const* xt, int cap, const Fill* fills, int nfills,
-            const RestList* rest, hipStream_t st);
+            const RoutedFlags* flags, hipStream_t st);
 // O += A on the rows of rs (O bf16, A fp32, D = 128)
 int merge_rows(const Geom& g, const RowSet& rs, const float* A, void* O, hipStream_t st);
 int pack_rows(const Geom& g, const RowSet& rs, const void* q, const void* dO, const float* lse, const float* delta,

@@ -60,19 +60,6 @@ bool pair_fwd(const l2a_params& p) {
     return use_mfma(p) && !(f & (L2A_FLAG_DENSE | L2A_FLAG_SKIP_LOCAL | L2A_FLAG_SKIP_GLOBAL | L2A_FLAG_SEQUENTIAL)) &&
            mfma_fwd_redo_entries(make_geom(p)) <= kPairMaxTiles;
 }
-// Shared inputs, a window shorter than the sequence: whether the routed rows' walk through the window and the keys before it
-// beats the branches on their own (pair_fwd or two launches).  While the tiles are few it is the longest one of the launch, and
-// where few rows are routed their tiles span many windows' starts, so the windows of all rows have to be enough to hide
-// it: T / 64 blocks of keys against B Hq (W - W^2 / 2T) / 2^16 per block of keys and compute unit, 1.25 times that.  Whole forward, us, apart /
-// in one walk: T = 4000, W = 1024, 5 % routed, 32 / 8 heads (30 against 63 blocks) 123 / 186; T = 12000 365 / 400; T = 5000, W =
-// 4096, 28 / 4 heads (63 against 78) 218 / 214; training step of T = 16379, W = 4096, 32 / 8 heads (450 against 256) 5651 / 5448.
-// More tiles: T = 24000, W = 1024, 5 % 1141 / 849; T = 32768, W = 4096, 20 % 3200 / 2920; in sequences of many windows it
-// gains nothing, T = 60000, W = 1024, 5 / 10 / 25 % 2861 / 2823, 4003 / 4117, 8347 / 8418; W = 4096, 5 % 5511 / 5294.
-bool one_walk_pays(const l2a_params& p) {
-    const Geom g = make_geom(p);
-    if (mfma_fwd_redo_entries(g) > kPairMaxTiles) return g.T / 32 <= g.W;
-    return (double)g.B * g.Hq * (g.W - 0.5 * g.W * g.W / g.T) >= 80000.0;
-}
 // The backward's dQ alike (its workspace is the same either way).  Measured with 128 Local rows per workgroup in both,
 // Hq = 28, Hkv = 4, both kernels / the pair, us:
 // T = 1000, 5 % routed 174 / 33, 20 % 122 / 33; T = 4096, W = 4096, 5 / 20 / 50 % 446 / 217, 389 / 244, 397 / 296;
@@ -230,31 +217,22 @@ int l2a_attn_fwd(const l2a_params* p, const void* q_loc, const void* k_loc, cons
     // matrix-core path: token-minor copy of each distinct V (layout pre-pass, one pass over V)
     char* vt_loc = (char*)workspace;
     char* vt_glb = vt_loc;
-    // Shared inputs.  While the window spans the sequence s = a, and every row is computed once.  Otherwise routed rows may
-    // take both branches in one walk and the other rows the window, in one launch (their list, or the routed rows' flags, lie
-    // where a second V copy would: 4 G bytes per token and KV head of 256, or G).  Lists without kblk_first_row take the
-    // branches as they come.
+    // Shared inputs, and the window spans the sequence: s = a, and every row is computed once (the routed rows' flags lie
+    // where a second V copy would: G bytes per token and KV head of 256).  Lists without kblk_first_row take the branches as
+    // they come.
     const bool one_input = mfma && do_local && do_global && !dense && kblk_first_row && q_glb == q_loc && k_glb == k_loc && v_glb == v_loc;
-    const bool whole = one_input && p->T - 1 <= p->W, shared = one_input && !whole && one_walk_pays(*p);
-    const bool pair = pair_fwd(*p) && !whole && !shared;
-    if (whole || shared) {
+    const bool whole = one_input && p->T - 1 <= p->W;
+    const bool pair = pair_fwd(*p) && !whole;
+    if (whole) {
         char* after_v = (char*)workspace + 2 * kv_copy_bytes(*p);
-        char* instead = (char*)workspace + kv_copy_bytes(*p);
-        int32_t* rest = (int32_t*)instead;
-        int32_t* n_rest = rest + (size_t)p->B * p->Hkv * p->T * g.G;
-        const RowSet rs_r{row_idx, count, kblk_first_row, 0};
-        const RestList rl{rs_r, whole ? nullptr : rest, whole ? nullptr : n_rest, whole ? (unsigned char*)instead : nullptr};
+        const RoutedFlags rf{RowSet{row_idx, count, kblk_first_row, 0}, (unsigned char*)workspace + kv_copy_bytes(*p)};
         const void* vs[1] = {v_loc};
         void* vts[1] = {vt_loc};
         // the flags of both branches where there is room for them (the second half stays zero)
         const Fill flags{(uint32_t*)after_v, (pair_fwd(*p) ? 2 : 1) * mfma_fwd_redo_entries(g), 0u};
-        if ((r = pack_kv(g, 1, vs, vts, kv_cap(*p), &flags, 1, &rl, st)) != L2A_OK) return r;
-        const FwdOut out_r{O, A_opt, lse_global, nullptr, nullptr, 1};
-        if (whole)
-            return mfma_fwd_whole(g, q_loc, k_loc, v_loc, vt_loc, kv_cap(*p), (int32_t*)after_v, rl.flags, out_r, S_opt, lse_local, st);
-        const FwdOut out_u{O, S_opt, lse_local, lse_global, A_opt, 0};
-        return mfma_fwd_shared(g, rs_r, RowSet{rest, n_rest, nullptr, 1}, q_loc, k_loc, v_loc, vt_loc, kv_cap(*p),
-                               (int32_t*)after_v, out_r, S_opt, lse_local, out_u, st);
+        if ((r = pack_kv(g, 1, vs, vts, kv_cap(*p), &flags, 1, &rf, st)) != L2A_OK) return r;
+        const FwdOut out{O, A_opt, lse_global, nullptr, nullptr, 1};
+        return mfma_fwd_whole(g, q_loc, k_loc, v_loc, vt_loc, kv_cap(*p), (int32_t*)after_v, rf.flags, out, S_opt, lse_local, st);
     }
     if (mfma) {
         const void* vs[2];

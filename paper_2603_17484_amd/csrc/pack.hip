@@ -31,7 +31,7 @@ struct PackArgs {
     int32_t* pos_c;       // position, -1 for padding
     int cap;              // rows per (b, kv head) in the outputs; multiple of 64
     Fill fill[3];         // buffers to be filled on the way
-    RestList rest;        // kv_rows: the rows that are not routed, listed on the way (rest.row_idx may be null)
+    RoutedFlags routed;   // kv_rows: which rows are routed, marked on the way (routed.flags may be null)
 };
 
 // A launch costs a short forward as much as the kernel it carries (about 3 us each), so the constants that its
@@ -48,40 +48,27 @@ __device__ __forceinline__ void run_fill(const Fill& f) {
     for (i += done; i < f.n; i += step) f.p[i] = f.value;
 }
 
-// The rows of positions 64 kb .. 64 kb + 63 that are not in the routed list, in ascending order, to their place in the rest
-// list: code - (routed rows before it).  Which are routed is gathered as bits from the list's entries first[kb] .. first[kb+1].
+// Which rows of positions 64 kb .. 64 kb + 63 are routed: gathered as bits from the list's entries first[kb] .. first[kb+1]
 constexpr int kMaxG = 16;  // Hq / Hkv at most
-__device__ __forceinline__ void list_rest(const Geom& gm, const RestList& rl, int bh, int kb, unsigned long long (&bits)[kMaxG]) {
-    const int nkb = (gm.T + 63) / 64, all = gm.T * gm.G, n = rows_total(rl.routed, gm, bh);
+__device__ __forceinline__ void mark_routed(const Geom& gm, const RoutedFlags& rf, int bh, int kb, unsigned long long (&bits)[kMaxG]) {
+    const int nkb = (gm.T + 63) / 64, n = rows_total(rf.routed, gm, bh);
     if (kb >= nkb) return;
-    const int32_t* first = rl.routed.kblk_first_row + (size_t)bh * (nkb + 1) + kb;
+    const int32_t* first = rf.routed.kblk_first_row + (size_t)bh * (nkb + 1) + kb;
     const int f0 = min(max(first[0], 0), n), f1 = min(max(first[1], f0), n);
     const int c0 = kb * 64 * gm.G, codes = min(64, gm.T - kb * 64) * gm.G;
     if (threadIdx.x < kMaxG) bits[threadIdx.x] = 0;
     __syncthreads();
     for (int i = f0 + (int)threadIdx.x; i < f1; i += kThreads) {
-        const int c = row_code(rl.routed, gm, bh, i) - c0;
+        const int c = row_code(rf.routed, gm, bh, i) - c0;
         if (c >= 0 && c < codes) atomicOr(&bits[c >> 6], 1ull << (c & 63));
     }
     __syncthreads();
-    if (rl.flags) {
-        for (int c = threadIdx.x; c < codes; c += kThreads) rl.flags[(size_t)bh * all + c0 + c] = bits[c >> 6] >> (c & 63) & 1;
-        return;
-    }
-    for (int c = threadIdx.x; c < codes; c += kThreads) {
-        int before = f0;
-        for (int w = 0; w < c >> 6; ++w) before += __popcll(bits[w]);
-        const unsigned long long word = bits[c >> 6];
-        before += __popcll(word & ((1ull << (c & 63)) - 1));
-        const int at = c0 + c - before;
-        if (!(word >> (c & 63) & 1) && at >= 0 && at < all) rl.row_idx[(size_t)bh * all + at] = c0 + c;
-    }
-    if (kb == nkb - 1 && threadIdx.x == 0) rl.count[bh] = all - n;
+    for (int c = threadIdx.x; c < codes; c += kThreads) rf.flags[(size_t)bh * gm.T * gm.G + c0 + c] = bits[c >> 6] >> (c & 63) & 1;
 }
 
 __global__ __launch_bounds__(kThreads) void pack_token_minor_kernel(PackArgs a) {
     __shared__ __attribute__((aligned(16))) __bf16 lds[2][kTileRows * kRowPad];
-    __shared__ unsigned long long rest_bits[kMaxG];
+    __shared__ unsigned long long routed_bits[kMaxG];
     const Geom& gm = a.gm;
     const int bh = blockIdx.y, b = bh / gm.Hkv, hk = bh - b * gm.Hkv;
     const int r0 = blockIdx.x * 64;
@@ -99,7 +86,7 @@ __global__ __launch_bounds__(kThreads) void pack_token_minor_kernel(PackArgs a) 
         return (((long long)b * gm.T + p) * gm.Hq + head) * kD;
     };
 
-    // ---- 64 rows, on their way while the constants and the list are written: a workgroup's time is the chain of its dependent
+    // ---- 64 rows, on their way while the constants and the flags are written: a workgroup's time is the chain of its dependent
     // loads (list bounds, list, then the rows), T = 1001 with 4 KV heads 6.9 -> 5.7 us; the rows of two tensors in flight
     // together, 2 x 4000 tokens with 4 KV heads 47.2 + 19.3 -> 42.0 + 17.1 us (5.4 TB/s).
     const int r4 = (threadIdx.x >> 4) * 4, c8 = (threadIdx.x & 15) * 8;
@@ -116,7 +103,7 @@ __global__ __launch_bounds__(kThreads) void pack_token_minor_kernel(PackArgs a) 
 #pragma unroll
     for (int i = 0; i < 3; ++i)
         if (a.fill[i].n) run_fill(a.fill[i]);
-    if (a.rest.row_idx || a.rest.flags) list_rest(gm, a.rest, bh, (int)blockIdx.x, rest_bits);
+    if (a.routed.flags) mark_routed(gm, a.routed, bh, (int)blockIdx.x, routed_bits);
     if (r0 >= n_rows) return;  // the readers stop at the last row's tile
 
     // ---- -> LDS (row-major, padded), and the compact row-major copy
@@ -187,7 +174,7 @@ __global__ __launch_bounds__(kThreads) void merge_rows_kernel(Geom gm, RowSet rs
 
 // rows = tokens of each KV head: x[i] [B,T,Hkv,128] -> xt[i] [B*Hkv][128][cap], cap = round_up(T, 64)
 int pack_kv(const Geom& g, int n, const void* const* x, void* const* xt, int cap, const Fill* fills, int nfills,
-            const RestList* rest, hipStream_t st) {
+            const RoutedFlags* flags, hipStream_t st) {
     if (n < 1 || n > 2 || nfills < 0 || nfills > 3) return L2A_ERR_UNSUPPORTED;
     PackArgs a{};
     a.gm = g;
@@ -199,7 +186,7 @@ int pack_kv(const Geom& g, int n, const void* const* x, void* const* xt, int cap
     }
     for (int i = 0; i < nfills; ++i) a.fill[i] = fills[i];
     a.cap = cap;
-    if (rest) a.rest = *rest;
+    if (flags) a.routed = *flags;
     KernelTimer kt("pack_kv", st);
     hipLaunchKernelGGL(pack_token_minor_kernel, dim3(cap / 64, g.B * g.Hkv), dim3(kThreads), 0, st, a);
     return launch_status();

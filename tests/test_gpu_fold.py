@@ -1,7 +1,8 @@
-"""A layer with shared inputs, where a routed row's window is computed once for both branches -- in the forward one walk
-over the window and then the keys before it, in the backward a Local pass over combined rows and a Global one over those keys: windows around the edges at which a row, a tile of rows or a block of keys has keys before the
-window at all (tiles of 32 and 256 rows, blocks of 64 and 128 keys), both tile widths, both orders, batches, every mask
-granularity, and scores so uneven that one branch's share of a row vanishes."""
+"""A layer with shared inputs, where the kernels may compute a routed row's window once for both branches: windows around the
+edges at which a row, a tile of rows or a block of keys has keys before the window at all (tiles of 32 and 256 rows, blocks of
+64 and 128 keys), both orders, batches, every mask granularity, and scores so uneven that one branch's share of a row vanishes.
+In bf16 that is while the window spans the sequence; the cases of shorter windows hold the branches, run apart, to the same bars.
+In fp32 the keys before the window are added in parts."""
 import numpy as np
 import pytest
 import torch

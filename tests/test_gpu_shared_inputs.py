@@ -1,5 +1,6 @@
 """Layers whose branches share q, k, v against the same layers with each branch on its own: sharing may save work, but not
 change what is computed -- neither the outputs' bits nor the roundings inside the gradients."""
+import numpy as np
 import pytest
 import torch
 
@@ -39,3 +40,34 @@ def test_gradients_are_the_sums_of_the_branches_gradients(T, W, Hq, Hkv, Hm, f, 
         over = (both - (l + g)).abs() - (2.0 ** -8 * (both.abs() + l.abs() + g.abs()) + 2e-5)
         print(name, "elements beyond the bound:", int((over > 0).sum()), "of", over.numel(), "worst", float(over.max()), flush=True)
         assert over.max() <= 0, name
+
+
+# Heads, batches and windows with which many rows have keys before their window, whole and ragged tiles of 128 and 256 rows;
+# windows that span the sequence (there every row is computed once)
+SHAPES = [(2, 1701, 64, 8, 1100, 1, 0.3), (9, 1030, 64, 8, 70, 64, 0.05), (2, 700, 8, 2, 100, 8, 0.4), (2, 1001, 28, 4, 1000, 1, 0.2),
+          (1, 2048, 65, 65, 4096, 65, 0.2), (1, 130, 16, 1, 200, 1, 1.0)]
+
+
+def forward(x, W, order=0, separate=False, mask=None):
+    lay = layer_from_numpy(x.q, x.k, x.v, x.mask if mask is None else mask, W, "bf16", order,
+                           **(dict(qg=x.q, kg=x.k, vg=x.v) if separate else {}))
+    lay.route()
+    lay.forward()
+    torch.cuda.synchronize()
+    return lay
+
+
+@pytest.mark.parametrize("Bn,T,Hq,Hkv,W,Hm,f", SHAPES)
+def test_the_same_bits_as_from_copies_of_the_inputs(Bn, T, Hq, Hkv, W, Hm, f):
+    x = make_case(B_=Bn, T=T, Hq=Hq, Hkv=Hkv, W=W, Hm=Hm, f=f, seed=T)
+    a, b = forward(x, W), forward(x, W, separate=True)
+    for n in ("O", "S", "A", "lse_l", "lse_g"):
+        assert torch.equal(getattr(a, n), getattr(b, n)), n
+
+
+@pytest.mark.parametrize("Bn,T,Hq,Hkv,W,Hm,f", SHAPES)
+def test_the_local_result_does_not_depend_on_who_else_is_routed(Bn, T, Hq, Hkv, W, Hm, f):
+    x = make_case(B_=Bn, T=T, Hq=Hq, Hkv=Hkv, W=W, Hm=Hm, f=f, seed=T + 1)
+    other = np.random.default_rng(T).random(x.mask.shape) < 0.5   # (not the complement, which groups the rows alike)
+    a, b = forward(x, W), forward(x, W, mask=other.astype(np.uint8))
+    assert torch.equal(a.S, b.S) and torch.equal(a.lse_l, b.lse_l)
