@@ -567,21 +567,19 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds&
     load_v(jb0, 0);
     dma_wait();
     __syncthreads();
-    // Reference of every row's exponentials: the largest score among the keys of the first two blocks that all rows of the
-    // 256-row tile see (by 32, no masks), or else (beginning of the sequence, routed rows far apart) among the row's own keys in
-    // these two blocks, 0 where there is none.  It is never updated: scores that come
+    // Reference of every row's exponentials: the largest score among the row's own keys in the first two blocks (no masks where
+    // the workgroup's rows see all of them), 0 where there is none.  It is never updated: scores that come
     // later may exceed it, which costs no accuracy in floating point; the epilogue checks that the
     // row sums stayed far from overflow and otherwise leaves the tile to running_max_body.  (Masks for every tile's two blocks took it to
-    // 5200 cycles of a tile's 57000 at 1001 tokens.  The first 32 keys alone would do, but the weights next to a row's largest
-    // are rounded best: error against 64 bits 1.2-1.6 % larger.)
+    // 5200 cycles of a tile's 57000 at 1001 tokens.  Fewer keys, the first 32 or those that all rows of the tile see, would do,
+    // but the weights next to a row's largest are rounded best -- error against 64 bits 1.2-1.6 % larger with 32 -- and a row
+    // whose largest score is its window's first key would overflow.)
     {  // wavefronts whose rows all lie past the end compute on a repeated row and store nothing
 #pragma unroll
         for (int c = 0; c < NQB; ++c) mref[c] = -INFINITY;
-        const int pmax_all = BQ == kBQ ? wg_pmax : row_code(a.rs, gm, bh, min(wg_r0 / kBQ * kBQ + kBQ, n_rows) - 1) / gm.G;
-        const int seen = LOCAL ? (max(pmax_all - gm.W, 0) + 31) / 32 * 32 - jb0 * kBK : 0;  // behind the first block's first key
-        if (seen <= 2 * kBK - 32 && (jb0 + 2) * kBK - 1 <= pmin_all) {
+        if ((jb0 + 2) * kBK - 1 <= wg_pmin && (!LOCAL || wg_pmax - gm.W <= jb0 * kBK)) {
 #pragma unroll 1
-            for (int at = seen; at <= 2 * kBK - 32; at += 32) {
+            for (int at = 0; at < 2 * kBK; at += 32) {
                 Scores S;
 #pragma unroll
                 for (int ks = 0; ks < 8; ++ks) {

@@ -5,8 +5,10 @@ import pytest
 import torch
 
 from paper_2603_17484_amd import binding as B
-from paper_2603_17484_amd.runner import layer_from_numpy
+from paper_2603_17484_amd.runner import layer_from_numpy, to_host
 from tests.gpu_helpers import make_case, run_and_check
+from tests.test_gpu_parity import growing_scores_case, redo_flags
+from tests.tolerance import compare
 
 pytestmark = pytest.mark.gpu
 
@@ -30,6 +32,23 @@ def test_both_widths_give_the_sequential_bits(Bn, Hkv, T, W):
         outs.append((lay.O, lay.S, lay.A, lay.lse_l, lay.lse_g))
     for a, b in zip(*outs):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("order", [0, B.L2A_FLAG_SEQUENTIAL])
+def test_the_reference_of_a_row_covers_its_own_first_keys(oracle, order):
+    """Scores fall by 3 per key, so that the first keys of a row's window have nearly all of its weight; a tile of 256 rows is 16
+    positions, whose windows begin up to 40 keys before the first half-block that all of them see.  Against the largest score
+    among the commonly seen keys such a row's sum would be e^120; against its own it is near one, and no tile needs a running
+    maximum.  (S and A are compared and not their sum: with so few keys they reach 4, and its two roundings 2.3e-2.)"""
+    x = growing_scores_case(-2700.0, T=900, Hq=16, Hkv=1, W=200)
+    ref = oracle.layer_fwd(oracle.Problem(x.q, x.k, x.v, x.mask, x.w.W))
+    lay = layer_from_numpy(x.q, x.k, x.v, x.mask, x.w.W, "bf16", order)
+    lay.route()
+    lay.forward()
+    torch.cuda.synchronize()
+    assert not redo_flags(lay).any()
+    compare("S", to_host(lay.S), ref["S"], "bf16")
+    compare("A", to_host(lay.A), ref["A"], "bf16")
 
 
 @pytest.mark.parametrize("offset", [0, 1, 15])
