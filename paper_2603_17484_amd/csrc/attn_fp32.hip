@@ -247,22 +247,6 @@ __device__ __forceinline__ unsigned keys_seen(const Geom& gm, const RowSet& rs, 
 }
 __device__ __forceinline__ float exp2_(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// The backward's weights exp(scale s - L) as exp2(c2 s - hi) f: hi = L log2(e) rounded, f what the rounding left out.  One
-// instruction and one rounding less than (scale s - L) log2(e).  (dK and dV, whose error is that of their long sums, keep
-// the latter: there the row's factor would be one more product, 2.5 % of the kernel.)
-struct RowScale {
-    float hi, f;
-};
-__device__ __forceinline__ RowScale row_scale(float L) {
-    constexpr float kLog2eLo = 1.925963033500e-8f;  // log2(e) - kLog2e
-    RowScale r;
-    r.hi = L * kLog2e;
-    const float lo = fmaf(L, kLog2e, -r.hi) + L * kLog2eLo;
-    r.f = 1.f - lo * kLn2;  // |lo| < 2^-24 |hi|
-    if (!(fabsf(lo) < 1.f)) r.f = 1.f;  // infinite or NaN: hi says it
-    return r;
-}
-
 // ---------------------------------------------------------------------------------------
 // Forward.  Workgroup = 16 RB rows, wavefront w takes the 16-key blocks w, w + NW, ... of the rows' keys with
 // a streaming softmax of its own (Alg. 1, running maximum per row); the partials are merged in LDS.
@@ -513,7 +497,7 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_bwd_dq_kernel(Geom gm, RowSet
             const int code = row_code(rs, gm, bh, min(tr.r0 + 16 * c + n, n_rows - 1));
             pos[c] = code / gm.G;
             const size_t st = ((size_t)b * gm.Hq + hk * gm.G + (code - pos[c] * gm.G)) * gm.T + pos[c];
-            L[c] = -row_scale(lse[st]).hi;
+            L[c] = lse[st];
             dl[c] = delta[st];
             pos[c] -= rs.shift;
             dx[c] = 0.f;
@@ -548,7 +532,8 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_bwd_dq_kernel(Geom gm, RowSet
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         const bool in = !MASK || ((ok >> r) & 1u);
-                        const float p = exp2_(fmaf(s[c][r], gm.scale_log2, L[c]));  // times the row's f: in the epilogue
+                        // scale s - L first: a rounded product of scale and log2(e) would put its error times the score into it
+                        const float p = exp2_(fmaf(s[c][r], gm.scale, -L[c]) * kLog2e);
                         dx[c] += in ? p * dp[c][r] : 0.f;
                         s[c][r] = in ? p * (dp[c][r] - dl[c]) : 0.f;  // dS
                     }
@@ -593,8 +578,6 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_bwd_dq_kernel(Geom gm, RowSet
 #pragma unroll
             for (int w = 0; w < NW; ++w) x += ld4(&so[w][row][ch]);
             const int code = row_code(rs, gm, bh, tr.r0 + row), p = code / gm.G, h = hk * gm.G + (code - p * gm.G);
-            const float f = row_scale(lse[((size_t)b * gm.Hq + h) * gm.T + p]).f;
-            x *= f;
             if (ro.far) {
                 const size_t at = part_row(gm, ro, bh, tr.r0 + row);
                 *reinterpret_cast<f32x4*>(parts.x + at * D + ch) = x;
@@ -602,7 +585,7 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_bwd_dq_kernel(Geom gm, RowSet
                     float d = 0.f;
 #pragma unroll
                     for (int w = 0; w < NW; ++w) d += sd[w][row];
-                    parts.s[at] = d * f;
+                    parts.s[at] = d;
                 }
                 continue;
             }
@@ -613,7 +596,7 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_bwd_dq_kernel(Geom gm, RowSet
                 float d = 0.f;
 #pragma unroll
                 for (int w = 0; w < NW; ++w) d += sd[w][row];
-                delta_main[((size_t)b * gm.Hq + h) * gm.T + p] = d * f;
+                delta_main[((size_t)b * gm.Hq + h) * gm.T + p] = d;
             }
         }
         __syncthreads();

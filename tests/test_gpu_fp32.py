@@ -6,7 +6,7 @@ import pytest
 import torch
 
 from paper_2603_17484_amd import binding as B
-from paper_2603_17484_amd.runner import layer_from_numpy, to_device
+from paper_2603_17484_amd.runner import Layer, layer_from_numpy, to_device
 from tests.gpu_helpers import make_case, run_and_check
 
 pytestmark = pytest.mark.gpu
@@ -55,3 +55,30 @@ def test_what_a_row_does_not_see_stays_out(T, bad):
     for a, b in zip(*out):
         assert np.isfinite(a[~np.isneginf(a)]).all()
         np.testing.assert_allclose(b, a, rtol=1e-5, atol=1e-5)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("T,flags,separate", [(200, 0, False), (300, 0, False), (300, 0, True), (300, B.L2A_FLAG_SKIP_LOCAL, False)])
+def test_weights_of_large_scores(T, flags, separate, D):
+    """The backward's weights exp(scale <q,k> - lse) where the score is 2000 and exact: all products of q and k are 20000, all
+    products of dO and v one, so that the exact delta it returns is the sum of a row's weights, for the log-sum-exp handed in.
+    Error: the exponent, at most log(300) = 5.7 (a row's window: 4), takes three roundings of 2^-24 (1.0e-6; with shared inputs
+    those of the fold's exp(lse_l - lse_g) too), exp2 an ulp and the sum of equal terms 300 x 2^-24 / 2 at the very most: 1.2e-5.
+    A product of scale and log2(e) rounded on its own would be off by 3e-8 of the score: 6e-5."""
+    W, scale = 50, 0.1
+    q, k, v, dO = (torch.zeros(1, T, h, D, device="cuda") for h in (2, 1, 1, 2))
+    q[..., 0], k[..., 0], v[..., 1], dO[..., 1] = 100.0, 200.0, 1.0, 1.0
+    mask = torch.zeros(1, 1, T, dtype=torch.uint8, device="cuda")
+    mask[0, 0, ::3] = 1
+    p = B.make_params(1, T, 2, 1, D, W, 1, B.L2A_FP32, flags, scale)
+    lay = Layer(p, q, k, v, mask, *([t.clone() for t in (q, k, v)] if separate else ()))
+    lay.route()
+    lay.forward()
+    lay.S.copy_(dO), lay.A.copy_(dO * mask[0, 0, None, :, None, None])
+    lay.backward(dO, separate=separate, want_delta=True)
+    torch.cuda.synchronize()
+    t = torch.arange(0, T, 3, device="cuda")
+    want = (t + 1) * torch.exp(20000.0 * np.float64(np.float32(scale)) - lay.lse_g[0, :, t].double())
+    err = ((lay.delta_g[0, :, t].double() - want) / want).abs().max()
+    print("largest relative error", float(err), flush=True)
+    assert err <= 1.2e-5
