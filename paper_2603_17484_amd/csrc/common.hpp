@@ -112,6 +112,7 @@ struct RowStats {
 };
 int row_stats(const Geom& g, int dtype, const void* dO, const RowStats* local, const RowStats* global, const RowSet& routed,
               float* share, hipStream_t st);
+bool row_stats_can_fold(const Geom& g);  // so many heads that there is no room to mark the routed rows: no share
 int fill_zero(void* ptr, size_t bytes, hipStream_t st);
 int fill_f32(float* ptr, size_t n, float value, hipStream_t st);
 

@@ -339,7 +339,7 @@ int l2a_attn_bwd(const l2a_params* p, const void* dO, const void* q_loc, const v
     // only take the keys before it (none at all while the window spans the sequence).  Behind the deltas the rows' shares
     // (row_stats), then the parts of dQ.  (bf16 computes the window for each branch: one rounding of P and dS for both
     // cost dK 1.4 % and dV 0.9 % of their error against 64 bits at 16379 tokens.)
-    const bool fold = fp32_parts(*p) && out_alias && workspace_bytes >= bwd_workspace_bytes(*p);
+    const bool fold = fp32_parts(*p) && out_alias && row_stats_can_fold(g) && workspace_bytes >= bwd_workspace_bytes(*p);
     float* share = fold ? (float*)packed_base : nullptr;
     const int far_shift = fold ? g.W + 1 : 0;
     const bool far_rows = !fold || g.T > far_shift;

@@ -118,7 +118,7 @@ __device__ __forceinline__ void head_deltas(const StatsArgs& a, const StatsBranc
 constexpr int kFlight = 4;  // rows of sixteen lanes whose loads are in flight together
 template <typename E, int DL>
 __global__ __launch_bounds__(kThreads) void row_stats_kernel(StatsArgs a) {
-    extern __shared__ float stage[];  // [2][Hq][tok] products, then one byte per row: routed
+    extern __shared__ float stage[];  // [2][Hq][tok] products; fold: then one byte per row, routed
     const Geom& gm = a.gm;
     const int b = blockIdx.y;
     if constexpr (sizeof(E) == 2) {
@@ -199,14 +199,21 @@ __global__ __launch_bounds__(kThreads) void fill_u32_kernel(uint32_t* p, size_t 
 
 }  // namespace
 
+namespace {
+constexpr size_t kStatsLds = 64 * 1024;
+size_t stats_lds(const Geom& g, int tok, bool fold) { return (size_t)g.Hq * tok * (2 * sizeof(float) + (fold ? 1 : 0)); }
+}  // namespace
+
+bool row_stats_can_fold(const Geom& g) { return stats_lds(g, 1, true) <= kStatsLds; }
+
 int row_stats(const Geom& g, int dtype, const void* dO, const RowStats* local, const RowStats* global, const RowSet& routed,
               float* share, hipStream_t st) {
-    auto lds_bytes = [&](int tok) { return (size_t)g.Hq * tok * 9; };
+    auto lds_bytes = [&](int tok) { return stats_lds(g, tok, share != nullptr); };
     int tok = 64;  // tokens per workgroup: as many as fit 64 KB of LDS with Hq heads
-    while (tok > 1 && lds_bytes(tok) > 64 * 1024) tok /= 2;
+    while (tok > 1 && lds_bytes(tok) > kStatsLds) tok /= 2;
     // short sequences: fewer tokens per workgroup rather than a grid that leaves most of the chip idle
     while (tok > 2 && tok * g.Hq > kFlight * (kThreads / 16) && (long long)((g.T + tok - 1) / tok) * g.B < 1024) tok /= 2;
-    if (lds_bytes(tok) > 64 * 1024) return L2A_ERR_UNSUPPORTED;
+    if (lds_bytes(tok) > kStatsLds) return L2A_ERR_UNSUPPORTED;
     StatsArgs a{};
     a.gm = g;
     a.dO = dO;
