@@ -42,14 +42,18 @@ struct StatsArgs {
     float* share;    // fold: a, 0 on rows that are not routed (null: no fold)
 };
 
-// marks the routed rows of positions t0 .. t0 + n - 1 (inside one block of 64) of KV head hk: flags[g * n + t - t0]
-__device__ __forceinline__ void mark_routed(const Geom& gm, const RowSet& rs, int b, int hk, int t0, int n, unsigned char* flags) {
-    const int bh = b * gm.Hkv + hk, total = rows_total(rs, gm, bh);
-    const int32_t* first = rs.kblk_first_row + (size_t)bh * ((gm.T + 63) / 64 + 1) + (t0 >> 6);
-    const int f0 = min(max(first[0], 0), total), f1 = min(max(first[1], f0), total);
-    for (int i = f0 + (int)threadIdx.x; i < f1; i += kThreads) {
-        const int code = row_code(rs, gm, bh, i), p = code / gm.G, t = p - t0;
-        if (t >= 0 && t < n) flags[(code - p * gm.G) * n + t] = 1;
+// Marks the routed rows of positions t0 .. t0 + n - 1 (inside one block of 64): flags[head * n + t - t0].  The KV heads side
+// by side, 64 or 16 lanes each: one after the other their three dependent loads were the workgroup's time where there are many.
+__device__ __forceinline__ void mark_routed(const Geom& gm, const RowSet& rs, int b, int t0, int n, unsigned char* flags) {
+    const int lanes = gm.Hkv >= kThreads / 16 ? 16 : 64;
+    for (int hk = (int)threadIdx.x / lanes; hk < gm.Hkv; hk += kThreads / lanes) {
+        const int bh = b * gm.Hkv + hk, total = rows_total(rs, gm, bh);
+        const int32_t* first = rs.kblk_first_row + (size_t)bh * ((gm.T + 63) / 64 + 1) + (t0 >> 6);
+        const int f0 = min(max(first[0], 0), total), f1 = min(max(first[1], f0), total);
+        for (int i = f0 + (int)threadIdx.x % lanes; i < f1; i += lanes) {
+            const int code = row_code(rs, gm, bh, i), p = code / gm.G, t = p - t0;
+            if (t >= 0 && t < n) flags[(hk * gm.G + code - p * gm.G) * n + t] = 1;
+        }
     }
 }
 
@@ -141,7 +145,7 @@ __global__ __launch_bounds__(kThreads) void row_stats_kernel(StatsArgs a) {
     if (a.share) {
         for (int i = threadIdx.x; i < rows; i += kThreads) flags[i] = 0;
         __syncthreads();
-        for (int hk = 0; hk < gm.Hkv; ++hk) mark_routed(gm, a.routed, b, hk, t0, ntok, flags + hk * gm.G * ntok);
+        mark_routed(gm, a.routed, b, t0, ntok, flags);
     }
     const size_t row0 = ((size_t)b * gm.T + t0) * gm.Hq;
     typedef E Vec __attribute__((ext_vector_type(DL)));  // one 16- or 32-byte load per array and lane
