@@ -51,8 +51,8 @@ enum {
                                  FlashAttention-style mode; mask and index arrays are ignored, may be NULL */
     L2A_FLAG_SKIP_LOCAL = 2,  /* run the Global branch only:  O = d a  */
     L2A_FLAG_SKIP_GLOBAL = 4, /* run the Local branch only:   O = s    */
-    L2A_FLAG_SEQUENTIAL = 8,  /* run the branches one after the other at every length (see l2a_attn_fwd: short
-                                 sequences otherwise run them in one launch; the backward's dQ alike) */
+    L2A_FLAG_SEQUENTIAL = 8,  /* run the branches one after the other at every length (see l2a_attn_fwd: they
+                                 otherwise may share launches and work; the backward's dQ alike) */
     L2A_FLAG_RING_CACHE = 16, /* l2a_attn_decode with L2A_FLAG_SKIP_GLOBAL: the cache is a ring (see there) */
     L2A_FLAG_SCALAR = 1 << 16 /* bf16 only: use the scalar-FMA kernels instead of the matrix-core ones
                                  (slow; for cross-checking, and the only bf16 path for D = 64) */
@@ -92,15 +92,14 @@ const char* l2a_strerror(int code);
  *             each branch's V (shared inputs: in place of the second, a flag per row: routed) and one int32 flag per tile of 256 rows (tiles per (b, KV head) rounded up to a
  *             multiple of 8; 1 for a tile whose softmax needed a running maximum); when both branches run in one launch (see
  *             l2a_attn_fwd) the flags twice and a [B,T,Hq,D] float buffer for a; L2A_FP32, both branches with
- *             routing lists, T > 256: optional room (at most 8 [B,T,Hq,D] float buffers and statistics) for the partial sums that
+ *             routing lists, T > 256, not L2A_FLAG_SEQUENTIAL: optional room (at most 8 [B,T,Hq,D] float buffers and statistics) for the partial sums that
  *             layers with shared inputs use; without it the branches run one after the other; else nothing
  *   backward  delta_t of each branch, [B,Hq,T] float, twice; on the matrix-core path also, per
  *             branch, compact row-major copies of the rows' Q and dO (ceil64(T G) rows per
  *             (b, KV head)) with three per-row statistics (summed dq of short sequences: before those, the
  *             Global branch's part in float); short sequences (fewer than 1024
  *             blocks of 128 keys over all (b, KV head)): up to 8 x 2 float copies of [B,T,Hkv,D],
- *             partial sums of the workgroups that share a key block's rows; L2A_FP32, both branches with
- *             routing lists, T > 256: room as for the forward, of which only the two deltas are required
+ *             partial sums of the workgroups that share a key block's rows; L2A_FP32 as above: room as for the forward, of which only the two deltas are required
  */
 size_t l2a_route_workspace_bytes(const l2a_params* p);
 size_t l2a_attn_workspace_bytes(const l2a_params* p, int backward);
@@ -180,14 +179,18 @@ int l2a_router_decide(const l2a_params* p, int32_t C, const void* x, const float
  *   S_opt       out optional [B,T,Hq,D]: s alone (needed by l2a_attn_bwd)
  *   A_opt       out optional [B,T,Hq,D]: d a alone, zero where d = 0 (needed by l2a_attn_bwd)
  *
- * With bf16, D = 128, both branches, routing lists in use and shared inputs (each *_glb pointer equal to its
- * *_loc partner), s = a for routed rows while W >= T - 1, and every row is computed once, in one launch, whatever the order flags.
- * Otherwise (and without kblk_first_row) the branches run apart.  While they are short (at most
- * 2048 tiles of 256 rows over all (b, KV head)) the Global rows' tiles alone would occupy a fraction of the chip, so
- * the two branches run in one launch, the Global one leaves a in fp32 in the workspace, and a
- * second, small kernel forms o = s + d a -- bit for bit the result of the sequential order, where
- * the Global kernel adds its fp32 result to the stored s.  L2A_FLAG_SEQUENTIAL keeps the sequential
- * order at every length.
+ * With both branches and routing lists in use the branches may share launches and work; L2A_FLAG_SEQUENTIAL runs them one
+ * after the other instead, at every length:
+ *   bf16, D = 128   with shared inputs (each *_glb pointer equal to its *_loc partner) s = a for routed rows while W >= T - 1,
+ *                   and every row is computed once, in one launch.  Otherwise (and without kblk_first_row), while
+ *                   sequences are short (at most 2048 tiles of 256 rows over all (b, KV head)), the Global rows' tiles alone would
+ *                   occupy a fraction of the chip: the two branches run in one launch, the Global one leaves a in fp32 in the
+ *                   workspace, and a second, small kernel forms o = s + d a.  Either gives the bits of the sequential
+ *                   order, where the Global kernel adds its fp32 result to the stored s -- but for tiles whose softmax needed a
+ *                   running maximum: which rows a tile holds, and so which are computed that way, differs.
+ *   fp32            with shared inputs, kblk_first_row and the optional workspace, T > 256: the keys before the window of a
+ *                   routed row are added to the window's sums; results differ by rounding.
+ * s and lse_local of a token do not depend on which other tokens are routed (but for such tiles in bf16).
  */
 int l2a_attn_fwd(const l2a_params* p, const void* q_loc, const void* k_loc, const void* v_loc,
                  const void* q_glb, const void* k_glb, const void* v_glb, const int32_t* row_idx,

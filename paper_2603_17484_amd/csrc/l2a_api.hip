@@ -71,7 +71,7 @@ bool pair_bwd(const l2a_params& p) { return pair_fwd(p); }
 // them the branches run one after the other)
 bool both_routed(const l2a_params& p) { return !(p.flags & (L2A_FLAG_DENSE | L2A_FLAG_SKIP_LOCAL | L2A_FLAG_SKIP_GLOBAL)); }
 // (Up to 256 tokens a launch for each branch and one for the parts with a combine behind it take the same few us.)
-bool fp32_parts(const l2a_params& p) { return p.dtype == L2A_FP32 && both_routed(p) && p.T > 256; }
+bool fp32_parts(const l2a_params& p) { return p.dtype == L2A_FP32 && both_routed(p) && !(p.flags & L2A_FLAG_SEQUENTIAL) && p.T > 256; }
 size_t fwd_workspace_bytes(const l2a_params& p) {
     if (fp32_parts(p)) return fp32_fwd_shared_bytes(make_geom(p));
     if (!use_mfma(p)) return 0;
@@ -221,7 +221,7 @@ int l2a_attn_fwd(const l2a_params* p, const void* q_loc, const void* k_loc, cons
     // where a second V copy would: G bytes per token and KV head of 256).  Lists without kblk_first_row take the branches as
     // they come.
     const bool one_input = mfma && do_local && do_global && !dense && kblk_first_row && q_glb == q_loc && k_glb == k_loc && v_glb == v_loc;
-    const bool whole = one_input && p->T - 1 <= p->W;
+    const bool whole = one_input && p->T - 1 <= p->W && !(p->flags & L2A_FLAG_SEQUENTIAL);
     const bool pair = pair_fwd(*p) && !whole;
     if (whole) {
         char* after_v = (char*)workspace + 2 * kv_copy_bytes(*p);

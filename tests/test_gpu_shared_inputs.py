@@ -6,7 +6,7 @@ import torch
 
 from paper_2603_17484_amd import binding as B
 from paper_2603_17484_amd.runner import layer_from_numpy, to_device
-from tests.gpu_helpers import make_case
+from tests.gpu_helpers import make_case, run_and_check
 
 pytestmark = pytest.mark.gpu
 
@@ -71,3 +71,25 @@ def test_the_local_result_does_not_depend_on_who_else_is_routed(Bn, T, Hq, Hkv, 
     other = np.random.default_rng(T).random(x.mask.shape) < 0.5   # (not the complement, which groups the rows alike)
     a, b = forward(x, W), forward(x, W, mask=other.astype(np.uint8))
     assert torch.equal(a.S, b.S) and torch.equal(a.lse_l, b.lse_l)
+
+
+def kernels_of(call):
+    B.profile_read()
+    B.profile_enable(True)
+    try:
+        call()
+        torch.cuda.synchronize()
+    finally:
+        B.profile_enable(False)
+    return [name for name, _ in B.profile_read()]
+
+
+@pytest.mark.parametrize("dtype,apart,together", [("bf16", {"fwd_local", "fwd_global", "bwd_dq_local", "bwd_dq_global"}, {"fwd_whole", "bwd_dq_pair"}),
+                                                  ("fp32", {"fp32_fwd_local", "fp32_fwd_global", "fp32_bwd_dq_local", "fp32_bwd_dq_global"},
+                                                   {"fp32_fwd_shared", "fp32_bwd_dq_shared"})])
+def test_the_sequential_flag_runs_the_branches_one_after_the_other(oracle, dtype, apart, together):
+    x = make_case(T=300, Hq=4, Hkv=2, W=400, Hm=4, f=0.3, dtype=dtype, seed=21)
+    for order, want, never in ((B.L2A_FLAG_SEQUENTIAL, apart, together), (0, together, apart)):
+        lay, _ = run_and_check(oracle, x, order)
+        names = set(kernels_of(lambda: (lay.forward(), lay.backward(to_device(x.dO, dtype)))))
+        assert want <= names and not names & never, names
