@@ -47,7 +47,7 @@ struct FwdArgs {
     const __bf16* v;   // V as given (running_max_body only)
     const __bf16* vt;  // token-minor copy of V: [B*Hkv][128][vt_cap]
     int vt_cap;
-    int32_t* redo;  // [B*Hkv][redo_stride]: set to 1 for a tile of 256 rows that was left to running_max_body
+    int32_t* redo;  // [B*Hkv][redo_stride]: set to 1 for a tile of 256 rows that was left to running_max_body (for diagnosis only)
     int redo_stride;
     FwdOut out;
     // kWhole: `out` is where a goes (main_out: o); s and its log-sum-exp
@@ -862,15 +862,11 @@ int mfma_fwd(const Geom& g, const RowSet& rs, const void* q, const void* k, cons
     FwdArgs a{g, rs, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (const __bf16*)vt, vt_cap, redo,
               (int)tiles_x(g), out};
     const dim3 grid(tiles_x(g), g.B * g.Hkv);
-    int r = fill_zero(redo, sizeof(int32_t) * grid.x * grid.y, st);
-    if (r != L2A_OK) return r;
-    {
-        KernelTimer kt(rs.local ? "fwd_local" : "fwd_global", st);
-        if (rs.local)
-            hipLaunchKernelGGL((fwd_kernel<true, kFwdNQB, kFwdNW>), grid, dim3(64 * kFwdNW), 0, st, a);
-        else
-            hipLaunchKernelGGL((fwd_kernel<false, kFwdNQB, kFwdNW>), grid, dim3(64 * kFwdNW), 0, st, a);
-    }
+    KernelTimer kt(rs.local ? "fwd_local" : "fwd_global", st);
+    if (rs.local)
+        hipLaunchKernelGGL((fwd_kernel<true, kFwdNQB, kFwdNW>), grid, dim3(64 * kFwdNW), 0, st, a);
+    else
+        hipLaunchKernelGGL((fwd_kernel<false, kFwdNQB, kFwdNW>), grid, dim3(64 * kFwdNW), 0, st, a);
     return launch_status();
 }
 

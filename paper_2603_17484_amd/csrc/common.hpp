@@ -118,11 +118,11 @@ int fill_f32(float* ptr, size_t n, float value, hipStream_t st);
 
 // ---- attn_fwd_bf16.hip / attn_bwd_bf16.hip : MFMA kernels (bf16, D = 128)
 // vt: token-minor copy of v from pack_kv, [B*Hkv][128][vt_cap]
-// redo: mfma_fwd_redo_entries(g) int32 of scratch
+// redo: mfma_fwd_redo_entries(g) int32, set to 1 for tiles whose softmax needed a running maximum (the caller clears them)
 int mfma_fwd(const Geom& g, const RowSet& rs, const void* q, const void* k, const void* v, const void* vt,
              int vt_cap, int32_t* redo, const FwdOut& out, hipStream_t st);
 size_t mfma_fwd_redo_entries(const Geom& g);
-// both branches in one launch; out_g must not merge; redo: 2 x mfma_fwd_redo_entries(g) int32, all zero
+// both branches in one launch; out_g must not merge; redo: 2 x mfma_fwd_redo_entries(g) int32
 int mfma_fwd_pair(const Geom& g, const RowSet& rs_l, const void* q_l, const void* k_l, const void* v_l,
                   const void* vt_l, const FwdOut& out_l, const RowSet& rs_g, const void* q_g, const void* k_g,
                   const void* v_g, const void* vt_g, const FwdOut& out_g, int vt_cap, int32_t* redo, hipStream_t st);

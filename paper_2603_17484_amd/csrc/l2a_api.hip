@@ -245,8 +245,9 @@ int l2a_attn_fwd(const l2a_params* p, const void* q_loc, const void* k_loc, cons
         }
         Fill fills[3];
         int nf = 0;
-        if (pair) {  // flags of the tiles to be computed again; what the Global branch leaves for tokens it never visits
-            fills[nf++] = Fill{(uint32_t*)((char*)workspace + 2 * kv_copy_bytes(*p)), 2 * mfma_fwd_redo_entries(g), 0u};
+        // the tiles' flags (one set for branches that run one after the other); what the Global branch leaves for tokens it never visits
+        fills[nf++] = Fill{(uint32_t*)((char*)workspace + 2 * kv_copy_bytes(*p)), (pair ? 2 : 1) * mfma_fwd_redo_entries(g), 0u};
+        if (pair) {
             fills[nf++] = Fill{(uint32_t*)lse_global, stat_elems(*p), 0xff800000u};  // -inf
             if (A_opt) fills[nf++] = Fill{(uint32_t*)A_opt, q_elems(*p) / 2, 0u};
         }

@@ -93,3 +93,14 @@ def test_the_sequential_flag_runs_the_branches_one_after_the_other(oracle, dtype
         lay, _ = run_and_check(oracle, x, order)
         names = set(kernels_of(lambda: (lay.forward(), lay.backward(to_device(x.dO, dtype)))))
         assert want <= names and not names & never, names
+
+
+@pytest.mark.parametrize("flags", [B.L2A_FLAG_DENSE, B.L2A_FLAG_SKIP_LOCAL, B.L2A_FLAG_SKIP_GLOBAL, B.L2A_FLAG_SEQUENTIAL, 0])
+def test_a_forward_is_its_pre_pass_and_its_branches(flags):
+    """No launch of its own for constants that the pre-pass can write."""
+    x = make_case(T=300, Hq=4, Hkv=2, W=100, Hm=4, f=0.3, seed=22)
+    lay = forward(x, 100, flags)
+    branches = {B.L2A_FLAG_SKIP_LOCAL: ["fwd_global"], B.L2A_FLAG_SKIP_GLOBAL: ["fwd_local"], 0: ["fwd_pair", "merge_rows"]}
+    left = 3 if flags == B.L2A_FLAG_SKIP_LOCAL else 0      # the Global branch alone: O, A and log-sum-exp of tokens it never visits
+    names = kernels_of(lay.forward)
+    assert sorted(names) == sorted(["pack_kv"] + branches.get(flags, ["fwd_local", "fwd_global"]) + left * ["fill"]), names
