@@ -13,7 +13,7 @@
 // a tile reads the same K/V.  K and the token-minor copy of V are streamed through LDS in blocks
 // of 64 keys by direct global->LDS loads (three and two buffers, one barrier per block).  With 32 rows
 // a wavefront needs 256 registers, so two share a SIMD (measured 2-5 % faster than 4 wavefronts of 64
-// rows at 500 registers, which the kernel template still covers).  Short sequences (half_tiles) have workgroups of 4
+// rows at 500 registers).  Short sequences (half_tiles) have workgroups of 4
 // wavefronts and 128 rows, half a tile each, and both branches in one launch.
 //
 // Everything is computed transposed so that a lane owns a query row:
@@ -33,7 +33,7 @@ namespace l2a {
 namespace {
 
 constexpr int kBK = 64;  // keys per block
-constexpr int kFwdNQB = 1, kFwdNW = 8;  // the kernel's shape: see fwd_kernel
+constexpr int kFwdNW = 8;  // wavefronts of 32 rows: two per SIMD, so that one's softmax can overlap the other's matrix instructions
 constexpr int kBQ = 256;                // rows of a tile
 constexpr int kAhead = 2;  // operand look-ahead, in operands (each feeds two instructions)
 
@@ -56,17 +56,9 @@ struct FwdArgs {
     const unsigned char* routed = nullptr;  // kWhole: [B*Hkv][T*G], by row code
 };
 
-template <int NQB>
-struct ScoresT {
-    f32x16 s[NQB];  // 32 keys x (NQB x 32) rows
-};
-
 template <int V>
 using Int = std::integral_constant<int, V>;
 
-// NW wavefronts of NQB x 32 rows each.  256 rows (NW * NQB = 8): 4 x 2 runs one wavefront per SIMD with 500 registers,
-// 8 x 1 runs two per SIMD with 256 each, so that one wavefront's softmax arithmetic can overlap the
-// other's matrix instructions.
 // What a workgroup computes for its rows.  kWhole: all rows of a layer whose branches share their inputs while the window
 // spans the sequence: s = a, and which rows are routed only matters to what is written.  (A shorter window is computed for each
 // branch: in one walk over the window and then the keys before it s and a share the roundings of the window's weights,
@@ -143,7 +135,7 @@ __device__ __forceinline__ void store_whole_lse(const FwdArgs& a, size_t so, flo
 template <bool LOCAL, int NW>
 __device__ __forceinline__ void running_max_body(const FwdArgs& a, const Tile t, FwdLds& lds, bool whole) {
     const FwdOut& out = a.out;
-    constexpr int NQB = 1, RW = 32 * NQB, BQ = NW * RW;
+    constexpr int RW = 32, BQ = NW * RW;
     typedef __bf16 K2[2][kTileRows * kRowPad];
     typedef __bf16 V2[2][kD * kColPad];
     static_assert(sizeof(K2) + sizeof(V2) <= sizeof(FwdLds), "both fit the pipeline's buffers");
@@ -171,21 +163,14 @@ __device__ __forceinline__ void running_max_body(const FwdArgs& a, const Tile t,
         wv_pmax = row_code(a.rs, gm, bh, wv_r1 - 1) / gm.G;
     }
 
-    int pos[NQB], head[NQB];
-    bool valid[NQB];
-    bf16x8 qreg[NQB][8];
+    const bool valid = wv_r0 + n < n_rows;
+    // rows past the end repeat the last row: computed, never written
+    const int code = row_code(a.rs, gm, bh, min(wv_r0 + n, n_rows - 1));
+    const int pos = code / gm.G, head = hk * gm.G + (code - pos * gm.G);
+    bf16x8 qreg[8];
+    const __bf16* qp = a.q + (((size_t)b * gm.T + pos) * gm.Hq + head) * kD + 8 * h;
 #pragma unroll
-    for (int c = 0; c < NQB; ++c) {
-        const int r = wv_r0 + c * 32 + n;
-        valid[c] = r < n_rows;
-        // rows past the end repeat the last row: computed, never written
-        const int code = row_code(a.rs, gm, bh, min(r, n_rows - 1));
-        pos[c] = code / gm.G;
-        head[c] = hk * gm.G + (code - pos[c] * gm.G);
-        const __bf16* qp = a.q + (((size_t)b * gm.T + pos[c]) * gm.Hq + head[c]) * kD + 8 * h;
-#pragma unroll
-        for (int ks = 0; ks < 8; ++ks) qreg[c][ks] = *reinterpret_cast<const bf16x8*>(qp + ks * 16);
-    }
+    for (int ks = 0; ks < 8; ++ks) qreg[ks] = *reinterpret_cast<const bf16x8*>(qp + ks * 16);
 
     // ---- K/V block range of the workgroup
     const int jb0 = LOCAL ? max(wg_pmin - gm.W, 0) / kBK : 0;
@@ -210,17 +195,12 @@ __device__ __forceinline__ void running_max_body(const FwdArgs& a, const Tile t,
         tile_store_transposed(vr, lds_v[buf]);
     };
 
-    f32x16 oacc[4][NQB];
-    float m[NQB], l[NQB];
+    f32x16 oacc[4];
+    float m = -INFINITY, l = 0.f;
 #pragma unroll
-    for (int c = 0; c < NQB; ++c) {
-        m[c] = -INFINITY;
-        l[c] = 0.f;
+    for (int d = 0; d < 4; ++d)
 #pragma unroll
-        for (int d = 0; d < 4; ++d)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) oacc[d][c][r] = 0.f;
-    }
+        for (int r = 0; r < 16; ++r) oacc[d][r] = 0.f;
 
     load_block(jb0);
     store_block(0);
@@ -240,74 +220,66 @@ __device__ __forceinline__ void running_max_body(const FwdArgs& a, const Tile t,
             const __bf16* vs_ = lds_v[cur];
 
             // S^T = K Q^T
-            f32x16 s[2][NQB];
+            f32x16 s[2];
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                for (int c = 0; c < NQB; ++c)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) s[kb][c][r] = 0.f;
+                for (int r = 0; r < 16; ++r) s[kb][r] = 0.f;
 #pragma unroll
             for (int ks = 0; ks < 8; ++ks) {
                 const bf16x8 a0 = lds_rowmajor(ks_, n, ks, h);
                 const bf16x8 a1 = lds_rowmajor(ks_, 32 + n, ks, h);
-#pragma unroll
-                for (int c = 0; c < NQB; ++c) {
-                    s[0][c] = mfma32(a0, qreg[c][ks], s[0][c]);
-                    s[1][c] = mfma32(a1, qreg[c][ks], s[1][c]);
-                }
+                s[0] = mfma32(a0, qreg[ks], s[0]);
+                s[1] = mfma32(a1, qreg[ks], s[1]);
             }
 
             // streaming softmax, one row per lane
-            bf16x8 pb[NQB][4];
-#pragma unroll
-            for (int c = 0; c < NQB; ++c) {
-                if (need_mask) {
-#pragma unroll
-                    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) {
-                            const int key = k0 + kb * 32 + c_row(r, h);
-                            bool ok = key <= pos[c];
-                            if (LOCAL) ok = ok && (key >= pos[c] - gm.W);
-                            s[kb][c][r] = ok ? s[kb][c][r] : -INFINITY;
-                        }
-                }
-                float mx = s[0][c][0];
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[kb][c][r]);
-                mx = fmaxf(mx, __shfl_xor(mx, 32));
-                // A row may have seen only masked keys so far (sliding window): its running max is
-                // then -inf and must not enter a subtraction.
-                const float mnew = fmaxf(m[c], mx * gm.scale_log2);
-                const bool grow = mnew > m[c];
-                if (__any(grow)) {
-                    const float alpha = grow ? fast_exp2(m[c] - mnew) : 1.f;
-                    l[c] *= alpha;
-#pragma unroll
-                    for (int d = 0; d < 4; ++d)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) oacc[d][c][r] *= alpha;
-                    m[c] = mnew;
-                }
-                const float negm = (m[c] == -INFINITY) ? 0.f : -m[c];
-                float rsum = 0.f;
+            bf16x8 pb[4];
+            if (need_mask) {
 #pragma unroll
                 for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
-                        const float p = fast_exp2(fmaf(s[kb][c][r], gm.scale_log2, negm));
-                        s[kb][c][r] = p;
-                        rsum += p;
+                        const int key = k0 + kb * 32 + c_row(r, h);
+                        bool ok = key <= pos;
+                        if (LOCAL) ok = ok && (key >= pos - gm.W);
+                        s[kb][r] = ok ? s[kb][r] : -INFINITY;
                     }
-                l[c] += rsum;
+            }
+            float mx = s[0][0];
 #pragma unroll
-                for (int kb = 0; kb < 2; ++kb) {
-                    pb[c][kb * 2 + 0] = pack8(s[kb][c], 0);
-                    pb[c][kb * 2 + 1] = pack8(s[kb][c], 1);
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[kb][r]);
+            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            // A row may have seen only masked keys so far (sliding window): its running max is
+            // then -inf and must not enter a subtraction.
+            const float mnew = fmaxf(m, mx * gm.scale_log2);
+            const bool grow = mnew > m;
+            if (__any(grow)) {
+                const float alpha = grow ? fast_exp2(m - mnew) : 1.f;
+                l *= alpha;
+#pragma unroll
+                for (int d = 0; d < 4; ++d)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) oacc[d][r] *= alpha;
+                m = mnew;
+            }
+            const float negm = (m == -INFINITY) ? 0.f : -m;
+            float rsum = 0.f;
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const float p = fast_exp2(fmaf(s[kb][r], gm.scale_log2, negm));
+                    s[kb][r] = p;
+                    rsum += p;
                 }
+            l += rsum;
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) {
+                pb[kb * 2 + 0] = pack8(s[kb], 0);
+                pb[kb * 2 + 1] = pack8(s[kb], 1);
             }
 
             // O^T += V^T P^T
@@ -316,8 +288,7 @@ __device__ __forceinline__ void running_max_body(const FwdArgs& a, const Tile t,
 #pragma unroll
                 for (int d = 0; d < 4; ++d) {
                     const bf16x8 av = lds_transposed(vs_, d * 32 + n, step, h);
-#pragma unroll
-                    for (int c = 0; c < NQB; ++c) oacc[d][c] = mfma32(av, pb[c][step], oacc[d][c]);
+                    oacc[d] = mfma32(av, pb[step], oacc[d]);
                 }
         }
 
@@ -330,60 +301,57 @@ __device__ __forceinline__ void running_max_body(const FwdArgs& a, const Tile t,
     __bf16* mo = (__bf16*)out.main_out;
     __bf16* co = (__bf16*)out.copy_out;
     __bf16* zf = (__bf16*)out.zero_fill;
+    const float lt = l + __shfl_xor(l, 32);
+    if (!valid) return;
+    const float inv = 1.f / lt;
+    const size_t base = (((size_t)b * gm.T + pos) * gm.Hq + head) * kD + 4 * h;
+    const bool routed = whole && a.routed[(size_t)bh * gm.T * gm.G + wv_r0 + n];
 #pragma unroll
-    for (int c = 0; c < NQB; ++c) {
-        const float lt = l[c] + __shfl_xor(l[c], 32);
-        if (!valid[c]) continue;
-        const float inv = 1.f / lt;
-        const size_t base = (((size_t)b * gm.T + pos[c]) * gm.Hq + head[c]) * kD + 4 * h;
-        const bool routed = whole && a.routed[(size_t)bh * gm.T * gm.G + wv_r0 + c * 32 + n];
+    for (int d = 0; d < 4; ++d)
 #pragma unroll
-        for (int d = 0; d < 4; ++d)
-#pragma unroll
-            for (int rg = 0; rg < 4; ++rg) {
-                const size_t off = base + d * 32 + 8 * rg;
-                f32x4 x = {oacc[d][c][4 * rg + 0] * inv, oacc[d][c][4 * rg + 1] * inv,
-                           oacc[d][c][4 * rg + 2] * inv, oacc[d][c][4 * rg + 3] * inv};
-                if (whole) {
-                    store_whole(a, off, x, routed);
-                    continue;
-                }
-                if (co) *reinterpret_cast<bf16x4*>(co + off) = __builtin_convertvector(x, bf16x4);
-                if (out.merge) {
-                    const bf16x4 old = *reinterpret_cast<const bf16x4*>(mo + off);
-                    x += __builtin_convertvector(old, f32x4);
-                }
-                if (out.wide_out) *reinterpret_cast<f32x4*>(out.wide_out + off) = x;
-                else *reinterpret_cast<bf16x4*>(mo + off) = __builtin_convertvector(x, bf16x4);
-                if (zf) {
-                    const u32x2 z = {0u, 0u};
-                    *reinterpret_cast<u32x2*>(zf + off) = z;
-                }
-            }
-        if (h == 0) {
-            const size_t so = ((size_t)b * gm.Hq + head[c]) * gm.T + pos[c];
+        for (int rg = 0; rg < 4; ++rg) {
+            const size_t off = base + d * 32 + 8 * rg;
+            f32x4 x = {oacc[d][4 * rg + 0] * inv, oacc[d][4 * rg + 1] * inv,
+                       oacc[d][4 * rg + 2] * inv, oacc[d][4 * rg + 3] * inv};
             if (whole) {
-                store_whole_lse(a, so, (m[c] + __builtin_amdgcn_logf(lt)) * kLn2, routed);
+                store_whole(a, off, x, routed);
                 continue;
             }
-            out.lse_out[so] = (m[c] + __builtin_amdgcn_logf(lt)) * kLn2;
-            if (out.lse_fill) out.lse_fill[so] = -INFINITY;
+            if (co) *reinterpret_cast<bf16x4*>(co + off) = __builtin_convertvector(x, bf16x4);
+            if (out.merge) {
+                const bf16x4 old = *reinterpret_cast<const bf16x4*>(mo + off);
+                x += __builtin_convertvector(old, f32x4);
+            }
+            if (out.wide_out) *reinterpret_cast<f32x4*>(out.wide_out + off) = x;
+            else *reinterpret_cast<bf16x4*>(mo + off) = __builtin_convertvector(x, bf16x4);
+            if (zf) {
+                const u32x2 z = {0u, 0u};
+                *reinterpret_cast<u32x2*>(zf + off) = z;
+            }
         }
+    if (h == 0) {
+        const size_t so = ((size_t)b * gm.Hq + head) * gm.T + pos;
+        if (whole) {
+            store_whole_lse(a, so, (m + __builtin_amdgcn_logf(lt)) * kLn2, routed);
+            return;
+        }
+        out.lse_out[so] = (m + __builtin_amdgcn_logf(lt)) * kLn2;
+        if (out.lse_fill) out.lse_fill[so] = -INFINITY;
     }
 }
 
-template <Kind KIND, int NQB, int NW>
+template <Kind KIND, int NW>
 __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds& lds) {
     auto& lds_k = lds.k;
     auto& lds_v = lds.v;
     constexpr bool LOCAL = KIND == kLocal;
-    constexpr int RW = 32 * NQB;       // rows per wavefront
+    constexpr int RW = 32;             // rows per wavefront
     constexpr int BQ = RW * NW;        // rows per workgroup: a tile, or a whole part of one
     static_assert(kBQ % BQ == 0, "a workgroup's rows lie in one tile");
-    constexpr int NS = 16 * NQB;       // slots (matrix instructions) per half-block: NS / 2 for S, NS / 2 for P V
+    constexpr int NS = 16;             // slots (matrix instructions) per half-block: NS / 2 for S, NS / 2 for P V
     constexpr int NL = 16 / NW;        // 16-byte loads a wavefront issues per K or V block
     constexpr int kLoadSlot0 = NS - 1 - 2 * NL;  // the loads of later blocks go out in the last slots of a block's first half
-    using Scores = ScoresT<NQB>;
+    using Scores = f32x16;             // 32 keys x 32 rows
 
     const Geom& gm = a.gm;
     const int bh = t.bh, tile = t.tile, n_rows = t.n_rows;
@@ -400,22 +368,15 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds&
     const int wv_r0 = wg_r0 + wave * RW;
     const bool wave_active = wv_r0 < n_rows;
 
-    int pos[NQB], head[NQB];
-    bool valid[NQB], routed[NQB];
-    bf16x8 qreg[NQB][8];
+    const bool valid = wv_r0 + n < n_rows;
+    // rows past the end repeat the last row: computed, never written
+    const int code = row_code(a.rs, gm, bh, min(wv_r0 + n, n_rows - 1));
+    const int pos = code / gm.G, head = hk * gm.G + (code - pos * gm.G);
+    const bool routed = KIND == kWhole && a.routed[(size_t)bh * gm.T * gm.G + code] != 0;
+    bf16x8 qreg[8];
+    const __bf16* qp = a.q + (((size_t)b * gm.T + pos) * gm.Hq + head) * kD + 8 * h;
 #pragma unroll
-    for (int c = 0; c < NQB; ++c) {
-        const int r = wv_r0 + c * 32 + n;
-        valid[c] = r < n_rows;
-        // rows past the end repeat the last row: computed, never written
-        const int code = row_code(a.rs, gm, bh, min(r, n_rows - 1));
-        pos[c] = code / gm.G;
-        head[c] = hk * gm.G + (code - pos[c] * gm.G);
-        const __bf16* qp = a.q + (((size_t)b * gm.T + pos[c]) * gm.Hq + head[c]) * kD + 8 * h;
-#pragma unroll
-        for (int ks = 0; ks < 8; ++ks) qreg[c][ks] = *reinterpret_cast<const bf16x8*>(qp + ks * 16);
-        routed[c] = KIND == kWhole && a.routed[(size_t)bh * gm.T * gm.G + code] != 0;
-    }
+    for (int ks = 0; ks < 8; ++ks) qreg[ks] = *reinterpret_cast<const bf16x8*>(qp + ks * 16);
 
     // ---- block range of the workgroup, and its three runs: blocks that need the window-start
     // mask (LOCAL only), blocks no row of the tile needs a mask for, blocks on the causal diagonal.  Parts of a
@@ -467,43 +428,34 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds&
         }
     };
 
-    f32x16 oacc[4][NQB];
-    float mref[NQB], negm[NQB], l[NQB];
+    f32x16 oacc[4];
+    float mref = -INFINITY, negm, l = 0.f;
 #pragma unroll
-    for (int c = 0; c < NQB; ++c) {
-        l[c] = 0.f;
+    for (int d = 0; d < 4; ++d)
 #pragma unroll
-        for (int d = 0; d < 4; ++d)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) oacc[d][c][r] = 0.f;
-    }
+        for (int r = 0; r < 16; ++r) oacc[d][r] = 0.f;
     const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     // keys of a score tile that starts at key k0 are k0 + c_row(r, h): those in reach have first <= c_row(r, 0) <= last
-    auto last_row = [&](int k0, int c) __attribute__((always_inline)) { return pos[c] - k0 - 4 * h; };
-    auto first_row = [&](int k0, int c) __attribute__((always_inline)) { return pos[c] - k0 - 4 * h - gm.W; };
+    auto last_row = [&](int k0) __attribute__((always_inline)) { return pos - k0 - 4 * h; };
+    auto first_row = [&](int k0) __attribute__((always_inline)) { return pos - k0 - 4 * h - gm.W; };
 
     // One half-block (32 keys, half KB of block jb; keys k0 .. k0+31): exp of `cur` against the
     // row's fixed reference, overlapped with the scores of the next half-block into `nxt` (K rows
-    // krow0.. of tile kt) and with O += P V for this half-block (tile vt).  32 matrix-core
-    // instructions = 32 slots:
+    // krow0.. of tile kt) and with O += P V for this half-block (tile vt).  16 matrix-core
+    // instructions = 16 slots:
     //   first half of the slots   next half-block's scores | exp, row sum, pack P  (pair q in slot 3 q / 2)
     //   second half               O += P V
-    auto score = [&](float x) __attribute__((always_inline)) { return NQB == 2 ? acc_read(x) : x; };
     auto half_block = [&](auto mask_tag, auto kb_tag, Scores& cur, Scores& nxt, const __bf16* kt, int krow0,
                           const __bf16* vt, int k0, auto&& side) __attribute__((always_inline)) {
         constexpr bool MASK = decltype(mask_tag)::value;
         constexpr int KB = decltype(kb_tag)::value;
         const float c2 = gm.scale_log2;
         bf16x8 opnd[16 + kAhead];
-        uint32_t pw[NQB][2][4];  // P as packed bf16 pairs: [row block][16-key group][dword]
-        float rsum[NQB];
+        uint32_t pw[2][4];  // P as packed bf16 pairs: [16-key group][dword]
+        float rsum = 0.f;
         const bf16x2 one2 = {(__bf16)1.0f, (__bf16)1.0f};
-        int last[NQB], first[NQB];
-#pragma unroll
-        for (int c = 0; c < NQB; ++c) {
-            rsum[c] = 0.f;
-            if (MASK) last[c] = last_row(k0, c), first[c] = LOCAL ? first_row(k0, c) : 0;
-        }
+        int last, first;
+        if (MASK) last = last_row(k0), first = LOCAL ? first_row(k0) : 0;
         // operand o: o < 8 -> K rows of the next half-block (ks = o); else V^T (16-key group, channel block)
         auto read_operand = [&](auto oc) {
             constexpr int o = decltype(oc)::value;
@@ -513,31 +465,30 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds&
         auto issue = [&](auto mc) {
             constexpr int mm = decltype(mc)::value;
             if constexpr (mm < NS / 2) {
-                constexpr int ks = mm / NQB, c = mm % NQB;
-                nxt.s[c] = mfma32(opnd[ks], qreg[c][ks], ks == 0 ? zero16 : nxt.s[c]);
+                nxt = mfma32(opnd[mm], qreg[mm], mm == 0 ? zero16 : nxt);
             } else {
-                constexpr int x = mm - NS / 2, grp = x / (4 * NQB), d = (x / NQB) & 3, c = x % NQB;
-                const u32x4 pv = {pw[c][grp][0], pw[c][grp][1], pw[c][grp][2], pw[c][grp][3]};
-                oacc[d][c] = mfma32(opnd[8 + x / NQB], __builtin_bit_cast(bf16x8, pv), oacc[d][c]);
+                constexpr int x = mm - NS / 2, grp = x / 4, d = x & 3;
+                const u32x4 pv = {pw[grp][0], pw[grp][1], pw[grp][2], pw[grp][3]};
+                oacc[d] = mfma32(opnd[8 + x], __builtin_bit_cast(bf16x8, pv), oacc[d]);
             }
         };
-        // exp of one pair of scores: pair q in 0 .. 8 NQB - 1, in the order the P V product consumes them
+        // exp of one pair of scores: pair q in 0 .. 7, in the order the P V product consumes them
         auto exp_pair = [&](auto qc) {
             constexpr int q = decltype(qc)::value;
-            constexpr int grp = q / (4 * NQB), c = (q >> 2) % NQB, i2 = (q & 3) * 2, r = grp * 8 + i2;
-            float p0 = fast_exp2(fmaf(score(cur.s[c][r]), c2, negm[c]));
-            float p1 = fast_exp2(fmaf(score(cur.s[c][r + 1]), c2, negm[c]));
+            constexpr int grp = q / 4, i2 = (q & 3) * 2, r = grp * 8 + i2;
+            float p0 = fast_exp2(fmaf(cur[r], c2, negm));
+            float p1 = fast_exp2(fmaf(cur[r + 1], c2, negm));
             if (MASK) {
                 constexpr int c0 = c_row(r, 0), c1 = c_row(r + 1, 0);
-                p0 = c0 <= last[c] && (!LOCAL || c0 >= first[c]) ? p0 : 0.f;
-                p1 = c1 <= last[c] && (!LOCAL || c1 >= first[c]) ? p1 : 0.f;
+                p0 = c0 <= last && (!LOCAL || c0 >= first) ? p0 : 0.f;
+                p1 = c1 <= last && (!LOCAL || c1 >= first) ? p1 : 0.f;
             }
             f32x2 f = {p0, p1};
             const bf16x2 pb = __builtin_convertvector(f, bf16x2);
-            pw[c][grp][i2 >> 1] = __builtin_bit_cast(uint32_t, pb);
+            pw[grp][i2 >> 1] = __builtin_bit_cast(uint32_t, pb);
             // row sum of the weights as the matrix cores will see them (rounded to bf16): one
             // v_dot2 per pair, and the normalisation is exact for the weights actually used
-            rsum[c] = __builtin_amdgcn_fdot2_f32_bf16(pb, one2, rsum[c], false);
+            rsum = __builtin_amdgcn_fdot2_f32_bf16(pb, one2, rsum, false);
         };
 
         static_for<0, kAhead>([&](auto oc) { read_operand(oc); });
@@ -545,19 +496,15 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds&
         static_for<0, NS>([&](auto mc) {
             constexpr int mm = decltype(mc)::value;
             issue(mc);
-            if constexpr (mm % NQB == 0) read_operand(Int<mm / NQB + kAhead>{});
-            static_for<0, 8 * NQB>([&](auto qc) {
+            read_operand(Int<mm + kAhead>{});
+            static_for<0, 8>([&](auto qc) {
                 constexpr int q = decltype(qc)::value;
                 if constexpr ((3 * q) / 2 == mm) exp_pair(qc);
             });
             side(mc);
             L2A_FENCE();
         });
-#pragma unroll
-        for (int c = 0; c < NQB; ++c) l[c] += rsum[c];
-        // With more than 256 registers both score buffers stay in AGPRs, where the matrix instructions
-        // write them; the VALU side fetches each element with acc_read where it is consumed.
-        if constexpr (NQB == 2) asm volatile("" : "+a"(nxt.s[0]), "+a"(nxt.s[1]));
+        l += rsum;
     };
 
     // ---- prologue: K of the first two blocks, V of the first
@@ -575,8 +522,6 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds&
     // but the weights next to a row's largest are rounded best -- error against 64 bits 1.2-1.6 % larger with 32 -- and a row
     // whose largest score is its window's first key would overflow.)
     {  // wavefronts whose rows all lie past the end compute on a repeated row and store nothing
-#pragma unroll
-        for (int c = 0; c < NQB; ++c) mref[c] = -INFINITY;
         if ((jb0 + 2) * kBK - 1 <= wg_pmin && (!LOCAL || wg_pmax - gm.W <= jb0 * kBK)) {
 #pragma unroll 1
             for (int at = 0; at < 2 * kBK; at += 32) {
@@ -584,13 +529,10 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds&
 #pragma unroll
                 for (int ks = 0; ks < 8; ++ks) {
                     const bf16x8 op = rm_operand(&lds_k[at / kBK][0], at % kBK + n, ks, h);
-#pragma unroll
-                    for (int c = 0; c < NQB; ++c) S.s[c] = mfma32(op, qreg[c][ks], ks == 0 ? zero16 : S.s[c]);
+                    S = mfma32(op, qreg[ks], ks == 0 ? zero16 : S);
                 }
 #pragma unroll
-                for (int c = 0; c < NQB; ++c)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) mref[c] = fmaxf(mref[c], S.s[c][r]);
+                for (int r = 0; r < 16; ++r) mref = fmaxf(mref, S[r]);
             }
         } else {
             const int nb = jb0 < jb1 ? 2 : 1;
@@ -601,34 +543,26 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds&
 #pragma unroll
                     for (int ks = 0; ks < 8; ++ks) {
                         const bf16x8 op = rm_operand(&lds_k[bi][0], kb * 32 + n, ks, h);
-#pragma unroll
-                        for (int c = 0; c < NQB; ++c) S.s[c] = mfma32(op, qreg[c][ks], ks == 0 ? zero16 : S.s[c]);
+                        S = mfma32(op, qreg[ks], ks == 0 ? zero16 : S);
                     }
+                    const int last = last_row((jb0 + bi) * kBK + kb * 32);
+                    const int first = LOCAL ? first_row((jb0 + bi) * kBK + kb * 32) : 0;
 #pragma unroll
-                    for (int c = 0; c < NQB; ++c) {
-                        const int last = last_row((jb0 + bi) * kBK + kb * 32, c);
-                        const int first = LOCAL ? first_row((jb0 + bi) * kBK + kb * 32, c) : 0;
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) {
-                            const bool ok = c_row(r, 0) <= last && (!LOCAL || c_row(r, 0) >= first);
-                            mref[c] = fmaxf(mref[c], ok ? S.s[c][r] : -INFINITY);
-                        }
+                    for (int r = 0; r < 16; ++r) {
+                        const bool ok = c_row(r, 0) <= last && (!LOCAL || c_row(r, 0) >= first);
+                        mref = fmaxf(mref, ok ? S[r] : -INFINITY);
                     }
                 }
             }
         }
-#pragma unroll
-        for (int c = 0; c < NQB; ++c) {
-            mref[c] = fmaxf(mref[c], __shfl_xor(mref[c], 32)) * gm.scale_log2;
-            if (!(mref[c] > -INFINITY)) mref[c] = 0.f;  // no key in reach yet: any finite reference will do
-            negm[c] = -mref[c];
-        }
+        mref = fmaxf(mref, __shfl_xor(mref, 32)) * gm.scale_log2;
+        if (!(mref > -INFINITY)) mref = 0.f;  // no key in reach yet: any finite reference will do
+        negm = -mref;
         // scores of the first half-block
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks) {
             const bf16x8 op = rm_operand(&lds_k[0][0], n, ks, h);
-#pragma unroll
-            for (int c = 0; c < NQB; ++c) Sa.s[c] = mfma32(op, qreg[c][ks], ks == 0 ? zero16 : Sa.s[c]);
+            Sa = mfma32(op, qreg[ks], ks == 0 ? zero16 : Sa);
         }
     }
 
@@ -668,23 +602,20 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds&
     // products with V: values beyond ~3e8 can still overflow an accumulator, so those are checked themselves
     // (x * 0 is NaN exactly when x is infinite or NaN).  A sum above 1e-30 (a reference of 0 may leave it small) still
     // holds every weight that counts beside it, none flushed to zero.
-    float lt[NQB];
+    float lt;
     bool bad = false;
     auto check_sums = [&]() __attribute__((always_inline)) {
+        lt = l + __shfl_xor(l, 32);
+        float chk = 0.f;
 #pragma unroll
-        for (int c = 0; c < NQB; ++c) {
-            lt[c] = l[c] + __shfl_xor(l[c], 32);
-            float chk = 0.f;
+        for (int d = 0; d < 4; ++d)
 #pragma unroll
-            for (int d = 0; d < 4; ++d)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) chk = fmaf(oacc[d][c][e], 0.f, chk);
-            bad = bad || (wave_active && valid[c] && !(lt[c] > 1.0e-30f && lt[c] < 1.0e30f && chk == 0.f));
-        }
+            for (int e = 0; e < 16; ++e) chk = fmaf(oacc[d][e], 0.f, chk);
+        bad = bad || (wave_active && valid && !(lt > 1.0e-30f && lt < 1.0e30f && chk == 0.f));
     };
-    auto row_base = [&](int c) __attribute__((always_inline)) { return (((size_t)b * gm.T + pos[c]) * gm.Hq + head[c]) * kD; };
-    auto row_stat = [&](int c) __attribute__((always_inline)) { return ((size_t)b * gm.Hq + head[c]) * gm.T + pos[c]; };
-    auto row_lse = [&](int c) __attribute__((always_inline)) { return (mref[c] + __builtin_amdgcn_logf(lt[c])) * kLn2; };
+    auto row_base = [&]() __attribute__((always_inline)) { return (((size_t)b * gm.T + pos) * gm.Hq + head) * kD; };
+    auto row_stat = [&]() __attribute__((always_inline)) { return ((size_t)b * gm.Hq + head) * gm.T + pos; };
+    auto row_lse = [&]() __attribute__((always_inline)) { return (mref + __builtin_amdgcn_logf(lt)) * kLn2; };
 
     // runs of blocks: window-start masks (LOCAL), no masks, causal diagonal
     for (int seg = 0; seg < 3; ++seg) {
@@ -715,27 +646,27 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds&
         // Through LDS, where a lane's 8 bytes of its own row become 16 bytes of rows that sixteen lanes write whole: written
         // straight from the accumulators a store touched 32 rows, and a tile's outputs took 4700 to 9300 cycles.  A wavefront's
         // rows lie 272 bytes apart; behind a row's 256 bytes, where it goes (elements) and what it is (-1: nowhere, else routed).
-        static_assert(NQB == 1 && NW * 32 * 272 < sizeof(FwdLds) - 16, "below the vote");
+        static_assert(NW * 32 * 272 < sizeof(FwdLds) - 16, "below the vote");
         char* const st = reinterpret_cast<char*>(&lds) + wave * (32 * 272);
-        const float inv = 1.f / lt[0];
+        const float inv = 1.f / lt;
         auto put = [&](bool sum) __attribute__((always_inline)) {  // s, or o where it differs
             __builtin_amdgcn_wave_barrier();
 #pragma unroll
             for (int d = 0; d < 4; ++d)
 #pragma unroll
                 for (int rg = 0; rg < 4; ++rg) {
-                    f32x4 x = {oacc[d][0][4 * rg + 0] * inv, oacc[d][0][4 * rg + 1] * inv, oacc[d][0][4 * rg + 2] * inv,
-                               oacc[d][0][4 * rg + 3] * inv};
+                    f32x4 x = {oacc[d][4 * rg + 0] * inv, oacc[d][4 * rg + 1] * inv, oacc[d][4 * rg + 2] * inv,
+                               oacc[d][4 * rg + 3] * inv};
                     bf16x4 y = __builtin_convertvector(x, bf16x4);
-                    if (KIND == kWhole && sum && routed[0]) y = __builtin_convertvector(x + __builtin_convertvector(y, f32x4), bf16x4);
+                    if (KIND == kWhole && sum && routed) y = __builtin_convertvector(x + __builtin_convertvector(y, f32x4), bf16x4);
                     *reinterpret_cast<bf16x4*>(st + n * 272 + d * 64 + rg * 16 + h * 8) = y;
                 }
             asm volatile("" ::: "memory");
             __builtin_amdgcn_wave_barrier();
         };
         if (h == 0) {
-            *reinterpret_cast<size_t*>(st + n * 272 + 256) = row_base(0);
-            *reinterpret_cast<int*>(st + n * 272 + 264) = valid[0] ? (KIND == kWhole && routed[0] ? 1 : 0) : -1;
+            *reinterpret_cast<size_t*>(st + n * 272 + 256) = row_base();
+            *reinterpret_cast<int*>(st + n * 272 + 264) = valid ? (KIND == kWhole && routed ? 1 : 0) : -1;
         }
         auto rows_out = [&](auto f) __attribute__((always_inline)) {  // f(16 bytes, element offset, routed)
 #pragma unroll
@@ -759,7 +690,7 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds&
             }
             put(true);
             rows_out([&](const u32x4& x, size_t off, int) __attribute__((always_inline)) { *reinterpret_cast<u32x4*>(mo + off) = x; });
-            if (h == 0 && valid[0]) store_whole_lse(a, row_stat(0), row_lse(0), routed[0]);
+            if (h == 0 && valid) store_whole_lse(a, row_stat(), row_lse(), routed);
         } else {
             __bf16 *co = (__bf16*)a.out.copy_out, *zf = (__bf16*)a.out.zero_fill;
             put(false);
@@ -768,9 +699,9 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds&
                 if (co) *reinterpret_cast<u32x4*>(co + off) = x;
                 if (zf) *reinterpret_cast<u32x4*>(zf + off) = u32x4{0u, 0u, 0u, 0u};
             });
-            if (h == 0 && valid[0]) {
-                a.out.lse_out[row_stat(0)] = row_lse(0);
-                if (a.out.lse_fill) a.out.lse_fill[row_stat(0)] = -INFINITY;
+            if (h == 0 && valid) {
+                a.out.lse_out[row_stat()] = row_lse();
+                if (a.out.lse_fill) a.out.lse_fill[row_stat()] = -INFINITY;
             }
         }
         return;
@@ -778,43 +709,40 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, const Tile t, FwdLds&
     __bf16* mo = (__bf16*)a.out.main_out;
     __bf16* co = (__bf16*)a.out.copy_out;
     __bf16* zf = (__bf16*)a.out.zero_fill;
-#pragma unroll
-    for (int c = 0; c < NQB; ++c) {
-        if (!valid[c]) continue;
-        const float inv = 1.f / lt[c];
-        const size_t base = row_base(c) + 4 * h;
-#pragma unroll
-        for (int d = 0; d < 4; ++d)
-#pragma unroll
-            for (int rg = 0; rg < 4; ++rg) {
-                const size_t off = base + d * 32 + 8 * rg;
-                f32x4 x = {oacc[d][c][4 * rg + 0] * inv, oacc[d][c][4 * rg + 1] * inv,
-                           oacc[d][c][4 * rg + 2] * inv, oacc[d][c][4 * rg + 3] * inv};
-                if (co) *reinterpret_cast<bf16x4*>(co + off) = __builtin_convertvector(x, bf16x4);
-                if (a.out.merge) {
-                    const bf16x4 old = *reinterpret_cast<const bf16x4*>(mo + off);
-                    x += __builtin_convertvector(old, f32x4);
-                }
-                if (a.out.wide_out) *reinterpret_cast<f32x4*>(a.out.wide_out + off) = x;
-                else *reinterpret_cast<bf16x4*>(mo + off) = __builtin_convertvector(x, bf16x4);
-                if (zf) {
-                    const u32x2 z = {0u, 0u};
-                    *reinterpret_cast<u32x2*>(zf + off) = z;
-                }
-            }
-        if (h == 0) {
-            const size_t so = row_stat(c);
-            a.out.lse_out[so] = row_lse(c);
-            if (a.out.lse_fill) a.out.lse_fill[so] = -INFINITY;
-        }
+    if (!valid) return;
+    if (h == 0) {
+        const size_t so = row_stat();
+        a.out.lse_out[so] = row_lse();
+        if (a.out.lse_fill) a.out.lse_fill[so] = -INFINITY;
     }
+    const float inv = 1.f / lt;
+    const size_t base = row_base() + 4 * h;
+#pragma unroll
+    for (int d = 0; d < 4; ++d)
+#pragma unroll
+        for (int rg = 0; rg < 4; ++rg) {
+            const size_t off = base + d * 32 + 8 * rg;
+            f32x4 x = {oacc[d][4 * rg + 0] * inv, oacc[d][4 * rg + 1] * inv,
+                       oacc[d][4 * rg + 2] * inv, oacc[d][4 * rg + 3] * inv};
+            if (co) *reinterpret_cast<bf16x4*>(co + off) = __builtin_convertvector(x, bf16x4);
+            if (a.out.merge) {
+                const bf16x4 old = *reinterpret_cast<const bf16x4*>(mo + off);
+                x += __builtin_convertvector(old, f32x4);
+            }
+            if (a.out.wide_out) *reinterpret_cast<f32x4*>(a.out.wide_out + off) = x;
+            else *reinterpret_cast<bf16x4*>(mo + off) = __builtin_convertvector(x, bf16x4);
+            if (zf) {
+                const u32x2 z = {0u, 0u};
+                *reinterpret_cast<u32x2*>(zf + off) = z;
+            }
+        }
 }
 
-template <bool LOCAL, int NQB, int NW>
+template <bool LOCAL, int NW>
 __global__ __launch_bounds__(64 * NW) void fwd_kernel(FwdArgs a) {
     __shared__ __attribute__((aligned(1024))) FwdLds lds;
-    const Tile t = tile_of<32 * NQB * NW>(a.gm, a.rs, LOCAL, (int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x, (int)gridDim.y);
-    fwd_body<LOCAL ? kLocal : kGlobal, NQB, NW>(a, t, lds);
+    const Tile t = tile_of<32 * NW>(a.gm, a.rs, LOCAL, (int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x, (int)gridDim.y);
+    fwd_body<LOCAL ? kLocal : kGlobal, NW>(a, t, lds);
 }
 
 // Shared inputs, the window spans the sequence: every row once, in identity order (no lists to wait for), no merge behind it.
@@ -823,7 +751,7 @@ __global__ __launch_bounds__(64 * NW) void fwd_kernel(FwdArgs a) {
 template <int NW>
 __global__ __launch_bounds__(64 * NW, 2) void fwd_whole_kernel(FwdArgs a) {
     __shared__ __attribute__((aligned(1024))) FwdLds lds;
-    fwd_body<kWhole, 1, NW>(a, tile_of<32 * NW>(a.gm, a.rs, false, (int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x, (int)gridDim.y), lds);
+    fwd_body<kWhole, NW>(a, tile_of<32 * NW>(a.gm, a.rs, false, (int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x, (int)gridDim.y), lds);
 }
 
 // Both branches in one launch, for sequences so short that the Global rows' tiles alone leave most
@@ -831,14 +759,14 @@ __global__ __launch_bounds__(64 * NW, 2) void fwd_whole_kernel(FwdArgs a) {
 // the others the Local rows'.  The branches then must not depend on each other: the Global one
 // writes its rows of A only (in fp32, besides the caller's bf16 copy), and O = S + A is formed
 // afterwards (merge_rows) with the one rounding the sequential order has.
-template <int NQB, int NW>
+template <int NW>
 __global__ __launch_bounds__(64 * NW, 2) void fwd_pair_kernel(FwdArgs ag, FwdArgs al, int gx_global) {
     __shared__ __attribute__((aligned(1024))) FwdLds lds;
-    constexpr int BQ = 32 * NQB * NW;
+    constexpr int BQ = 32 * NW;
     if ((int)blockIdx.x < gx_global)
-        fwd_body<kGlobal, NQB, NW>(ag, tile_of<BQ>(ag.gm, ag.rs, false, (int)blockIdx.x, (int)blockIdx.y, gx_global, (int)gridDim.y), lds);
+        fwd_body<kGlobal, NW>(ag, tile_of<BQ>(ag.gm, ag.rs, false, (int)blockIdx.x, (int)blockIdx.y, gx_global, (int)gridDim.y), lds);
     else
-        fwd_body<kLocal, NQB, NW>(al, tile_of<BQ>(al.gm, al.rs, true, (int)blockIdx.x - gx_global, (int)blockIdx.y,
+        fwd_body<kLocal, NW>(al, tile_of<BQ>(al.gm, al.rs, true, (int)blockIdx.x - gx_global, (int)blockIdx.y,
                                                   (int)gridDim.x - gx_global, (int)gridDim.y), lds);
 }
 
@@ -864,9 +792,9 @@ int mfma_fwd(const Geom& g, const RowSet& rs, const void* q, const void* k, cons
     const dim3 grid(tiles_x(g), g.B * g.Hkv);
     KernelTimer kt(rs.local ? "fwd_local" : "fwd_global", st);
     if (rs.local)
-        hipLaunchKernelGGL((fwd_kernel<true, kFwdNQB, kFwdNW>), grid, dim3(64 * kFwdNW), 0, st, a);
+        hipLaunchKernelGGL((fwd_kernel<true, kFwdNW>), grid, dim3(64 * kFwdNW), 0, st, a);
     else
-        hipLaunchKernelGGL((fwd_kernel<false, kFwdNQB, kFwdNW>), grid, dim3(64 * kFwdNW), 0, st, a);
+        hipLaunchKernelGGL((fwd_kernel<false, kFwdNW>), grid, dim3(64 * kFwdNW), 0, st, a);
     return launch_status();
 }
 
@@ -885,9 +813,9 @@ int mfma_fwd_pair(const Geom& g, const RowSet& rs_l, const void* q_l, const void
     {
         KernelTimer kt("fwd_pair", st);
         if (half_tiles(entries))
-            hipLaunchKernelGGL((fwd_pair_kernel<1, 4>), dim3(4 * gx, g.B * g.Hkv), dim3(256), 0, st, ag, al, (int)(2 * gx));
+            hipLaunchKernelGGL((fwd_pair_kernel<4>), dim3(4 * gx, g.B * g.Hkv), dim3(256), 0, st, ag, al, (int)(2 * gx));
         else
-            hipLaunchKernelGGL((fwd_pair_kernel<kFwdNQB, kFwdNW>), dim3(2 * gx, g.B * g.Hkv), dim3(64 * kFwdNW), 0, st, ag,
+            hipLaunchKernelGGL((fwd_pair_kernel<kFwdNW>), dim3(2 * gx, g.B * g.Hkv), dim3(64 * kFwdNW), 0, st, ag,
                                al, (int)gx);
     }
     return launch_status();
