@@ -19,8 +19,8 @@
 // ones, these matrix instructions leave no room under them (microbenchmark, two wavefronts per SIMD: 13.7 ns
 // alone, 19.0 with one vector instruction behind each, 24.1 with four).  So addresses are kept out of the loops and, in
 // the forward and dQ, masks in code of their own (dK/dV tests every pair: a uniform branch there gained nothing).  With
-// D = 128 the registers are all taken: 9 (dK/dV), 16 and 18 (forward and dQ, 32-row tiles) are spilled, none of them inside
-// a matrix loop.  (dK/dV with its second computation inlined in the tile loop and a branch for each of the four stores
+// D = 128 the registers are all taken: 10 (dK/dV), 16 and 19 (forward and dQ, 32-row tiles) are spilled, 33, 27 and 25 where the
+// branches share their inputs, none of them inside a matrix loop.  (dK/dV with its second computation inlined in the tile loop and a branch for each of the four stores
 // of a row's data spilled 221, four of which came back from scratch on every row tile: 4096 tokens, Hq = 8, Hkv = 2, W =
 // 1024, whole step 1174 us, now 1129; 3000 tokens, Hq = Hkv = 8, W = 256 942, now 870.)  A workgroup owns one small tile (16 or 32 query rows, 16 keys) and its NW
 // wavefronts share the *other* axis, each with a partial result of its own, and these meet in LDS at the end:
@@ -681,7 +681,7 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_bwd_dkdv_kernel(Geom gm, Dkdv
                 r0 = k0 * gm.G;
                 r1 = (int)min((long long)k0 + 15 + gm.W, (long long)gm.T - 1) * gm.G + gm.G;
             } else {
-                r0 = rs.kblk_first_row ? max(rs.kblk_first_row[(size_t)bh * (nkb + 1) + min((k0 + rs.shift) >> 6, nkb)], 0) : k0 * gm.G;
+                r0 = rs.kblk_first_row ? max(rs.kblk_first_row[(size_t)bh * (nkb + 1) + walk::list_bounds(k0, rs.shift, nkb).lo], 0) : k0 * gm.G;
                 r1 = num_rows(rs, gm, bh);
             }
             const int rt0 = r0 + 16 * wave;

@@ -114,7 +114,11 @@ __device__ __forceinline__ Tile tile_of(const Geom& gm, const RowSet& rs, bool w
 // The same tile by the classical streaming softmax with a running maximum and rescaling (App. C Alg. 1 as printed, with the
 // rescaling factor read as exp(m_old - m_new)): for tiles the pipeline below gives up on, because a score exceeded
 // a row's fixed reference by so much that a sum left the safe range.  V is transposed on its way into LDS.  A launch of its own
-// for such tiles cost 4.6 us in a prompt of 1000 tokens that had none (42.8 us, now 41.4).
+// for such tiles cost 3 to 5 us per branch where there were none.  Inside the pipeline's kernels it takes the registers that they
+// have, and 14 to 36 of a kernel's are spilled (3 to 5 without it): in the prologue and in this walk, none in the pipeline's loops.
+// Whole forward, us, launch of its own / inside: dense 1001 tokens 82.1 / 72.4, 32768 tokens 8298 / 8263, routed rows alone 32768
+// tokens 1447 / 1441, windows alone 32768 tokens 1805 / 1781, 60000 tokens with W = 1024 1140 / 1113, separate modules 32768 tokens
+// 3233 / 3202.
 struct FwdLds {
     __bf16 k[3][kBK * 128];
     __bf16 v[2][kD * kBK];

@@ -8,6 +8,7 @@
 // backward: the standard softmax-attention gradient restricted to the routed rows (Sec. 3.2).
 #pragma once
 #include "common.hpp"
+#include "dkdv_walk.hpp"
 
 namespace l2a {
 namespace {
@@ -197,7 +198,7 @@ __device__ __forceinline__ void simple_dkdv_key(const Geom& gm, const DkdvSets& 
             r0 = j * gm.G;
             r1 = (last + 1) * gm.G;
         } else {
-            r0 = rs.kblk_first_row ? max(rs.kblk_first_row[(size_t)bh * (nkb + 1) + min((j + rs.shift) >> 6, nkb)], 0) : (j >> 6) * 64 * gm.G;
+            r0 = rs.kblk_first_row ? max(rs.kblk_first_row[(size_t)bh * (nkb + 1) + walk::list_bounds(j, rs.shift, nkb).lo], 0) : (j >> 6) * 64 * gm.G;
             r1 = num_rows(rs, gm, bh);
         }
         for (int r = r0; r < r1; ++r) {

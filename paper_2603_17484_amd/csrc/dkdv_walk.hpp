@@ -108,6 +108,16 @@ L2A_WALK_FN bool walk_down(int kblk, int chunk, int T, int W) {
 // Row sets as the walk sees them.
 enum RowKind { kLocalRows = 0, kDenseRows = 1, kListRows = 2 };
 
+// Entries of kblk_first_row (nkb + 1 of them, entry k = rows with pos < 64 k) that bound a list set's rows for the key
+// block at k0: no row before entry `lo` sees a key of it, all rows from entry `hi` on see all of them.  Rows see
+// keys 0 .. pos - shift; with a shift both are rounded to whole entries, outwards, and the masks do the rest.
+struct ListBounds {
+    int lo, hi;
+};
+L2A_WALK_FN ListBounds list_bounds(int k0, int shift, int nkb) {
+    return ListBounds{imin((k0 + shift) >> 6, nkb), imin((k0 + kKeysPerWg + shift + 63) >> 6, nkb)};
+}
+
 // The tiles [tb, te) of one set that can see the key block starting at key k0, in three runs:
 // [tb, th) may hold rows that lie before some key of the block (causal mask), [th, tt) need no mask,
 // [tt, te) hold rows whose window has moved past some key, or the ragged end of the set.
@@ -121,16 +131,6 @@ struct Runs {
 //                           below k0 / below min(k0 + 128, ceil64(T)) (entries of kblk_first_row)
 //   rows        rows of the set (identity sets: T G)
 //   nsplit, z   the set's tiles are shared between nsplit workgroups; this is workgroup z
-// Entries of kblk_first_row (nkb + 1 of them, entry k = rows with pos < 64 k) that bound a list set's rows for the key
-// block at k0: no row before entry `lo` sees a key of it, all rows from entry `hi` on see all of them.  Rows see
-// keys 0 .. pos - shift; with a shift both are rounded to whole entries, outwards, and the masks do the rest.
-struct ListBounds {
-    int lo, hi;
-};
-L2A_WALK_FN ListBounds list_bounds(int k0, int shift, int nkb) {
-    return ListBounds{imin((k0 + shift) >> 6, nkb), imin((k0 + kKeysPerWg + shift + 63) >> 6, nkb)};
-}
-
 L2A_WALK_FN Runs tile_runs(int kind, int k0, int T, int G, int W, int first_k0, int first_kend, int rows, int nsplit,
                            int z) {
     Runs r{0, 0, 0, 0};
