@@ -16,6 +16,18 @@ def assert_lse(name, got, ref, dtype):
         assert err <= (LSE_FP32 if dtype == "fp32" else LSE_BF16), f"{name}: max err {err:.3e}"
 
 
+def kernels_of(call):
+    """Names of the kernels that a call launches, in order."""
+    B.profile_read()
+    B.profile_enable(True)
+    try:
+        call()
+        torch.cuda.synchronize()
+    finally:
+        B.profile_enable(False)
+    return [name for name, _ in B.profile_read()]
+
+
 def make_case(B_=1, T=600, Hq=4, Hkv=2, D=128, W=100, dtype="bf16", Hm=1, f=0.3, seed=0, mask=None, scale=None):
     w = gen.Workload("case", B_, T, Hq, Hkv, D, W, dtype, "bernoulli", Hm, f)
     x = gen.make_inputs(w, seed, with_dO=True)

@@ -201,8 +201,8 @@ def growing_scores_case(top, T=900, Hq=4, Hkv=2, W=200, seed=40):
 
 
 def redo_flags(lay):
-    """Flags of the tiles the pipelined forward kernel left to the fix-up kernel: they sit behind the two
-    token-minor V copies in the forward workspace -- those of the last branch run, or of both branches
+    """Flags of the tiles the pipelined forward left to the computation with a running maximum: they sit behind the two
+    token-minor V copies in the forward workspace -- one set for branches that ran one after the other, or one for each
     when one launch carried both (short sequences without L2A_FLAG_SEQUENTIAL)."""
     p = lay.p
     up = lambda x, m: (x + m - 1) // m * m

@@ -6,7 +6,7 @@ import torch
 
 from paper_2603_17484_amd import binding as B
 from paper_2603_17484_amd.runner import layer_from_numpy, to_device
-from tests.gpu_helpers import make_case, run_and_check
+from tests.gpu_helpers import kernels_of, make_case, run_and_check
 
 pytestmark = pytest.mark.gpu
 
@@ -71,17 +71,6 @@ def test_the_local_result_does_not_depend_on_who_else_is_routed(Bn, T, Hq, Hkv, 
     other = np.random.default_rng(T).random(x.mask.shape) < 0.5   # (not the complement, which groups the rows alike)
     a, b = forward(x, W), forward(x, W, mask=other.astype(np.uint8))
     assert torch.equal(a.S, b.S) and torch.equal(a.lse_l, b.lse_l)
-
-
-def kernels_of(call):
-    B.profile_read()
-    B.profile_enable(True)
-    try:
-        call()
-        torch.cuda.synchronize()
-    finally:
-        B.profile_enable(False)
-    return [name for name, _ in B.profile_read()]
 
 
 @pytest.mark.parametrize("dtype,apart,together", [("bf16", {"fwd_local", "fwd_global", "bwd_dq_local", "bwd_dq_global"}, {"fwd_whole", "bwd_dq_pair"}),
