@@ -92,7 +92,7 @@ const char* l2a_strerror(int code);
  *             each branch's V (shared inputs: in place of the second, a flag per row: routed) and one int32 flag per tile of 256 rows (tiles per (b, KV head) rounded up to a
  *             multiple of 8; 1 for a tile whose softmax needed a running maximum); when both branches run in one launch (see
  *             l2a_attn_fwd) the flags twice and a [B,T,Hq,D] float buffer for a; L2A_FP32, both branches with
- *             routing lists, T > 256, not L2A_FLAG_SEQUENTIAL: optional room (at most 8 [B,T,Hq,D] float buffers and statistics) for the partial sums that
+ *             routing lists, T > 256, not L2A_FLAG_SEQUENTIAL: optional room (at most 4 [B,T,Hq,D] float buffers and statistics) for the partial sums that
  *             layers with shared inputs use; without it the branches run one after the other; else nothing
  *   backward  delta_t of each branch, [B,Hq,T] float, twice; on the matrix-core path also, per
  *             branch, compact row-major copies of the rows' Q and dO (ceil64(T G) rows per
@@ -188,8 +188,8 @@ int l2a_router_decide(const l2a_params* p, int32_t C, const void* x, const float
  *                   workspace, and a second, small kernel forms o = s + d a.  Either gives the bits of the sequential
  *                   order, where the Global kernel adds its fp32 result to the stored s -- but for tiles whose softmax needed a
  *                   running maximum: which rows a tile holds, and so which are computed that way, differs.
- *   fp32            with shared inputs, kblk_first_row and the optional workspace, T > 256: the keys before the window of a
- *                   routed row are added to the window's sums; results differ by rounding.
+ *   fp32            with shared inputs, kblk_first_row and the optional workspace, T > 256: both branches in one launch and a
+ *                   second, small kernel, the keys of a routed row in parts; results differ by rounding.
  * s and lse_local of a token do not depend on which other tokens are routed (but for such tiles in bf16).
  */
 int l2a_attn_fwd(const l2a_params* p, const void* q_loc, const void* k_loc, const void* v_loc,

@@ -19,19 +19,21 @@
 // ones, these matrix instructions leave no room under them (microbenchmark, two wavefronts per SIMD: 13.7 ns
 // alone, 19.0 with one vector instruction behind each, 24.1 with four).  So addresses are kept out of the loops and, in
 // the forward and dQ, masks in code of their own (dK/dV tests every pair: a uniform branch there gained nothing).  With
-// D = 128 the registers are all taken: 10 (dK/dV), 16 and 19 (forward and dQ, 32-row tiles) are spilled, 33, 27 and 25 where the
+// D = 128 the registers are all taken: 10 (dK/dV), 16 and 19 (forward and dQ, 32-row tiles) are spilled, 33, 20 and 23 where the
 // branches share their inputs, none of them inside a matrix loop.  (dK/dV with its second computation inlined in the tile loop and a branch for each of the four stores
 // of a row's data spilled 221, four of which came back from scratch on every row tile: 4096 tokens, Hq = 8, Hkv = 2, W =
 // 1024, whole step 1174 us, now 1129; 3000 tokens, Hq = Hkv = 8, W = 256 942, now 870.)  A workgroup owns one small tile (16 or 32 query rows, 16 keys) and its NW
 // wavefronts share the *other* axis, each with a partial result of its own, and these meet in LDS at the end:
 // with 16-row tiles a sequence of a few thousand tokens gives a few hundred workgroups, and a serial walk of a
 // whole prefix by one wavefront would set the kernel's time.
-// Layers whose branches share q, k, v compute a routed row's window once for both (row_stats explains the backward's
-// rows), and the keys before it in parts (Parts) in the Local rows' launch: the few routed tiles of a short sequence walked their
-// prefixes alone on a tenth of the chip.  Training step, us, the branches one after the other / this: T = 2048, 1 head, D = 64, W = 256,
-// 20 % routed 109.6 / 70.0 (forward 8.5 + 29 -> 15 + 6, dQ 9.5 + 35 -> 16 + 4); T = 3000, 1 head, D = 128, W = 1024, 5 % 290 / 155; T = 4096,
-// Hq = 8, Hkv = 2, D = 128, W = 1024, 20 % 1135 / 990 (forward 307 -> 252 + 7, dQ 388 -> 318 + 6, dK/dV 523 -> 467).
-// Errors against 64 bits there, dK / dV: 7.6e-7 / 7.3e-7 -> 5.9e-7 / 5.2e-7 of the norm, because rows are walked downwards.
+// Layers whose branches share q, k, v take both branches' forward in one launch, and dQ alike, the routed rows' keys in parts
+// (Parts): the few routed tiles of a short sequence walked their prefixes alone on a tenth of the chip.  In dK and dV a routed row's
+// window counts once for both branches (row_stats).  a and dQ do not take over the Local rows' sums: the errors of s and a are then
+// one error twice, which their sum does not average out (O and dQ up to 3.4 and 2.6 % further from 64 bits at 4096 tokens).
+// Training step, us, the branches one after the other / this: T = 2048, 1 head, D = 64, W = 256, 20 % routed 110.5 / 70.3 (forward
+// 41 -> 23, dQ 48 -> 24); T = 3000, 1 head, D = 128, W = 1024, 5 % 290 / 148; T = 4096, Hq = 8, Hkv = 2, D = 128, W = 1024, 20 %
+// 1134 / 1048 (forward 283 -> 267, dQ 363 -> 342, dK/dV 493 -> 439).
+// Errors against 64 bits there, dK / dV: 7.7e-7 / 7.5e-7 -> 6.0e-7 / 5.2e-7 of the norm, because rows are walked downwards.
 #include "attn_simple.hpp"
 
 
@@ -205,32 +207,31 @@ __device__ __forceinline__ TileRange tile_range(const Geom& gm, const RowSet& rs
     TileRange t;
     t.r0 = tile * 16 * RB;
     t.n_rows = n_rows;
-    t.pmin = __builtin_amdgcn_readfirstlane(row_code(rs, gm, bh, t.r0) / gm.G) - rs.shift;  // the last keys its rows see
-    t.pmax = __builtin_amdgcn_readfirstlane(row_code(rs, gm, bh, min(t.r0 + 16 * RB, n_rows) - 1) / gm.G) - rs.shift;
-    const int first = (rs.local ? max(t.pmin - gm.W, 0) : 0) & ~15, all = t.pmax < 0 ? 0 : max(t.pmax - first, 0) / 16 + 1;
+    t.pmin = __builtin_amdgcn_readfirstlane(row_code(rs, gm, bh, t.r0) / gm.G);
+    t.pmax = __builtin_amdgcn_readfirstlane(row_code(rs, gm, bh, min(t.r0 + 16 * RB, n_rows) - 1) / gm.G);
+    const int first = (rs.local ? max(t.pmin - gm.W, 0) : 0) & ~15, all = max(t.pmax - first, 0) / 16 + 1;
     const int b0 = all * z / nz;
     t.key0 = first + 16 * b0;
     t.nblk = all * (z + 1) / nz - b0;
     return t;
 }
-// Keys before the window, for rows whose branches share their inputs: a tile's blocks are shared between nz workgroups, and
-// what each finds goes to its rows' places in x ([bh][z][row of the list][D]) and s ([bh][z][row][2]), which are added up
-// (combine kernels) together with the window's part.
+// Routed rows beside the Local ones, in one launch: a tile's blocks are shared between nz workgroups, and what each finds goes
+// to its rows' places in x ([bh][z][row of the list][D]) and s (forward [bh][z][row][2], dQ [bh][z][row]), which the combine
+// kernels add up.
 struct Parts {
     float *x, *s;
     int nz;
-    int groups;     // the first `groups` workgroups of the grid take these tiles (nz each), the others the tiles of the main set
-    float* main_s;  // forward: reference and row sum of the main set's rows, [bh][row][2]
+    int groups;  // the first `groups` workgroups of the grid take these tiles (nz each), the others the Local ones
 };
 // Which tile a workgroup starts with, how far the next one is, and which part it takes
 struct Role {
-    bool far;
+    bool part;
     int it, step, z, nz;
 };
-template <bool SHARED>  // false: a launch of one set's tiles
+template <bool PARTS>  // false: a launch of one set's tiles
 __device__ __forceinline__ Role role_of(const Parts& p) {
     const int x = blockIdx.x;
-    if (!SHARED) return Role{false, x, (int)gridDim.x, 0, 1};
+    if (!PARTS) return Role{false, x, (int)gridDim.x, 0, 1};
     if (x < p.groups) return Role{true, x / p.nz, p.groups / p.nz, x % p.nz, p.nz};
     return Role{false, x - p.groups, (int)gridDim.x - p.groups, 0, 1};
 }
@@ -251,8 +252,8 @@ __device__ __forceinline__ float exp2_(float x) { return __builtin_amdgcn_exp2f(
 // Forward.  Workgroup = 16 RB rows, wavefront w takes the 16-key blocks w, w + NW, ... of the rows' keys with
 // a streaming softmax of its own (Alg. 1, running maximum per row); the partials are merged in LDS.
 // ---------------------------------------------------------------------------------------
-template <int D, int RB, int NW, bool SHARED>
-__global__ __launch_bounds__(64 * NW, 2) void fp32_fwd_kernel(Geom gm, RowSet rs_main, RowSet rs_far, const float* __restrict__ q,
+template <int D, int RB, int NW, bool PARTS>
+__global__ __launch_bounds__(64 * NW, 2) void fp32_fwd_kernel(Geom gm, RowSet rs_main, RowSet rs_parts, const float* __restrict__ q,
                                                               const float* __restrict__ k, const float* __restrict__ v,
                                                               FwdOut out, Parts parts) {
     constexpr int R = 16 * RB;
@@ -265,8 +266,8 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_fwd_kernel(Geom gm, RowSet rs
     const int bh = blockIdx.y, b = bh / gm.Hkv, hk = bh - b * gm.Hkv;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 15, kq = lane >> 4;
-    const Role ro = role_of<SHARED>(parts);
-    const RowSet rs = ro.far ? rs_far : rs_main;
+    const Role ro = role_of<PARTS>(parts);
+    const RowSet rs = ro.part ? rs_parts : rs_main;
     const int n_rows = num_rows(rs, gm, bh), n_tiles = (n_rows + R - 1) / R;
     const size_t kv_row = (size_t)gm.Hkv * D;
     const size_t kv0 = ((size_t)b * gm.T * gm.Hkv + hk) * D;
@@ -288,7 +289,7 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_fwd_kernel(Geom gm, RowSet rs
         float m[RB], l[RB];
 #pragma unroll
         for (int c = 0; c < RB; ++c) {
-            pos[c] = row_code(rs, gm, bh, min(tr.r0 + 16 * c + n, n_rows - 1)) / gm.G - rs.shift;
+            pos[c] = row_code(rs, gm, bh, min(tr.r0 + 16 * c + n, n_rows - 1)) / gm.G;
             o[c].zero();
             m[c] = -INFINITY;
             l[c] = 0.f;
@@ -347,13 +348,13 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_fwd_kernel(Geom gm, RowSet rs
         for (int c = 0; c < RB; ++c) chk = fmaf(l[c], 0.f, chk + o[c].check());
         if (__syncthreads_or(chk != 0.f)) {
             const int r = tr.r0 + (int)(threadIdx.x >> 2), part = threadIdx.x & 3;
-            if (threadIdx.x < 4 * R && !ro.far) {
-                simple_fwd_row<float, D / 4>(gm, rs, q, k, v, out, bh, r, part, parts.main_s);
+            if (threadIdx.x < 4 * R && !ro.part) {
+                simple_fwd_row<float, D / 4>(gm, rs, q, k, v, out, bh, r, part);
             } else if (threadIdx.x < 4 * R && r < n_rows) {
                 const Row row = get_row(rs, gm, bh, r);
                 float m_, l_, acc[D / 4];
                 simple_fwd_keys<float, D / 4>(gm, q, k, v, b, hk, (((size_t)b * gm.T + row.pos) * gm.Hq + hk * gm.G + row.g) * D + part * (D / 4),
-                                              part, tr.key0, min(tr.key0 + 16 * tr.nblk - 1, row.pos - rs.shift), m_, l_, acc);
+                                              part, tr.key0, min(tr.key0 + 16 * tr.nblk - 1, row.pos), m_, l_, acc);
                 const size_t at = part_row(gm, ro, bh, r);
                 for (int i = 0; i < D / 4; ++i) parts.x[at * D + part * (D / 4) + i] = acc[i];
                 if (part == 0) parts.s[2 * at] = m_ / gm.scale, parts.s[2 * at + 1] = l_;
@@ -384,7 +385,7 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_fwd_kernel(Geom gm, RowSet rs
                 lt += f * sl[w][row];
                 x += f * ld4(&so[w][row][ch]);
             }
-            if (ro.far) {
+            if (ro.part) {
                 const size_t at = part_row(gm, ro, bh, tr.r0 + row);
                 *reinterpret_cast<f32x4*>(parts.x + at * D + ch) = x;
                 if (ch == 0) parts.s[2 * at] = mm, parts.s[2 * at + 1] = lt;
@@ -400,10 +401,6 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_fwd_kernel(Geom gm, RowSet rs
             if (ch == 0) {
                 const size_t st = ((size_t)b * gm.Hq + h) * gm.T + p;
                 out.lse_out[st] = fmaf(mm, gm.scale, logf(lt));
-                if (SHARED && parts.main_s) {
-                    float* ms = parts.main_s + 2 * ((size_t)bh * gm.T * gm.G + tr.r0 + row);
-                    ms[0] = mm, ms[1] = lt;
-                }
                 if (out.lse_fill) out.lse_fill[st] = -INFINITY;
             }
         }
@@ -411,21 +408,19 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_fwd_kernel(Geom gm, RowSet rs
     }
 }
 
-// a of the routed rows: the window's sums (S lies in O, its reference and row sum in main_s) and those of the parts before
-// it; o = s + a.  D / 4 lanes per row.
+// a of the routed rows from their parts, and o = s + a (s lies in O).  nz = 0: the window spans the sequence, a = s.  D / 4 lanes
+// per row.
 template <int D>
-__global__ __launch_bounds__(256) void fp32_fwd_combine_kernel(Geom gm, RowSet rs, Parts parts, FwdOut out) {
+__global__ __launch_bounds__(256) void fp32_fwd_combine_kernel(Geom gm, RowSet rs, Parts parts, const float* __restrict__ lse_l, FwdOut out) {
     const int bh = blockIdx.y, b = bh / gm.Hkv, hk = bh - b * gm.Hkv;
     const int n_rows = num_rows(rs, gm, bh), ch = (threadIdx.x % (D / 4)) * 4;
     for (int r = blockIdx.x * (1024 / D) + threadIdx.x / (D / 4); r < n_rows; r += gridDim.x * (1024 / D)) {
         const int code = row_code(rs, gm, bh, r), p = code / gm.G, h = hk * gm.G + (code - p * gm.G);
-        const size_t off = (((size_t)b * gm.T + p) * gm.Hq + h) * D + ch;
-        const float* ms = parts.main_s + 2 * ((size_t)bh * gm.T * gm.G + code);
+        const size_t off = (((size_t)b * gm.T + p) * gm.Hq + h) * D + ch, so = ((size_t)b * gm.Hq + h) * gm.T + p;
         const f32x4 sx = ld4((const float*)out.main_out + off);
-        float top = ms[0], sum = ms[1];
-        f32x4 x = sx * sum;
-        const int nz = p >= rs.shift ? parts.nz : 0;
-        for (int z = 0; z < nz; ++z) {
+        float top = -INFINITY, sum = 0.f;
+        f32x4 x = {0.f, 0.f, 0.f, 0.f};
+        for (int z = 0; z < parts.nz; ++z) {
             const size_t at = ((size_t)bh * parts.nz + z) * gm.T * gm.G + r;
             const float m = parts.s[2 * at], l = parts.s[2 * at + 1];
             const f32x4 px = ld4(parts.x + at * D + ch);
@@ -436,26 +431,25 @@ __global__ __launch_bounds__(256) void fp32_fwd_combine_kernel(Geom gm, RowSet r
             top = up;
         }
         x *= 1.f / sum;
-        if (nz == 0) x = sx;
+        if (parts.nz == 0) x = sx;
         if (out.copy_out) *reinterpret_cast<f32x4*>((float*)out.copy_out + off) = x;
         *reinterpret_cast<f32x4*>((float*)out.main_out + off) = sx + x;
-        if (ch == 0) out.lse_out[((size_t)b * gm.Hq + h) * gm.T + p] = fmaf(top, gm.scale, logf(sum));
+        if (ch == 0) out.lse_out[so] = parts.nz == 0 ? lse_l[so] : fmaf(top, gm.scale, logf(sum));
     }
 }
 
 // ---------------------------------------------------------------------------------------
 // dQ.  Tiles and key split as in the forward; the exact delta = sum_j p dp replaces the one from the saved output.
 // ---------------------------------------------------------------------------------------
-template <int D, int RB, int NW, bool SHARED>
-__global__ __launch_bounds__(64 * NW, 2) void fp32_bwd_dq_kernel(Geom gm, RowSet rs_main, RowSet rs_far,
+template <int D, int RB, int NW, bool PARTS>
+__global__ __launch_bounds__(64 * NW, 2) void fp32_bwd_dq_kernel(Geom gm, RowSet rs_main, RowSet rs_parts,
                                                                  const float* __restrict__ q,
                                                                  const float* __restrict__ k,
                                                                  const float* __restrict__ v,
                                                                  const float* __restrict__ dO,
                                                                  const float* __restrict__ lse_main,
-                                                                 const float* __restrict__ lse_far, float* delta_main,
-                                                                 const float* __restrict__ delta_far,
-                                                                 const float* __restrict__ share, float* dq, int accumulate,
+                                                                 const float* __restrict__ lse_parts, float* delta_main,
+                                                                 const float* __restrict__ delta_parts, float* dq, int accumulate,
                                                                  Parts parts) {
     constexpr int R = 16 * RB;
     // first the Q and dO rows and the wavefronts' K, V tiles, then the partial results
@@ -468,9 +462,9 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_bwd_dq_kernel(Geom gm, RowSet
     const int bh = blockIdx.y, b = bh / gm.Hkv, hk = bh - b * gm.Hkv;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 15, kq = lane >> 4;
-    const Role ro = role_of<SHARED>(parts);
-    const RowSet rs = ro.far ? rs_far : rs_main;
-    const float *lse = ro.far ? lse_far : lse_main, *delta = ro.far ? delta_far : delta_main;
+    const Role ro = role_of<PARTS>(parts);
+    const RowSet rs = ro.part ? rs_parts : rs_main;
+    const float *lse = ro.part ? lse_parts : lse_main, *delta = ro.part ? delta_parts : delta_main;
     const int n_rows = num_rows(rs, gm, bh), n_tiles = (n_rows + R - 1) / R;
     const size_t kv_row = (size_t)gm.Hkv * D;
     const size_t kv0 = ((size_t)b * gm.T * gm.Hkv + hk) * D;
@@ -499,7 +493,6 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_bwd_dq_kernel(Geom gm, RowSet
             const size_t st = ((size_t)b * gm.Hq + hk * gm.G + (code - pos[c] * gm.G)) * gm.T + pos[c];
             L[c] = lse[st];
             dl[c] = delta[st];
-            pos[c] -= rs.shift;
             dx[c] = 0.f;
             acc[c].zero();
         }
@@ -549,15 +542,15 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_bwd_dq_kernel(Geom gm, RowSet
         for (int c = 0; c < RB; ++c) chk += acc[c].check();
         if (__syncthreads_or(chk != 0.f)) {
             const int r = tr.r0 + (int)(threadIdx.x >> 2), part = threadIdx.x & 3;
-            if (threadIdx.x < 4 * R && !ro.far) {
-                simple_dq_row<float, D / 4>(gm, rs, q, k, v, dO, lse, delta_main, dq, accumulate, bh, r, part, share);
+            if (threadIdx.x < 4 * R && !ro.part) {
+                simple_dq_row<float, D / 4>(gm, rs, q, k, v, dO, lse, delta_main, dq, accumulate, bh, r, part);
             } else if (threadIdx.x < 4 * R && r < n_rows) {
                 const Row row = get_row(rs, gm, bh, r);
                 const int h = hk * gm.G + row.g;
                 const size_t so = ((size_t)b * gm.Hq + h) * gm.T + row.pos;
                 float dx_, acc_[D / 4];
                 simple_dq_keys<float, D / 4>(gm, q, k, v, dO, b, hk, (((size_t)b * gm.T + row.pos) * gm.Hq + h) * D + part * (D / 4), part,
-                                             tr.key0, min(tr.key0 + 16 * tr.nblk - 1, row.pos - rs.shift), lse[so], delta[so], dx_, acc_);
+                                             tr.key0, min(tr.key0 + 16 * tr.nblk - 1, row.pos), lse[so], delta[so], dx_, acc_);
                 const size_t at = part_row(gm, ro, bh, r);
                 for (int i = 0; i < D / 4; ++i) parts.x[at * D + part * (D / 4) + i] = acc_[i];
                 if (part == 0) parts.s[at] = dx_;
@@ -578,7 +571,7 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_bwd_dq_kernel(Geom gm, RowSet
 #pragma unroll
             for (int w = 0; w < NW; ++w) x += ld4(&so[w][row][ch]);
             const int code = row_code(rs, gm, bh, tr.r0 + row), p = code / gm.G, h = hk * gm.G + (code - p * gm.G);
-            if (ro.far) {
+            if (ro.part) {
                 const size_t at = part_row(gm, ro, bh, tr.r0 + row);
                 *reinterpret_cast<f32x4*>(parts.x + at * D + ch) = x;
                 if (ch == 0) {
@@ -590,7 +583,7 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_bwd_dq_kernel(Geom gm, RowSet
                 continue;
             }
             float* dst = dq + (((size_t)b * gm.T + p) * gm.Hq + h) * D + ch;
-            x *= SHARED && share ? gm.scale * (1.f + share[((size_t)b * gm.Hq + h) * gm.T + p]) : gm.scale;
+            x *= gm.scale;
             *reinterpret_cast<f32x4*>(dst) = accumulate ? ld4(dst) + x : x;
             if (ch == 0) {
                 float d = 0.f;
@@ -603,8 +596,9 @@ __global__ __launch_bounds__(64 * NW, 2) void fp32_bwd_dq_kernel(Geom gm, RowSet
     }
 }
 
-// dQ of the routed rows: the parts before the window are added; their exact deltas, and the delta of the row that
-// both branches' rows make in the window (row_stats), which the dK/dV kernel takes.
+// dQ of the routed rows: their parts are added to the Local branch's.  nz = 0: the window spans the sequence, and what lies in dq is
+// that of the row that the two branches make (row_stats), which counts 1 + a times.  Then the exact deltas: delta_g, and delta_l
+// of the row that the branches make in the window, which the dK/dV kernel takes.
 template <int D>
 __global__ __launch_bounds__(256) void fp32_dq_combine_kernel(Geom gm, RowSet rs, Parts parts, const float* __restrict__ share,
                                                               float* delta_l, float* delta_g, float* dq) {
@@ -613,17 +607,18 @@ __global__ __launch_bounds__(256) void fp32_dq_combine_kernel(Geom gm, RowSet rs
     for (int r = blockIdx.x * (1024 / D) + threadIdx.x / (D / 4); r < n_rows; r += gridDim.x * (1024 / D)) {
         const int code = row_code(rs, gm, bh, r), p = code / gm.G, h = hk * gm.G + (code - p * gm.G);
         const size_t off = (((size_t)b * gm.T + p) * gm.Hq + h) * D + ch, so = ((size_t)b * gm.Hq + h) * gm.T + p;
+        const float a = share[so];
         f32x4 x = {0.f, 0.f, 0.f, 0.f};
         float d = 0.f;
-        const int nz = p >= rs.shift ? parts.nz : 0;
-        for (int z = 0; z < nz; ++z) {
+        for (int z = 0; z < parts.nz; ++z) {
             const size_t at = ((size_t)bh * parts.nz + z) * gm.T * gm.G + r;
             x += ld4(parts.x + at * D + ch);
             d += parts.s[at];
         }
-        if (nz) *reinterpret_cast<f32x4*>(dq + off) = ld4(dq + off) + x * gm.scale;
+        const f32x4 y = ld4(dq + off);
+        *reinterpret_cast<f32x4*>(dq + off) = parts.nz ? y + x * gm.scale : y * (1.f + a);
         if (ch == 0) {
-            const float a = share[so], dl = delta_l[so], dg = a * dl + d;
+            const float dl = delta_l[so], dg = parts.nz ? d : a * dl;
             delta_g[so] = dg;
             delta_l[so] = (dl + a * dg) / (1.f + a);
         }
@@ -815,31 +810,40 @@ bool wide_tiles(const Geom& g, const RowSet& rs) {
     return (rs.row_idx ? tiles / 4 : tiles) >= 1024;
 }
 
-// Workgroups that share a routed tile's keys before the window (none if no row has such keys): until there are two workgroups
-// per CU if a quarter of all rows is routed, and until none takes more than about 1024 keys, so that they end with the Local
-// rows' (fewer where their partial sums would be many times the tensors); at least 256 keys each.
-int far_parts(const Geom& g) {
-    const long long tiles = std::max(1LL, (long long)g.T * g.G / 64 * g.B * g.Hkv), keys = (long long)g.T - g.W - 1;
-    if (keys <= 0) return 0;
-    const long long want = std::max((512 + tiles - 1) / tiles, std::min((keys + 512) / 1024, std::max(1LL, 8192 / tiles)));
-    return (int)std::min(std::min(want, 8LL), std::max(1LL, keys / 256));
+// Workgroups that share a routed tile's keys.  Each part has a tile's first and last steps of its own, so that many of them cost
+// most where many rows are routed, and few of them leave the longest tiles to themselves where few are.  Forward and dQ, the
+// branches one after the other / this, 5 / 20 / 50 % routed, W = 256, by parts:
+//   narrow tiles   1 head, D = 64, T = 2000    1: 1.13 / 1.12 / 1.13   3: 1.92 / 1.95 / 1.78   6: 2.12 / 1.90 / 1.57
+//                  8 heads of their own K and V, D = 128, T = 2000     1: 1.08 / 0.93 / 1.07   2: 1.28 / 1.12 / 1.16   4: 1.35 / 1.06 / 0.99
+//                  8 query, 2 KV heads, D = 128, T = 700               1: 1.46 / 1.41 / 1.21   2: 1.45 / 1.35 / 1.08
+//                  ditto T = 2000      1: 1.23 / 1.15 / 0.99   2: 1.45 / 1.17 / 0.92   4: 1.39 / 1.05 / 0.78
+//   wide tiles     ditto T = 4096      2: 1.15 / 0.82 / 1.04   4: 1.44 / 1.00 / 1.01   8: 1.40 / 0.92 / 0.87
+//                  ditto T = 16384, W = 1024      2: 1.92 / 1.07 / 1.01   4: 1.93 / 1.06 / 1.00   8: 1.87 / 1.03 / 0.95
+// Wide tiles, which are so for the Local rows' sake, take at least two: no wavefront's sums are then longer than in the routed
+// set's own narrow ones.  None while the window spans the sequence and the tiles are narrow: the Local rows then hold the very
+// bits that a has.
+int routed_parts(const Geom& g) {
+    const bool wide = wide_tiles(g, RowSet{nullptr, nullptr, nullptr, 1});
+    if (g.T - 1 <= g.W && !wide) return 0;
+    const long long tiles = (long long)g.T * g.G / 64 * g.B * g.Hkv;  // of 16 rows, a quarter of them routed
+    if (wide) return (int)std::max(2LL, std::min(std::min((g.T + 512) / 1024LL, 4LL), 8192 / tiles));
+    if (tiles <= 64) return std::min(std::max(g.T / 128, 1), 3);
+    return g.G >= 4 && tiles >= 128 ? 1 : 2;
 }
 size_t round256(size_t n) { return (n + 255) / 256 * 256; }
 size_t all_rows(const Geom& g) { return (size_t)g.B * g.Hkv * g.T * g.G; }
-Parts place_parts(const Geom& g, char* ws, int stats, bool main_s) {  // stats: floats per row and part
+Parts place_parts(const Geom& g, char* ws) {
     Parts p{};
-    p.nz = far_parts(g);
+    p.nz = routed_parts(g);
     p.x = (float*)ws;
     p.s = (float*)(ws + round256(all_rows(g) * p.nz * g.D * sizeof(float)));
-    if (main_s) p.main_s = (float*)((char*)p.s + round256(all_rows(g) * p.nz * stats * sizeof(float)));
     return p;
 }
-size_t parts_bytes(const Geom& g, int stats, bool main_s) {
-    const int nz = far_parts(g);
-    return round256(all_rows(g) * nz * g.D * sizeof(float)) + round256(all_rows(g) * nz * stats * sizeof(float)) +
-           (main_s ? round256(all_rows(g) * 2 * sizeof(float)) : 0);
+size_t parts_bytes(const Geom& g, int stats) {  // stats: floats per row and part
+    const int nz = routed_parts(g);
+    return round256(all_rows(g) * nz * g.D * sizeof(float)) + round256(all_rows(g) * nz * stats * sizeof(float));
 }
-// The grid of tiles of 16 RB rows: those of the main set, behind parts.nz workgroups for each tile of the far set
+// The grid of tiles of 16 RB rows: those of the main set, behind parts.nz workgroups for each tile of the routed rows
 dim3 role_grid(const Geom& g, int rows, Parts& parts) {
     const long long tiles = std::min(((long long)g.T * g.G + rows - 1) / rows, kMaxTiles / 16);
     parts.groups = (int)tiles * parts.nz;
@@ -847,7 +851,7 @@ dim3 role_grid(const Geom& g, int rows, Parts& parts) {
 }
 
 struct FwdCall {
-    RowSet main, far;
+    RowSet main, routed;
     const void *q, *k, *v;
     FwdOut out;
     Parts parts;
@@ -855,19 +859,18 @@ struct FwdCall {
 template <int D, int RB, int NW>
 void launch_fwd(const Geom& g, FwdCall c, hipStream_t st) {
     const dim3 grid = role_grid(g, 16 * RB, c.parts);
-    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(64 * NW), 0, st, g, c.main, c.far, cf(c.q), cf(c.k), cf(c.v), c.out, c.parts); };
-    c.parts.main_s ? launch(fp32_fwd_kernel<D, RB, NW, true>) : launch(fp32_fwd_kernel<D, RB, NW, false>);
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(64 * NW), 0, st, g, c.main, c.routed, cf(c.q), cf(c.k), cf(c.v), c.out, c.parts); };
+    c.parts.nz ? launch(fp32_fwd_kernel<D, RB, NW, true>) : launch(fp32_fwd_kernel<D, RB, NW, false>);
 }
 void run_fwd(const Geom& g, const FwdCall& c, bool wide, hipStream_t st) {
     if (g.D == 64) wide ? launch_fwd<64, 2, 4>(g, c, st) : launch_fwd<64, 1, 8>(g, c, st);
     else wide ? launch_fwd<128, 2, 4>(g, c, st) : launch_fwd<128, 1, 8>(g, c, st);
 }
 struct DqCall {
-    RowSet main, far;
+    RowSet main, routed;
     const void *q, *k, *v, *dO;
-    const float *lse_main, *lse_far;
-    float *delta_main, *delta_far;
-    const float* share;
+    const float *lse_main, *lse_parts;
+    float *delta_main, *delta_parts;
     void* dq;
     int accumulate;
     Parts parts;
@@ -876,10 +879,10 @@ template <int D, int RB, int NW>
 void launch_dq(const Geom& g, DqCall c, hipStream_t st) {
     const dim3 grid = role_grid(g, 16 * RB, c.parts);
     auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, grid, dim3(64 * NW), 0, st, g, c.main, c.far, cf(c.q), cf(c.k), cf(c.v), cf(c.dO), c.lse_main, c.lse_far,
-                           c.delta_main, c.delta_far, c.share, (float*)c.dq, c.accumulate, c.parts);
+        hipLaunchKernelGGL(kernel, grid, dim3(64 * NW), 0, st, g, c.main, c.routed, cf(c.q), cf(c.k), cf(c.v), cf(c.dO), c.lse_main, c.lse_parts,
+                           c.delta_main, c.delta_parts, (float*)c.dq, c.accumulate, c.parts);
     };
-    c.share ? launch(fp32_bwd_dq_kernel<D, RB, NW, true>) : launch(fp32_bwd_dq_kernel<D, RB, NW, false>);
+    c.parts.nz ? launch(fp32_bwd_dq_kernel<D, RB, NW, true>) : launch(fp32_bwd_dq_kernel<D, RB, NW, false>);
 }
 void run_dq(const Geom& g, const DqCall& c, bool wide, hipStream_t st) {
     if (g.D == 64) wide ? launch_dq<64, 2, 4>(g, c, st) : launch_dq<64, 1, 8>(g, c, st);
@@ -899,19 +902,19 @@ int fp32_fwd(const Geom& g, const RowSet& rs, const void* q, const void* k, cons
     return launch_status();
 }
 
-size_t fp32_fwd_shared_bytes(const Geom& g) { return parts_bytes(g, 2, true); }
+size_t fp32_fwd_shared_bytes(const Geom& g) { return parts_bytes(g, 2); }
 
 int fp32_fwd_shared(const Geom& g, const RowSet& rs_l, const RowSet& rs_g, const void* q, const void* k, const void* v,
                     const FwdOut& out_l, const FwdOut& out_g, void* ws, hipStream_t st) {
     if (g.D != 64 && g.D != 128) return L2A_ERR_UNSUPPORTED;
-    const Parts parts = place_parts(g, (char*)ws, 2, true);
+    const Parts parts = place_parts(g, (char*)ws);
     {
         KernelTimer kt("fp32_fwd_shared", st);
         run_fwd(g, FwdCall{rs_l, rs_g, q, k, v, out_l, parts}, wide_tiles(g, rs_l), st);
     }
     KernelTimer kt("fp32_fwd_combine", st);
-    if (g.D == 64) hipLaunchKernelGGL(fp32_fwd_combine_kernel<64>, row_grid(g), dim3(256), 0, st, g, rs_g, parts, out_g);
-    else hipLaunchKernelGGL(fp32_fwd_combine_kernel<128>, row_grid(g), dim3(256), 0, st, g, rs_g, parts, out_g);
+    if (g.D == 64) hipLaunchKernelGGL(fp32_fwd_combine_kernel<64>, row_grid(g), dim3(256), 0, st, g, rs_g, parts, (const float*)out_l.lse_out, out_g);
+    else hipLaunchKernelGGL(fp32_fwd_combine_kernel<128>, row_grid(g), dim3(256), 0, st, g, rs_g, parts, (const float*)out_l.lse_out, out_g);
     return launch_status();
 }
 
@@ -919,20 +922,22 @@ int fp32_bwd_dq(const Geom& g, const RowSet& rs, const void* q, const void* k, c
                 const float* lse, float* delta, void* dq, int accumulate, hipStream_t st) {
     if (g.D != 64 && g.D != 128) return L2A_ERR_UNSUPPORTED;
     KernelTimer kt(rs.local ? "fp32_bwd_dq_local" : "fp32_bwd_dq_global", st);
-    run_dq(g, DqCall{rs, rs, q, k, v, dO, lse, lse, delta, delta, nullptr, dq, accumulate, Parts{}}, wide_tiles(g, rs), st);
+    run_dq(g, DqCall{rs, rs, q, k, v, dO, lse, lse, delta, delta, dq, accumulate, Parts{}}, wide_tiles(g, rs), st);
     return launch_status();
 }
 
-size_t fp32_dq_shared_bytes(const Geom& g) { return parts_bytes(g, 1, false); }
+size_t fp32_dq_shared_bytes(const Geom& g) { return parts_bytes(g, 1); }
+
+bool fp32_window_is_all(const Geom& g) { return routed_parts(g) == 0; }
 
 int fp32_bwd_dq_shared(const Geom& g, const RowSet& rs_l, const RowSet& rs_g, const void* q, const void* k, const void* v,
                        const void* dO, const float* lse_l, const float* lse_g, float* delta_l, float* delta_g, const float* share,
                        void* dq, void* ws, hipStream_t st) {
     if (g.D != 64 && g.D != 128) return L2A_ERR_UNSUPPORTED;
-    const Parts parts = place_parts(g, (char*)ws, 1, false);
+    const Parts parts = place_parts(g, (char*)ws);
     {
         KernelTimer kt("fp32_bwd_dq_shared", st);
-        run_dq(g, DqCall{rs_l, rs_g, q, k, v, dO, lse_l, lse_g, delta_l, delta_g, share, dq, 0, parts}, wide_tiles(g, rs_l), st);
+        run_dq(g, DqCall{rs_l, rs_g, q, k, v, dO, lse_l, lse_g, delta_l, delta_g, dq, 0, parts}, wide_tiles(g, rs_l), st);
     }
     KernelTimer kt("fp32_dq_combine", st);
     if (g.D == 64) hipLaunchKernelGGL(fp32_dq_combine_kernel<64>, row_grid(g), dim3(256), 0, st, g, rs_g, parts, share, delta_l, delta_g, (float*)dq);

@@ -76,7 +76,7 @@ __device__ __forceinline__ void simple_fwd_keys(const Geom& gm, const E* __restr
 template <typename E, int DL>
 __device__ __forceinline__ void simple_fwd_row(const Geom& gm, const RowSet& rs, const E* __restrict__ q,
                                                const E* __restrict__ k, const E* __restrict__ v, const FwdOut& out,
-                                               int bh, int r, int part, float* row_s = nullptr) {
+                                               int bh, int r, int part) {
     const int b = bh / gm.Hkv, hk = bh % gm.Hkv;
     if (r >= num_rows(rs, gm, bh)) return;
     const Row row = get_row(rs, gm, bh, r);
@@ -100,10 +100,6 @@ __device__ __forceinline__ void simple_fwd_row(const Geom& gm, const RowSet& rs,
     if (part == 0) {
         const size_t so = ((size_t)b * gm.Hq + h) * gm.T + row.pos;
         out.lse_out[so] = m + logf(l);
-        if (row_s) {  // reference (of the unscaled scores) and row sum, by row
-            float* rs_ = row_s + 2 * ((size_t)bh * gm.T * gm.G + r);
-            rs_[0] = m / gm.scale, rs_[1] = l;
-        }
         if (out.lse_fill) out.lse_fill[so] = -INFINITY;
     }
 }
@@ -144,8 +140,7 @@ template <typename E, int DL>
 __device__ __forceinline__ void simple_dq_row(const Geom& gm, const RowSet& rs, const E* __restrict__ q,
                                               const E* __restrict__ k, const E* __restrict__ v,
                                               const E* __restrict__ dO, const float* __restrict__ lse, float* delta,
-                                              E* dq, int accumulate, int bh, int r, int part,
-                                              const float* __restrict__ share = nullptr) {
+                                              E* dq, int accumulate, int bh, int r, int part) {
     const int b = bh / gm.Hkv, hk = bh % gm.Hkv;
     if (r >= num_rows(rs, gm, bh)) return;
     const Row row = get_row(rs, gm, bh, r);
@@ -159,7 +154,7 @@ __device__ __forceinline__ void simple_dq_row(const Geom& gm, const RowSet& rs, 
     if (part == 0) delta[so] = dl_exact;
 #pragma unroll
     for (int i = 0; i < DL; ++i) {
-        float x = acc[i] * gm.scale * (share ? 1.f + share[so] : 1.f);
+        float x = acc[i] * gm.scale;
         if (accumulate) x += ld(dq + qoff + i);
         st(dq + qoff + i, x);
     }

@@ -22,7 +22,7 @@ struct RowSet {
     const int32_t* count;    // [B,Hkv]     or nullptr = T*G rows
     const int32_t* kblk_first_row;  // [B,Hkv,ceil(T/64)+1] or nullptr (identity: 64*k*G)
     int local;               // 1: sliding-window branch
-    int shift = 0;           // GLOBAL, fp32: keys 0..pos - shift only (what the fp32 kernels leave to this set with shared inputs: W + 1)
+    int shift = 0;           // GLOBAL, fp32 dK/dV: keys 0..pos - shift only (what it leaves to this set with shared inputs: W + 1)
 };
 
 constexpr float kLog2e = 1.4426950408889634f;
@@ -76,9 +76,10 @@ int fp32_bwd_dq(const Geom& g, const RowSet& rs, const void* q, const void* k, c
 int fp32_bwd_dkdv(const Geom& g, const RowSet* sets, int nsets, const void* q, const void* k, const void* v,
                   const void* dO, const float* const* lse, const float* const* delta, const float* const* share, void* dk,
                   void* dv, hipStream_t st);
-// Shared inputs: a routed row's window once for both branches (rs_l), and the keys before it (rs_g, shift = W + 1), in one launch and
-// a combine.  out_l: s of all rows, in O; out_g: a, added to O.  dq: on return delta_l is that of the rows folded by `share`
-// (row_stats), delta_g complete, both exact.
+// Shared inputs: the Local rows and the routed rows' keys in parts, in one launch and a combine.  out_l: s of all rows, in O; out_g:
+// a, added to O.  dq: on return delta_g is complete and delta_l that of the rows folded by `share` (row_stats), both exact.
+// fp32_window_is_all: there are no parts, a = s, and dq takes the folded rows' deltas.
+bool fp32_window_is_all(const Geom& g);
 size_t fp32_fwd_shared_bytes(const Geom& g);
 int fp32_fwd_shared(const Geom& g, const RowSet& rs_l, const RowSet& rs_g, const void* q, const void* k, const void* v,
                     const FwdOut& out_l, const FwdOut& out_g, void* ws, hipStream_t st);
@@ -103,7 +104,7 @@ int router_decide(const l2a_params& p, int C, const void* x, const float* w, flo
 // ---- util.hip
 // The backward's per-row statistics: delta of the branches that are run (bf16: the first 64 tokens' from the definition).
 // share (optional; fp32, both branches with the same q, k, v): the two branches of a routed row in its window become one row:
-// share[b,h,t] = a = exp(lse_local - lse_global) (0 on rows not in `routed`) and the Local delta is that
+// share[b,h,t] = a = exp(lse_local - lse_global) (0 on rows not in `routed`), and with fold_delta the Local delta is that
 // of the folded row, (delta_l + a delta_g) / (1 + a)
 struct RowStats {
     const void *q, *k, *v, *out;  // out: the saved s or a
@@ -111,7 +112,7 @@ struct RowStats {
     float* delta;
 };
 int row_stats(const Geom& g, int dtype, const void* dO, const RowStats* local, const RowStats* global, const RowSet& routed,
-              float* share, hipStream_t st);
+              float* share, bool fold_delta, hipStream_t st);
 bool row_stats_can_fold(const Geom& g);  // so many heads that there is no room to mark the routed rows: no share
 int fill_zero(void* ptr, size_t bytes, hipStream_t st);
 int fill_f32(float* ptr, size_t n, float value, hipStream_t st);

@@ -67,7 +67,7 @@ bool pair_fwd(const l2a_params& p) {
 bool pair_bwd(const l2a_params& p) { return pair_fwd(p); }
 // two token-minor copies of V (one per branch) and the forward kernels' redo flags; short sequences:
 // flags for both branches at once and room for A in fp32
-// fp32 with shared inputs: the parts that a routed row's keys before the window are found in (an option: without room for
+// fp32 with shared inputs: the parts that a routed row's sums are found in (an option: without room for
 // them the branches run one after the other)
 bool both_routed(const l2a_params& p) { return !(p.flags & (L2A_FLAG_DENSE | L2A_FLAG_SKIP_LOCAL | L2A_FLAG_SKIP_GLOBAL)); }
 // (Up to 256 tokens a launch for each branch and one for the parts with a combine behind it take the same few us.)
@@ -265,10 +265,10 @@ int l2a_attn_fwd(const l2a_params* p, const void* q_loc, const void* k_loc, cons
             return r;
         return merge_rows(g, rs_g, A32, O, st);
     }
-    if (fp32_parts(*p) && kblk_first_row && q_glb == q_loc && k_glb == k_loc && v_glb == v_loc && workspace &&
-        workspace_bytes >= fwd_workspace_bytes(*p) && !misaligned(workspace)) {
+    auto room = [&](size_t bytes) { return bytes == 0 || (workspace && workspace_bytes >= bytes && !misaligned(workspace)); };
+    if (fp32_parts(*p) && kblk_first_row && q_glb == q_loc && k_glb == k_loc && v_glb == v_loc && room(fwd_workspace_bytes(*p))) {
         const FwdOut out_l{O, S_opt, lse_local, lse_global, A_opt, 0}, out_g{O, A_opt, lse_global, nullptr, nullptr, 1};
-        return fp32_fwd_shared(g, RowSet{nullptr, nullptr, nullptr, 1}, RowSet{row_idx, count, kblk_first_row, 0, g.W + 1}, q_loc, k_loc,
+        return fp32_fwd_shared(g, RowSet{nullptr, nullptr, nullptr, 1}, RowSet{row_idx, count, kblk_first_row, 0}, q_loc, k_loc,
                                v_loc, out_l, out_g, workspace, st);
     }
     auto fwd_branch = [&](const RowSet& rs, const void* q, const void* k, const void* v, const void* vt,
@@ -336,14 +336,13 @@ int l2a_attn_bwd(const l2a_params* p, const void* dO, const void* q_loc, const v
     float* delta_g = delta_glb_opt ? delta_glb_opt : (float*)((char*)workspace + delta_bytes(*p));
     const bool mfma = use_mfma(*p), fp32 = p->dtype == L2A_FP32;
     char* packed_base = (char*)workspace + 2 * delta_bytes(*p);
-    // fp32, shared inputs and summed gradients: the window of a routed row counts once for both branches, and the Global rows
-    // only take the keys before it (none at all while the window spans the sequence).  Behind the deltas the rows' shares
-    // (row_stats), then the parts of dQ.  (bf16 computes the window for each branch: one rounding of P and dS for both
-    // cost dK 1.4 % and dV 0.9 % of their error against 64 bits at 16379 tokens.)
+    // fp32, shared inputs and summed gradients: both branches' dQ in one launch, and in dK, dV the window of a routed row counts
+    // once for both branches, the Global rows only taking the keys before it (none at all while the window spans the sequence).
+    // Behind the deltas the rows' shares (row_stats), then the parts of dQ.  (bf16 computes the window for each branch: one rounding
+    // of P and dS for both cost dK 1.4 % and dV 0.9 % of their error against 64 bits at 16379 tokens.)
     const bool fold = fp32_parts(*p) && out_alias && row_stats_can_fold(g) && workspace_bytes >= bwd_workspace_bytes(*p);
     float* share = fold ? (float*)packed_base : nullptr;
-    const int far_shift = fold ? g.W + 1 : 0;
-    const bool far_rows = !fold || g.T > far_shift;
+    const bool far_rows = !fold || g.T > g.W + 1;
     auto bwd_dq = [&](const RowSet& rs, const void* q, const void* k, const void* v, const float* lse, float* delta,
                       void* dq, int acc) {
         if (mfma) return mfma_bwd_dq(g, rs, q, k, v, dO, lse, delta, dq, acc, st);
@@ -351,9 +350,9 @@ int l2a_attn_bwd(const l2a_params* p, const void* dO, const void* q_loc, const v
                     : simple_bwd_dq(g, rs, q, k, v, dO, lse, delta, dq, acc, st);
     };
     const RowSet rs_l{nullptr, nullptr, nullptr, 1};
-    const RowSet rs_g = dense ? RowSet{nullptr, nullptr, nullptr, 0} : RowSet{row_idx, count, kblk_first_row, 0, far_shift};
+    const RowSet rs_g = dense ? RowSet{nullptr, nullptr, nullptr, 0} : RowSet{row_idx, count, kblk_first_row, 0};
     const RowStats stats_l{q_loc, k_loc, v_loc, S, lse_local, delta_l}, stats_g{q_glb, k_glb, v_glb, A, lse_global, delta_g};
-    if ((r = row_stats(g, p->dtype, dO, do_local ? &stats_l : nullptr, do_global ? &stats_g : nullptr, rs_g, share, st)) != L2A_OK)
+    if ((r = row_stats(g, p->dtype, dO, do_local ? &stats_l : nullptr, do_global ? &stats_g : nullptr, rs_g, share, fold && fp32_window_is_all(g), st)) != L2A_OK)
         return r;
 
     // dQ: one pass per branch over that branch's rows; short sequences: both in one launch, the Global branch's
@@ -403,7 +402,8 @@ int l2a_attn_bwd(const l2a_params* p, const void* dO, const void* q_loc, const v
         return mfma_bwd_dkdv(g, sets, n, packed, cap, k, v, dk, dv, part, st);
     };
     if (out_alias) {
-        const RowSet sets[2] = {rs_l, rs_g};
+        RowSet sets[2] = {rs_l, rs_g};
+        if (fold) sets[1].shift = g.W + 1;
         const void* qs[2] = {q_loc, q_loc};
         const float* lses[2] = {lse_local, lse_global};
         const float* deltas[2] = {delta_l, delta_g};

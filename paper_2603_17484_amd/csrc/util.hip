@@ -15,10 +15,11 @@ namespace {
 // constant, p_g = a p_l with a = exp(lse_l - lse_g) <= 1, and what they add up to there is one row's gradient:
 //     p_l + p_g = p',   p_l (dP - delta_l) + p_g (dP - delta_g) = p' (dP - delta'),
 //     p' = exp(s - lse_l + log(1 + a)),   delta' = (delta_l + a delta_g) / (1 + a).
-// The Local pass runs over these rows, and the Global pass only over the keys before the window: the window's
+// dK and dV take these rows for the Local ones, and of the Global rows only the keys before the window: the window's
 // (row, key) pairs are computed once instead of twice.  fp32 only: in bf16 dK and dV would take one rounding of the sum of two
 // weights where they take two independent ones, and their error against 64 bits at 16379 tokens would be 1.4 % and 0.9 % larger
-// (2.83e-3 -> 2.87e-3, 2.31e-3 -> 2.33e-3 of the norm).
+// (2.83e-3 -> 2.87e-3, 2.31e-3 -> 2.33e-3 of the norm).  Not dQ (but where s = a to the bit): the two branches' sums over the window
+// would share their roundings, which their sum does not average out (up to 2.6 % more error at 4096 tokens).
 //
 // Memory-bound: a workgroup takes `tok` consecutive tokens of one sequence -- a contiguous
 // stretch of [t, h, D] rows, sixteen lanes per row, four rows of each in flight -- and transposes its results through
@@ -40,6 +41,7 @@ struct StatsArgs {
     int row_blocks;  // workgroups per sequence that take rows; the ones behind them the first tokens, one head each
     RowSet routed;   // share: the routed rows and kblk_first_row
     float* share;    // fold: a, 0 on rows that are not routed (null: no fold)
+    bool fold_delta;
 };
 
 // Marks the routed rows of positions t0 .. t0 + n - 1 (inside one block of 64): flags[head * n + t - t0].  The KV heads side
@@ -62,7 +64,7 @@ __device__ __forceinline__ void store_stats(const StatsArgs& a, size_t so, float
         float f = 0.f;
         if (routed) {
             f = expf(a.br[0].lse[so] - a.br[1].lse[so]);
-            dl = (dl + f * dg) / (1.f + f);
+            if (a.fold_delta) dl = (dl + f * dg) / (1.f + f);
         }
         a.share[so] = f;
     }
@@ -211,7 +213,7 @@ size_t stats_lds(const Geom& g, int tok, bool fold) { return (size_t)g.Hq * tok 
 bool row_stats_can_fold(const Geom& g) { return stats_lds(g, 1, true) <= kStatsLds; }
 
 int row_stats(const Geom& g, int dtype, const void* dO, const RowStats* local, const RowStats* global, const RowSet& routed,
-              float* share, hipStream_t st) {
+              float* share, bool fold_delta, hipStream_t st) {
     auto lds_bytes = [&](int tok) { return stats_lds(g, tok, share != nullptr); };
     int tok = 64;  // tokens per workgroup: as many as fit 64 KB of LDS with Hq heads
     while (tok > 1 && lds_bytes(tok) > kStatsLds) tok /= 2;
@@ -225,6 +227,7 @@ int row_stats(const Geom& g, int dtype, const void* dO, const RowStats* local, c
     a.row_blocks = (g.T + tok - 1) / tok;
     a.routed = routed;
     a.share = share;
+    a.fold_delta = fold_delta;
     if (local) a.br[0] = StatsBranch{local->q, local->k, local->v, local->out, local->lse, local->delta, 1};
     if (global) a.br[1] = StatsBranch{global->q, global->k, global->v, global->out, global->lse, global->delta, 0};
     // bf16: the first tokens of a head need 2 x 64 floats
