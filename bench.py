@@ -29,8 +29,8 @@ PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA peak
 # committed profile are repeated here; they are reported only for exactly that workload.
 TRAFFIC_SOURCE = ("NOT measured in this run: constant copied from profiles/all_kernels_train_128k_hbm_bytes.md, two "
                   "rocprofv3 --pmc runs of `bench.py --sparse-only --calibrate-copy` on the same workload")
-MEASURED_TRAFFIC_BYTES = {"bwd_dkdv": 1.564e10, "bwd_dq_global": 2.966e10, "bwd_dq_local": 4.25e9,
-                          "fwd_global": 2.646e10, "fwd_local": 5.44e9}
+MEASURED_TRAFFIC_BYTES = {"bwd_dkdv": 1.955e10, "bwd_dq_global": 2.645e10, "bwd_dq_local": 3.91e9,
+                          "fwd_global": 2.624e10, "fwd_local": 5.19e9}
 
 
 def pair_counts(mask: np.ndarray, Hq: int, Hkv: int, T: int, W: int, dense: bool):

@@ -751,7 +751,7 @@ __global__ __launch_bounds__(64 * NW) void fwd_kernel(FwdArgs a) {
 
 // Shared inputs, the window spans the sequence: every row once, in identity order (no lists to wait for), no merge behind it.
 // Whole forward, 20 % routed, 28 / 4 heads, the two branches in one launch and a merge / this, us: T = 600 35.3 / 29.0, T = 1001
-// 42.3 / 35.2, T = 4096 173.0 / 143.4.
+// 42.3 / 33.4, T = 4096 172.8 / 138.5.
 template <int NW>
 __global__ __launch_bounds__(64 * NW, 2) void fwd_whole_kernel(FwdArgs a) {
     __shared__ __attribute__((aligned(1024))) FwdLds lds;
