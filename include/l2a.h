@@ -189,7 +189,8 @@ int l2a_router_decide(const l2a_params* p, int32_t C, const void* x, const float
  *                   order, where the Global kernel adds its fp32 result to the stored s -- but for tiles whose softmax needed a
  *                   running maximum: which rows a tile holds, and so which are computed that way, differs.
  *   fp32            with shared inputs, kblk_first_row and the optional workspace, T > 256: both branches in one launch and a
- *                   second, small kernel, the keys of a routed row in parts; results differ by rounding.
+ *                   second, small kernel, the keys of a routed row in parts, whose number follows from the sizes, the
+ *                   batch among them; results differ by rounding.
  * s and lse_local of a token do not depend on which other tokens are routed (but for such tiles in bf16).
  */
 int l2a_attn_fwd(const l2a_params* p, const void* q_loc, const void* k_loc, const void* v_loc,
